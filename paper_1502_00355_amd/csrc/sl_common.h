@@ -63,7 +63,19 @@ struct ValStats {
     int32_t n_free;
     int32_t max_deg_free;
     int32_t max_inc_free;
+    int32_t nnz_free, ninc_free;   // row entries and incidences of the free nodes
+    uint64_t box[4];               // min x, min y, max x, max y as order-preserving bit patterns
 };
+
+// SplitMix64 output function (Steele, Lea, Flood, OOPSLA 2014), applied to
+// the caller's node id: the colouring priority.
+__device__ __forceinline__ uint64_t splitmix64(uint64_t v)
+{
+    uint64_t z = v + 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
 
 // ------------------------------------------------------ device memory --
 

@@ -39,21 +39,10 @@ __host__ __device__ __forceinline__ double from_ord_bits(uint64_t u)
     return d;
 }
 
-// SplitMix64 output function (Steele, Lea, Flood, OOPSLA 2014), applied to
-// the caller's node id: the colouring priority.
-__device__ __forceinline__ uint64_t splitmix64(uint64_t v)
-{
-    uint64_t z = v + 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
 // ---------------------------------------------------------------- scan ----
 //
-// Reduce, then scan: one pass sums each tile of kScanTile values, one
-// work-group scans the tile sums, and a second pass scans each tile from its
-// offset.  Each work-item holds 16 consecutive values, loaded and stored as
+// Reduce, then scan: one pass sums each tile of kScanTile values, and a
+// second pass scans each tile from its offset.  Each work-item holds 16 consecutive values, loaded and stored as
 // four 16-byte vectors when the arrays allow it.
 
 constexpr int kScanPer = 16;
@@ -120,38 +109,33 @@ __global__ __launch_bounds__(kBS) void k_scan_sums(const int32_t* __restrict__ i
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// Exclusive scan of the nb tile sums in place, by one work-group; *total =
-// their sum.
-__global__ __launch_bounds__(kSumsBS) void k_scan_offsets(int32_t* __restrict__ sums, int32_t nb,
-                                                          int32_t* __restrict__ total)
+// Sum of sums[0..b) over a work-group of BS work-items (every one gets it).
+template <int BS>
+__device__ __forceinline__ int32_t sums_before(const int32_t* __restrict__ sums, int b, int32_t* s_wave)
 {
-    __shared__ int32_t s_wave[kSumsBS / 64];
-    const int per = (nb + kSumsBS - 1) / kSumsBS;
-    const int b0 = min(static_cast<int>(threadIdx.x) * per, nb), b1 = min(b0 + per, nb);
     int32_t x = 0;
-    for (int b = b0; b < b1; ++b) x += sums[b];
+    for (int q = threadIdx.x; q < b; q += BS) x += sums[q];
     int32_t all;
-    int32_t run = group_excl_scan<kSumsBS>(x, s_wave, &all);
-    for (int b = b0; b < b1; ++b) {
-        const int32_t t = sums[b];
-        sums[b] = run;
-        run += t;
-    }
-    if (threadIdx.x == 0) *total = all;
+    (void)group_excl_scan<BS>(x, s_wave, &all);
+    return all;
 }
 
-__global__ __launch_bounds__(kBS) void k_scan_tiles(const int32_t* __restrict__ in, int32_t* __restrict__ out,
-                                                    int64_t n, bool vec, const int32_t* __restrict__ offs)
+// Scans this work-group's tile from its offset, the sum of the earlier
+// tiles' sums, which it adds up itself: at most a few thousand values out of
+// L2, which costs less than a launch of one work-group to scan them first.
+// The last tile also writes the total.
+__device__ __forceinline__ void scan_tile(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n, bool vec,
+                                          const int32_t* __restrict__ sums, int32_t* total, int32_t* s_wave)
 {
-    __shared__ int32_t s_wave[kBS / 64];
     const int64_t base = (static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x) * kScanPer;
     int32_t v[kScanPer];
     scan_load(in, n, base, vec, v);
     int32_t x = 0;
 #pragma unroll
     for (int j = 0; j < kScanPer; ++j) x += v[j];
-    int32_t total;
-    int32_t run = offs[blockIdx.x] + group_excl_scan<kBS>(x, s_wave, &total);
+    const int32_t off = sums_before<kBS>(sums, static_cast<int>(blockIdx.x), s_wave);
+    int32_t all;
+    int32_t run = off + group_excl_scan<kBS>(x, s_wave, &all);
 #pragma unroll
     for (int j = 0; j < kScanPer; ++j) {
         const int32_t t = v[j];
@@ -167,10 +151,19 @@ __global__ __launch_bounds__(kBS) void k_scan_tiles(const int32_t* __restrict__ 
         for (int j = 0; j < kScanPer; ++j)
             if (base + j < n) out[base + j] = v[j];
     }
+    if (threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total = off + all;
+}
+
+__global__ __launch_bounds__(kBS) void k_scan_tiles(const int32_t* __restrict__ in, int32_t* __restrict__ out,
+                                                    int64_t n, bool vec, const int32_t* __restrict__ sums,
+                                                    int32_t* __restrict__ total)
+{
+    __shared__ int32_t s_wave[kBS / 64];
+    scan_tile(in, out, n, vec, sums, total, s_wave);
 }
 
 // Exclusive scan of a short in[0..n) by one work-group, kSumsBS*kScanPer
-// values at a time with a running carry: one launch in place of three, for
+// values at a time with a running carry: one launch in place of two, for
 // setups whose time goes into launches (a batch of small meshes).  In place
 // (in == out) is allowed: every value is read and written by one work-item.
 __global__ __launch_bounds__(kSumsBS) void k_scan_one(const int32_t* in, int32_t* out, int64_t n, bool vec,
@@ -207,9 +200,10 @@ __global__ __launch_bounds__(kSumsBS) void k_scan_one(const int32_t* in, int32_t
     if (threadIdx.x == 0) *total = carry;
 }
 
-// Scans this long or shorter take the one-launch path (at most 16 passes of
-// its loop).
-constexpr int64_t kScanOneMax = int64_t(16) * kSumsBS * kScanPer;
+// Scans this long or shorter take the one-launch path (one pass of its loop:
+// each further pass is a serial trip to memory, 28 us for 100K values
+// against 8 us for the two launches).
+constexpr int64_t kScanOneMax = int64_t(1) * kSumsBS * kScanPer;
 
 // Exclusive scan of in[0..n) into out[0..n); *total = sum.  The tile sums
 // come from `ar` when given, else from the allocator.
@@ -227,15 +221,18 @@ sl_status scan_rec(const int32_t* in, int32_t* out, int64_t n, int32_t* total, h
     if (r) return r;
     const bool vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
     k_scan_sums<<<nb, kBS, 0, st>>>(in, n, vec, sums);
-    k_scan_offsets<<<1, kSumsBS, 0, st>>>(sums, nb, total);
-    k_scan_tiles<<<nb, kBS, 0, st>>>(in, out, n, vec, sums);
+    k_scan_tiles<<<nb, kBS, 0, st>>>(in, out, n, vec, sums, total);
     if (!ar) dfree(sums, st);
     SL_HIP(hipGetLastError());
     return SL_OK;
 }
 
+}  // namespace
+
 // Arena bytes the temporaries of a scan of n values take.
 size_t scan_bytes(int64_t n) { return Arena::piece(4 * static_cast<size_t>(div_up(n > 0 ? n : 1, kScanTile))); }
+
+namespace {
 
 // ----------------------------------------------------------- validation ---
 
@@ -263,40 +260,33 @@ __device__ __forceinline__ bool row_has(const int32_t* __restrict__ idx, int32_t
     return false;
 }
 
-__global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict__ tris, int32_t n_tris, int32_t n,
-                                                       ValStats* __restrict__ vs)
-{
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
-    uint32_t e = 0;
-    if (t < n_tris) {
-        const int32_t a = tris[3 * t], b = tris[3 * t + 1], c = tris[3 * t + 2];
-        if (a < 0 || b < 0 || c < 0 || a >= n || b >= n || c >= n) e |= VE_RANGE;
-        if (a == b || b == c || a == c) e |= VE_TRIREP;
-    }
-    if (e) atomicOr(&vs->err, e);
-}
-
 // Incidence rows that disagree (for the Form A tile path, which lists a
 // triangle once per tile and scores it for every own vertex): a triangle
 // listed by some of its free vertices but not by all of them.  One
 // work-item per triangle looks for it in its free vertices' rows, the three
-// rows' offsets and first kIncRegs entries loaded together.  Vertices out of
-// range and offsets out of order are left to the other checks.
+// rows' offsets and first kIncRegs entries loaded together.  Offsets out of
+// order are left to the other checks.  Without `incidence` only the
+// triangle's own vertices are checked.
 constexpr int kIncRegs = 8;
-__global__ __launch_bounds__(kBS) void k_validate_incidence(const int32_t* __restrict__ tris, int32_t n_tris, int32_t n,
-                                                            const uint8_t* __restrict__ bnd,
-                                                            const int32_t* __restrict__ tri_ptr,
-                                                            const int32_t* __restrict__ tri_idx, int64_t ninc,
-                                                            ValStats* __restrict__ vs)
+template <bool INCIDENCE>
+__global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict__ tris, int32_t n_tris, int32_t n,
+                                                       const uint8_t* __restrict__ bnd,
+                                                       const int32_t* __restrict__ tri_ptr,
+                                                       const int32_t* __restrict__ tri_idx, int64_t ninc,
+                                                       ValStats* __restrict__ vs)
 {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
     if (t >= n_tris) return;
     int32_t v[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) v[k] = tris[3 * t + k];
+    uint32_t e = 0;
+    if (v[0] == v[1] || v[1] == v[2] || v[0] == v[2]) e |= VE_TRIREP;
 #pragma unroll
     for (int k = 0; k < 3; ++k)
-        if (v[k] < 0 || v[k] >= n) return;
+        if (v[k] < 0 || v[k] >= n) e |= VE_RANGE;
+    if (e) atomicOr(&vs->err, e);
+    if (!INCIDENCE || (e & VE_RANGE)) return;
     int32_t ob[3], oe[3];
     uint8_t fl[3];
 #pragma unroll
@@ -331,13 +321,57 @@ __global__ __launch_bounds__(kBS) void k_validate_incidence(const int32_t* __res
     if (lists > 0 && lists < free_v) atomicOr(&vs->err, static_cast<uint32_t>(VI_INCIDENCE));
 }
 
+// Statistics of a wave or work-group, folded pairwise.
+__device__ __forceinline__ void fold_stats(ValStats& a, const ValStats& b)
+{
+    a.err |= b.err;
+    a.n_free += b.n_free;
+    a.max_deg_free = max(a.max_deg_free, b.max_deg_free);
+    a.max_inc_free = max(a.max_inc_free, b.max_inc_free);
+    a.nnz_free += b.nnz_free;
+    a.ninc_free += b.ninc_free;
+    a.box[0] = min(a.box[0], b.box[0]);
+    a.box[1] = min(a.box[1], b.box[1]);
+    a.box[2] = max(a.box[2], b.box[2]);
+    a.box[3] = max(a.box[3], b.box[3]);
+}
+
+__device__ __forceinline__ void fold_stats_wave(ValStats& a)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        ValStats b;
+        b.err = __shfl_xor(a.err, off);
+        b.n_free = __shfl_xor(a.n_free, off);
+        b.max_deg_free = __shfl_xor(a.max_deg_free, off);
+        b.max_inc_free = __shfl_xor(a.max_inc_free, off);
+        b.nnz_free = __shfl_xor(a.nnz_free, off);
+        b.ninc_free = __shfl_xor(a.ninc_free, off);
+        for (int q = 0; q < 4; ++q)
+            b.box[q] = static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(a.box[q]), off));
+        fold_stats(a, b);
+    }
+}
+
+// An empty set's statistics.
+__device__ __forceinline__ ValStats empty_stats()
+{
+    return ValStats{0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}};
+}
+
+// One work-item per node; each work-group leaves its statistics (with the
+// bounding box of its nodes' coordinates, so that no pass of its own has to
+// read them again) in a slot of its own.
 __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __restrict__ part)
 {
     const int32_t i = static_cast<int32_t>(blockIdx.x * kBS + threadIdx.x);
     uint32_t e = 0;
     int is_free = 0, deg = 0, inc = 0;
+    ValStats me = empty_stats();
     if (i < a.n) {
-        const double x = a.coords[2 * static_cast<int64_t>(i)], y = a.coords[2 * static_cast<int64_t>(i) + 1];
+        const double2 xy = reinterpret_cast<const double2*>(a.coords)[i];
+        const double x = xy.x, y = xy.y;
+        me.box[0] = me.box[2] = ord_bits(x);
+        me.box[1] = me.box[3] = ord_bits(y);
         // finite and below the limit in magnitude (2^500 in double, 2^61 in
         // single precision): squared edge lengths, their sums and cross
         // products cannot overflow, so every quality is a finite number
@@ -411,26 +445,19 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
             }
         }
     }
-    // block reductions: free count, max degree, max incidence, error bits
-    __shared__ int32_t s_cnt[kBS / 64], s_deg[kBS / 64], s_inc[kBS / 64];
-    __shared__ uint32_t s_err[kBS / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int df = is_free ? deg : 0, inf = is_free ? inc : 0;
-    int32_t c = __popcll(__ballot(is_free != 0));
-    int32_t md = df, mi = inf;
-    uint32_t me = e;
-    for (int off = 32; off > 0; off >>= 1) {
-        md = max(md, __shfl_xor(md, off));
-        mi = max(mi, __shfl_xor(mi, off));
-        me |= __shfl_xor(me, off);
+    me.err = e;
+    if (is_free) {
+        me.n_free = 1;
+        me.max_deg_free = me.nnz_free = deg;
+        me.max_inc_free = me.ninc_free = inc;
     }
-    if (lane == 0) { s_cnt[w] = c; s_deg[w] = md; s_inc[w] = mi; s_err[w] = me; }
+    fold_stats_wave(me);
+    __shared__ ValStats s_part[kBS / 64];
+    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = me;
     __syncthreads();
     if (threadIdx.x == 0) {
-        int32_t C = 0, D = 0, I = 0;
-        uint32_t E = 0;
-        for (int q = 0; q < kBS / 64; ++q) { C += s_cnt[q]; D = max(D, s_deg[q]); I = max(I, s_inc[q]); E |= s_err[q]; }
-        part[blockIdx.x] = ValStats{E, C, D, I};
+        for (int q = 1; q < kBS / 64; ++q) fold_stats(me, s_part[q]);
+        part[blockIdx.x] = me;
     }
 }
 
@@ -440,94 +467,19 @@ __global__ __launch_bounds__(1024) void k_validate_fold(const ValStats* __restri
                                                         ValStats* __restrict__ vs)
 {
     __shared__ ValStats s_part[16];
-    uint32_t e = 0;
-    int32_t c = 0, d = 0, in = 0;
-    for (int32_t b = threadIdx.x; b < nb; b += 1024) {
-        const ValStats p = part[b];
-        e |= p.err;
-        c += p.n_free;
-        d = max(d, p.max_deg_free);
-        in = max(in, p.max_inc_free);
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        e |= __shfl_xor(e, off);
-        c += __shfl_xor(c, off);
-        d = max(d, __shfl_xor(d, off));
-        in = max(in, __shfl_xor(in, off));
-    }
-    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = ValStats{e, c, d, in};
+    ValStats me = empty_stats();
+    for (int32_t b = threadIdx.x; b < nb; b += 1024) fold_stats(me, part[b]);
+    fold_stats_wave(me);
+    if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = me;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int q = 1; q < 16; ++q) {
-            e |= s_part[q].err;
-            c += s_part[q].n_free;
-            d = max(d, s_part[q].max_deg_free);
-            in = max(in, s_part[q].max_inc_free);
-        }
-        vs->err |= e;
-        vs->n_free = c;
-        vs->max_deg_free = d;
-        vs->max_inc_free = in;
+        for (int q = 1; q < 16; ++q) fold_stats(me, s_part[q]);
+        me.err |= vs->err;
+        *vs = me;
     }
 }
 
 // ------------------------------------------------------------- ordering ---
-
-constexpr int kBboxBlocks = 1024;
-
-// Per-block bounding box of the coordinates, as order-preserving bit
-// patterns {min x, min y, max x, max y}; k_bbox_fold folds the blocks.
-__global__ __launch_bounds__(kBS) void k_bbox(const double* __restrict__ coords, int32_t n, uint64_t* __restrict__ part)
-{
-    uint64_t mnx = ~0ull, mny = ~0ull, mxx = 0, mxy = 0;
-    const double2* c2 = reinterpret_cast<const double2*>(coords);
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * kBS) {
-        const double2 p = c2[i];
-        const uint64_t ox = ord_bits(p.x), oy = ord_bits(p.y);
-        mnx = min(mnx, ox); mxx = max(mxx, ox);
-        mny = min(mny, oy); mxy = max(mxy, oy);
-    }
-    __shared__ uint64_t s_bb[kBS / 64][4];
-    for (int off = 32; off > 0; off >>= 1) {
-        mnx = min(mnx, static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(mnx), off)));
-        mny = min(mny, static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(mny), off)));
-        mxx = max(mxx, static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(mxx), off)));
-        mxy = max(mxy, static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(mxy), off)));
-    }
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) {
-        s_bb[w][0] = mnx; s_bb[w][1] = mny; s_bb[w][2] = mxx; s_bb[w][3] = mxy;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < kBS / 64; ++q) {
-            mnx = min(mnx, s_bb[q][0]); mny = min(mny, s_bb[q][1]);
-            mxx = max(mxx, s_bb[q][2]); mxy = max(mxy, s_bb[q][3]);
-        }
-        uint64_t* o = part + 4 * static_cast<int64_t>(blockIdx.x);
-        o[0] = mnx; o[1] = mny; o[2] = mxx; o[3] = mxy;
-    }
-}
-
-__global__ __launch_bounds__(kBS) void k_bbox_fold(const uint64_t* __restrict__ part, int nb, uint64_t* __restrict__ bb)
-{
-    uint64_t mnx = ~0ull, mny = ~0ull, mxx = 0, mxy = 0;
-    for (int b = threadIdx.x; b < nb; b += kBS) {
-        mnx = min(mnx, part[4 * b]); mny = min(mny, part[4 * b + 1]);
-        mxx = max(mxx, part[4 * b + 2]); mxy = max(mxy, part[4 * b + 3]);
-    }
-    __shared__ uint64_t s_bb[kBS][4];
-    s_bb[threadIdx.x][0] = mnx; s_bb[threadIdx.x][1] = mny; s_bb[threadIdx.x][2] = mxx; s_bb[threadIdx.x][3] = mxy;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < kBS; ++q) {
-            mnx = min(mnx, s_bb[q][0]); mny = min(mny, s_bb[q][1]);
-            mxx = max(mxx, s_bb[q][2]); mxy = max(mxy, s_bb[q][3]);
-        }
-        bb[0] = mnx; bb[1] = mny; bb[2] = mxx; bb[3] = mxy;
-    }
-}
 
 // Hilbert index of cell (x, y) on a 2^bits x 2^bits grid.
 __device__ __forceinline__ uint32_t hilbert_index(int bits, uint32_t x, uint32_t y)
@@ -547,15 +499,15 @@ __device__ __forceinline__ uint32_t hilbert_index(int bits, uint32_t x, uint32_t
 // Bucket of each free node: colour * 4^bits + Hilbert cell (bits may be 0).
 __global__ __launch_bounds__(kBS) void k_bucket(const double* __restrict__ coords, const uint8_t* __restrict__ bnd,
                                                 const int32_t* __restrict__ color, int32_t n, int bits,
-                                                const uint64_t* __restrict__ bb, int32_t* __restrict__ key,
+                                                const ValStats* __restrict__ vs, int32_t* __restrict__ key,
                                                 int32_t* __restrict__ count, int32_t* __restrict__ rank)
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
     if (i >= n || bnd[i]) return;
     uint32_t cell = 0;
     if (bits > 0) {
-        const double x0 = from_ord_bits(bb[0]), y0 = from_ord_bits(bb[1]);
-        const double ext = fmax(from_ord_bits(bb[2]) - x0, from_ord_bits(bb[3]) - y0);
+        const double x0 = from_ord_bits(vs->box[0]), y0 = from_ord_bits(vs->box[1]);
+        const double ext = fmax(from_ord_bits(vs->box[2]) - x0, from_ord_bits(vs->box[3]) - y0);
         const double side = static_cast<double>(1u << bits);
         const double sc = ext > 0.0 ? side / ext : 0.0;
         const uint32_t lim = (1u << bits) - 1u;
@@ -702,16 +654,47 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v)
 
 // ------------------------------------------------------------ relabel -----
 
-__global__ __launch_bounds__(kBS) void k_degrees(const int32_t* __restrict__ perm, int32_t n_free,
-                                                 const int32_t* __restrict__ nbr_ptr,
-                                                 const int32_t* __restrict__ tri_ptr, int32_t* __restrict__ deg,
-                                                 int32_t* __restrict__ inc)
+// Row lengths and incidence counts of the free nodes in device order, and
+// their sums over each tile of kScanTile nodes (sums[b] and sums[nb + b]):
+// the first pass of both offset scans, which k_offset_tiles finishes.
+__global__ __launch_bounds__(kBS) void k_degree_sums(const int32_t* __restrict__ perm, int32_t n_free,
+                                                     const int32_t* __restrict__ nbr_ptr,
+                                                     const int32_t* __restrict__ tri_ptr, int32_t* __restrict__ deg,
+                                                     int32_t* __restrict__ inc, int32_t* __restrict__ sums)
 {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
-    if (k >= n_free) return;
-    const int32_t o = perm[k];
-    deg[k] = nbr_ptr[o + 1] - nbr_ptr[o];
-    inc[k] = tri_ptr[o + 1] - tri_ptr[o];
+    __shared__ int32_t s_wave[kBS / 64];
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kScanTile + threadIdx.x;
+    int32_t x = 0, y = 0;
+#pragma unroll
+    for (int j = 0; j < kScanPer; ++j) {
+        const int64_t k = base + j * kBS;
+        if (k < n_free) {
+            const int32_t o = perm[k];
+            const int32_t d = nbr_ptr[o + 1] - nbr_ptr[o], c = tri_ptr[o + 1] - tri_ptr[o];
+            deg[k] = d;
+            inc[k] = c;
+            x += d;
+            y += c;
+        }
+    }
+    int32_t tx, ty;
+    (void)group_excl_scan<kBS>(x, s_wave, &tx);
+    (void)group_excl_scan<kBS>(y, s_wave, &ty);
+    if (threadIdx.x == 0) {
+        sums[blockIdx.x] = tx;
+        sums[gridDim.x + blockIdx.x] = ty;
+    }
+}
+
+// Row offsets (blockIdx.y == 0) and incidence offsets (1).
+__global__ __launch_bounds__(kBS) void k_offset_tiles(const int32_t* __restrict__ deg, const int32_t* __restrict__ inc,
+                                                      int64_t n, const int32_t* __restrict__ sums,
+                                                      int32_t* __restrict__ row_ptr, int32_t* __restrict__ fan_ptr)
+{
+    __shared__ int32_t s_wave[kBS / 64];
+    int32_t* const out = blockIdx.y ? fan_ptr : row_ptr;
+    // (arena pieces: 256-byte aligned)
+    scan_tile(blockIdx.y ? inc : deg, out, n, true, sums + (blockIdx.y ? gridDim.x : 0), out + n, s_wave);
 }
 
 __global__ __launch_bounds__(kBS) void k_rows_fans(const int32_t* __restrict__ perm,
@@ -866,11 +849,13 @@ __global__ __launch_bounds__(kBS) void k_unpermute_flags(const uint64_t* __restr
             const int64_t i = 8 * B + q;
             if (i >= n) break;
             const int32_t k = new_of_old[i];
-            if (k < n_free && ((bits[s * words + k / 64] >> (k % 64)) & 1ull)) byte |= 1u << q;
+            if (static_cast<uint32_t>(k) < static_cast<uint32_t>(n_free) && ((bits[s * words + k / 64] >> (k % 64)) & 1ull)) byte |= 1u << q;
         }
     }
     out[g] = static_cast<uint8_t>(byte);
 }
+
+}  // namespace
 
 // Bits per axis of the Hilbert cells of the counting sort for n_free free
 // nodes in nc colour classes: grown while a class still has about two nodes
@@ -885,16 +870,16 @@ int hilbert_bits(int64_t n_free, int nc)
     return bits;
 }
 
+namespace {
+
 // Scratch bytes make_order takes for n nodes (at most 128 colour classes).
 size_t order_bytes(int64_t n)
 {
     const int64_t nbk = std::max<int64_t>(4 * 128, 2 * n);
-    return 3 * Arena::piece(4 * static_cast<size_t>(n + 1)) + Arena::piece(4 * sizeof(uint64_t)) +
-           Arena::piece(4 * sizeof(uint64_t) * kBboxBlocks) +
-           2 * Arena::piece(4 * static_cast<size_t>(nbk + 1)) + scan_bytes(std::max<int64_t>(n, nbk));
+    return 3 * Arena::piece(4 * static_cast<size_t>(n + 1)) + 2 * Arena::piece(4 * static_cast<size_t>(nbk + 1)) + scan_bytes(std::max<int64_t>(n, nbk));
 }
 
-sl_status make_order(const SetupArgs& a, const sl_options& o, const uint8_t* bnd, int32_t n_free,
+sl_status make_order(const SetupArgs& a, const sl_options& o, const uint8_t* bnd, int32_t n_free, const ValStats* vs,
                      const int32_t* color, int32_t n_colors, DevMesh& m, hipStream_t st, Arena& scratch)
 {
     const int32_t n = a.n;
@@ -911,16 +896,11 @@ sl_status make_order(const SetupArgs& a, const sl_options& o, const uint8_t* bnd
         const int nc = color ? n_colors : 1;
         const int bits = hilbert_bits(n_free, nc);
         const int64_t nbk = static_cast<int64_t>(nc) << (2 * bits);
-        const int nbb = std::min(gb, kBboxBlocks);
-        uint64_t *bb = nullptr, *bbp = nullptr;
         int32_t *count = nullptr, *start = nullptr, *key = nullptr;
-        if ((r = scratch.take(&bb, 4)) || (r = scratch.take(&bbp, 4 * static_cast<size_t>(nbb))) ||
-            (r = scratch.take(&count, nbk)) || (r = scratch.take(&start, nbk + 1)) || (r = scratch.take(&key, n)))
+        if ((r = scratch.take(&count, nbk)) || (r = scratch.take(&start, nbk + 1)) || (r = scratch.take(&key, n)))
             return r;
-        k_bbox<<<nbb, kBS, 0, st>>>(a.coords, n, bbp);
-        k_bbox_fold<<<1, kBS, 0, st>>>(bbp, nbb, bb);
         k_fill_i32<<<div_up(nbk, 256), 256, 0, st>>>(count, nbk, 0);
-        k_bucket<<<gb, kBS, 0, st>>>(a.coords, bnd, color, n, bits, bb, key, count, flag);
+        k_bucket<<<gb, kBS, 0, st>>>(a.coords, bnd, color, n, bits, vs, key, count, flag);
         if ((r = scan_exclusive(count, start, nbk, st, &scratch))) return r;
         if (color) {
             // nc <= 128: the class starts fit the mesh's table
@@ -999,7 +979,7 @@ constexpr int32_t kLargeClassMesh = 1 << 20;
 // 0.033 ms with either.
 constexpr int32_t kLargeTileMesh = 1 << 19;
 
-static int32_t tile_size_for(const sl_options& o, int32_t n)
+int32_t tile_size_for(const sl_options& o, int32_t n)
 {
     if (o.form == SL_JACOBI) {
         if (o.tile_nodes || tuned_shape().tile_nodes) return resolve_tile_nodes(o);
@@ -1039,12 +1019,55 @@ size_t mesh_block_bytes(int32_t n, int64_t nnz, int64_t ninc, const sl_options& 
 size_t setup_scratch_bytes(int32_t n)
 {
     const size_t un = static_cast<size_t>(n);
-    const size_t rows_bytes = 2 * Arena::piece(4 * un) + scan_bytes(n);
+    const size_t rows_bytes = 2 * Arena::piece(4 * un) + 2 * scan_bytes(n);
     const int gb = div_up(n, kBS);
     return Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(ValStats) * static_cast<size_t>(gb)) +
            Arena::piece(4 * un) + Arena::piece(4) +
            std::max({order_bytes(n), rows_bytes, tile_scratch_bytes(),
                      2 * Arena::piece(4 * un) + Arena::piece(8)});   // the colouring's lists
+}
+
+// Queues the checks of one mesh's arrays; *vs (zeroed before) receives the
+// statistics, part a slot per work-group of k_validate_nodes.  incidence:
+// also whether the incidence rows agree (VI_INCIDENCE).
+static void queue_validation(const ValArgs& a, bool incidence, ValStats* vs, ValStats* part, hipStream_t st)
+{
+    if (a.n_tris > 0) {
+        const int gt = div_up(a.n_tris, kBS);
+        if (incidence && a.ninc > 0)
+            k_validate_tris<true><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
+        else
+            k_validate_tris<false><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
+    }
+    const int gb = div_up(a.n, kBS);
+    k_validate_nodes<<<gb, kBS, 0, st>>>(a, part);
+    k_validate_fold<<<1, 1024, 0, st>>>(part, gb, vs);
+}
+
+// SL_OK, or the error that the validation's bits stand for.
+sl_status validation_status(uint32_t err, const sl_options& o)
+{
+    if (err & (VE_PTR | VE_RANGE | VE_COORD)) {
+        std::string msg = "invalid input:";
+        if (err & VE_PTR) msg += " CSR offsets not monotone or out of range;";
+        if (err & VE_RANGE) msg += " node or triangle id out of range;";
+        if (err & VE_COORD)
+            msg += o.precision == SL_F32 ? " coordinate not finite or of magnitude >= 2^61 (single precision);"
+                                         : " coordinate not finite or of magnitude >= 2^500;";
+        return fail(SL_EINVAL, msg);
+    }
+    if (err & kValErrors & ~(o.form == SL_JACOBI ? VE_ASYM : 0u)) {
+        std::string msg = "invalid topology:";
+        if (err & VE_SELF) msg += " node lists itself as a neighbour;";
+        if (err & VE_TRIREP) msg += " triangle with a repeated vertex;";
+        if (err & VE_NOTIN) msg += " incident triangle does not contain its node;";
+        if (err & VE_MISSING) msg += " triangle vertex missing from the node's neighbour row;";
+        if (err & VE_EMPTY) msg += " free node without neighbours;";
+        if (err & VE_VALENCE) msg += " free node with more than 127 neighbours;";
+        if (err & VE_ASYM) msg += " neighbour rows are not symmetric (needed by the coloured form);";
+        return fail(SL_ETOPO, msg);
+    }
+    return SL_OK;
 }
 
 sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_t mesh, hipStream_t st)
@@ -1098,36 +1121,12 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     SL_HIP(hipMemsetAsync(vs, 0, sizeof(ValStats), st));
     ValArgs va{a.coords, n, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, a.n_tris, a.boundary,
                a.nnz, a.ninc, o.form == SL_INPLACE_COLORED, o.precision == SL_F32 ? 0x1p61 : 0x1p500};
-    if (a.n_tris > 0) k_validate_tris<<<div_up(a.n_tris, kBS), kBS, 0, st>>>(a.tris, a.n_tris, n, vs);
-    if (want_tiles && o.form == SL_JACOBI && a.n_tris > 0 && a.ninc > 0)
-        k_validate_incidence<<<div_up(a.n_tris, kBS), kBS, 0, st>>>(a.tris, a.n_tris, n, a.boundary, a.tri_ptr,
-                                                                  a.tri_idx, a.ninc, vs);
-    k_validate_nodes<<<gb, kBS, 0, st>>>(va, vpart);
-    k_validate_fold<<<1, 1024, 0, st>>>(vpart, gb, vs);
+    queue_validation(va, want_tiles && o.form == SL_JACOBI, vs, vpart, st);
     SL_HIP(hipGetLastError());
     ValStats h{};
     SL_HIP(hipMemcpyAsync(&h, vs, sizeof(ValStats), hipMemcpyDeviceToHost, st));
     SL_HIP(hipStreamSynchronize(st));
-    if (h.err & (VE_PTR | VE_RANGE | VE_COORD)) {
-        std::string msg = "invalid input:";
-        if (h.err & VE_PTR) msg += " CSR offsets not monotone or out of range;";
-        if (h.err & VE_RANGE) msg += " node or triangle id out of range;";
-        if (h.err & VE_COORD)
-            msg += o.precision == SL_F32 ? " coordinate not finite or of magnitude >= 2^61 (single precision);"
-                                         : " coordinate not finite or of magnitude >= 2^500;";
-        return fail(SL_EINVAL, msg);
-    }
-    if (h.err & kValErrors) {
-        std::string msg = "invalid topology:";
-        if (h.err & VE_SELF) msg += " node lists itself as a neighbour;";
-        if (h.err & VE_TRIREP) msg += " triangle with a repeated vertex;";
-        if (h.err & VE_NOTIN) msg += " incident triangle does not contain its node;";
-        if (h.err & VE_MISSING) msg += " triangle vertex missing from the node's neighbour row;";
-        if (h.err & VE_EMPTY) msg += " free node without neighbours;";
-        if (h.err & VE_VALENCE) msg += " free node with more than 127 neighbours;";
-        if (h.err & VE_ASYM) msg += " neighbour rows are not symmetric (needed by the coloured form);";
-        return fail(SL_ETOPO, msg);
-    }
+    if ((r = validation_status(h.err, o))) return r;
     m.n_free = h.n_free;
     m.max_deg = h.max_deg_free;
     m.max_inc = h.max_inc_free;
@@ -1183,7 +1182,7 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     }
 
     // ---- node order
-    if ((r = make_order(a, o, a.boundary, m.n_free, color, m.n_colors, m, st, scratch))) return r;
+    if ((r = make_order(a, o, a.boundary, m.n_free, vs, color, m.n_colors, m, st, scratch))) return r;
 
     // ---- rows and fans of free nodes
     if ((r = persist.take(&m.row_ptr, static_cast<size_t>(m.n_free) + 1)) ||
@@ -1193,17 +1192,15 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     int32_t *deg = nullptr, *inc = nullptr;
     if ((r = scratch.take(&deg, m.n_free)) || (r = scratch.take(&inc, m.n_free))) return r;
     const int gf = div_up(m.n_free > 0 ? m.n_free : 1, kBS);
-    if (m.n_free > 0) k_degrees<<<gf, kBS, 0, st>>>(m.perm, m.n_free, a.nbr_ptr, a.tri_ptr, deg, inc);
-    if ((r = scan_exclusive(deg, m.row_ptr, m.n_free, st, &scratch)) ||
-        (r = scan_exclusive(inc, m.fan_ptr, m.n_free, st, &scratch)))
-        return r;
-    int32_t tot[2] = {0, 0};
-    SL_HIP(hipMemcpyAsync(&tot[0], m.row_ptr + m.n_free, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    SL_HIP(hipMemcpyAsync(&tot[1], m.fan_ptr + m.n_free, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    SL_HIP(hipStreamSynchronize(st));
+    const int gt = div_up(m.n_free > 0 ? m.n_free : 1, kScanTile);
+    int32_t* dsum = nullptr;
+    if ((r = scratch.take(&dsum, 2 * static_cast<size_t>(gt)))) return r;
+    k_degree_sums<<<gt, kBS, 0, st>>>(m.perm, m.n_free, a.nbr_ptr, a.tri_ptr, deg, inc, dsum);
+    k_offset_tiles<<<dim3(gt, 2), kBS, 0, st>>>(deg, inc, m.n_free, dsum, m.row_ptr, m.fan_ptr);
+    SL_HIP(hipGetLastError());
     scratch.rewind(mk);
-    m.nnz_free = tot[0];
-    m.ninc_free = tot[1];
+    m.nnz_free = h.nnz_free;     // the offsets' totals, counted by the validation
+    m.ninc_free = h.ninc_free;
     // coordinate buffers: one block, X[1] right after X[0], in the sweep's precision
     const size_t n2 = 2 * un;
     if (m.precision == SL_F32) {
@@ -1260,16 +1257,21 @@ sl_status unpermute_coords(const DevMesh& m, int src, double* coords_out, hipStr
     return SL_OK;
 }
 
+sl_status unpermute_flags_raw(const uint64_t* bits, int64_t words, const int32_t* new_of_old, int32_t n, int32_t n_free,
+                              int32_t iterations, const MeshState* state, uint8_t* out, hipStream_t st)
+{
+    const int64_t total = (static_cast<int64_t>(n) + 7) / 8 * iterations;
+    if (total == 0) return SL_OK;
+    k_unpermute_flags<<<div_up(total, kBS), kBS, 0, st>>>(bits, words, new_of_old, n, n_free, iterations, state, out);
+    SL_HIP(hipGetLastError());
+    return SL_OK;
+}
+
 sl_status unpermute_flags(const DevMesh& m, const uint64_t* bits, int32_t iterations, const MeshState* state,
                           uint8_t* out, hipStream_t st)
 {
-    const int64_t words = (static_cast<int64_t>(m.n_free) + 63) / 64;
-    const int64_t total = (static_cast<int64_t>(m.n) + 7) / 8 * iterations;
-    if (total == 0) return SL_OK;
-    k_unpermute_flags<<<div_up(total, kBS), kBS, 0, st>>>(bits, words, m.new_of_old, m.n, m.n_free, iterations, state,
-                                                          out);
-    SL_HIP(hipGetLastError());
-    return SL_OK;
+    return unpermute_flags_raw(bits, (static_cast<int64_t>(m.n_free) + 63) / 64, m.new_of_old, m.n, m.n_free,
+                               iterations, state, out, st);
 }
 
 }  // namespace sl

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "sl_common.h"
+#include "sl_flow.h"
 
 namespace sl {
 
@@ -107,7 +108,15 @@ sl_status check_options(const sl_options& o)
     return SL_OK;
 }
 
-sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh_index, DevMesh& m, hipStream_t st)
+// Checks a caller mesh's arguments and reads the CSR ends (through a pinned
+// pad, when they are on the device only).
+static __global__ void k_read_ends(const int32_t* nbr_ptr, const int32_t* tri_ptr, int32_t n, int32_t* out)
+{
+    const int32_t* const p = threadIdx.x < 2 ? nbr_ptr : tri_ptr;
+    if (threadIdx.x < 4) out[threadIdx.x] = p[(threadIdx.x & 1) ? n : 0];
+}
+
+sl_status check_input(const MeshInput& in, SetupArgs* sa, hipStream_t st)
 {
     if (!in.coords || !in.nbr_ptr || !in.tri_ptr || !in.boundary) return fail(SL_EINVAL, "null array argument");
     // coordinates are read and written as (x, y) pairs of 16 bytes
@@ -118,22 +127,39 @@ sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh_in
     if (in.n_tris > (INT32_MAX / 3)) return fail(SL_EINVAL, "n_tris too large");
     int32_t ends[4] = {in.ends[0], in.ends[1], in.ends[2], in.ends[3]};
     if (!in.ends_known) {
-        SL_HIP(hipMemcpyAsync(&ends[0], in.nbr_ptr, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        SL_HIP(hipMemcpyAsync(&ends[1], in.nbr_ptr + in.n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        SL_HIP(hipMemcpyAsync(&ends[2], in.tri_ptr, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        SL_HIP(hipMemcpyAsync(&ends[3], in.tri_ptr + in.n, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        PinnedPad pad;
+        const sl_status r = pad.init();
+        if (r) return r;
+        k_read_ends<<<1, 64, 0, st>>>(in.nbr_ptr, in.tri_ptr, in.n, static_cast<int32_t*>(pad.p));
+        SL_HIP(hipGetLastError());
         SL_HIP(hipStreamSynchronize(st));
+        std::memcpy(ends, pad.p, sizeof(ends));
     }
     if (ends[0] != 0 || ends[2] != 0) return fail(SL_EINVAL, "nbr_ptr[0] and tri_ptr[0] must be 0");
     if (ends[1] < 0 || ends[3] < 0) return fail(SL_EINVAL, "negative CSR length");
     if (ends[1] > 0 && !in.nbr_idx) return fail(SL_EINVAL, "null nbr_idx with nbr_ptr[n] > 0");
     if (ends[3] > 0 && !in.tri_idx) return fail(SL_EINVAL, "null tri_idx with tri_ptr[n] > 0");
+    *sa = SetupArgs{in.coords, in.n, in.nbr_ptr, in.nbr_idx, in.tri_ptr, in.tri_idx, in.tris, in.n_tris, in.boundary,
+                    ends[1], ends[3]};
+    return SL_OK;
+}
+
+sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh_index, DevMesh& m, hipStream_t st)
+{
+    SetupArgs sa{};
+    const sl_status r = check_input(in, &sa, st);
+    if (r) return r;
+    return prepare_mesh(sa, o, mesh_index, m, st);
+}
+
+sl_status prepare_mesh(const SetupArgs& sa, const sl_options& o, int32_t mesh_index, DevMesh& m, hipStream_t st)
+{
     if (m.region) {
         // everything from the caller's region: the mesh's arrays, then the
         // setup's temporaries, which the caller's region_after bytes reuse
         // once setup is done
-        const size_t pb = Arena::piece(mesh_block_bytes(in.n, ends[1], ends[3], o, m.class_tiles_ok));
-        const size_t sb = setup_scratch_bytes(in.n);
+        const size_t pb = Arena::piece(mesh_block_bytes(sa.n, sa.nnz, sa.ninc, o, m.class_tiles_ok));
+        const size_t sb = setup_scratch_bytes(sa.n);
         const size_t need = pb + std::max(sb, m.region_after);
         if (need > m.region_bytes)
             return fail(SL_ENOMEM, "the mesh needs " + std::to_string(need) + " bytes of device workspace; the "
@@ -143,8 +169,6 @@ sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh_in
         m.scratch_carve = m.region + pb;
         m.scratch_carve_bytes = m.region_bytes - pb;
     }
-    SetupArgs sa{in.coords, in.n, in.nbr_ptr, in.nbr_idx, in.tri_ptr, in.tri_idx, in.tris, in.n_tris, in.boundary,
-                 ends[1], ends[3]};
     return setup_mesh(sa, o, m, mesh_index, st);
 }
 
@@ -183,8 +207,7 @@ struct CallState {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
         if (own_events)
-            for (auto& e : ev)
-                if (e) (void)hipEventDestroy(e);
+            for (auto& e : ev) give_timer(e);
     }
 };
 
@@ -226,7 +249,8 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         cs.m.region_bytes = ws->bytes;
         cs.m.region_after = aux_bytes(n, iterations, want_bits);
     } else {
-        for (auto& e : cs.ev) SL_HIP(hipEventCreate(&e));
+        for (auto& e : cs.ev)
+            if ((r = take_timer(&e))) return r;
     }
     SL_HIP(hipEventRecord(cs.ev[0], stream));
     MeshInput in{coords, n, nbr_ptr, nbr_idx, tri_ptr, tri_idx, tris, n_tris, boundary};
@@ -234,7 +258,19 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         in.ends_known = true;
         for (int k = 0; k < 4; ++k) in.ends[k] = known_ends[k];
     }
-    if ((r = prepare_mesh(in, o, 0, cs.m, stream))) return r;
+    SetupArgs sa{};
+    if ((r = check_input(in, &sa, stream))) return r;
+    // small and medium meshes: every sweep in one launch
+    bool done = false;
+    if ((r = flow_run(sa, o, iterations, tol, report, coords, stream, ws ? ws->base : nullptr, ws ? ws->bytes : 0, cs.ev,
+                      &done)))
+        return r;
+    if (done) {
+        if (report)
+            report->total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+        return SL_OK;
+    }
+    if ((r = prepare_mesh(sa, o, 0, cs.m, stream))) return r;
     SL_HIP(hipEventRecord(cs.ev[1], stream));
 
     const int32_t its = iterations;

@@ -490,7 +490,10 @@ struct MeshInput {
     int32_t ends[4] = {0, 0, 0, 0};
 };
 
-// Argument checks, then setup_mesh.
+// Argument checks; fills the setup's arguments.
+sl_status check_input(const MeshInput& in, SetupArgs* sa, hipStream_t st);
+// Argument checks (in the first form), then setup_mesh.
+sl_status prepare_mesh(const SetupArgs& sa, const sl_options& o, int32_t mesh, DevMesh& m, hipStream_t st);
 sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh, DevMesh& m, hipStream_t st);
 sl_status check_options(const sl_options& o);
 void keep_pool_warm();
@@ -519,6 +522,26 @@ struct PooledStream {
     }
     sl_status init() { return take_stream(&s); }
 };
+
+// A small piece of pinned host memory from a per-device pool: kernels write
+// a call's few result words straight into it, which the host reads after its
+// wait (a copy into pageable memory is an extra trip through the runtime's
+// staging).  Its holder must have waited for the kernels that write it.
+constexpr size_t kPadBytes = 4096;
+struct PinnedPad {
+    void* p = nullptr;
+    int dev = -1;
+    PinnedPad() = default;
+    PinnedPad(const PinnedPad&) = delete;
+    PinnedPad& operator=(const PinnedPad&) = delete;
+    ~PinnedPad();
+    sl_status init();
+};
+
+// Timing events of the current device from a pool (given back by a holder
+// that has waited for the work they mark).
+sl_status take_timer(hipEvent_t* ev);
+void give_timer(hipEvent_t ev);
 
 // One caller mesh's host arrays copied into a single device allocation
 // (nnz = nbr_ptr[n], ninc = tri_ptr[n], already read by the caller), with

@@ -1,0 +1,67 @@
+// The flow path: small and medium meshes, every sweep in one launch
+// (sl_flow.hip), with the setup kernels it shares (sl_setup.hip).
+#pragma once
+
+#include "sl_common.h"
+
+namespace sl {
+
+constexpr int kFlowClasses = 32;               // colour classes at most (Form B)
+constexpr uint32_t kFlowStop = 0x80000000u;    // FlowState::decided: no sweep after this count
+
+// Device state of one call, zeroed before it.
+struct FlowState {
+    uint32_t decline;       // != 0: the mesh does not fit the tiles' limits
+    uint32_t abort;         // != 0: a wait took too long
+    int32_t n_colors;       // colour classes (Form B)
+    uint32_t pad0[29];
+    uint32_t decided;       // with a tolerance: sweeps decided, | kFlowStop with the last one
+    uint32_t pad1[31];
+    unsigned long long maxd;   // with a tolerance: displacement maximum of the last sweep
+};
+
+// What a tile's work-group leaves.
+struct FlowGroup {
+    unsigned long long maxd, acc_last, acc_total;
+};
+
+// What the host reads back, written by the last kernel into pinned memory.
+struct FlowReport {
+    ValStats vs;
+    uint32_t decline, abort;
+    int32_t n_colors, sweeps;
+    unsigned long long maxd, acc_last, acc_total;
+};
+
+// Arrays of the flow path's node order.
+struct FlowOrder {
+    ValStats *vs, *part;          // the mesh's statistics; one slot per work-group of the checks
+    int32_t *count, *start;       // [buckets], [buckets + 1]
+    int32_t *key, *rank;          // [n]
+    int32_t *new_of_old, *perm;   // [n]; fixed nodes: -1; free nodes only
+    int bits;
+};
+
+// Bits per axis of the Hilbert cells of a mesh of n free nodes in nc classes.
+int hilbert_bits(int64_t n_free, int nc);
+// Arena bytes of a scan's temporaries.
+size_t scan_bytes(int64_t n);
+// Queues the checks (with symmetry of the rows, and for Form A the incidence
+// rows') and the Hilbert order of the free nodes; nothing is read back.
+sl_status queue_flow_order(const SetupArgs& a, const sl_options& o, const FlowOrder& f, Arena& scratch, hipStream_t st);
+// SL_OK, or the error that the checks' bits stand for.
+sl_status validation_status(uint32_t err, const sl_options& o);
+// Free nodes per tile that the tile path would take.
+int32_t tile_size_for(const sl_options& o, int32_t n);
+// Accept bits to the caller's layout: `words` 64-bit words per sweep.
+sl_status unpermute_flags_raw(const uint64_t* bits, int64_t words, const int32_t* new_of_old, int32_t n, int32_t n_free,
+                              int32_t iterations, const MeshState* state, uint8_t* out, hipStream_t st);
+
+// Runs a whole call on the flow path when options, size and the device's
+// free groups allow it.  *done = false (with SL_OK): not run, or the mesh
+// turned out not to fit; the caller's arrays are untouched.  ws / ws_bytes:
+// a region to carve every device array from, instead of allocating.
+sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, double tol, sl_report* report,
+                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, hipEvent_t* ev, bool* done);
+
+}  // namespace sl

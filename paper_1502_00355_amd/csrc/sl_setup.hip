@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "sl_common.h"
+#include "sl_flow.h"
 
 namespace sl {
 
@@ -529,6 +530,23 @@ __global__ __launch_bounds__(kBS) void k_bucket_scatter(const uint8_t* __restric
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
     if (i >= n || bnd[i]) return;
+    const int32_t pos = start[key[i]] + rank[i];
+    new_of_old[i] = pos;
+    perm[pos] = static_cast<int32_t>(i);
+}
+
+// The same for the flow path, where fixed nodes have no place (-1).
+__global__ __launch_bounds__(kBS) void k_flow_scatter(const uint8_t* __restrict__ bnd, int32_t n,
+                                                      const int32_t* __restrict__ key, const int32_t* __restrict__ rank,
+                                                      const int32_t* __restrict__ start,
+                                                      int32_t* __restrict__ new_of_old, int32_t* __restrict__ perm)
+{
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
+    if (i >= n) return;
+    if (bnd[i]) {
+        new_of_old[i] = -1;
+        return;
+    }
     const int32_t pos = start[key[i]] + rank[i];
     new_of_old[i] = pos;
     perm[pos] = static_cast<int32_t>(i);
@@ -1272,6 +1290,22 @@ sl_status unpermute_flags(const DevMesh& m, const uint64_t* bits, int32_t iterat
 {
     return unpermute_flags_raw(bits, (static_cast<int64_t>(m.n_free) + 63) / 64, m.new_of_old, m.n, m.n_free,
                                iterations, state, out, st);
+}
+
+sl_status queue_flow_order(const SetupArgs& a, const sl_options& o, const FlowOrder& f, Arena& scratch, hipStream_t st)
+{
+    const int32_t n = a.n;
+    const int gb = div_up(n, kBS);
+    ValArgs va{a.coords, n, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, a.n_tris, a.boundary,
+               a.nnz, a.ninc, 1, 0x1p500};
+    queue_validation(va, o.form == SL_JACOBI, f.vs, f.part, st);
+    // (keys and ranks are in range whatever the checks find)
+    k_bucket<<<gb, kBS, 0, st>>>(a.coords, a.boundary, nullptr, n, f.bits, f.vs, f.key, f.count, f.rank);
+    sl_status r = scan_exclusive(f.count, f.start, int64_t(1) << (2 * f.bits), st, &scratch);
+    if (r) return r;
+    k_flow_scatter<<<gb, kBS, 0, st>>>(a.boundary, n, f.key, f.rank, f.start, f.new_of_old, f.perm);
+    SL_HIP(hipGetLastError());
+    return SL_OK;
 }
 
 }  // namespace sl

@@ -263,6 +263,80 @@ void give_stream(hipStream_t st)
 
 namespace {
 
+// Free pads and event sets, per device.  Both pools are bounded by what is
+// in use at once, and keep at most kKept of each.
+constexpr size_t kKept = 64;
+std::mutex g_small_mu;
+std::vector<void*> g_pads[64];
+std::vector<hipEvent_t> g_timers[64];
+
+}  // namespace
+
+sl_status PinnedPad::init()
+{
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(SL_EDEVICE, "no current device");
+    {
+        std::lock_guard<std::mutex> lk(g_small_mu);
+        if (!g_pads[dev].empty()) {
+            p = g_pads[dev].back();
+            g_pads[dev].pop_back();
+            return SL_OK;
+        }
+    }
+    if (hipHostMalloc(&p, kPadBytes, hipHostMallocDefault) != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();
+        return fail(SL_ENOMEM, "pinned memory allocation failed");
+    }
+    return SL_OK;
+}
+
+PinnedPad::~PinnedPad()
+{
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> lk(g_small_mu);
+        if (g_pads[dev].size() < kKept) {
+            g_pads[dev].push_back(p);
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
+sl_status take_timer(hipEvent_t* ev)
+{
+    *ev = nullptr;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(SL_EDEVICE, "no current device");
+    {
+        std::lock_guard<std::mutex> lk(g_small_mu);
+        if (!g_timers[dev].empty()) {
+            *ev = g_timers[dev].back();
+            g_timers[dev].pop_back();
+            return SL_OK;
+        }
+    }
+    SL_HIP(hipEventCreate(ev));
+    return SL_OK;
+}
+
+void give_timer(hipEvent_t ev)
+{
+    if (!ev) return;
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
+        std::lock_guard<std::mutex> lk(g_small_mu);
+        if (g_timers[dev].size() < 4 * kKept) {
+            g_timers[dev].push_back(ev);
+            return;
+        }
+    }
+    (void)hipEventDestroy(ev);
+}
+
+namespace {
+
 // per device; a batch gives back a few blocks per mesh at once, and a
 // free costs about 0.24 ms of host time, so the count bound is loose and
 // the byte bound is what limits the cache

@@ -108,15 +108,14 @@ sl_status check_options(const sl_options& o)
     return SL_OK;
 }
 
-// Checks a caller mesh's arguments and reads the CSR ends (through a pinned
-// pad, when they are on the device only).
+// The CSR ends, to a pinned pad.
 static __global__ void k_read_ends(const int32_t* nbr_ptr, const int32_t* tri_ptr, int32_t n, int32_t* out)
 {
     const int32_t* const p = threadIdx.x < 2 ? nbr_ptr : tri_ptr;
     if (threadIdx.x < 4) out[threadIdx.x] = p[(threadIdx.x & 1) ? n : 0];
 }
 
-sl_status check_input(const MeshInput& in, SetupArgs* sa, hipStream_t st)
+sl_status check_arguments(const MeshInput& in)
 {
     if (!in.coords || !in.nbr_ptr || !in.tri_ptr || !in.boundary) return fail(SL_EINVAL, "null array argument");
     // coordinates are read and written as (x, y) pairs of 16 bytes
@@ -125,6 +124,13 @@ sl_status check_input(const MeshInput& in, SetupArgs* sa, hipStream_t st)
     if (in.n_tris < 0) return fail(SL_EINVAL, "n_tris must be >= 0");
     if (in.n_tris > 0 && !in.tris) return fail(SL_EINVAL, "null tris with n_tris > 0");
     if (in.n_tris > (INT32_MAX / 3)) return fail(SL_EINVAL, "n_tris too large");
+    return SL_OK;
+}
+
+sl_status check_input(const MeshInput& in, SetupArgs* sa, hipStream_t st)
+{
+    const sl_status rc = check_arguments(in);
+    if (rc) return rc;
     int32_t ends[4] = {in.ends[0], in.ends[1], in.ends[2], in.ends[3]};
     if (!in.ends_known) {
         PinnedPad pad;
@@ -149,11 +155,6 @@ sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh_in
     SetupArgs sa{};
     const sl_status r = check_input(in, &sa, st);
     if (r) return r;
-    return prepare_mesh(sa, o, mesh_index, m, st);
-}
-
-sl_status prepare_mesh(const SetupArgs& sa, const sl_options& o, int32_t mesh_index, DevMesh& m, hipStream_t st)
-{
     if (m.region) {
         // everything from the caller's region: the mesh's arrays, then the
         // setup's temporaries, which the caller's region_after bytes reuse
@@ -248,29 +249,29 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         cs.m.region = ws->base;
         cs.m.region_bytes = ws->bytes;
         cs.m.region_after = aux_bytes(n, iterations, want_bits);
-    } else {
-        for (auto& e : cs.ev)
-            if ((r = take_timer(&e))) return r;
     }
-    SL_HIP(hipEventRecord(cs.ev[0], stream));
     MeshInput in{coords, n, nbr_ptr, nbr_idx, tri_ptr, tri_idx, tris, n_tris, boundary};
     if (known_ends) {
         in.ends_known = true;
         for (int k = 0; k < 4; ++k) in.ends[k] = known_ends[k];
     }
-    SetupArgs sa{};
-    if ((r = check_input(in, &sa, stream))) return r;
+    if ((r = check_arguments(in))) return r;
     // small and medium meshes: every sweep in one launch
     bool done = false;
-    if ((r = flow_run(sa, o, iterations, tol, report, coords, stream, ws ? ws->base : nullptr, ws ? ws->bytes : 0, cs.ev,
-                      &done)))
+    const SetupArgs fa{coords, n, nbr_ptr, nbr_idx, tri_ptr, tri_idx, tris, n_tris, boundary,
+                       in.ends_known ? in.ends[1] : -1, in.ends_known ? in.ends[3] : -1};
+    if ((r = flow_run(fa, o, iterations, tol, report, coords, stream, ws ? ws->base : nullptr, ws ? ws->bytes : 0, &done)))
         return r;
     if (done) {
         if (report)
             report->total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         return SL_OK;
     }
-    if ((r = prepare_mesh(sa, o, 0, cs.m, stream))) return r;
+    if (!ws)
+        for (auto& e : cs.ev)
+            if ((r = take_timer(&e))) return r;
+    SL_HIP(hipEventRecord(cs.ev[0], stream));
+    if ((r = prepare_mesh(in, o, 0, cs.m, stream))) return r;
     SL_HIP(hipEventRecord(cs.ev[1], stream));
 
     const int32_t its = iterations;

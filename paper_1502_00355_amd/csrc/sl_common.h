@@ -490,10 +490,10 @@ struct MeshInput {
     int32_t ends[4] = {0, 0, 0, 0};
 };
 
-// Argument checks; fills the setup's arguments.
+// Argument checks on the host; and with the CSR ends, filling the setup's arguments.
+sl_status check_arguments(const MeshInput& in);
 sl_status check_input(const MeshInput& in, SetupArgs* sa, hipStream_t st);
-// Argument checks (in the first form), then setup_mesh.
-sl_status prepare_mesh(const SetupArgs& sa, const sl_options& o, int32_t mesh, DevMesh& m, hipStream_t st);
+// Argument checks, then setup_mesh.
 sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh, DevMesh& m, hipStream_t st);
 sl_status check_options(const sl_options& o);
 void keep_pool_warm();

@@ -18,6 +18,7 @@ struct FlowState {
     uint32_t decided;       // with a tolerance: sweeps decided, | kFlowStop with the last one
     uint32_t pad1[31];
     unsigned long long maxd;   // with a tolerance: displacement maximum of the last sweep
+    unsigned long long t_begin, t_sweep;   // the device's clock at the call's first kernel and at the sweeps
 };
 
 // What a tile's work-group leaves.
@@ -31,6 +32,8 @@ struct FlowReport {
     uint32_t decline, abort;
     int32_t n_colors, sweeps;
     unsigned long long maxd, acc_last, acc_total;
+    unsigned long long t[3];     // clock: first kernel, first sweep, after the last
+    int32_t nnz, ninc;           // nbr_ptr[n], tri_ptr[n]
 };
 
 // Arrays of the flow path's node order.
@@ -44,6 +47,8 @@ struct FlowOrder {
 
 // Bits per axis of the Hilbert cells of a mesh of n free nodes in nc classes.
 int hilbert_bits(int64_t n_free, int nc);
+// Work-groups of the node checks (slots of FlowOrder::part).
+int val_groups(int32_t n);
 // Arena bytes of a scan's temporaries.
 size_t scan_bytes(int64_t n);
 // Queues the checks (with symmetry of the rows, and for Form A the incidence
@@ -60,8 +65,9 @@ sl_status unpermute_flags_raw(const uint64_t* bits, int64_t words, const int32_t
 // Runs a whole call on the flow path when options, size and the device's
 // free groups allow it.  *done = false (with SL_OK): not run, or the mesh
 // turned out not to fit; the caller's arrays are untouched.  ws / ws_bytes:
-// a region to carve every device array from, instead of allocating.
+// a region to carve every device array from, instead of allocating.  The
+// CSR ends in `a` need not be known (-1).
 sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, double tol, sl_report* report,
-                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, hipEvent_t* ev, bool* done);
+                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, bool* done);
 
 }  // namespace sl

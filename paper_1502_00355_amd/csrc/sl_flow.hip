@@ -10,16 +10,17 @@
 // the new positions of its halo nodes.
 //
 // Exchange: a node that other tiles read is published, as two 8-byte
-// device-scope stores, in ring[v % 3] for version v (the position after v
+// device-scope stores, in ring[v % 4] for version v (the position after v
 // sweeps).  A reader polls the node's own slot until neither half is the
 // sentinel (a NaN pattern, which no position has: coordinates are finite),
-// so one trip through memory carries data and signal together.  Before
-// version v is published its node's slot for v + 1 is set back to the
-// sentinel; that slot held version v - 2.  Every reader is done with it:
-// tiles read each other both ways (neighbour rows are checked to be
-// symmetric), the writer has seen version v - 1 of some node of the reader's
-// tile, and the reader published that after it had read version v - 2 of all
-// its halo.
+// so one trip through memory carries data and signal together.  While
+// version v is made, the node's slot for v + 2 is set back to the sentinel;
+// that slot held version v - 2.  Every reader is done with it: tiles read
+// each other both ways (neighbour rows are checked to be symmetric), the
+// writer has seen version v - 1 of some node of the reader's tile, and the
+// reader published that after it had read version v - 2 of all its halo.
+// The store that sets a slot back is waited for a sweep later, before the
+// version ahead of it is published, so that no reader finds the old value.
 //
 // Form A reads one LDS buffer and writes the other; Form B updates one in
 // place, class by class, reading class c's halo nodes after its own class c.
@@ -94,6 +95,22 @@ __device__ __forceinline__ void st_dev(uint32_t* p, uint32_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The maximum over a wave (all lanes active; values >= 0).
+__device__ __forceinline__ double wave_max(double v)
+{
+    const double m = -group_min<16>(-v);
+    double r = 0.0;
+#pragma unroll
+    for (int l = 0; l < 64; l += 16) {
+        const long long b = __double_as_longlong(m);
+        const int lo = __builtin_amdgcn_readlane(static_cast<int>(b), l);
+        const int hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), l);
+        const double t = __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<uint32_t>(lo));
+        r = t > r ? t : r;
+    }
+    return r;
+}
+
 // Whether the mesh is not for the flow kernels after all (every kernel after
 // the checks asks; the host learns it with the report).  What it reads does
 // not change while a kernel that asks runs, so a group's waves agree: the
@@ -131,7 +148,7 @@ struct FlowInitArgs {
     int64_t n_count;
     int32_t* color;      // nullable
     int64_t n;
-    u64* ring1;          // [2n]
+    u64* ring12;         // [2][2n]: the slots of versions 1 and 2
     u64* dmax;           // nullable, [n_dmax]
     int64_t n_dmax;
     u64* bits;           // nullable, [n_bits]
@@ -144,9 +161,11 @@ __global__ __launch_bounds__(256) void k_flow_init(FlowInitArgs a)
     if (blockIdx.x == 0) {
         for (int q = threadIdx.x; q < static_cast<int>(sizeof(ValStats) / 4); q += 256) reinterpret_cast<uint32_t*>(a.vs)[q] = 0;
         for (int q = threadIdx.x; q < static_cast<int>(sizeof(FlowState) / 4); q += 256) reinterpret_cast<uint32_t*>(a.fs)[q] = 0;
+        __syncthreads();
+        if (threadIdx.x == 0) a.fs->t_begin = wall_clock64();
     }
     for (int64_t q = g; q < a.n_count; q += stride) a.count[q] = 0;
-    for (int64_t q = g; q < 2 * a.n; q += stride) a.ring1[q] = kSent;
+    for (int64_t q = g; q < 4 * a.n; q += stride) a.ring12[q] = kSent;
     if (a.color)
         for (int64_t q = g; q < a.n; q += stride) a.color[q] = -1;
     for (int64_t q = g; q < a.n_dmax; q += stride) a.dmax[q] = kSent;
@@ -166,7 +185,7 @@ __global__ __launch_bounds__(256) void k_flow_color(const int32_t* __restrict__ 
                                                     const ValStats* __restrict__ vs, FlowState* fs, u64 wait)
 {
     if (vs->err != 0) return;
-    constexpr int R = 16;
+    constexpr int R = 8;
     const int32_t i = static_cast<int32_t>(blockIdx.x * 256 + threadIdx.x);
     const bool mine = i < n && bnd[i] == 0;
     int32_t b = 0, d = 0;
@@ -185,23 +204,39 @@ __global__ __launch_bounds__(256) void k_flow_color(const int32_t* __restrict__ 
     Waiter w(fs, wait);
     bool done = !mine;
     int32_t c = -1;
+    uint64_t used0 = 0, used1 = 0;
+    auto use = [&](int32_t cj) {
+        if (cj < 64) used0 |= 1ull << cj;
+        else used1 |= 1ull << (cj - 64);
+    };
+    const uint32_t* const col = reinterpret_cast<const uint32_t*>(color);
     for (;;) {
         if (!done) {
             bool ready = true;
-            uint64_t used0 = 0, used1 = 0;
-            auto see = [&](int32_t j) {
-                const int32_t cj = static_cast<int32_t>(ld_dev(reinterpret_cast<const uint32_t*>(color) + j));
-                if (cj < 0) ready = false;
-                else if (cj < 64) used0 |= 1ull << cj;
-                else used1 |= 1ull << (cj - 64);
-            };
+            int32_t cj[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) cj[j] = -1;
 #pragma unroll
             for (int j = 0; j < R; ++j)
-                if (above[j] >= 0) see(above[j]);
-            for (int32_t k = b + R; k < b + d; ++k) {
-                const int32_t j = nbr_idx[k];
-                if (bnd[j] == 0 && !(splitmix64(static_cast<uint64_t>(j)) < pi)) see(j);
+                if (above[j] >= 0) cj[j] = static_cast<int32_t>(ld_dev(col + above[j]));
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (above[j] < 0) continue;
+                if (cj[j] >= 0) {
+                    use(cj[j]);
+                    above[j] = -1;
+                } else {
+                    ready = false;
+                }
             }
+            if (d > R && ready)
+                for (int32_t k = b + R; k < b + d; ++k) {
+                    const int32_t j = nbr_idx[k];
+                    if (bnd[j] != 0 || splitmix64(static_cast<uint64_t>(j)) < pi) continue;
+                    const int32_t q = static_cast<int32_t>(ld_dev(col + j));
+                    if (q >= 0) use(q);
+                    else ready = false;
+                }
             if (ready) {
                 c = (~used0) ? __builtin_ctzll(~used0) : 64 + __builtin_ctzll(~used1);
                 st_dev(reinterpret_cast<uint32_t*>(color) + i, static_cast<uint32_t>(c));
@@ -268,7 +303,7 @@ struct FlowBuildArgs {
 template <int T, bool CLS>
 __global__ __launch_bounds__((T > 256 ? T : 256)) void k_flow_build(FlowBuildArgs a)
 {
-    constexpr int BS = T > 256 ? T : 256, LPN = BS / T, HS = 4 * T, SPT = HS / BS, U = 4;
+    constexpr int BS = T > 256 ? T : 256, LPN = BS / T, HS = 4 * T, SPT = HS / BS, U = LPN > 1 ? 2 : 4;
     constexpr FlowLayout L(T);
     __shared__ int32_t htab[HS];
     __shared__ uint16_t hidx[HS];
@@ -474,7 +509,7 @@ struct FlowArgs {
     const int32_t* perm;
     const double* coords;       // the caller's positions, read only
     const unsigned char* rec;
-    u64* ring;                  // [3][2n]: published versions
+    u64* ring;                  // [4][2n]: published versions
     double* out;                // [2n] final positions (without a tolerance), device order
     double* hist;               // [kFlowHist][2n] (with a tolerance)
     u64* dmax;                  // [kFlowHist][tiles * waves]: displacement maxima per sweep (with a tolerance)
@@ -486,33 +521,84 @@ struct FlowArgs {
     int32_t iters;
     double tol2;
     u64 wait;                   // clock ticks a wait may take
+    const int32_t *nbr_end, *tri_end;   // nbr_ptr + n, tri_ptr + n
 };
 
-// Candidate and worst qualities of node i by W lanes (this one is lane j).
+// What a lane needs to know of its next node, read from the record ahead of
+// its positions: the chain order -> offsets -> entries is off the path from
+// an exchange to the next one.
+constexpr int kRefRow = 8, kRefFan = 2;   // row entries, and fan entries of the lane
+struct NodeRef {
+    int i, r0, d, f, f1;          // node, row, the lane's first fan entry and the fan's end
+    uint32_t row[kRefRow / 2];    // the first entries, two u16 each
+    uint32_t fan[kRefFan];
+    bool border;
+};
+
+struct FlowRec {
+    const uint16_t *rs, *fo, *ord, *rows;
+    const uint32_t* fans;
+    const uint8_t* flag;
+};
+
 template <int W>
-__device__ __forceinline__ void flow_node(int i, int j, const double2* X, const uint16_t* rs, const uint16_t* fo,
-                                          const uint16_t* rows, const uint32_t* fans, const double* recip, double2& o,
-                                          double2& c, double& qo, double& qn)
+__device__ __forceinline__ void load_ref(NodeRef& n, const FlowRec& t, int q, int j)
 {
-    constexpr int R = 8, F = 2;   // row entries, and fan entries, whose reads overlap
-    const int r0 = rs[i], d = rs[i + 1] - r0, f1 = fo[i + 1];
-    o = X[i];
+    n.i = t.ord[q];
+    n.r0 = t.rs[n.i];
+    n.d = t.rs[n.i + 1] - n.r0;
+    n.f = t.fo[n.i] + j;
+    n.f1 = t.fo[n.i + 1];
+    n.border = t.flag[n.i] != 0;
+#pragma unroll
+    for (int u = 0; u < kRefRow; u += 2)
+        n.row[u / 2] = static_cast<uint32_t>(t.rows[n.r0 + min(u, n.d - 1)]) |
+                       (static_cast<uint32_t>(t.rows[n.r0 + min(u + 1, n.d - 1)]) << 16);
+#pragma unroll
+    for (int u = 0; u < kRefFan; ++u) n.fan[u] = t.fans[max(min(n.f + u * W, n.f1 - 1), 0)];
+    if (n.f1 == t.fo[n.i]) {   // a node in no triangle: its own position stands in
+#pragma unroll
+        for (int u = 0; u < kRefFan; ++u) n.fan[u] = static_cast<uint32_t>(n.i) | (static_cast<uint32_t>(n.i) << 12);
+    }
+}
+
+// Candidate and worst qualities of node n by W lanes (this one is lane j).
+template <int W>
+__device__ __forceinline__ void flow_node(const NodeRef& n, const FlowRec& t, const double2* X, const double* recip,
+                                          double2& o, double2& c, double& qo, double& qn)
+{
+    o = X[n.i];
+    // the fan's vertices and the row's positions in flight together
+    double2 va[kRefFan], vb[kRefFan];
+    double2 p[kRefRow];
+#pragma unroll
+    for (int u = 0; u < kRefRow; ++u) p[u] = X[(n.row[u / 2] >> (16 * (u & 1))) & 0xFFFFu];
+#pragma unroll
+    for (int u = 0; u < kRefFan; ++u) {
+        va[u] = X[n.fan[u] & 0xFFFu];
+        vb[u] = X[(n.fan[u] >> 12) & 0xFFFu];
+    }
     double sx = 0.0, sy = 0.0;
-    for (int j0 = 0; j0 < d; j0 += R) {
-        int l[R];
 #pragma unroll
-        for (int u = 0; u < R; ++u) l[u] = rows[r0 + min(j0 + u, d - 1)];
-        double2 p[R];
+    for (int u = 0; u < kRefRow; ++u)
+        if (u < n.d) {
+            sx += p[u].x;
+            sy += p[u].y;
+        }
+    for (int j0 = kRefRow; j0 < n.d; j0 += 4) {
+        int l[4];
 #pragma unroll
-        for (int u = 0; u < R; ++u) p[u] = X[l[u]];
+        for (int u = 0; u < 4; ++u) l[u] = t.rows[n.r0 + min(j0 + u, n.d - 1)];
 #pragma unroll
-        for (int u = 0; u < R; ++u)
-            if (j0 + u < d) {
+        for (int u = 0; u < 4; ++u) p[u] = X[l[u]];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j0 + u < n.d) {
                 sx += p[u].x;
                 sy += p[u].y;
             }
     }
-    const double dn = static_cast<double>(d), y = recip[d];
+    const double dn = static_cast<double>(n.d), y = recip[n.d];
     c.x = div_small(sx, dn, y);
     c.y = div_small(sy, dn, y);
     const bool tiny = !(fabs(sx) >= kStepMin) || !(fabs(sy) >= kStepMin);
@@ -523,19 +609,21 @@ __device__ __forceinline__ void flow_node(int i, int j, const double2* X, const 
         }
     }
     qo = qn = INFINITY;
-    for (int f = fo[i] + j; f < f1; f += F * W) {
-        uint32_t e[F];
+    for (int f = n.f, first = 1; f < n.f1; f += kRefFan * W, first = 0) {
+        uint32_t e[kRefFan];
 #pragma unroll
-        for (int u = 0; u < F; ++u) e[u] = fans[min(f + u * W, f1 - 1)];
-        double2 va[F], vb[F];
+        for (int u = 0; u < kRefFan; ++u) e[u] = n.fan[u];
+        if (!first) {
 #pragma unroll
-        for (int u = 0; u < F; ++u) {
-            va[u] = X[e[u] & 0xFFFu];
-            vb[u] = X[(e[u] >> 12) & 0xFFFu];
+            for (int u = 0; u < kRefFan; ++u) {
+                e[u] = t.fans[min(f + u * W, n.f1 - 1)];
+                va[u] = X[e[u] & 0xFFFu];
+                vb[u] = X[(e[u] >> 12) & 0xFFFu];
+            }
         }
 #pragma unroll
-        for (int u = 0; u < F; ++u) {
-            if (f + u * W < f1) {
+        for (int u = 0; u < kRefFan; ++u) {
+            if (f + u * W < n.f1) {
                 double v, w;
                 fan_qualities(static_cast<int>(e[u] >> 24), o, c, va[u], vb[u], v, w);
                 qo = v < qo ? v : qo;
@@ -582,10 +670,7 @@ __device__ void flow_control(const FlowArgs& a, int waves, int BS)
                 m = x > m ? x : m;
             }
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            const double t = __shfl_xor(m, off);
-            m = t > m ? t : m;
-        }
+        m = wave_max(m);
         if ((tid & 63) == 0) s_m[tid >> 6] = m;
         __syncthreads();
         if (s_bad) return;
@@ -656,6 +741,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     }
     __syncthreads();
 
+    const FlowRec t{rs, fo, ord, rows, fans, flag};
     const int g = tid / W, j = tid % W, groups = BS / W;
     const int64_t n2 = 2 * a.n, dcap = static_cast<int64_t>(a.tiles) * waves;
     u64* const dslot = TOL ? a.dmax + static_cast<int64_t>(tile) * waves + wv : nullptr;
@@ -663,38 +749,39 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     double d2 = 0.0;
     int s = 0, phase = 0;
     uint32_t stop = 0;
+    NodeRef ref;   // the lane's first node of the class (Form A: of the tile) to come
+    if (g < (B ? cls[1] : nown)) load_ref<W>(ref, t, g, j);
+    if (tile == 0 && tid == 0) a.fs->t_sweep = wall_clock64();
     while (stop == 0 && (TOL || s < a.iters)) {
         const double2* const cur = buf + (!B && (s & 1) ? span : 0);
         double2* const nxt = buf + (!B && !(s & 1) ? span : 0);
         const int v = s + 1;   // the version this sweep makes
-        u64* const ring_v = a.ring + (v % 3) * n2;
-        u64* const ring_next = a.ring + ((v + 1) % 3) * n2;
-        if (TOL && lane == 0) st_dev(dslot + ((s + 1) & (kFlowHist - 1)) * dcap, kSent);
+        u64* const ring_v = a.ring + (v & 3) * n2;
+        u64* const ring_ahead = a.ring + ((v + 2) & 3) * n2;
         int acc = 0;
         bool whole = true;   // every class of the sweep done
         d2 = 0.0;
         for (int c = 0; c < C; ++c) {
             const int lo = B ? cls[c] : 0, hi = B ? cls[c + 1] : nown;
             const bool last_class = c + 1 == C;
-            // the slots of the next version are set back before this one is published
+            // every slot set back in the sweep before has been (stores that
+            // old are done: nothing waits here)
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            if (TOL && c == 0 && lane == 0) st_dev(dslot + ((s + 1) & (kFlowHist - 1)) * dcap, kSent);
             for (int q = lo + g; q < hi; q += groups) {
-                const int i = ord[q];
-                if (flag[i] && j == 0) {
-                    st_dev(ring_next + 2 * (k0 + i), kSent);
-                    st_dev(ring_next + 2 * (k0 + i) + 1, kSent);
+                if (q != lo + g || (!B && groups < nown)) load_ref<W>(ref, t, q, j);
+                const int i = ref.i;
+                if (ref.border && j == 0) {
+                    st_dev(ring_ahead + 2 * (k0 + i), kSent);
+                    st_dev(ring_ahead + 2 * (k0 + i) + 1, kSent);
                 }
-            }
-            for (int q = lo + g; q < hi; q += groups) {
-                const int i = ord[q];
                 double2 o, cd;
                 double qo, qn;
-                flow_node<W>(i, j, cur, rs, fo, rows, fans, s_recip, o, cd, qo, qn);
+                flow_node<W>(ref, t, cur, s_recip, o, cd, qo, qn);
                 const bool accepted = GT ? (qn > qo) : (qn >= qo);
                 const double nx = accepted ? cd.x : o.x, ny = accepted ? cd.y : o.y;
                 if (j == 0) {
-                    if (flag[i]) {
-                        // the stores that set slots back have been performed
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    if (ref.border) {
                         st_dev(ring_v + 2 * (k0 + i), static_cast<u64>(__double_as_longlong(nx)));
                         st_dev(ring_v + 2 * (k0 + i) + 1, static_cast<u64>(__double_as_longlong(ny)));
                     }
@@ -702,23 +789,16 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                     if (TOL)
                         reinterpret_cast<double2*>(a.hist + (v & (kFlowHist - 1)) * n2)[k0 + i] = make_double2(nx, ny);
                     const double dx = nx - o.x, dy = ny - o.y;
-                    const double t = dx * dx + dy * dy;
-                    d2 = t > d2 ? t : d2;
+                    const double e = dx * dx + dy * dy;
+                    d2 = e > d2 ? e : d2;
                     acc += accepted ? 1 : 0;
                     if (a.bits != nullptr && accepted)
                         atomicOr(a.bits + s * a.words + ((k0 + i) >> 6), 1ull << ((k0 + i) & 63));
                 }
             }
-            if (TOL && last_class) {
-                double m = d2;
-                for (int off = 32; off > 0; off >>= 1) {
-                    const double t = __shfl_xor(m, off);
-                    m = t > m ? t : m;
-                }
-                if (lane == 0) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                    st_dev(dslot + (s & (kFlowHist - 1)) * dcap, static_cast<u64>(__double_as_longlong(m)));
-                }
+            if (B) {   // the next class's node, while this class's values travel
+                const int cn = last_class ? 0 : c + 1, q = cls[cn] + g;
+                if (q < cls[cn + 1]) load_ref<W>(ref, t, q, j);
             }
             // this class's halo nodes at the new version
             if (!(last_class && v == a.iters)) {
@@ -748,7 +828,15 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                     }
                 }
             }
-            if (TOL && last_class && tid == 0) {
+            if (TOL && last_class) {
+                const double m = wave_max(d2);
+                if (lane == 0) {
+                    // (the slot of the next sweep has been set back)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    st_dev(dslot + (s & (kFlowHist - 1)) * dcap, static_cast<u64>(__double_as_longlong(m)));
+                }
+            }
+            if (TOL && last_class && tid == BS - 1) {   // (a wave that rarely has halo nodes to read)
                 // sweep v runs once every sweep up to v - kFlowLag is decided;
                 // after the last sweep the final decision is awaited
                 const uint32_t need = static_cast<uint32_t>(max(v - kFlowLag + 1, 0));
@@ -823,6 +911,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double* __restrict__ coords,
                                                      FlowReport* __restrict__ rep, MeshState* __restrict__ ms)
 {
+    const u64 t_end = wall_clock64();
     const bool off = flow_off(a.vs, a.fs) || a.fs->abort != 0;
     const int n_free = a.vs->n_free, sweeps = tol ? static_cast<int>(a.fs->decided & ~kFlowStop) : a.iters;
     if (blockIdx.x == 0) {
@@ -865,6 +954,11 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
             rep->maxd = tol ? a.fs->maxd : m;
             rep->acc_last = al;
             rep->acc_total = at;
+            rep->nnz = a.nbr_end[0];
+            rep->ninc = a.tri_end[0];
+            rep->t[0] = a.fs->t_begin;
+            rep->t[1] = a.fs->t_sweep;
+            rep->t[2] = t_end;
             if (ms) ms->s = sweeps;
         }
     }
@@ -937,7 +1031,8 @@ FlowShape flow_shape(int32_t n, bool b)
 }
 constexpr int32_t kFlowMaxNodes = 512 * 500;
 constexpr int32_t kFlowMaxSweeps = 1 << 20;   // of one launch
-constexpr u64 kFlowWait = 200000000ull;       // 2 s of the 100 MHz clock
+constexpr double kTickMs = 1e-5;              // the device's constant clock runs at 100 MHz
+constexpr u64 kFlowWait = 200000000ull;       // 2 s of it
 
 size_t flow_lds_bytes(const FlowShape& p, bool b)
 {
@@ -984,7 +1079,7 @@ void launch_build(const FlowBuildArgs& b, int T, int tiles, hipStream_t st)
 }  // namespace
 
 sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, double tol, sl_report* report,
-                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, hipEvent_t* ev, bool* done)
+                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, bool* done)
 {
     *done = false;
     const int32_t n = a.n;
@@ -993,7 +1088,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     // meshes whose tiles the device holds all at once
     if (o.kernel != SL_KERNEL_AUTO || o.precision != SL_F64 || o.reorder != SL_REORDER_HILBERT || o.tile_nodes != 0 ||
         o.tile_wg_per_cu != 0 || o.block_size != 0 || iterations < 1 || iterations > kFlowMaxSweeps || n > kFlowMaxNodes ||
-        a.n_tris <= 0 || a.ninc <= 0)
+        a.n_tris <= 0 || !a.nbr_idx || !a.tri_idx || !a.tris)
         return SL_OK;
     const FlowShape p = flow_shape(n, b);
     const FlowLayout L(p.T);
@@ -1010,10 +1105,10 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     const bool want_bits = o.flags_out != nullptr;
     const size_t n_bits = want_bits ? static_cast<size_t>(words) * static_cast<size_t>(iterations) : 0;
     const size_t n_dmax = tl ? static_cast<size_t>(kFlowHist) * tiles * waves : 0;
-    const size_t bytes = Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(ValStats) * static_cast<size_t>(gb)) +
+    const size_t bytes = Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(ValStats) * static_cast<size_t>(val_groups(n))) +
                          Arena::piece(4 * static_cast<size_t>(nbk)) + Arena::piece(4 * static_cast<size_t>(nbk + 1)) +
                          scan_bytes(nbk) + 5 * Arena::piece(4 * un) + Arena::piece(sizeof(FlowState)) +
-                         Arena::piece(static_cast<size_t>(tiles) * L.bytes) + Arena::piece(3 * 16 * un) +
+                         Arena::piece(static_cast<size_t>(tiles) * L.bytes) + Arena::piece(4 * 16 * un) +
                          Arena::piece((tl ? kFlowHist : 1) * 16 * un) + Arena::piece(8 * n_dmax) +
                          Arena::piece(sizeof(FlowGroup) * static_cast<size_t>(tiles)) + Arena::piece(8 * n_bits) +
                          Arena::piece(sizeof(MeshState));
@@ -1042,11 +1137,11 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     unsigned char* rec = nullptr;
     MeshState* ms = nullptr;
     uint64_t* bits = nullptr;
-    if ((r = ar.take(&vs, 1)) || (r = ar.take(&f.part, gb)) || (r = ar.take(&f.count, nbk)) ||
+    if ((r = ar.take(&vs, 1)) || (r = ar.take(&f.part, val_groups(n))) || (r = ar.take(&f.count, nbk)) ||
         (r = ar.take(&f.start, nbk + 1)) || (r = ar.take(&f.key, un)) || (r = ar.take(&f.rank, un)) ||
         (r = ar.take(&f.new_of_old, un)) || (r = ar.take(&perm, un)) || (r = ar.take(&color, un)) ||
         (r = ar.take(&fs, 1)) || (r = ar.take(&rec, static_cast<size_t>(tiles) * L.bytes)) ||
-        (r = ar.take(&fa.ring, 3 * 2 * un)) || (r = ar.take(&fa.out, (tl ? kFlowHist : 1) * 2 * un)) ||
+        (r = ar.take(&fa.ring, 4 * 2 * un)) || (r = ar.take(&fa.out, (tl ? kFlowHist : 1) * 2 * un)) ||
         (r = ar.take(&fa.dmax, n_dmax)) || (r = ar.take(&fa.groups, static_cast<size_t>(tiles))) ||
         (r = ar.take(&bits, n_bits)) || (r = ar.take(&ms, 1)))
         return r;
@@ -1066,6 +1161,8 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     fa.iters = iterations;
     fa.tol2 = tl ? tol * tol : 0.0;
     fa.wait = kFlowWait;
+    fa.nbr_end = a.nbr_ptr + n;
+    fa.tri_end = a.tri_ptr + n;
 
     const FlowInitArgs ia{vs, fs, f.count, nbk, b ? color : nullptr, n, fa.ring + 2 * un, fa.dmax,
                           static_cast<int64_t>(n_dmax), fa.bits, static_cast<int64_t>(n_bits)};
@@ -1076,17 +1173,14 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     if (b) launch_build<true>(ba, p.T, tiles, st);
     else launch_build<false>(ba, p.T, tiles, st);
     SL_HIP(hipGetLastError());
-    SL_HIP(hipEventRecord(ev[1], st));
     if ((r = launch_flow(fa, p, b, o.accept == SL_ACCEPT_GT, tl, st))) return r;
-    SL_HIP(hipEventRecord(ev[3], st));
     FlowReport* const rep = static_cast<FlowReport*>(pad.p);
     k_flow_result<<<gb, 256, 0, st>>>(fa, tl ? 1 : 0, coords, rep, want_bits ? ms : nullptr);
     SL_HIP(hipGetLastError());
     SL_HIP(hipStreamSynchronize(st));
 
     const FlowReport h = *rep;
-    // (asymmetric rows are an error of Form B only; Form A then takes the other kernels)
-    if ((r = validation_status(h.vs.err, o))) return r;
+    // (what the checks found wrong, the other path finds and reports too)
     if (h.vs.err != 0 || h.vs.n_free == 0 || h.decline || h.abort || h.n_colors > kFlowClasses) return SL_OK;
     if (want_bits) {
         if ((r = unpermute_flags_raw(bits, words, f.new_of_old, n, h.vs.n_free, iterations, ms, o.flags_out, st))) return r;
@@ -1100,14 +1194,11 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
         std::memcpy(&rp.max_disp_sq_last, &h.maxd, sizeof(double));
         rp.accepted_last = static_cast<int64_t>(h.acc_last);
         rp.accepted_total = static_cast<int64_t>(h.acc_total);
-        float t = 0.f;
-        SL_HIP(hipEventElapsedTime(&t, ev[0], ev[1]));
-        rp.setup_ms = t;
-        SL_HIP(hipEventElapsedTime(&t, ev[1], ev[3]));
-        rp.sweep_ms = t;
+        rp.setup_ms = static_cast<double>(h.t[1] - h.t[0]) * kTickMs;
+        rp.sweep_ms = static_cast<double>(h.t[2] - h.t[1]) * kTickMs;
         // the kernel family of the mesh's size and form, as without this path
         rp.kernel_used = !b ? SL_KERNEL_TILE
-                            : (resident_fits(n, a.nnz, a.ninc, true) ? SL_KERNEL_RESIDENT : SL_KERNEL_NODE);
+                            : (resident_fits(n, h.nnz, h.ninc, true) ? SL_KERNEL_RESIDENT : SL_KERNEL_NODE);
         rp.tile_nodes = !b ? tile_size_for(o, n) : 0;
         *report = rp;
     }

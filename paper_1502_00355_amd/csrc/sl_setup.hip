@@ -247,12 +247,14 @@ struct ValArgs {
     const int32_t* tris;
     int32_t n_tris;
     const uint8_t* boundary;
-    int64_t nnz, ninc;
+    int64_t nnz, ninc;     // < 0: read from the ends of the offsets
     int check_symmetry;
     double coord_limit;    // coordinates must be below this in magnitude
 };
 
-constexpr int kRowRegs = 16;
+constexpr int kRowRegs = 16;   // row entries held in registers (k_rows_fans)
+constexpr int kRowLds = 16;    // row entries held in LDS (k_validate_nodes)
+constexpr int kSymRegs = 8;    // entries of a neighbour's row looked at together
 
 __device__ __forceinline__ bool row_has(const int32_t* __restrict__ idx, int32_t b, int32_t e, int32_t v)
 {
@@ -276,6 +278,8 @@ __global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict
                                                        const int32_t* __restrict__ tri_idx, int64_t ninc,
                                                        ValStats* __restrict__ vs)
 {
+    if (ninc < 0) ninc = tri_ptr[n];   // not known on the host
+    const bool listed = INCIDENCE && ninc > 0;
     const int64_t t = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
     if (t >= n_tris) return;
     int32_t v[3];
@@ -287,7 +291,7 @@ __global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict
     for (int k = 0; k < 3; ++k)
         if (v[k] < 0 || v[k] >= n) e |= VE_RANGE;
     if (e) atomicOr(&vs->err, e);
-    if (!INCIDENCE || (e & VE_RANGE)) return;
+    if (!listed || (e & VE_RANGE)) return;
     int32_t ob[3], oe[3];
     uint8_t fl[3];
 #pragma unroll
@@ -337,9 +341,12 @@ __device__ __forceinline__ void fold_stats(ValStats& a, const ValStats& b)
     a.box[3] = max(a.box[3], b.box[3]);
 }
 
-__device__ __forceinline__ void fold_stats_wave(ValStats& a)
+// Over each N consecutive lanes of a wave.
+template <int N>
+__device__ __forceinline__ void fold_stats_lanes(ValStats& a)
 {
-    for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+    for (int off = N / 2; off > 0; off >>= 1) {
         ValStats b;
         b.err = __shfl_xor(a.err, off);
         b.n_free = __shfl_xor(a.n_free, off);
@@ -359,106 +366,171 @@ __device__ __forceinline__ ValStats empty_stats()
     return ValStats{0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}};
 }
 
-// One work-item per node; each work-group leaves its statistics (with the
-// bounding box of its nodes' coordinates, so that no pass of its own has to
-// read them again) in a slot of its own.
+// LANES work-items per node, which share its neighbours and triangles; the
+// work-groups take the nodes in strides and each leaves its statistics (with
+// the bounding box of its nodes' coordinates, so that no pass of its own has
+// to read them again) in a slot of its own.  Rows of up to kRowLds entries are
+// held in an LDS column for the membership tests; longer ones are searched
+// in memory.  The loops over the row and the incidences are kept rolled, a
+// few loads in flight together: with the row in registers and every test
+// unrolled the kernel was 26 KB of code, and on small meshes fetching that
+// took most of its time (64 x 64 grid 16 us, 100K shuffled nodes 44 us).
+template <int LANES>
 __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __restrict__ part)
 {
-    const int32_t i = static_cast<int32_t>(blockIdx.x * kBS + threadIdx.x);
-    uint32_t e = 0;
-    int is_free = 0, deg = 0, inc = 0;
+    __shared__ int32_t s_row[kRowLds][kBS / LANES];
+    constexpr int U = 4;   // entries whose loads are in flight together
+    const int tid = threadIdx.x / LANES, sub = threadIdx.x % LANES;
+    const int64_t nnz = a.nnz >= 0 ? a.nnz : a.nbr_ptr[a.n], ninc = a.ninc >= 0 ? a.ninc : a.tri_ptr[a.n];
     ValStats me = empty_stats();
-    if (i < a.n) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && (a.nbr_ptr[0] != 0 || a.tri_ptr[0] != 0)) me.err |= VE_PTR;
+    for (int64_t i64 = static_cast<int64_t>(blockIdx.x) * (kBS / LANES) + tid; i64 < a.n;
+         i64 += static_cast<int64_t>(gridDim.x) * (kBS / LANES)) {
+        const int32_t i = static_cast<int32_t>(i64);
+        uint32_t e = 0;
+        int deg = 0, inc = 0;
         const double2 xy = reinterpret_cast<const double2*>(a.coords)[i];
-        const double x = xy.x, y = xy.y;
-        me.box[0] = me.box[2] = ord_bits(x);
-        me.box[1] = me.box[3] = ord_bits(y);
+        const uint64_t ox = ord_bits(xy.x), oy = ord_bits(xy.y);
+        me.box[0] = min(me.box[0], ox);
+        me.box[1] = min(me.box[1], oy);
+        me.box[2] = max(me.box[2], ox);
+        me.box[3] = max(me.box[3], oy);
         // finite and below the limit in magnitude (2^500 in double, 2^61 in
         // single precision): squared edge lengths, their sums and cross
         // products cannot overflow, so every quality is a finite number
-        if (!(fabs(x) < a.coord_limit) || !(fabs(y) < a.coord_limit)) e |= VE_COORD;
+        if (!(fabs(xy.x) < a.coord_limit) || !(fabs(xy.y) < a.coord_limit)) e |= VE_COORD;
         const int32_t b = a.nbr_ptr[i], en = a.nbr_ptr[i + 1];
-        const bool row_ok = 0 <= b && b <= en && en <= a.nnz;
+        const bool row_ok = 0 <= b && b <= en && en <= nnz;
         const int32_t tb = a.tri_ptr[i], te = a.tri_ptr[i + 1];
-        const bool trow_ok = 0 <= tb && tb <= te && te <= a.ninc;
+        const bool trow_ok = 0 <= tb && tb <= te && te <= ninc;
         if (!row_ok || !trow_ok) e |= VE_PTR;
-        is_free = a.boundary[i] == 0;
-        // rows of up to kRowRegs entries are held in registers for the
-        // membership tests below; longer rows are searched in memory
-        int32_t rowv[kRowRegs];
-        const bool in_regs = row_ok && en - b <= kRowRegs;
+        const bool is_free = a.boundary[i] == 0;
+        const bool in_lds = row_ok && en - b <= kRowLds;
         if (row_ok) {
             deg = en - b;
-#pragma unroll
-            for (int k = 0; k < kRowRegs; ++k) rowv[k] = (in_regs && k < deg) ? a.nbr_idx[b + k] : -1;
-            auto check = [&](int32_t j) {
-                if (j < 0 || j >= a.n) {
-                    e |= VE_RANGE;
-                    return;
-                }
-                if (j == i) e |= VE_SELF;
-                if (is_free && a.check_symmetry && a.boundary[j] == 0) {
-                    const int32_t jb = a.nbr_ptr[j], je = a.nbr_ptr[j + 1];
-                    if (!(0 <= jb && jb <= je && je <= a.nnz) || !row_has(a.nbr_idx, jb, je, i)) e |= VE_ASYM;
-                }
-            };
-            if (in_regs) {
-#pragma unroll
-                for (int k = 0; k < kRowRegs; ++k)
-                    if (k < deg) check(rowv[k]);
-            } else {
-                for (int32_t k = b; k < en; ++k) check(a.nbr_idx[k]);
-            }
             if (is_free && deg == 0) e |= VE_EMPTY;
             if (is_free && deg > kMaxValence) e |= VE_VALENCE;
-        }
-        auto in_row = [&](int32_t v) -> bool {
-            if (!in_regs) return row_has(a.nbr_idx, b, en, v);
-            bool f = false;
+            const bool sym = is_free && a.check_symmetry;
+            // U neighbours at a time; for the symmetry test their offsets
+            // and then the first kSymRegs entries of their rows together
+#pragma unroll 1
+            for (int k0 = U * sub; k0 < deg; k0 += U * LANES) {
+                int32_t j[U], jb[U], je[U];
+                bool look[U];
 #pragma unroll
-            for (int k = 0; k < kRowRegs; ++k) f |= rowv[k] == v;
-            return f;
-        };
-        if (trow_ok) {
-            inc = te - tb;
-            // incident triangles four at a time: their loads are in flight together
-            for (int32_t k0 = tb; k0 < te; k0 += 4) {
-                int32_t t[4], v[4][3];
+                for (int u = 0; u < U; ++u) j[u] = a.nbr_idx[b + min(k0 + u, deg - 1)];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) t[u] = k0 + u < te ? a.tri_idx[k0 + u] : -1;
+                for (int u = 0; u < U; ++u) {
+                    if (in_lds && k0 + u < deg) s_row[k0 + u][tid] = j[u];
+                    const bool in = j[u] >= 0 && j[u] < a.n;
+                    if (!in) e |= VE_RANGE;
+                    if (j[u] == i) e |= VE_SELF;
+                    look[u] = in && sym;
+                }
+                if (!sym) continue;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const bool ok = t[u] >= 0 && t[u] < a.n_tris;
-                    if (k0 + u < te && !ok) e |= VE_RANGE;
+                for (int u = 0; u < U; ++u) {
+                    const int32_t jj = look[u] ? j[u] : i;
+                    if (a.boundary[jj] != 0) look[u] = false;
+                    jb[u] = a.nbr_ptr[jj];
+                    je[u] = a.nbr_ptr[jj + 1];
+                }
+                int32_t x[U][kSymRegs];
 #pragma unroll
-                    for (int s3 = 0; s3 < 3; ++s3) v[u][s3] = ok ? a.tris[3 * static_cast<int64_t>(t[u]) + s3] : -1;
+                for (int u = 0; u < U; ++u) {
+                    if (look[u] && !(0 <= jb[u] && jb[u] <= je[u] && je[u] <= nnz)) {
+                        e |= VE_ASYM;
+                        look[u] = false;
+                    }
+                    if (!look[u]) jb[u] = b, je[u] = en;   // (this node's own row: any in range)
+#pragma unroll
+                    for (int q = 0; q < kSymRegs; ++q) x[u][q] = je[u] > jb[u] ? a.nbr_idx[min(jb[u] + q, je[u] - 1)] : -1;
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (!(t[u] >= 0 && t[u] < a.n_tris)) continue;
-                    const int32_t v0 = v[u][0], v1 = v[u][1], v2 = v[u][2];
-                    if (v0 != i && v1 != i && v2 != i) { e |= VE_NOTIN; continue; }
-                    // the other two vertices, in stored cyclic order after i
-                    const int32_t o1 = v0 == i ? v1 : (v1 == i ? v2 : v0);
-                    const int32_t o2 = v0 == i ? v2 : (v1 == i ? v0 : v1);
-                    if (is_free && row_ok && (!in_row(o1) || !in_row(o2))) e |= VE_MISSING;
+                for (int u = 0; u < U; ++u) {
+                    bool found = !look[u];
+#pragma unroll
+                    for (int q = 0; q < kSymRegs; ++q) found |= x[u][q] == i;
+                    look[u] = !found;
                 }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (look[u] && !row_has(a.nbr_idx, min(jb[u] + kSymRegs, je[u]), je[u], i)) e |= VE_ASYM;
             }
         }
+        // (a node's lanes are of one wave: their LDS writes are in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (trow_ok) {
+            inc = te - tb;
+            // incident triangles U at a time: their loads are in flight together
+#pragma unroll 1
+            for (int32_t k0 = tb + U * sub; k0 < te; k0 += U * LANES) {
+                int32_t t[U], v[U][3];
+#pragma unroll
+                for (int u = 0; u < U; ++u) t[u] = a.tri_idx[min(k0 + u, te - 1)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool ok = t[u] >= 0 && t[u] < a.n_tris;
+                    if (!ok) {
+                        e |= VE_RANGE;
+                        t[u] = -1;
+                    }
+#pragma unroll
+                    for (int s3 = 0; s3 < 3; ++s3) v[u][s3] = ok ? a.tris[3 * static_cast<int64_t>(t[u]) + s3] : i;
+                }
+                bool f1[U], f2[U];
+                int32_t o1[U], o2[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int32_t v0 = v[u][0], v1 = v[u][1], v2 = v[u][2];
+                    const bool has = v0 == i || v1 == i || v2 == i;
+                    if (!has) e |= VE_NOTIN;
+                    // the other two vertices, in stored cyclic order after i
+                    o1[u] = v0 == i ? v1 : (v1 == i ? v2 : v0);
+                    o2[u] = v0 == i ? v2 : (v1 == i ? v0 : v1);
+                    f1[u] = f2[u] = !has || t[u] < 0 || !is_free || !row_ok;
+                }
+                if (in_lds) {
+#pragma unroll 1
+                    for (int k = 0; k < deg; ++k) {
+                        const int32_t r = s_row[k][tid];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            f1[u] |= r == o1[u];
+                            f2[u] |= r == o2[u];
+                        }
+                    }
+                } else if (row_ok && is_free) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        if (!f1[u]) f1[u] = row_has(a.nbr_idx, b, en, o1[u]);
+                        if (!f2[u]) f2[u] = row_has(a.nbr_idx, b, en, o2[u]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (!f1[u] || !f2[u]) e |= VE_MISSING;
+            }
+        }
+        me.err |= e;
+        if (is_free && sub == 0) {
+            me.n_free += 1;
+            me.max_deg_free = max(me.max_deg_free, deg);
+            me.max_inc_free = max(me.max_inc_free, inc);
+            me.nnz_free += deg;
+            me.ninc_free += inc;
+        }
+        // (the next node's row takes this one's place: program order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    me.err = e;
-    if (is_free) {
-        me.n_free = 1;
-        me.max_deg_free = me.nnz_free = deg;
-        me.max_inc_free = me.ninc_free = inc;
-    }
-    fold_stats_wave(me);
+    fold_stats_lanes<64>(me);
     __shared__ ValStats s_part[kBS / 64];
     if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = me;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < kBS / 64; ++q) fold_stats(me, s_part[q]);
-        part[blockIdx.x] = me;
+    if (threadIdx.x < 64) {
+        me = s_part[threadIdx.x & (kBS / 64 - 1)];
+        fold_stats_lanes<kBS / 64>(me);
+        if (threadIdx.x == 0) part[blockIdx.x] = me;
     }
 }
 
@@ -470,13 +542,16 @@ __global__ __launch_bounds__(1024) void k_validate_fold(const ValStats* __restri
     __shared__ ValStats s_part[16];
     ValStats me = empty_stats();
     for (int32_t b = threadIdx.x; b < nb; b += 1024) fold_stats(me, part[b]);
-    fold_stats_wave(me);
+    fold_stats_lanes<64>(me);
     if ((threadIdx.x & 63) == 0) s_part[threadIdx.x >> 6] = me;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < 16; ++q) fold_stats(me, s_part[q]);
-        me.err |= vs->err;
-        *vs = me;
+    if (threadIdx.x < 64) {
+        me = s_part[threadIdx.x & 15];
+        fold_stats_lanes<16>(me);
+        if (threadIdx.x == 0) {
+            me.err |= vs->err;
+            *vs = me;
+        }
     }
 }
 
@@ -1034,12 +1109,22 @@ size_t mesh_block_bytes(int32_t n, int64_t nnz, int64_t ninc, const sl_options& 
     return pb;
 }
 
+// Lanes per node of the node checks: on meshes that leave most of the device
+// idle a node's checks are a serial chain of some twenty trips to memory,
+// which four lanes shorten (4K nodes 12.5 -> 8.9 us, 46K refined ones 31 ->
+// 14); with the device full, two lanes, and at many millions of nodes one
+// (1M shuffled nodes 130 -> 125 us with two, 2.2M 198 -> 176; 16.8M 572 ->
+// 579).
+static int val_lanes(int32_t n) { return n <= (1 << 18) ? 4 : (n <= (1 << 22) ? 2 : 1); }
+
+// Work-groups of the node checks, each with a slot for its statistics.
+int val_groups(int32_t n) { return std::min(div_up(static_cast<int64_t>(n) * val_lanes(n), kBS), 8192); }
+
 size_t setup_scratch_bytes(int32_t n)
 {
     const size_t un = static_cast<size_t>(n);
     const size_t rows_bytes = 2 * Arena::piece(4 * un) + 2 * scan_bytes(n);
-    const int gb = div_up(n, kBS);
-    return Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(ValStats) * static_cast<size_t>(gb)) +
+    return Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(ValStats) * static_cast<size_t>(val_groups(n))) +
            Arena::piece(4 * un) + Arena::piece(4) +
            std::max({order_bytes(n), rows_bytes, tile_scratch_bytes(),
                      2 * Arena::piece(4 * un) + Arena::piece(8)});   // the colouring's lists
@@ -1052,13 +1137,16 @@ static void queue_validation(const ValArgs& a, bool incidence, ValStats* vs, Val
 {
     if (a.n_tris > 0) {
         const int gt = div_up(a.n_tris, kBS);
-        if (incidence && a.ninc > 0)
+        if (incidence && a.ninc != 0)
             k_validate_tris<true><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
         else
             k_validate_tris<false><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
     }
-    const int gb = div_up(a.n, kBS);
-    k_validate_nodes<<<gb, kBS, 0, st>>>(a, part);
+    const int gb = val_groups(a.n);
+    const int lanes = val_lanes(a.n);
+    if (lanes == 4) k_validate_nodes<4><<<gb, kBS, 0, st>>>(a, part);
+    else if (lanes == 2) k_validate_nodes<2><<<gb, kBS, 0, st>>>(a, part);
+    else k_validate_nodes<1><<<gb, kBS, 0, st>>>(a, part);
     k_validate_fold<<<1, 1024, 0, st>>>(part, gb, vs);
 }
 
@@ -1135,7 +1223,7 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
 
     // ---- validation
     ValStats *vs = nullptr, *vpart = nullptr;
-    if ((r = scratch.take(&vs, 1)) || (r = scratch.take(&vpart, gb))) return r;
+    if ((r = scratch.take(&vs, 1)) || (r = scratch.take(&vpart, val_groups(n)))) return r;
     SL_HIP(hipMemsetAsync(vs, 0, sizeof(ValStats), st));
     ValArgs va{a.coords, n, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, a.n_tris, a.boundary,
                a.nnz, a.ninc, o.form == SL_INPLACE_COLORED, o.precision == SL_F32 ? 0x1p61 : 0x1p500};

@@ -176,6 +176,7 @@ sl_status prepare_mesh(const MeshInput& in, const sl_options& o, int32_t mesh_in
 namespace {
 
 constexpr int32_t kSweepChunk = 32;   // even
+constexpr int32_t kDirectSweeps = 4;  // even: a chunk after them starts from buffer 0
 
 // A device's static workspace, for the entry point that allocates nothing:
 // its device address and the call's timing events, both set up once per
@@ -190,6 +191,7 @@ struct StaticWorkspace {
 struct CallState {
     hipStream_t st = nullptr;
     DevMesh m;
+    PinnedPad pad;                      // the sweep state as the host reads it
     Arena aux;                          // the sweep state, the tile launches' counters, the flag words
     MeshState* state = nullptr;
     int32_t* sched = nullptr;
@@ -222,6 +224,20 @@ size_t aux_bytes(int64_t n, int32_t iterations, bool want_bits)
            (want_bits ? Arena::piece(8 * words * static_cast<size_t>(iterations)) : 0);
 }
 
+// A call's start: its sweep state, the counters zero.
+__global__ __launch_bounds__(256) void k_begin_call(MeshState* state, MeshState h0, int32_t* sched)
+{
+    const int k = static_cast<int>(blockIdx.x * 256 + threadIdx.x);
+    if (k < kTileSchedInts) sched[k] = 0;
+    if (k == 0) *state = h0;
+}
+
+// A call's end: the sweep state to pinned memory.
+__global__ void k_end_call(const MeshState* __restrict__ state, MeshState* __restrict__ out)
+{
+    if (threadIdx.x == 0) *out = *state;
+}
+
 sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const int32_t* nbr_idx,
                      const int32_t* tri_ptr, const int32_t* tri_idx, const int32_t* tris, int32_t n_tris,
                      const uint8_t* boundary, int32_t iterations, double tol, const sl_options* opts,
@@ -241,6 +257,7 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     CallState cs;
     cs.st = stream;
     cs.m.class_tiles_ok = true;   // Form B may sweep colour-class tiles
+    cs.m.one_buffer = true;       // sweep 0 reads buffer 0 and writes all of buffer 1
     if (ws) {
         // every device array from the static workspace: the mesh's arrays,
         // the setup's temporaries, then (over those) the sweep state
@@ -257,12 +274,12 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     }
     if ((r = check_arguments(in))) return r;
     // small and medium meshes: every sweep in one launch
-    bool done = false;
+    bool flowed = false;
     const SetupArgs fa{coords, n, nbr_ptr, nbr_idx, tri_ptr, tri_idx, tris, n_tris, boundary,
                        in.ends_known ? in.ends[1] : -1, in.ends_known ? in.ends[3] : -1};
-    if ((r = flow_run(fa, o, iterations, tol, report, coords, stream, ws ? ws->base : nullptr, ws ? ws->bytes : 0, &done)))
+    if ((r = flow_run(fa, o, iterations, tol, report, coords, stream, ws ? ws->base : nullptr, ws ? ws->bytes : 0, &flowed)))
         return r;
-    if (done) {
+    if (flowed) {
         if (report)
             report->total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         return SL_OK;
@@ -271,6 +288,7 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         for (auto& e : cs.ev)
             if ((r = take_timer(&e))) return r;
     SL_HIP(hipEventRecord(cs.ev[0], stream));
+    if ((r = cs.pad.init())) return r;
     if ((r = prepare_mesh(in, o, 0, cs.m, stream))) return r;
     SL_HIP(hipEventRecord(cs.ev[1], stream));
 
@@ -288,8 +306,8 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         return r;
     }
     if ((r = cs.aux.take(&cs.state, 1)) || (r = cs.aux.take(&cs.sched, kTileSchedInts))) return r;
-    SL_HIP(hipMemcpyAsync(cs.state, &h0, sizeof(MeshState), hipMemcpyHostToDevice, stream));
-    SL_HIP(hipMemsetAsync(cs.sched, 0, sizeof(int32_t) * kTileSchedInts, stream));
+    k_begin_call<<<div_up(kTileSchedInts, 256), 256, 0, stream>>>(cs.state, h0, cs.sched);
+    SL_HIP(hipGetLastError());
     if (want_bits) {
         if ((r = cs.aux.take(&cs.bits, n_bits))) return r;
         SL_HIP(hipMemsetAsync(cs.bits, 0, sizeof(uint64_t) * n_bits, stream));
@@ -343,8 +361,13 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         const size_t lds = resident_lds_bytes(cs.m.n, cs.m.n_free, cs.m.nnz_free, cs.m.ninc_free, in_place);
         if ((r = launch_sweep_resident(d_ra, 1, lds, o.layout, o.accept, stream))) return r;
     }
+    // The first few sweeps are launched directly: the device works on them
+    // while the host captures and instantiates the graph (50-90 us).
     const bool use_graph = !ws && !cs.m.resident && !cs.bits && its >= 2 * kSweepChunk;
+    int32_t done = cs.m.resident ? its : 0;
     if (use_graph) {
+        for (; done < kDirectSweeps; ++done)
+            if ((r = enqueue(done, stream))) return r;
         if ((r = take_stream(&cs.capture))) return r;
         SL_HIP(hipStreamBeginCapture(cs.capture, hipStreamCaptureModeThreadLocal));
         sl_status cr = SL_OK;
@@ -354,7 +377,7 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         if (ce != hipSuccess) return fail(SL_EDEVICE, std::string("graph capture failed: ") + hipGetErrorString(ce));
         SL_HIP(hipGraphInstantiate(&cs.exec, cs.graph, nullptr, nullptr, 0));
     }
-    for (int32_t done = cs.m.resident ? its : 0; done < its;) {
+    while (done < its) {
         const int32_t c = std::min(kSweepChunk, its - done);
         if (use_graph && c == kSweepChunk) {
             SL_HIP(hipGraphLaunch(cs.exec, stream));
@@ -364,10 +387,10 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         }
         done += c;
         if (tol2 > 0.0 && done < its) {
-            MeshState cur{};
-            SL_HIP(hipMemcpyAsync(&cur, cs.state, sizeof(MeshState), hipMemcpyDeviceToHost, stream));
+            k_end_call<<<1, 64, 0, stream>>>(cs.state, static_cast<MeshState*>(cs.pad.p));
+            SL_HIP(hipGetLastError());
             SL_HIP(hipStreamSynchronize(stream));
-            if (!cur.active) break;
+            if (!static_cast<const MeshState*>(cs.pad.p)->active) break;
         }
     }
     SL_HIP(hipEventRecord(cs.ev[3], stream));
@@ -376,9 +399,11 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     if ((r = unpermute_coords(cs.m, 0, coords, stream, o.form == SL_JACOBI ? cs.state : nullptr))) return r;
     if (o.flags_out && its > 0)
         if ((r = unpermute_flags(cs.m, cs.bits, its, cs.state, o.flags_out, stream))) return r;
-    MeshState hs{};
-    SL_HIP(hipMemcpyAsync(&hs, cs.state, sizeof(MeshState), hipMemcpyDeviceToHost, stream));
+    k_end_call<<<1, 64, 0, stream>>>(cs.state, static_cast<MeshState*>(cs.pad.p));
+    SL_HIP(hipGetLastError());
     SL_HIP(hipStreamSynchronize(stream));
+    MeshState hs{};
+    std::memcpy(&hs, cs.pad.p, sizeof(hs));
     const int32_t runs = hs.s;
 
     if (report) {

@@ -64,6 +64,8 @@ struct ValStats {
     int32_t max_deg_free;
     int32_t max_inc_free;
     int32_t nnz_free, ninc_free;   // row entries and incidences of the free nodes
+    int32_t unordered;             // != 0: some incidence row is not strictly ascending
+    int32_t check_tris;            // != 0: the triangles need a check of their own
     uint64_t box[4];               // min x, min y, max x, max y as order-preserving bit patterns
 };
 
@@ -408,6 +410,9 @@ struct DevMesh {
     int32_t precision = SL_F64;          // element type of X: double, or float for SL_F32
     void* X[2] = {nullptr, nullptr};     // one block of 4n elements: X[1] = X[0] + 2n;
                                          // AoS (x,y pairs) or SoA (x[n] then y[n]) inside each
+    // Set before setup: only X[0] needs the start positions of the free nodes
+    // (the caller's first sweep reads it and writes all of X[1]).
+    bool one_buffer = false;
     bool resident = false;               // Form A on the resident kernel (node-path arrays built)
     int32_t lane_width = 0;              // node path: > 0 sweeps with lane groups of this width
     // Tile path: Form A, or Form B on colour-class tiles (n_tile_classes > 0)

@@ -15,6 +15,7 @@
 //     of the vertices at stored positions p+1 and p+2 mod 3 (bits 2-8, 9-15).
 #include <algorithm>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "sl_common.h"
@@ -271,17 +272,11 @@ __device__ __forceinline__ bool row_has(const int32_t* __restrict__ idx, int32_t
 // order are left to the other checks.  Without `incidence` only the
 // triangle's own vertices are checked.
 constexpr int kIncRegs = 8;
-template <bool INCIDENCE>
-__global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict__ tris, int32_t n_tris, int32_t n,
-                                                       const uint8_t* __restrict__ bnd,
-                                                       const int32_t* __restrict__ tri_ptr,
-                                                       const int32_t* __restrict__ tri_idx, int64_t ninc,
-                                                       ValStats* __restrict__ vs)
+__device__ __forceinline__ void check_triangle(int64_t t, const int32_t* __restrict__ tris, int32_t n,
+                                               const uint8_t* __restrict__ bnd, const int32_t* __restrict__ tri_ptr,
+                                               const int32_t* __restrict__ tri_idx, int64_t ninc, bool listed,
+                                               ValStats* vs)
 {
-    if (ninc < 0) ninc = tri_ptr[n];   // not known on the host
-    const bool listed = INCIDENCE && ninc > 0;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
-    if (t >= n_tris) return;
     int32_t v[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) v[k] = tris[3 * t + k];
@@ -326,6 +321,21 @@ __global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict
     if (lists > 0 && lists < free_v) atomicOr(&vs->err, static_cast<uint32_t>(VI_INCIDENCE));
 }
 
+// Runs after the fold; most inputs leave it nothing to do (4096^2: 550 us of
+// random reads before that was seen).
+template <bool INCIDENCE>
+__global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict__ tris, int32_t n_tris, int32_t n,
+                                                       const uint8_t* __restrict__ bnd,
+                                                       const int32_t* __restrict__ tri_ptr,
+                                                       const int32_t* __restrict__ tri_idx, int64_t ninc, ValStats* vs)
+{
+    if (vs->check_tris == 0) return;
+    if (ninc < 0) ninc = tri_ptr[n];   // not known on the host
+    for (int64_t t = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x; t < n_tris;
+         t += static_cast<int64_t>(gridDim.x) * kBS)
+        check_triangle(t, tris, n, bnd, tri_ptr, tri_idx, ninc, INCIDENCE && ninc > 0, vs);
+}
+
 // Statistics of a wave or work-group, folded pairwise.
 __device__ __forceinline__ void fold_stats(ValStats& a, const ValStats& b)
 {
@@ -335,6 +345,7 @@ __device__ __forceinline__ void fold_stats(ValStats& a, const ValStats& b)
     a.max_inc_free = max(a.max_inc_free, b.max_inc_free);
     a.nnz_free += b.nnz_free;
     a.ninc_free += b.ninc_free;
+    a.unordered |= b.unordered;
     a.box[0] = min(a.box[0], b.box[0]);
     a.box[1] = min(a.box[1], b.box[1]);
     a.box[2] = max(a.box[2], b.box[2]);
@@ -354,6 +365,7 @@ __device__ __forceinline__ void fold_stats_lanes(ValStats& a)
         b.max_inc_free = __shfl_xor(a.max_inc_free, off);
         b.nnz_free = __shfl_xor(a.nnz_free, off);
         b.ninc_free = __shfl_xor(a.ninc_free, off);
+        b.unordered = __shfl_xor(a.unordered, off);
         for (int q = 0; q < 4; ++q)
             b.box[q] = static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(a.box[q]), off));
         fold_stats(a, b);
@@ -363,7 +375,7 @@ __device__ __forceinline__ void fold_stats_lanes(ValStats& a)
 // An empty set's statistics.
 __device__ __forceinline__ ValStats empty_stats()
 {
-    return ValStats{0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}};
+    return ValStats{0, 0, 0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}};
 }
 
 // LANES work-items per node, which share its neighbours and triangles; the
@@ -468,6 +480,12 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
                 int32_t t[U], v[U][3];
 #pragma unroll
                 for (int u = 0; u < U; ++u) t[u] = a.tri_idx[min(k0 + u, te - 1)];
+                int32_t before = k0 > tb ? a.tri_idx[k0 - 1] : -1;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (k0 + u < te && t[u] <= before) me.unordered = 1;
+                    before = t[u];
+                }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const bool ok = t[u] >= 0 && t[u] < a.n_tris;
@@ -534,9 +552,14 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
     }
 }
 
-// Folds the per-block statistics into *vs (whose error bits the triangle
-// check may already have set); one work-group, no atomics.
-__global__ __launch_bounds__(1024) void k_validate_fold(const ValStats* __restrict__ part, int32_t nb,
+// Folds the per-block statistics into *vs (one work-group, no atomics), and
+// decides whether the triangles need a check of their own.  They do not when
+// every incidence row is strictly ascending (no entry twice), every entry
+// names a triangle that holds its node, and the rows of all nodes have three
+// entries per triangle between them: a triangle has at most one entry in the
+// row of each of its distinct vertices, so it then has three distinct
+// vertices, all in range, and is in all their rows.
+__global__ __launch_bounds__(1024) void k_validate_fold(const ValStats* __restrict__ part, int32_t nb, ValArgs a,
                                                         ValStats* __restrict__ vs)
 {
     __shared__ ValStats s_part[16];
@@ -549,7 +572,9 @@ __global__ __launch_bounds__(1024) void k_validate_fold(const ValStats* __restri
         me = s_part[threadIdx.x & 15];
         fold_stats_lanes<16>(me);
         if (threadIdx.x == 0) {
-            me.err |= vs->err;
+            const int64_t ninc = a.ninc >= 0 ? a.ninc : a.tri_ptr[a.n];
+            me.check_tris = (me.err & (VE_PTR | VE_RANGE | VE_NOTIN)) != 0 || me.unordered != 0 ||
+                            ninc != 3 * static_cast<int64_t>(a.n_tris);
             *vs = me;
         }
     }
@@ -573,13 +598,17 @@ __device__ __forceinline__ uint32_t hilbert_index(int bits, uint32_t x, uint32_t
 }
 
 // Bucket of each free node: colour * 4^bits + Hilbert cell (bits may be 0).
+// Fixed nodes: buckets of 2^fixed_shift cells from fixed_base on, or none
+// (fixed_base < 0).
 __global__ __launch_bounds__(kBS) void k_bucket(const double* __restrict__ coords, const uint8_t* __restrict__ bnd,
                                                 const int32_t* __restrict__ color, int32_t n, int bits,
-                                                const ValStats* __restrict__ vs, int32_t* __restrict__ key,
+                                                int32_t fixed_base, int fixed_shift, const ValStats* __restrict__ vs, int32_t* __restrict__ key,
                                                 int32_t* __restrict__ count, int32_t* __restrict__ rank)
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
-    if (i >= n || bnd[i]) return;
+    if (i >= n) return;
+    const bool fixed = bnd[i] != 0;
+    if (fixed && fixed_base < 0) return;
     uint32_t cell = 0;
     if (bits > 0) {
         const double x0 = from_ord_bits(vs->box[0]), y0 = from_ord_bits(vs->box[1]);
@@ -592,19 +621,19 @@ __global__ __launch_bounds__(kBS) void k_bucket(const double* __restrict__ coord
         const uint32_t cy = fy <= 0.0 ? 0u : (fy >= lim ? lim : static_cast<uint32_t>(fy));
         cell = hilbert_index(bits, cx, cy);
     }
-    const int32_t k = (color ? color[i] : 0) * (1 << (2 * bits)) + static_cast<int32_t>(cell);
+    const int32_t k = fixed ? fixed_base + static_cast<int32_t>(cell >> fixed_shift)
+                            : (color ? color[i] : 0) * (1 << (2 * bits)) + static_cast<int32_t>(cell);
     key[i] = k;
     rank[i] = atomicAdd(count + k, 1);   // place inside the bucket (in no particular order)
 }
 
-__global__ __launch_bounds__(kBS) void k_bucket_scatter(const uint8_t* __restrict__ bnd, int32_t n,
-                                                        const int32_t* __restrict__ key,
+__global__ __launch_bounds__(kBS) void k_bucket_scatter(int32_t n, const int32_t* __restrict__ key,
                                                         const int32_t* __restrict__ rank,
                                                         const int32_t* __restrict__ start,
                                                         int32_t* __restrict__ new_of_old, int32_t* __restrict__ perm)
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
-    if (i >= n || bnd[i]) return;
+    if (i >= n) return;
     const int32_t pos = start[key[i]] + rank[i];
     new_of_old[i] = pos;
     perm[pos] = static_cast<int32_t>(i);
@@ -679,44 +708,83 @@ __device__ __forceinline__ void append_group(bool keep, int32_t v, int32_t* __re
     if (keep) list[s_tmp[kColorBS / 64] + s_tmp[wv] + __popcll(mask & ((1ull << lane) - 1ull))] = v;
 }
 
-constexpr int kColorRounds = 8;
+constexpr int kColorRounds = 4;    // rounds between two looks of the host
+constexpr int kColorTries = 24;    // tries of a node inside a round
 
 // One Jones-Plassmann round over the listed (uncoloured) free nodes: a node
 // whose neighbours of higher priority are all coloured takes the smallest
-// colour none of them has; the others go to the next list.  The colour a
-// node gets depends only on those neighbours' colours, so neither the
-// round nor the list order changes the result.
+// colour none of them has; the others go to the next list.  A node tries
+// several times before it gives up, so that a chain of nodes that wait for
+// each other is walked inside one launch as far as its nodes run at the same
+// time (a bounded number of tries, no waiting: 2.2M nodes take 3 rounds
+// instead of 21).  The colour a node gets depends only on those neighbours'
+// colours, so neither the rounds nor the list order change the result.
+// cnt[0]: the list's length, cnt[1]: the next one's; top: the largest colour.
 __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restrict__ nbr_ptr,
                                                      const int32_t* __restrict__ nbr_idx,
                                                      const uint8_t* __restrict__ bnd, int32_t* color,
-                                                     const int32_t* __restrict__ list, const int32_t* cnt_in,
-                                                     int32_t* __restrict__ next, int32_t* __restrict__ next_cnt)
+                                                     const int32_t* __restrict__ list, int32_t* cnt,
+                                                     int32_t* __restrict__ next, int32_t* top)
 {
+    constexpr int R = 8;
     __shared__ int32_t s_tmp[kColorBS / 64 + 1];
-    const int32_t cnt = *cnt_in;   // the list's length, left by the previous round
+    const int32_t n_list = cnt[0];   // left by the previous round
     const int32_t t = static_cast<int32_t>(blockIdx.x * kColorBS + threadIdx.x);
-    bool left = false;
-    int32_t i = -1;
-    if (t < cnt) {
+    bool left = t < n_list;
+    int32_t i = -1, c = -1;
+    if (left) {
         i = list[t];
         const uint64_t pi = splitmix64(static_cast<uint64_t>(i));
+        const int32_t b = nbr_ptr[i], d = nbr_ptr[i + 1] - b;
+        int32_t above[R];   // the first R neighbours that must have a colour first, else -1
+#pragma unroll
+        for (int j = 0; j < R; ++j) above[j] = j < d ? nbr_idx[b + j] : -1;
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+            if (above[j] >= 0 && (bnd[above[j]] != 0 || splitmix64(static_cast<uint64_t>(above[j])) < pi)) above[j] = -1;
         uint64_t used0 = 0, used1 = 0;
-        bool ready = true;
-        for (int32_t k = nbr_ptr[i]; k < nbr_ptr[i + 1]; ++k) {
-            const int32_t j = nbr_idx[k];
-            if (bnd[j] || splitmix64(static_cast<uint64_t>(j)) < pi) continue;
-            const int32_t cj = __atomic_load_n(color + j, __ATOMIC_RELAXED);
-            if (cj < 0) { ready = false; break; }
-            if (cj < 64) used0 |= 1ull << cj; else used1 |= 1ull << (cj - 64);
-        }
-        if (ready) {
-            const int32_t c = (~used0) ? __builtin_ctzll(~used0) : 64 + __builtin_ctzll(~used1);
-            __atomic_store_n(color + i, c, __ATOMIC_RELAXED);
-        } else {
-            left = true;
+        auto use = [&](int32_t cj) {
+            if (cj < 64) used0 |= 1ull << cj;
+            else used1 |= 1ull << (cj - 64);
+        };
+        for (int tries = 0; tries < kColorTries && left; ++tries) {
+            bool ready = true;
+            int32_t cj[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) cj[j] = -1;
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (above[j] >= 0)
+                    cj[j] = __hip_atomic_load(color + above[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (above[j] < 0) continue;
+                if (cj[j] >= 0) {
+                    use(cj[j]);
+                    above[j] = -1;
+                } else {
+                    ready = false;
+                }
+            }
+            if (d > R && ready)
+                for (int32_t k = b + R; k < b + d; ++k) {
+                    const int32_t j = nbr_idx[k];
+                    if (bnd[j] || splitmix64(static_cast<uint64_t>(j)) < pi) continue;
+                    const int32_t q = __hip_atomic_load(color + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (q >= 0) use(q);
+                    else ready = false;
+                }
+            if (ready) {
+                c = (~used0) ? __builtin_ctzll(~used0) : 64 + __builtin_ctzll(~used1);
+                __hip_atomic_store(color + i, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                left = false;
+            }
         }
     }
-    append_group(left, i, next, next_cnt, s_tmp);
+    append_group(left, i, next, cnt + 1, s_tmp);
+    for (int off = 32; off > 0; off >>= 1) c = max(c, __shfl_xor(c, off));
+    if ((threadIdx.x & 63) == 0 && c > __hip_atomic_load(top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(top, c);
 }
 
 // Every node uncoloured; the free ones listed (in no particular order).
@@ -729,14 +797,10 @@ __global__ __launch_bounds__(kColorBS) void k_color_init(int32_t n, const uint8_
     append_group(i < n && !bnd[i], static_cast<int32_t>(i), list, count, s_tmp);
 }
 
-__global__ __launch_bounds__(kBS) void k_max_i32(const int32_t* __restrict__ v, int32_t n, int32_t* __restrict__ out)
+// out[k] = in[k * stride] for k < n: a few words to pinned host memory.
+__global__ void k_tell(const int32_t* __restrict__ in, int32_t n, int64_t stride, int32_t* __restrict__ out)
 {
-    int32_t m = -1;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * kBS)
-        m = max(m, v[i]);
-    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0) atomicMax(out, m);
+    for (int32_t k = threadIdx.x; k < n; k += blockDim.x) out[k] = in[k * stride];
 }
 
 __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v)
@@ -890,24 +954,25 @@ __global__ __launch_bounds__(kBS) void k_fan_group(const int32_t* __restrict__ f
     split[k] = static_cast<uint32_t>(c0) | (static_cast<uint32_t>(c0 + c1) << 16);
 }
 
-// Both buffers of the ping-pong pair start at the caller's positions,
-// rounded to R (float for the single-precision form).
+// Both buffers of the ping-pong pair start at the caller's positions (X1
+// from label x1_from on), rounded to R (float for the single-precision form).
 template <typename R>
 __global__ __launch_bounds__(kBS) void k_init_coords(const double* __restrict__ coords,
                                                      const int32_t* __restrict__ perm, int32_t n, int soa,
-                                                     R* __restrict__ X0, R* __restrict__ X1)
+                                                     R* __restrict__ X0, R* __restrict__ X1, int32_t x1_from)
 {
     const int64_t k = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
     if (k >= n) return;
     const int64_t o = perm[k];
     const double2 p = *reinterpret_cast<const double2*>(coords + 2 * o);
     const R x = static_cast<R>(p.x), y = static_cast<R>(p.y);
+    const bool both = k >= x1_from;
     if (soa) {
         X0[k] = x; X0[n + k] = y;
-        X1[k] = x; X1[n + k] = y;
+        if (both) X1[k] = x, X1[n + k] = y;
     } else {
         X0[2 * k] = x; X0[2 * k + 1] = y;
-        X1[2 * k] = x; X1[2 * k + 1] = y;
+        if (both) X1[2 * k] = x, X1[2 * k + 1] = y;
     }
 }
 
@@ -965,15 +1030,19 @@ int hilbert_bits(int64_t n_free, int nc)
 
 namespace {
 
+constexpr int kFixedShift = 6;   // cells per bucket of fixed nodes: 2^6
+
 // Scratch bytes make_order takes for n nodes (at most 128 colour classes).
 size_t order_bytes(int64_t n)
 {
-    const int64_t nbk = std::max<int64_t>(4 * 128, 2 * n);
+    // (and the fixed nodes' buckets: at least 4 cells each, or a single one)
+    const int64_t nbk = std::max<int64_t>(4 * 128, 2 * n) + n / 2 + 16;
     return 3 * Arena::piece(4 * static_cast<size_t>(n + 1)) + 2 * Arena::piece(4 * static_cast<size_t>(nbk + 1)) + scan_bytes(std::max<int64_t>(n, nbk));
 }
 
 sl_status make_order(const SetupArgs& a, const sl_options& o, const uint8_t* bnd, int32_t n_free, const ValStats* vs,
-                     const int32_t* color, int32_t n_colors, DevMesh& m, hipStream_t st, Arena& scratch)
+                     const int32_t* color, int32_t n_colors, DevMesh& m, hipStream_t st, Arena& scratch,
+                     PinnedPad& pad)
 {
     const int32_t n = a.n;
     const int gb = div_up(n, kBS);
@@ -988,24 +1057,26 @@ sl_status make_order(const SetupArgs& a, const sl_options& o, const uint8_t* bnd
         // which no result depends on (rows and triangles keep their order).
         const int nc = color ? n_colors : 1;
         const int bits = hilbert_bits(n_free, nc);
-        const int64_t nbk = static_cast<int64_t>(nc) << (2 * bits);
+        // the fixed nodes' buckets follow (coarser cells: they are few)
+        const int64_t nfree_bk = static_cast<int64_t>(nc) << (2 * bits);
+        const int fshift = std::min(kFixedShift, 2 * bits);
+        const int64_t nbk = nfree_bk + (int64_t(1) << (2 * bits - fshift));
         int32_t *count = nullptr, *start = nullptr, *key = nullptr;
         if ((r = scratch.take(&count, nbk)) || (r = scratch.take(&start, nbk + 1)) || (r = scratch.take(&key, n)))
             return r;
         k_fill_i32<<<div_up(nbk, 256), 256, 0, st>>>(count, nbk, 0);
-        k_bucket<<<gb, kBS, 0, st>>>(a.coords, bnd, color, n, bits, vs, key, count, flag);
+        k_bucket<<<gb, kBS, 0, st>>>(a.coords, bnd, color, n, bits, static_cast<int32_t>(nfree_bk), fshift, vs, key, count, flag);
         if ((r = scan_exclusive(count, start, nbk, st, &scratch))) return r;
         if (color) {
-            // nc <= 128: the class starts fit the mesh's table
-            for (int c = 0; c <= nc; ++c) {
-                SL_HIP(hipMemcpyAsync(&cs[c], start + (static_cast<int64_t>(c) << (2 * bits)), sizeof(int32_t),
-                                      hipMemcpyDeviceToHost, st));
-            }
+            // nc <= 128: the class starts fit the mesh's table and the pad
+            k_tell<<<1, 64, 0, st>>>(start, nc + 1, int64_t(1) << (2 * bits), static_cast<int32_t*>(pad.p));
+            SL_HIP(hipGetLastError());
             SL_HIP(hipStreamSynchronize(st));
+            std::memcpy(cs, pad.p, sizeof(int32_t) * static_cast<size_t>(nc + 1));
         } else {
             cs[1] = n_free;
         }
-        k_bucket_scatter<<<gb, kBS, 0, st>>>(bnd, n, key, flag, start, m.new_of_old, m.perm);
+        k_bucket_scatter<<<gb, kBS, 0, st>>>(n, key, flag, start, m.new_of_old, m.perm);
     } else if (n_free > 0) {
         // stable: free nodes (by colour class when coloured) in caller order
         const int nc = color ? n_colors : 1;
@@ -1021,7 +1092,7 @@ sl_status make_order(const SetupArgs& a, const sl_options& o, const uint8_t* bnd
             cs[c + 1] = base;
         }
     }
-    if (n_free < n) {
+    if (n_free < n && (o.reorder != SL_REORDER_HILBERT || n_free == 0)) {
         k_select<<<gb, kBS, 0, st>>>(bnd, nullptr, 0, 1, n, flag);
         if ((r = scan_exclusive(flag, pos, n, st, &scratch))) return r;
         k_place<<<gb, kBS, 0, st>>>(flag, pos, n_free, n, m.new_of_old, m.perm);
@@ -1125,29 +1196,28 @@ size_t setup_scratch_bytes(int32_t n)
     const size_t un = static_cast<size_t>(n);
     const size_t rows_bytes = 2 * Arena::piece(4 * un) + 2 * scan_bytes(n);
     return Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(ValStats) * static_cast<size_t>(val_groups(n))) +
-           Arena::piece(4 * un) + Arena::piece(4) +
+           Arena::piece(4 * un) +
            std::max({order_bytes(n), rows_bytes, tile_scratch_bytes(),
-                     2 * Arena::piece(4 * un) + Arena::piece(8)});   // the colouring's lists
+                     2 * Arena::piece(4 * un) + Arena::piece(4 * (kColorRounds + 2))});   // the colouring's lists
 }
 
-// Queues the checks of one mesh's arrays; *vs (zeroed before) receives the
-// statistics, part a slot per work-group of k_validate_nodes.  incidence:
+// Queues the checks of one mesh's arrays; *vs receives the statistics, part a slot per work-group of k_validate_nodes.  incidence:
 // also whether the incidence rows agree (VI_INCIDENCE).
 static void queue_validation(const ValArgs& a, bool incidence, ValStats* vs, ValStats* part, hipStream_t st)
 {
-    if (a.n_tris > 0) {
-        const int gt = div_up(a.n_tris, kBS);
-        if (incidence && a.ninc != 0)
-            k_validate_tris<true><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
-        else
-            k_validate_tris<false><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
-    }
     const int gb = val_groups(a.n);
     const int lanes = val_lanes(a.n);
     if (lanes == 4) k_validate_nodes<4><<<gb, kBS, 0, st>>>(a, part);
     else if (lanes == 2) k_validate_nodes<2><<<gb, kBS, 0, st>>>(a, part);
     else k_validate_nodes<1><<<gb, kBS, 0, st>>>(a, part);
-    k_validate_fold<<<1, 1024, 0, st>>>(part, gb, vs);
+    k_validate_fold<<<1, 1024, 0, st>>>(part, gb, a, vs);
+    if (a.n_tris > 0) {
+        const int gt = std::min(div_up(a.n_tris, kBS), 8192);
+        if (incidence && a.ninc != 0)
+            k_validate_tris<true><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
+        else
+            k_validate_tris<false><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
+    }
 }
 
 // SL_OK, or the error that the validation's bits stand for.
@@ -1224,14 +1294,17 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     // ---- validation
     ValStats *vs = nullptr, *vpart = nullptr;
     if ((r = scratch.take(&vs, 1)) || (r = scratch.take(&vpart, val_groups(n)))) return r;
-    SL_HIP(hipMemsetAsync(vs, 0, sizeof(ValStats), st));
     ValArgs va{a.coords, n, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, a.n_tris, a.boundary,
                a.nnz, a.ninc, o.form == SL_INPLACE_COLORED, o.precision == SL_F32 ? 0x1p61 : 0x1p500};
     queue_validation(va, want_tiles && o.form == SL_JACOBI, vs, vpart, st);
     SL_HIP(hipGetLastError());
-    ValStats h{};
-    SL_HIP(hipMemcpyAsync(&h, vs, sizeof(ValStats), hipMemcpyDeviceToHost, st));
+    PinnedPad pad;   // what the host has to know, written by the kernels
+    if ((r = pad.init())) return r;
+    k_tell<<<1, 64, 0, st>>>(reinterpret_cast<const int32_t*>(vs), sizeof(ValStats) / 4, 1, static_cast<int32_t*>(pad.p));
+    SL_HIP(hipGetLastError());
     SL_HIP(hipStreamSynchronize(st));
+    ValStats h{};
+    std::memcpy(&h, pad.p, sizeof(h));
     if ((r = validation_status(h.err, o))) return r;
     m.n_free = h.n_free;
     m.max_deg = h.max_deg_free;
@@ -1243,38 +1316,39 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     int32_t* color = nullptr;
     m.n_colors = 0;
     if (o.form == SL_INPLACE_COLORED && m.n_free > 0) {
-        int32_t* remaining = nullptr;
-        if ((r = scratch.take(&color, n)) || (r = scratch.take(&remaining, 1))) return r;
-        // rounds over a shrinking list of the uncoloured free nodes
+        if ((r = scratch.take(&color, n))) return r;
+        // rounds over a shrinking list of the uncoloured free nodes; words:
+        // the largest colour, then the lists' lengths, a place per round
+        // between two looks
         const size_t cmark = scratch.mark();
-        int32_t *list = nullptr, *next = nullptr, *cnt2 = nullptr;
+        int32_t *list = nullptr, *next = nullptr, *words = nullptr;
         if ((r = scratch.take(&list, m.n_free)) || (r = scratch.take(&next, m.n_free)) ||
-            (r = scratch.take(&cnt2, 2)))
+            (r = scratch.take(&words, kColorRounds + 2)))
             return r;
-        k_fill_i32<<<1, 2, 0, st>>>(cnt2, 2, 0);
-        k_color_init<<<div_up(n, kColorBS), kColorBS, 0, st>>>(n, a.boundary, color, list, cnt2);
+        k_fill_i32<<<1, 64, 0, st>>>(words, kColorRounds + 2, 0);
+        k_color_init<<<div_up(n, kColorBS), kColorBS, 0, st>>>(n, a.boundary, color, list, words + 1);
         // rounds read their list's length on the device; the host looks at
         // it every kColorRounds rounds (rounds past the last are empty), and
         // sizes the launches by the last length it saw
-        int32_t left = m.n_free, cur = 0;
+        int32_t left = m.n_free, mx = -1;
         for (int round = 0; left > 0; round += kColorRounds) {
             if (round > m.n_free) return fail(SL_EDEVICE, "colouring made no progress");
-            for (int k = 0; k < kColorRounds; ++k) {
-                k_fill_i32<<<1, 1, 0, st>>>(cnt2 + (cur ^ 1), 1, 0);
-                k_color_round<<<div_up(left, kColorBS), kColorBS, 0, st>>>(a.nbr_ptr, a.nbr_idx, a.boundary, color,
-                                                                          list, cnt2 + cur, next, cnt2 + (cur ^ 1));
-                std::swap(list, next);
-                cur ^= 1;
+            if (round > 0) {
+                k_tell<<<1, 64, 0, st>>>(words + 1 + kColorRounds, 1, 1, words + 1);
+                k_fill_i32<<<1, 64, 0, st>>>(words + 2, kColorRounds, 0);
             }
-            SL_HIP(hipMemcpyAsync(&left, cnt2 + cur, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+            for (int k = 0; k < kColorRounds; ++k) {
+                k_color_round<<<div_up(left, kColorBS), kColorBS, 0, st>>>(a.nbr_ptr, a.nbr_idx, a.boundary, color, list,
+                                                                          words + 1 + k, next, words);
+                std::swap(list, next);
+            }
+            k_tell<<<1, 64, 0, st>>>(words, kColorRounds + 2, 1, static_cast<int32_t*>(pad.p));
+            SL_HIP(hipGetLastError());
             SL_HIP(hipStreamSynchronize(st));
+            left = static_cast<const int32_t*>(pad.p)[1 + kColorRounds];
+            mx = static_cast<const int32_t*>(pad.p)[0];
         }
         scratch.rewind(cmark);
-        k_fill_i32<<<1, 1, 0, st>>>(remaining, 1, -1);
-        k_max_i32<<<std::min(gb, 1024), kBS, 0, st>>>(color, n, remaining);
-        int32_t mx = -1;
-        SL_HIP(hipMemcpyAsync(&mx, remaining, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        SL_HIP(hipStreamSynchronize(st));
         m.n_colors = mx + 1;
         if (m.n_colors > 128) return fail(SL_ETOPO, "more than 128 colour classes");
         // the resident kernel holds a bounded number of classes: an automatic
@@ -1288,7 +1362,7 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     }
 
     // ---- node order
-    if ((r = make_order(a, o, a.boundary, m.n_free, vs, color, m.n_colors, m, st, scratch))) return r;
+    if ((r = make_order(a, o, a.boundary, m.n_free, vs, color, m.n_colors, m, st, scratch, pad))) return r;
 
     // ---- rows and fans of free nodes
     if ((r = persist.take(&m.row_ptr, static_cast<size_t>(m.n_free) + 1)) ||
@@ -1309,18 +1383,19 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     m.ninc_free = h.ninc_free;
     // coordinate buffers: one block, X[1] right after X[0], in the sweep's precision
     const size_t n2 = 2 * un;
+    const int32_t x1_from = m.one_buffer ? m.n_free : 0;
     if (m.precision == SL_F32) {
         float* xf = nullptr;
         if ((r = persist.take(&xf, 2 * n2))) return r;
         m.X[0] = xf;
         m.X[1] = xf + n2;
-        k_init_coords<float><<<gb, kBS, 0, st>>>(a.coords, m.perm, n, o.layout == SL_SOA, xf, xf + n2);
+        k_init_coords<float><<<gb, kBS, 0, st>>>(a.coords, m.perm, n, o.layout == SL_SOA, xf, xf + n2, x1_from);
     } else {
         double* xd = nullptr;
         if ((r = persist.take(&xd, 2 * n2))) return r;
         m.X[0] = xd;
         m.X[1] = xd + n2;
-        k_init_coords<double><<<gb, kBS, 0, st>>>(a.coords, m.perm, n, o.layout == SL_SOA, xd, xd + n2);
+        k_init_coords<double><<<gb, kBS, 0, st>>>(a.coords, m.perm, n, o.layout == SL_SOA, xd, xd + n2, x1_from);
     }
     // tile path for Form A (which needs consistent incidence rows: a tile
     // lists a triangle once and scores it for every own vertex) and, on
@@ -1388,7 +1463,7 @@ sl_status queue_flow_order(const SetupArgs& a, const sl_options& o, const FlowOr
                a.nnz, a.ninc, 1, 0x1p500};
     queue_validation(va, o.form == SL_JACOBI, f.vs, f.part, st);
     // (keys and ranks are in range whatever the checks find)
-    k_bucket<<<gb, kBS, 0, st>>>(a.coords, a.boundary, nullptr, n, f.bits, f.vs, f.key, f.count, f.rank);
+    k_bucket<<<gb, kBS, 0, st>>>(a.coords, a.boundary, nullptr, n, f.bits, -1, 0, f.vs, f.key, f.count, f.rank);
     sl_status r = scan_exclusive(f.count, f.start, int64_t(1) << (2 * f.bits), st, &scratch);
     if (r) return r;
     k_flow_scatter<<<gb, kBS, 0, st>>>(a.boundary, n, f.key, f.rank, f.start, f.new_of_old, f.perm);

@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstdlib>
+#include <cstring>
 
 #include "sl_common.h"
 
@@ -489,39 +490,39 @@ __global__ __launch_bounds__(256) void k_class_fan_sort(const TileWork* __restri
     }
 }
 
-// Largest halo, padded row segment and triangle list over the tiles (one
-// work-group).
-__global__ __launch_bounds__(1024) void k_tile_caps(const TileWork* __restrict__ work, int32_t nt,
-                                                    int32_t* __restrict__ mx)
+// Largest halo, padded row segment and triangle list over the tiles
+// (mx[0..2], zeroed before), 256 tiles per work-group.
+__global__ __launch_bounds__(256) void k_tile_caps(const TileWork* __restrict__ work, int32_t nt, int32_t* mx)
 {
-    __shared__ int32_t s_h[16], s_r[16], s_t[16];
-    int32_t h = 0, r = 0, c = 0;
-    for (int32_t t = threadIdx.x; t < nt; t += 1024) {
-        h = max(h, work[t].halo_cnt);
-        r = max(r, 4 * work[t].row_words);
-        c = max(c, work[t].tri_cnt);
+    __shared__ int32_t s_m[3][4];
+    const int32_t t = static_cast<int32_t>(blockIdx.x * 256 + threadIdx.x);
+    int32_t m[3] = {0, 0, 0};
+    if (t < nt) {
+        m[0] = work[t].halo_cnt;
+        m[1] = 4 * work[t].row_words;
+        m[2] = work[t].tri_cnt;
     }
-    for (int off = 32; off > 0; off >>= 1) {
-        h = max(h, __shfl_xor(h, off));
-        r = max(r, __shfl_xor(r, off));
-        c = max(c, __shfl_xor(c, off));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        s_h[threadIdx.x >> 6] = h;
-        s_r[threadIdx.x >> 6] = r;
-        s_t[threadIdx.x >> 6] = c;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        for (int off = 32; off > 0; off >>= 1) m[k] = max(m[k], __shfl_xor(m[k], off));
+        if ((threadIdx.x & 63) == 0) s_m[k][threadIdx.x >> 6] = m[k];
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < 16; ++q) {
-            h = max(h, s_h[q]);
-            r = max(r, s_r[q]);
-            c = max(c, s_t[q]);
-        }
-        mx[0] = h;
-        mx[1] = r;
-        mx[2] = c;
+    if (threadIdx.x < 3) {
+        const int32_t* const w = s_m[threadIdx.x];
+        atomicMax(mx + threadIdx.x, max(max(w[0], w[1]), max(w[2], w[3])));
     }
+}
+
+// The build's error bits and caps to pinned memory.
+__global__ void k_tile_tell(const int32_t* __restrict__ flags, int32_t* __restrict__ out)
+{
+    if (threadIdx.x < 4) out[threadIdx.x] = flags[threadIdx.x];
+}
+
+__global__ void k_tile_zero(int32_t* flags)
+{
+    if (threadIdx.x < 4) flags[threadIdx.x] = 0;
 }
 
 }  // namespace
@@ -562,7 +563,9 @@ sl_status build_tiles(const SetupArgs& a, DevMesh& m, int tile_nodes, int mesh, 
     sl_status r = SL_OK;
     int32_t* flags = nullptr;   // {err, largest halo, largest row segment, largest triangle list}
     if ((r = scratch.take(&flags, 4))) return r;
-    SL_HIP(hipMemsetAsync(flags, 0, 4 * sizeof(int32_t), st));
+    PinnedPad pad;
+    if ((r = pad.init())) return r;
+    k_tile_zero<<<1, 64, 0, st>>>(flags);
     const size_t data_bytes =
         static_cast<size_t>(classes ? class_record(static_cast<int32_t>(m.nnz_free), static_cast<int32_t>(m.ninc_free), nt, T)
                                     : tile_record(static_cast<int32_t>(m.nnz_free), static_cast<int32_t>(m.ninc_free), nt, T));
@@ -597,11 +600,12 @@ sl_status build_tiles(const SetupArgs& a, DevMesh& m, int tile_nodes, int mesh, 
         if (T == 256) k_tile_build<256, false><<<nt, kBuildBS, 0, st>>>(b);
         else k_tile_build<512, false><<<nt, kBuildBS, 0, st>>>(b);
     }
-    k_tile_caps<<<1, 1024, 0, st>>>(m.work, nt, flags + 1);
+    k_tile_caps<<<div_up(nt, 256), 256, 0, st>>>(m.work, nt, flags + 1);
+    k_tile_tell<<<1, 64, 0, st>>>(flags, static_cast<int32_t*>(pad.p));
     SL_HIP(hipGetLastError());
-    int32_t h[4] = {0, 0, 0, 0};
-    SL_HIP(hipMemcpyAsync(h, flags, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, st));
     SL_HIP(hipStreamSynchronize(st));
+    int32_t h[4];
+    std::memcpy(h, pad.p, sizeof(h));
     scratch.rewind(smark);
     if (h[0] & 1) return fail(SL_ETOPO, "triangle vertex outside its tile's neighbourhood");
     // a tile denser than the staging holds, or a halo or row segment too big

@@ -142,6 +142,7 @@ struct sl_mesh {
     int32_t cur = 0;                        // the buffer holding the current positions (Form A)
     int64_t sweeps = 0;                     // sweeps run so far (equal to state->s)
     hipStream_t own = nullptr;              // the library's stream: setup, host downloads, release
+    std::shared_ptr<sl::EventRef> mine;     // the handle's own event
     std::shared_ptr<sl::EventRef> last;     // recorded after the last work queued on the mesh
     hipStream_t last_stream = nullptr;      // where that work was queued
     hipEvent_t t0 = nullptr, t1 = nullptr;  // around the sweeps of the last smooth call
@@ -231,13 +232,14 @@ struct sl_mesh {
         return SL_OK;
     }
 
+    // (the handle's own event, recorded again: a stream that waits for the
+    // earlier record keeps doing so, and this call's work comes after it)
     sl_status mark(hipStream_t st)
     {
-        std::shared_ptr<sl::EventRef> e;
-        sl_status r = sl::new_event(&e);
-        if (r) return r;
-        SL_HIP(hipEventRecord(e->ev, st));
-        last = std::move(e);
+        sl_status r;
+        if (!mine && (r = sl::new_event(&mine))) return r;
+        SL_HIP(hipEventRecord(mine->ev, st));
+        last = mine;
         last_stream = st;
         return SL_OK;
     }

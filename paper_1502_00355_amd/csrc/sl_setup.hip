@@ -687,7 +687,7 @@ __global__ __launch_bounds__(kBS) void k_place(const int32_t* __restrict__ flag,
 // one atomic per work-group reserves the group's places (one per wave, or
 // per work-item, on a single counter would queue behind each other).  Every
 // work-item of the group must call it.
-constexpr int kColorBS = 1024;
+constexpr int kColorBS = 256;
 __device__ __forceinline__ void append_group(bool keep, int32_t v, int32_t* __restrict__ list,
                                              int32_t* __restrict__ count, int32_t* s_tmp /* [kColorBS/64 + 1] */)
 {
@@ -708,32 +708,33 @@ __device__ __forceinline__ void append_group(bool keep, int32_t v, int32_t* __re
     if (keep) list[s_tmp[kColorBS / 64] + s_tmp[wv] + __popcll(mask & ((1ull << lane) - 1ull))] = v;
 }
 
-constexpr int kColorRounds = 4;    // rounds between two looks of the host
-constexpr int kColorTries = 24;    // tries of a node inside a round
+constexpr int kColorRounds = 3;    // rounds between two looks of the host
+constexpr int kColorTries = 80;    // tries of a node inside a round
 
 // One Jones-Plassmann round over the listed (uncoloured) free nodes: a node
 // whose neighbours of higher priority are all coloured takes the smallest
 // colour none of them has; the others go to the next list.  A node tries
 // several times before it gives up, so that a chain of nodes that wait for
 // each other is walked inside one launch as far as its nodes run at the same
-// time (a bounded number of tries, no waiting: 2.2M nodes take 3 rounds
-// instead of 21).  The colour a node gets depends only on those neighbours'
+// time (a bounded number of tries, no waiting: 2.2M nodes take 2 rounds
+// instead of 21; small work-groups, whose places free up early).  The colour a node gets depends only on those neighbours'
 // colours, so neither the rounds nor the list order change the result.
-// cnt[0]: the list's length, cnt[1]: the next one's; top: the largest colour.
+// cnt[0]: the list's length, cnt[1]: the next one's; top: the largest
+// colour.  list null: the first round, over all n nodes.
 __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restrict__ nbr_ptr,
                                                      const int32_t* __restrict__ nbr_idx,
                                                      const uint8_t* __restrict__ bnd, int32_t* color,
-                                                     const int32_t* __restrict__ list, int32_t* cnt,
+                                                     const int32_t* __restrict__ list, int32_t n, int32_t* cnt,
                                                      int32_t* __restrict__ next, int32_t* top)
 {
     constexpr int R = 8;
     __shared__ int32_t s_tmp[kColorBS / 64 + 1];
-    const int32_t n_list = cnt[0];   // left by the previous round
+    const int32_t n_list = list ? cnt[0] : n;   // left by the previous round
     const int32_t t = static_cast<int32_t>(blockIdx.x * kColorBS + threadIdx.x);
-    bool left = t < n_list;
+    bool left = t < n_list && (list || !bnd[t]);
     int32_t i = -1, c = -1;
     if (left) {
-        i = list[t];
+        i = list ? list[t] : t;
         const uint64_t pi = splitmix64(static_cast<uint64_t>(i));
         const int32_t b = nbr_ptr[i], d = nbr_ptr[i + 1] - b;
         int32_t above[R];   // the first R neighbours that must have a colour first, else -1
@@ -785,16 +786,6 @@ __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restr
     for (int off = 32; off > 0; off >>= 1) c = max(c, __shfl_xor(c, off));
     if ((threadIdx.x & 63) == 0 && c > __hip_atomic_load(top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
         atomicMax(top, c);
-}
-
-// Every node uncoloured; the free ones listed (in no particular order).
-__global__ __launch_bounds__(kColorBS) void k_color_init(int32_t n, const uint8_t* __restrict__ bnd, int32_t* color,
-                                                         int32_t* __restrict__ list, int32_t* __restrict__ count)
-{
-    __shared__ int32_t s_tmp[kColorBS / 64 + 1];
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * kColorBS + threadIdx.x;
-    if (i < n) color[i] = -1;
-    append_group(i < n && !bnd[i], static_cast<int32_t>(i), list, count, s_tmp);
 }
 
 // out[k] = in[k * stride] for k < n: a few words to pinned host memory.
@@ -1326,11 +1317,11 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
             (r = scratch.take(&words, kColorRounds + 2)))
             return r;
         k_fill_i32<<<1, 64, 0, st>>>(words, kColorRounds + 2, 0);
-        k_color_init<<<div_up(n, kColorBS), kColorBS, 0, st>>>(n, a.boundary, color, list, words + 1);
+        k_fill_i32<<<div_up(n, 256), 256, 0, st>>>(color, n, -1);
         // rounds read their list's length on the device; the host looks at
         // it every kColorRounds rounds (rounds past the last are empty), and
         // sizes the launches by the last length it saw
-        int32_t left = m.n_free, mx = -1;
+        int32_t left = n, mx = -1;
         for (int round = 0; left > 0; round += kColorRounds) {
             if (round > m.n_free) return fail(SL_EDEVICE, "colouring made no progress");
             if (round > 0) {
@@ -1338,7 +1329,8 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
                 k_fill_i32<<<1, 64, 0, st>>>(words + 2, kColorRounds, 0);
             }
             for (int k = 0; k < kColorRounds; ++k) {
-                k_color_round<<<div_up(left, kColorBS), kColorBS, 0, st>>>(a.nbr_ptr, a.nbr_idx, a.boundary, color, list,
+                k_color_round<<<div_up(left, kColorBS), kColorBS, 0, st>>>(a.nbr_ptr, a.nbr_idx, a.boundary, color,
+                                                                          round + k > 0 ? list : nullptr, n,
                                                                           words + 1 + k, next, words);
                 std::swap(list, next);
             }

@@ -89,7 +89,11 @@ typedef enum {
     SL_KERNEL_AUTO = 0,  /* Form A: the tile kernel when the mesh fits it, else the node kernel.
                             Form B: the resident kernel when the mesh fits it (never in a
                             server or on a handle), else the node kernel (faster there than
-                            colour-class tiles, which SL_KERNEL_TILE asks for) */
+                            colour-class tiles, which SL_KERNEL_TILE asks for).  One-call smooths
+                            of meshes of at most 256,000 nodes, and Form A handles of such meshes,
+                            run every sweep in one launch when the other options are automatic
+                            too: one work-group per tile, all on the device at once; the report
+                            names the kernel that the mesh's size and form would otherwise take */
     SL_KERNEL_NODE = 1,  /* one work-item per free node, neighbours gathered from HBM/L2 */
     SL_KERNEL_TILE = 2,  /* work-group per tile of free nodes staged in LDS: Form A's tiles of
                             consecutive free nodes, or Form B's tiles of one colour class each
@@ -221,7 +225,7 @@ SL_API sl_status smooth_mesh_device(double* coords, int32_t n_nodes, const int32
  * library runs them one at a time (the call returns only when its work on
  * `stream` is done); the sweep loop is launched directly, not through a
  * captured graph.  The first call on a device looks up the workspace's
- * device address and creates the call's four timing events.
+ * device address.
  */
 SL_API sl_status smooth_mesh_device_noalloc(double* coords, int32_t n_nodes, const int32_t* nbr_ptr,
                                      const int32_t* nbr_idx, const int32_t* tri_ptr, const int32_t* tri_idx,
@@ -291,7 +295,9 @@ typedef struct sl_mesh sl_mesh;
 
 /* Creates a handle from host arrays (as for smooth_mesh; desc->coords gives
  * the initial positions and is not written).  Synchronous.  Device memory:
- * about 135 bytes per node in double precision, freed by sl_mesh_destroy. */
+ * about 135 bytes per node in double precision (350 for Form A meshes of at
+ * most 256,000 nodes with automatic options, whose sweeps run in one launch),
+ * freed by sl_mesh_destroy. */
 SL_API sl_status sl_mesh_create(const sl_mesh_desc* desc, const sl_options* opts, sl_mesh** out);
 
 /* The same from device arrays (as for smooth_mesh_device), read on `stream`

@@ -179,12 +179,10 @@ constexpr int32_t kSweepChunk = 32;   // even
 constexpr int32_t kDirectSweeps = 4;  // even: a chunk after them starts from buffer 0
 
 // A device's static workspace, for the entry point that allocates nothing:
-// its device address and the call's timing events, both set up once per
-// device.
+// its device address, looked up once per device.
 struct StaticWorkspace {
     unsigned char* base = nullptr;
     size_t bytes = 0;
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
 };
 
 // Everything a call allocates, released on every exit path.
@@ -196,8 +194,6 @@ struct CallState {
     MeshState* state = nullptr;
     int32_t* sched = nullptr;
     uint64_t* bits = nullptr;
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
-    bool own_events = true;             // false: a static workspace's events
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t capture = nullptr;      // where the sweep chunk is captured
@@ -209,8 +205,6 @@ struct CallState {
         (void)hipStreamSynchronize(st);
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
-        if (own_events)
-            for (auto& e : ev) give_timer(e);
     }
 };
 
@@ -229,7 +223,10 @@ __global__ __launch_bounds__(256) void k_begin_call(MeshState* state, MeshState 
 {
     const int k = static_cast<int>(blockIdx.x * 256 + threadIdx.x);
     if (k < kTileSchedInts) sched[k] = 0;
-    if (k == 0) *state = h0;
+    if (k == 0) {
+        h0.t_begin = h0.t_end = wall_clock64();
+        *state = h0;
+    }
 }
 
 // A call's end: the sweep state to pinned memory.
@@ -261,8 +258,6 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     if (ws) {
         // every device array from the static workspace: the mesh's arrays,
         // the setup's temporaries, then (over those) the sweep state
-        for (int k = 0; k < 4; ++k) cs.ev[k] = ws->ev[k];
-        cs.own_events = false;
         cs.m.region = ws->base;
         cs.m.region_bytes = ws->bytes;
         cs.m.region_after = aux_bytes(n, iterations, want_bits);
@@ -284,13 +279,8 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
             report->total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         return SL_OK;
     }
-    if (!ws)
-        for (auto& e : cs.ev)
-            if ((r = take_timer(&e))) return r;
-    SL_HIP(hipEventRecord(cs.ev[0], stream));
     if ((r = cs.pad.init())) return r;
     if ((r = prepare_mesh(in, o, 0, cs.m, stream))) return r;
-    SL_HIP(hipEventRecord(cs.ev[1], stream));
 
     const int32_t its = iterations;
     const int64_t words = (static_cast<int64_t>(cs.m.n_free) + 63) / 64;
@@ -347,7 +337,6 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     // without the graph.  The chunk is captured on a stream of the library's
     // own (the caller's may be the legacy default stream, which cannot be
     // captured) and replayed on the caller's stream.
-    SL_HIP(hipEventRecord(cs.ev[2], stream));
     if (cs.m.resident) {
         // every sweep in one launch
         const bool in_place = o.form == SL_INPLACE_COLORED;
@@ -393,7 +382,6 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
             if (!static_cast<const MeshState*>(cs.pad.p)->active) break;
         }
     }
-    SL_HIP(hipEventRecord(cs.ev[3], stream));
 
     // the result buffer and the sweeps run are read on the device: one wait
     if ((r = unpermute_coords(cs.m, 0, coords, stream, o.form == SL_JACOBI ? cs.state : nullptr))) return r;
@@ -413,11 +401,8 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
         std::memcpy(&rep.max_disp_sq_last, &hs.maxd_last, sizeof(double));
         rep.accepted_last = static_cast<int64_t>(hs.acc_last);
         rep.accepted_total = static_cast<int64_t>(hs.acc_total);
-        float ms = 0.f;
-        SL_HIP(hipEventElapsedTime(&ms, cs.ev[0], cs.ev[1]));
-        rep.setup_ms = ms;
-        SL_HIP(hipEventElapsedTime(&ms, cs.ev[2], cs.ev[3]));
-        rep.sweep_ms = ms;
+        rep.setup_ms = static_cast<double>(hs.t_begin - cs.m.t_setup) * kTickMs;
+        rep.sweep_ms = static_cast<double>(hs.t_end - hs.t_begin) * kTickMs;
         rep.total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         rep.kernel_used = kernel_used(cs.m);
         rep.tile_nodes = cs.m.tile_nodes;
@@ -443,8 +428,7 @@ struct StaticSlot {
 };
 StaticSlot g_static[64];
 
-// Sets up the current device's workspace: its address and the four timing
-// events of a call.
+// Sets up the current device's workspace: its address.
 void init_static(StaticSlot& s)
 {
     void* p = nullptr;
@@ -453,14 +437,6 @@ void init_static(StaticSlot& s)
         s.status = SL_EDEVICE;
         s.error = std::string("hipGetSymbolAddress of the static workspace failed: ") + hipGetErrorString(e);
         return;
-    }
-    for (auto& ev : s.ws.ev) {
-        e = hipEventCreate(&ev);
-        if (e != hipSuccess) {
-            s.status = SL_EDEVICE;
-            s.error = std::string("hipEventCreate failed: ") + hipGetErrorString(e);
-            return;
-        }
     }
     s.ws.base = static_cast<unsigned char*>(p);
     s.ws.bytes = kStaticWorkspaceBytes;

@@ -67,6 +67,7 @@ struct ValStats {
     int32_t unordered;             // != 0: some incidence row is not strictly ascending
     int32_t check_tris;            // != 0: the triangles need a check of their own
     uint64_t box[4];               // min x, min y, max x, max y as order-preserving bit patterns
+    uint64_t t0;                   // the device's clock when the checks began
 };
 
 // SplitMix64 output function (Steele, Lea, Flood, OOPSLA 2014), applied to
@@ -189,7 +190,12 @@ struct MeshState {
     unsigned long long maxd_last;   // last completed sweep
     unsigned long long acc_last;
     unsigned long long acc_total;
+    // the device's constant clock (kTickMs per tick) when the call's sweeps
+    // began and when the last one closed: kernels stamp it, since an event
+    // record between two kernels costs some 5 us of the device
+    unsigned long long t_begin, t_end;
 };
+constexpr double kTickMs = 1e-5;   // 100 MHz
 
 // Closes one sweep of one mesh: counts it if the mesh ran it, moves the
 // sweep's folds to the *_last fields and decides whether the next sweep
@@ -209,6 +215,7 @@ __device__ __forceinline__ void close_state(MeshState* p)
     m.acc_cur = 0;
     const double last = __longlong_as_double(static_cast<long long>(m.maxd_last));
     m.active = (m.s < m.iters) && !(m.tol2 > 0.0 && last < m.tol2);
+    m.t_end = wall_clock64();
     *p = m;
 }
 
@@ -413,6 +420,11 @@ struct DevMesh {
     // Set before setup: only X[0] needs the start positions of the free nodes
     // (the caller's first sweep reads it and writes all of X[1]).
     bool one_buffer = false;
+    // Set before setup: also the flow path's records (sl_flow.h), if the mesh
+    // is for it.
+    bool want_flow = false;
+    struct FlowMesh* flow = nullptr;
+    uint64_t t_setup = 0;                // the device's clock when setup began
     bool resident = false;               // Form A on the resident kernel (node-path arrays built)
     int32_t lane_width = 0;              // node path: > 0 sweeps with lane groups of this width
     // Tile path: Form A, or Form B on colour-class tiles (n_tile_classes > 0)
@@ -542,11 +554,6 @@ struct PinnedPad {
     ~PinnedPad();
     sl_status init();
 };
-
-// Timing events of the current device from a pool (given back by a holder
-// that has waited for the work they mark).
-sl_status take_timer(hipEvent_t* ev);
-void give_timer(hipEvent_t ev);
 
 // One caller mesh's host arrays copied into a single device allocation
 // (nnz = nbr_ptr[n], ninc = tri_ptr[n], already read by the caller), with

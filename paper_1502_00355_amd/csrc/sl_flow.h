@@ -70,4 +70,19 @@ sl_status unpermute_flags_raw(const uint64_t* bits, int64_t words, const int32_t
 sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, double tol, sl_report* report,
                    double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, bool* done);
 
+// A set-up mesh's part of the flow path (mesh handles): its tile records and
+// the exchange's slots.  Built by setup when DevMesh::want_flow is set; null
+// when the mesh does not fit.
+sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st);
+void flow_mesh_free(FlowMesh*& f, hipStream_t st);
+// Whether handles of a mesh of n nodes with these (caller's) options have one.
+bool flow_wanted(const sl_options& o, int32_t n);
+// Queues `iterations` sweeps of m from buffer `cur` into the other one (the
+// free nodes; *state counts them, as the per-sweep closes would) when the
+// device has room for its groups now; *done tells.  The caller then records
+// an event after the work and hands it to flow_mesh_settle.
+sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t iterations, double tol2, MeshState* state,
+                           hipStream_t st, bool* done);
+void flow_mesh_settle(FlowMesh* f, hipEvent_t after);
+
 }  // namespace sl

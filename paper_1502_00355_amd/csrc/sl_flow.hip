@@ -45,6 +45,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <vector>
 
 #include "sl_common.h"
 #include "sl_flow.h"
@@ -60,7 +61,7 @@ constexpr u64 kSent = 0xFFF8DEAD5EA15EA1ull;   // a quiet NaN: "not published ye
 constexpr int kFlowLag = 3;                    // sweeps a tile may run past the last decided one
 constexpr int kFlowHist = 4;                   // positions kept per node with a tolerance (kFlowLag + 1)
 constexpr uint32_t kDeclineColor = 8u;         // FlowState::decline: not coloured in time (1, 2, 4: the build)
-constexpr int32_t kFixedKey = INT32_MIN;       // halo key of fixed caller node i: kFixedKey + i
+constexpr int32_t kFixedKey = INT32_MIN;       // halo key of a fixed node: kFixedKey + its place in the positions
 
 // Tile records in global memory and, with the same layout, in LDS.
 struct FlowLayout {
@@ -142,7 +143,7 @@ struct Waiter {
 // Everything a call must find set before its kernels: counters and states
 // zero, no node coloured, no version published, no maxima.
 struct FlowInitArgs {
-    ValStats* vs;
+    ValStats* vs;        // nullable
     FlowState* fs;
     int32_t* count;
     int64_t n_count;
@@ -159,7 +160,9 @@ __global__ __launch_bounds__(256) void k_flow_init(FlowInitArgs a)
 {
     const int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * 256;
     if (blockIdx.x == 0) {
-        for (int q = threadIdx.x; q < static_cast<int>(sizeof(ValStats) / 4); q += 256) reinterpret_cast<uint32_t*>(a.vs)[q] = 0;
+        if (a.vs)
+            for (int q = threadIdx.x; q < static_cast<int>(sizeof(ValStats) / 4); q += 256)
+                reinterpret_cast<uint32_t*>(a.vs)[q] = 0;
         for (int q = threadIdx.x; q < static_cast<int>(sizeof(FlowState) / 4); q += 256) reinterpret_cast<uint32_t*>(a.fs)[q] = 0;
         __syncthreads();
         if (threadIdx.x == 0) a.fs->t_begin = wall_clock64();
@@ -284,7 +287,7 @@ struct FlowBuildArgs {
     const ValStats* vs;
     FlowState* fs;
     const int32_t* perm;
-    const int32_t* new_of_old;   // fixed nodes: negative
+    const int32_t* new_of_old;   // fixed nodes: negative, or labels from the free nodes' count on
     const int32_t* nbr_ptr;
     const int32_t* nbr_idx;
     const int32_t* tri_ptr;
@@ -359,7 +362,7 @@ __global__ __launch_bounds__((T > 256 ? T : 256)) void k_flow_build(FlowBuildArg
     auto in_tile = [&](int32_t key) { return key >= k0 && key < k0 + nown; };
     auto key_of = [&](int32_t id) {
         const int32_t l = a.new_of_old[id];
-        return l >= 0 ? l : kFixedKey + id;
+        return l >= 0 && l < n_free ? l : kFixedKey + (l >= 0 ? l : id);
     };
     auto home = [&](int32_t key) {
         return static_cast<int>((static_cast<uint32_t>(key) * 2654435761u) >> (32 - __builtin_ctz(HS)));
@@ -506,11 +509,11 @@ __global__ __launch_bounds__((T > 256 ? T : 256)) void k_flow_build(FlowBuildArg
 struct FlowArgs {
     const ValStats* vs;
     FlowState* fs;
-    const int32_t* perm;
-    const double* coords;       // the caller's positions, read only
+    const int32_t* perm;        // place of each free node in `coords`; null: its label
+    const double* coords;       // the start positions, read only
     const unsigned char* rec;
     u64* ring;                  // [4][2n]: published versions
-    double* out;                // [2n] final positions (without a tolerance), device order
+    double* out;                // [2n] final positions, device order
     double* hist;               // [kFlowHist][2n] (with a tolerance)
     u64* dmax;                  // [kFlowHist][tiles * waves]: displacement maxima per sweep (with a tolerance)
     FlowGroup* groups;          // [tiles]
@@ -519,6 +522,7 @@ struct FlowArgs {
     int64_t n;
     int32_t T, tiles;           // tiles of n nodes (the free ones may fill fewer)
     int32_t iters;
+    int32_t v0;                 // version of the start positions (mod 4)
     double tol2;
     u64 wait;                   // clock ticks a wait may take
     const int32_t *nbr_end, *tri_end;   // nbr_ptr + n, tri_ptr + n
@@ -732,10 +736,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     const uint32_t* const fans = reinterpret_cast<const uint32_t*>(rec + L.fans);
     const int nown = head[0], H = head[1], C = B ? a.fs->n_colors : 1;
     const double2* const c2 = reinterpret_cast<const double2*>(a.coords);
-    for (int i = tid; i < nown; i += BS) buf[i] = c2[a.perm[k0 + i]];
+    for (int i = tid; i < nown; i += BS) buf[i] = c2[a.perm ? a.perm[k0 + i] : k0 + i];
     for (int h = tid; h < H; h += BS) {
         const int32_t key = halo[h];
-        const double2 p = c2[key < 0 ? key - kFixedKey : a.perm[key]];
+        const double2 p = c2[key < 0 ? key - kFixedKey : (a.perm ? a.perm[key] : key)];
         buf[T + h] = p;
         if (!B) buf[span + T + h] = p;   // fixed nodes stay in both buffers
     }
@@ -756,8 +760,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         const double2* const cur = buf + (!B && (s & 1) ? span : 0);
         double2* const nxt = buf + (!B && !(s & 1) ? span : 0);
         const int v = s + 1;   // the version this sweep makes
-        u64* const ring_v = a.ring + (v & 3) * n2;
-        u64* const ring_ahead = a.ring + ((v + 2) & 3) * n2;
+        u64* const ring_v = a.ring + ((a.v0 + v) & 3) * n2;
+        u64* const ring_ahead = a.ring + ((a.v0 + v + 2) & 3) * n2;
         int acc = 0;
         bool whole = true;   // every class of the sweep done
         d2 = 0.0;
@@ -874,7 +878,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     }
     if (TOL) {
         // the sweeps after the stopping one are taken back
-        const int lag = s - static_cast<int>(stop & ~kFlowStop);
+        const int ran = static_cast<int>(stop & ~kFlowStop), lag = s - ran;
+        const double2* const fin = reinterpret_cast<const double2*>(a.hist + (ran & (kFlowHist - 1)) * n2);
+        for (int i = tid; i < nown; i += BS) reinterpret_cast<double2*>(a.out)[k0 + i] = fin[k0 + i];
         if (lag > 0) acc_total -= acc0;
         if (lag > 1) acc_total -= acc1;
         if (lag > 2) acc_total -= acc2;
@@ -906,6 +912,36 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     }
 }
 
+// The groups' words folded by a work-group of BS work-items (work-item 0 has
+// the result; non-negative doubles order as their bit patterns).
+template <int BS>
+__device__ __forceinline__ FlowGroup fold_groups(const FlowGroup* __restrict__ groups, int n)
+{
+    __shared__ FlowGroup s_f[BS / 64];
+    u64 m = 0, al = 0, at = 0;
+    for (int q = threadIdx.x; q < n; q += BS) {
+        const FlowGroup g = groups[q];
+        m = g.maxd > m ? g.maxd : m;
+        al += g.acc_last;
+        at += g.acc_total;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        const u64 t = __shfl_xor(m, o);
+        m = t > m ? t : m;
+        al += __shfl_xor(al, o);
+        at += __shfl_xor(at, o);
+    }
+    if ((threadIdx.x & 63) == 0) s_f[threadIdx.x >> 6] = FlowGroup{m, al, at};
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int q = 1; q < BS / 64; ++q) {
+            m = s_f[q].maxd > m ? s_f[q].maxd : m;
+            al += s_f[q].acc_last;
+            at += s_f[q].acc_total;
+        }
+    return FlowGroup{m, al, at};
+}
+
 // Results to the caller's order -- nothing unless every group ran to its end
 // -- and the report to the host.
 __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double* __restrict__ coords,
@@ -915,45 +951,16 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
     const bool off = flow_off(a.vs, a.fs) || a.fs->abort != 0;
     const int n_free = a.vs->n_free, sweeps = tol ? static_cast<int>(a.fs->decided & ~kFlowStop) : a.iters;
     if (blockIdx.x == 0) {
-        __shared__ u64 s_d[4], s_l[4], s_t[4];
-        double d2 = 0.0;
-        u64 al = 0, at = 0;
-        if (!off)
-            for (int q = threadIdx.x; q < (n_free + a.T - 1) / a.T; q += 256) {
-                const FlowGroup g = a.groups[q];
-                const double x = __longlong_as_double(static_cast<long long>(g.maxd));
-                d2 = x > d2 ? x : d2;
-                al += g.acc_last;
-                at += g.acc_total;
-            }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double t = __shfl_xor(d2, o);
-            d2 = t > d2 ? t : d2;
-            al += __shfl_xor(al, o);
-            at += __shfl_xor(at, o);
-        }
-        if ((threadIdx.x & 63) == 0) {
-            s_d[threadIdx.x >> 6] = static_cast<u64>(__double_as_longlong(d2));
-            s_l[threadIdx.x >> 6] = al;
-            s_t[threadIdx.x >> 6] = at;
-        }
-        __syncthreads();
+        const FlowGroup f = fold_groups<256>(a.groups, off ? 0 : (n_free + a.T - 1) / a.T);
         if (threadIdx.x == 0) {
-            // (non-negative doubles order as their bit patterns)
-            u64 m = s_d[0];
-            for (int q = 1; q < 4; ++q) {
-                m = s_d[q] > m ? s_d[q] : m;
-                al += s_l[q];
-                at += s_t[q];
-            }
             rep->vs = *a.vs;
             rep->decline = a.fs->decline;
             rep->abort = a.fs->abort;
             rep->n_colors = a.fs->n_colors;
             rep->sweeps = sweeps;
-            rep->maxd = tol ? a.fs->maxd : m;
-            rep->acc_last = al;
-            rep->acc_total = at;
+            rep->maxd = tol ? a.fs->maxd : f.maxd;
+            rep->acc_last = f.acc_last;
+            rep->acc_total = f.acc_total;
             rep->nnz = a.nbr_end[0];
             rep->ninc = a.tri_end[0];
             rep->t[0] = a.fs->t_begin;
@@ -963,10 +970,129 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
         }
     }
     if (off) return;
-    const double2* const src = reinterpret_cast<const double2*>(
-        tol ? a.hist + (sweeps & (kFlowHist - 1)) * 2 * a.n : a.out);
+    const double2* const src = reinterpret_cast<const double2*>(a.out);
     const int64_t k = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (k < n_free) reinterpret_cast<double2*>(coords)[a.perm[k]] = src[k];
+}
+
+// The end of a handle's run, one work-group: the sweep state, from the
+// groups' words.  A handle's call does not wait for the device, so when the
+// run was given up (Waiter) the sweeps are made here, tile after tile and
+// sweep after sweep from the untouched start positions: no group waits for
+// another, slow, and as good as never needed.  Calls of very few tiles and
+// sweeps (kSerialSteps) are made this way to begin with (serial): one launch.
+constexpr int kFinishBS = 512;
+template <bool GT>
+__global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, int serial, MeshState* ms)
+{
+    extern __shared__ double2 flow_lds[];
+    __shared__ double s_recip[kMaxValence + 1];
+    __shared__ double s_d2[kFinishBS / 64];
+    __shared__ u64 s_acc[kFinishBS / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, T = a.T, n_free = a.vs->n_free;
+    const int tiles = (n_free + T - 1) / T;
+    const u64 t_begin = serial ? wall_clock64() : a.fs->t_sweep;
+    if (!serial && a.fs->abort == 0) {   // (no group runs any more)
+        const FlowGroup f = fold_groups<kFinishBS>(a.groups, tiles);
+        if (tid == 0) {
+            MeshState m = *ms;
+            const int ran = tol ? static_cast<int>(a.fs->decided & ~kFlowStop) : a.iters;
+            m.iters = m.s + a.iters;
+            m.s += ran;
+            m.active = 0;
+            m.tol2 = a.tol2;
+            m.maxd_cur = m.acc_cur = 0;
+            m.maxd_last = tol ? a.fs->maxd : f.maxd;
+            m.acc_last = f.acc_last;
+            m.acc_total += f.acc_total;
+            m.t_begin = t_begin;
+            m.t_end = wall_clock64();
+            *ms = m;
+        }
+        return;
+    }
+    const FlowLayout L(T);
+    double2* const X = flow_lds;
+    unsigned char* const rec = reinterpret_cast<unsigned char*>(flow_lds + T + L.hc);
+    for (int q = tid; q <= kMaxValence; q += kFinishBS) s_recip[q] = q ? 1.0 / static_cast<double>(q) : 0.0;
+    double2* const buf[2] = {reinterpret_cast<double2*>(const_cast<double*>(a.coords)), reinterpret_cast<double2*>(a.out)};
+    int s = 0;
+    double m = 0.0;
+    u64 acc = 0, acc_total = 0;
+    while (s < a.iters) {
+        const double2* const in = buf[s & 1];
+        double2* const to = buf[(s & 1) ^ 1];
+        double d2 = 0.0;
+        u64 n_acc = 0;
+        for (int tile = 0; tile < tiles; ++tile) {
+            __syncthreads();   // the previous tile's LDS is read
+            const uint4* src = reinterpret_cast<const uint4*>(a.rec + static_cast<int64_t>(tile) * L.bytes);
+            for (int q = tid; q < L.bytes / 16; q += kFinishBS) reinterpret_cast<uint4*>(rec)[q] = src[q];
+            __syncthreads();
+            const int32_t* const head = reinterpret_cast<const int32_t*>(rec);
+            const int32_t* const halo = reinterpret_cast<const int32_t*>(rec + L.halo);
+            const int k0 = tile * T, nown = head[0];
+            for (int i = tid; i < nown; i += kFinishBS) X[i] = in[k0 + i];
+            for (int h = tid; h < head[1]; h += kFinishBS) X[T + h] = in[halo[h] < 0 ? halo[h] - kFixedKey : halo[h]];
+            __syncthreads();
+            const FlowRec t{reinterpret_cast<const uint16_t*>(rec + L.rs),   reinterpret_cast<const uint16_t*>(rec + L.fs),
+                            reinterpret_cast<const uint16_t*>(rec + L.ord),  reinterpret_cast<const uint16_t*>(rec + L.rows),
+                            reinterpret_cast<const uint32_t*>(rec + L.fans), rec + L.flag};
+            for (int q = tid; q < nown; q += kFinishBS) {
+                NodeRef ref;
+                load_ref<1>(ref, t, q, 0);
+                double2 o, c;
+                double qo, qn;
+                flow_node<1>(ref, t, X, s_recip, o, c, qo, qn);
+                const bool accepted = GT ? (qn > qo) : (qn >= qo);
+                const double nx = accepted ? c.x : o.x, ny = accepted ? c.y : o.y;
+                to[k0 + ref.i] = make_double2(nx, ny);
+                const double dx = nx - o.x, dy = ny - o.y, e = dx * dx + dy * dy;
+                d2 = e > d2 ? e : d2;
+                n_acc += accepted ? 1 : 0;
+            }
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            const double t = __shfl_xor(d2, off);
+            d2 = t > d2 ? t : d2;
+            n_acc += __shfl_xor(n_acc, off);
+        }
+        __syncthreads();
+        if (lane == 0) {
+            s_d2[wv] = d2;
+            s_acc[wv] = n_acc;
+        }
+        __threadfence();   // the next sweep reads this one's positions
+        __syncthreads();
+        m = 0.0;
+        acc = 0;
+        for (int q = 0; q < kFinishBS / 64; ++q) {
+            m = s_d2[q] > m ? s_d2[q] : m;
+            acc += s_acc[q];
+        }
+        acc_total += acc;
+        ++s;
+        if (tol && a.tol2 > 0.0 && m < a.tol2) break;
+    }
+    if ((s & 1) == 0)   // the result belongs in `out`
+        for (int k = tid; k < n_free; k += kFinishBS) buf[1][k] = buf[0][k];
+    // after a run given up: the exchange as a new mesh finds it
+    for (int64_t q = serial ? 8 * a.n : tid; q < 8 * a.n; q += kFinishBS) a.ring[q] = kSent;
+    if (tid == 0) {
+        MeshState st = *ms;
+        st.iters = st.s + a.iters;
+        st.s += s;
+        st.active = 0;
+        st.tol2 = a.tol2;
+        st.maxd_cur = st.acc_cur = 0;
+        st.maxd_last = static_cast<u64>(__double_as_longlong(m));
+        st.acc_last = acc;
+        st.acc_total += acc_total;
+        st.t_begin = t_begin;
+        st.t_end = wall_clock64();
+        *ms = st;
+        if (!serial) a.fs->abort = 0;
+    }
 }
 
 // ------------------------------------------------------------------ host --
@@ -975,15 +1101,21 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
 // unit (each takes at most 80 KB of LDS, 512 work-items and 128 registers),
 // so that all of them are resident together and none waits for a group that
 // cannot start.  A call that finds too few left takes the other kernels.
-struct FlowSlots {
-    static std::mutex mu;
-    static int used[64], limit[64];
-    int dev = -1, held = 0;
+// A handle's calls return before their work is done: it keeps its places
+// between calls, and another taker gets them once the event recorded after
+// the last of them has passed.
+class FlowSlots {
+public:
     ~FlowSlots() { give(); }
+    // Places for `groups` work-groups (kept from before, or taken now).
     bool take(int groups)
     {
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
         std::lock_guard<std::mutex> lk(mu);
+        if (held) {
+            ev = nullptr;   // in use: not to be taken back
+            return true;
+        }
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
         if (limit[dev] == 0) {
             int cus = 0;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
@@ -992,21 +1124,47 @@ struct FlowSlots {
             }
             limit[dev] = 2 * cus;
         }
+        if (used[dev] + groups > limit[dev])
+            for (size_t k = keepers.size(); k-- > 0;) {
+                FlowSlots* const f = keepers[k];
+                if (f->dev == dev && f->ev && hipEventQuery(f->ev) == hipSuccess) f->drop();
+            }
         if (used[dev] + groups > limit[dev]) return false;
         used[dev] += groups;
         held = groups;
         return true;
     }
+    // Kept until `after` has passed.
+    void keep(hipEvent_t after)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (!held) return;
+        ev = after;
+        if (std::find(keepers.begin(), keepers.end(), this) == keepers.end()) keepers.push_back(this);
+    }
     void give()
     {
-        if (!held) return;
         std::lock_guard<std::mutex> lk(mu);
+        if (held) drop();
+    }
+
+private:
+    void drop()
+    {
         used[dev] -= held;
         held = 0;
+        ev = nullptr;
+        keepers.erase(std::remove(keepers.begin(), keepers.end(), this), keepers.end());
     }
+    static std::mutex mu;
+    static int used[64], limit[64];
+    static std::vector<FlowSlots*> keepers;
+    int dev = -1, held = 0;
+    hipEvent_t ev = nullptr;   // set while kept between calls
 };
 std::mutex FlowSlots::mu;
 int FlowSlots::used[64], FlowSlots::limit[64];
+std::vector<FlowSlots*> FlowSlots::keepers;
 
 // Tile size, lanes per node and work-group size for n nodes.  The smallest
 // tiles that still give every compute unit at most one group win while they
@@ -1031,8 +1189,14 @@ FlowShape flow_shape(int32_t n, bool b)
 }
 constexpr int32_t kFlowMaxNodes = 512 * 500;
 constexpr int32_t kFlowMaxSweeps = 1 << 20;   // of one launch
-constexpr double kTickMs = 1e-5;              // the device's constant clock runs at 100 MHz
-constexpr u64 kFlowWait = 200000000ull;       // 2 s of it
+constexpr u64 kFlowWait = 200000000ull;       // 2 s of the 100 MHz clock
+
+// Automatic choices only, in double precision and the default order.
+bool flow_options(const sl_options& o, int32_t n)
+{
+    return o.kernel == SL_KERNEL_AUTO && o.precision == SL_F64 && o.reorder == SL_REORDER_HILBERT && o.tile_nodes == 0 &&
+           o.tile_wg_per_cu == 0 && o.block_size == 0 && n <= kFlowMaxNodes;
+}
 
 size_t flow_lds_bytes(const FlowShape& p, bool b)
 {
@@ -1086,9 +1250,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     const bool b = o.form == SL_INPLACE_COLORED, tl = tol > 0.0;
     // automatic choices only, in double precision and the default order, for
     // meshes whose tiles the device holds all at once
-    if (o.kernel != SL_KERNEL_AUTO || o.precision != SL_F64 || o.reorder != SL_REORDER_HILBERT || o.tile_nodes != 0 ||
-        o.tile_wg_per_cu != 0 || o.block_size != 0 || iterations < 1 || iterations > kFlowMaxSweeps || n > kFlowMaxNodes ||
-        a.n_tris <= 0 || !a.nbr_idx || !a.tri_idx || !a.tris)
+    if (!flow_options(o, n) || iterations < 1 || iterations > kFlowMaxSweeps || a.n_tris <= 0 || !a.nbr_idx || !a.tri_idx || !a.tris)
         return SL_OK;
     const FlowShape p = flow_shape(n, b);
     const FlowLayout L(p.T);
@@ -1109,7 +1271,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
                          Arena::piece(4 * static_cast<size_t>(nbk)) + Arena::piece(4 * static_cast<size_t>(nbk + 1)) +
                          scan_bytes(nbk) + 5 * Arena::piece(4 * un) + Arena::piece(sizeof(FlowState)) +
                          Arena::piece(static_cast<size_t>(tiles) * L.bytes) + Arena::piece(4 * 16 * un) +
-                         Arena::piece((tl ? kFlowHist : 1) * 16 * un) + Arena::piece(8 * n_dmax) +
+                         Arena::piece(16 * un) + Arena::piece((tl ? kFlowHist : 0) * 16 * un) + Arena::piece(8 * n_dmax) +
                          Arena::piece(sizeof(FlowGroup) * static_cast<size_t>(tiles)) + Arena::piece(8 * n_bits) +
                          Arena::piece(sizeof(MeshState));
     if (ws && bytes > ws_bytes) return SL_OK;
@@ -1141,7 +1303,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
         (r = ar.take(&f.start, nbk + 1)) || (r = ar.take(&f.key, un)) || (r = ar.take(&f.rank, un)) ||
         (r = ar.take(&f.new_of_old, un)) || (r = ar.take(&perm, un)) || (r = ar.take(&color, un)) ||
         (r = ar.take(&fs, 1)) || (r = ar.take(&rec, static_cast<size_t>(tiles) * L.bytes)) ||
-        (r = ar.take(&fa.ring, 4 * 2 * un)) || (r = ar.take(&fa.out, (tl ? kFlowHist : 1) * 2 * un)) ||
+        (r = ar.take(&fa.ring, 4 * 2 * un)) || (r = ar.take(&fa.out, 2 * un)) || (r = ar.take(&fa.hist, (tl ? kFlowHist : 0) * 2 * un)) ||
         (r = ar.take(&fa.dmax, n_dmax)) || (r = ar.take(&fa.groups, static_cast<size_t>(tiles))) ||
         (r = ar.take(&bits, n_bits)) || (r = ar.take(&ms, 1)))
         return r;
@@ -1152,7 +1314,6 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     fa.perm = perm;
     fa.coords = a.coords;
     fa.rec = rec;
-    fa.hist = fa.out;
     fa.bits = want_bits ? reinterpret_cast<u64*>(bits) : nullptr;
     fa.words = words;
     fa.n = n;
@@ -1204,5 +1365,159 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     }
     return SL_OK;
 }
+
+// -------------------------------------------------------------- handles --
+
+struct FlowMesh {
+    Arena ar;
+    FlowShape p{};
+    int tiles = 0;
+    FlowArgs fa{};
+    FlowSlots slots;
+    bool fresh = true;      // the exchange's slots are to be set up before the next run
+    uint32_t version = 0;   // of the positions, as the exchange counts them
+};
+
+namespace {
+
+__global__ void k_flow_mesh_begin(ValStats* vs, FlowState* fs, int32_t n_free)
+{
+    if (threadIdx.x == 0) {
+        *vs = ValStats{};
+        vs->n_free = n_free;
+        *fs = FlowState{};
+    }
+}
+
+__global__ void k_flow_mesh_tell(const FlowState* __restrict__ fs, uint32_t* __restrict__ out)
+{
+    if (threadIdx.x == 0) *out = fs->decline;
+}
+
+template <bool GT>
+sl_status launch_finish_v(const FlowArgs& a, const FlowShape& p, bool tol, bool serial, MeshState* state, hipStream_t st)
+{
+    const FlowLayout L(p.T);
+    const size_t lds = static_cast<size_t>(p.T + L.hc) * 16 + static_cast<size_t>(L.bytes);
+    k_flow_finish<GT><<<1, kFinishBS, lds, st>>>(a, tol ? 1 : 0, serial ? 1 : 0, state);
+    SL_HIP(hipGetLastError());
+    return SL_OK;
+}
+
+sl_status launch_finish(const FlowArgs& a, const FlowShape& p, bool gt, bool tol, bool serial, MeshState* state,
+                        hipStream_t st)
+{
+    return gt ? launch_finish_v<true>(a, p, tol, serial, state, st) : launch_finish_v<false>(a, p, tol, serial, state, st);
+}
+
+// Tiles times sweeps up to which one work-group makes them all: 4 tile steps
+// take some 15 us, about what the two launches of a run take before and
+// after its sweeps.
+constexpr int64_t kSerialSteps = 4;
+
+}  // namespace
+
+bool flow_wanted(const sl_options& o, int32_t n)
+{
+    return flow_options(o, n) && o.form == SL_JACOBI && o.layout == SL_AOS;
+}
+
+void flow_mesh_free(FlowMesh*& f, hipStream_t st)
+{
+    if (!f) return;
+    f->ar.release(st);
+    delete f;
+    f = nullptr;
+}
+
+sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st)
+{
+    const size_t un = static_cast<size_t>(m.n);
+    auto* f = new FlowMesh;
+    f->p = flow_shape(m.n, false);
+    f->tiles = div_up(m.n, f->p.T);
+    const FlowLayout L(f->p.T);
+    const size_t n_dmax = static_cast<size_t>(kFlowHist) * f->tiles * (f->p.BS / 64);
+    FlowArgs& fa = f->fa;
+    unsigned char* rec = nullptr;
+    ValStats* vs = nullptr;
+    PinnedPad pad;
+    sl_status r = pad.init();
+    if (r || (r = f->ar.reserve(Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(FlowState)) +
+                                    Arena::piece(static_cast<size_t>(f->tiles) * L.bytes) + Arena::piece(4 * 16 * un) +
+                                    Arena::piece(kFlowHist * 16 * un) + Arena::piece(8 * n_dmax) +
+                                    Arena::piece(sizeof(FlowGroup) * static_cast<size_t>(f->tiles)),
+                                st)) ||
+        (r = f->ar.take(&vs, 1)) || (r = f->ar.take(&fa.fs, 1)) ||
+        (r = f->ar.take(&rec, static_cast<size_t>(f->tiles) * L.bytes)) || (r = f->ar.take(&fa.ring, 8 * un)) ||
+        (r = f->ar.take(&fa.hist, kFlowHist * 2 * un)) || (r = f->ar.take(&fa.dmax, n_dmax)) ||
+        (r = f->ar.take(&fa.groups, static_cast<size_t>(f->tiles)))) {
+        flow_mesh_free(f, st);
+        return r;
+    }
+    fa.vs = vs;
+    fa.rec = rec;
+    fa.n = m.n;
+    fa.T = f->p.T;
+    fa.tiles = f->tiles;
+    fa.wait = kFlowWait;
+    k_flow_mesh_begin<<<1, 64, 0, st>>>(vs, fa.fs, m.n_free);
+    const FlowBuildArgs ba{vs, fa.fs, m.perm, m.new_of_old, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, nullptr, rec};
+    launch_build<false>(ba, f->p.T, f->tiles, st);
+    k_flow_mesh_tell<<<1, 64, 0, st>>>(fa.fs, static_cast<uint32_t*>(pad.p));
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
+        flow_mesh_free(f, st);
+        return fail(SL_EDEVICE, "building the flow records failed");
+    }
+    if (*static_cast<const uint32_t*>(pad.p) != 0 || m.n_free == 0) {
+        flow_mesh_free(f, st);   // does not fit: the tile path
+        return SL_OK;
+    }
+    m.flow = f;
+    return SL_OK;
+}
+
+sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t iterations, double tol2, MeshState* state,
+                           hipStream_t st, bool* done)
+{
+    *done = false;
+    FlowMesh* const f = m.flow;
+    const bool tl = tol2 > 0.0;
+    // a captured stream's work may run any number of times, later: not with places taken now
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (!f || iterations < 2 || iterations > kFlowMaxSweeps) return SL_OK;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return SL_OK;
+    }
+    const bool gt = accept == SL_ACCEPT_GT;
+    FlowArgs a = f->fa;
+    a.coords = static_cast<const double*>(m.X[cur]);
+    a.out = static_cast<double*>(m.X[cur ^ 1]);
+    a.iters = iterations;
+    a.tol2 = tol2;
+    if (static_cast<int64_t>(f->tiles) * iterations <= kSerialSteps) {
+        *done = true;
+        return launch_finish(a, f->p, gt, tl, true, state, st);
+    }
+    if (!f->slots.take(f->tiles + 1)) return SL_OK;   // (+ 1: a run with a tolerance has a controller)
+    if (f->fresh || tl) {
+        // (a run with a tolerance leaves groups some sweeps apart)
+        f->version = 0;
+        const FlowInitArgs ia{nullptr, a.fs, nullptr, 0, nullptr, m.n, a.ring + 2 * static_cast<int64_t>(m.n), a.dmax,
+                              tl ? static_cast<int64_t>(kFlowHist) * f->tiles * (f->p.BS / 64) : 0, nullptr, 0};
+        k_flow_init<<<std::min(div_up(m.n, 256), 1024), 256, 0, st>>>(ia);
+        SL_HIP(hipGetLastError());
+    }
+    a.v0 = static_cast<int32_t>(f->version & 3u);
+    sl_status r = launch_flow(a, f->p, false, gt, tl, st);
+    if (r || (r = launch_finish(a, f->p, gt, tl, false, state, st))) return r;
+    f->fresh = tl;
+    f->version += static_cast<uint32_t>(iterations);
+    *done = true;
+    return SL_OK;
+}
+
+void flow_mesh_settle(FlowMesh* f, hipEvent_t after) { f->slots.keep(after); }
 
 }  // namespace sl

@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "sl_common.h"
+#include "sl_flow.h"
 
 namespace sl {
 
@@ -53,6 +54,7 @@ __global__ void k_begin_run(MeshState* __restrict__ s, int32_t n, int32_t iters,
     m.tol2 = tol2;
     m.maxd_cur = 0;
     m.acc_cur = 0;
+    m.t_begin = m.t_end = wall_clock64();
     s[i] = m;
 }
 
@@ -132,7 +134,7 @@ __global__ __launch_bounds__(256) void k_copy_buffers(const MergeSrc* __restrict
 
 struct sl_mesh {
     int device = 0;
-    sl_options o{};
+    sl_options o{}, o0{};                   // with automatic values resolved; the defaults
     int32_t wg_auto = 0;
     int32_t block = 0;
     sl::DevMesh m;
@@ -145,8 +147,7 @@ struct sl_mesh {
     std::shared_ptr<sl::EventRef> mine;     // the handle's own event
     std::shared_ptr<sl::EventRef> last;     // recorded after the last work queued on the mesh
     hipStream_t last_stream = nullptr;      // where that work was queued
-    hipEvent_t t0 = nullptr, t1 = nullptr;  // around the sweeps of the last smooth call
-    bool timed = false;
+    bool timed = false;                     // the state's clock stamps are of a smooth call
     double setup_ms = 0.0;
     hipGraph_t graph[2] = {nullptr, nullptr};   // a chunk of sweeps from buffer 0 / buffer 1
     hipGraphExec_t exec[2] = {nullptr, nullptr};
@@ -164,8 +165,6 @@ struct sl_mesh {
             (void)hipStreamSynchronize(own);
             sl::give_stream(own);
         }
-        if (t0) (void)hipEventDestroy(t0);
-        if (t1) (void)hipEventDestroy(t1);
     }
 
     bool tiles() const { return o.form == SL_JACOBI && m.tile_nodes > 0; }
@@ -290,8 +289,6 @@ sl_status finish_create(sl_mesh* h, std::chrono::steady_clock::time_point t0)
         return r;
     SL_HIP(hipMemsetAsync(h->state, 0, sizeof(MeshState), h->own));
     SL_HIP(hipMemsetAsync(h->sched, 0, sizeof(int32_t) * kTileSchedInts, h->own));
-    SL_HIP(hipEventCreate(&h->t0));
-    SL_HIP(hipEventCreate(&h->t1));
     if ((r = h->mark(h->own))) return r;
     SL_HIP(hipStreamSynchronize(h->own));
     h->setup_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
@@ -313,10 +310,28 @@ sl_status smooth_handle(sl_mesh* h, int32_t iterations, double tol, hipStream_t 
     if (h->sweeps + iterations > INT32_MAX) return fail(SL_EINVAL, "more than 2^31 sweeps on one mesh");
     const double tol2 = tol > 0.0 ? tol * tol : 0.0;
     if ((r = h->after_last(st))) return r;
-    SL_HIP(hipEventRecord(h->t0, st));
+    const bool jacobi = h->o.form == SL_JACOBI;
+    if (h->m.flow) {
+        // all the sweeps in one launch, from the current buffer into the other
+        bool ran = false;
+        if ((r = flow_mesh_sweeps(h->m, h->cur, h->o.accept, iterations, tol2, h->state, st, &ran))) return r;
+        if (ran) {
+            h->cur ^= 1;
+            h->timed = true;
+            if ((r = h->mark(st))) return r;
+            flow_mesh_settle(h->m.flow, h->mine->ev);
+            if (tol2 > 0.0) {
+                MeshState ms{};
+                if ((r = read_state(h, &ms, st))) return r;
+                h->sweeps = ms.s;
+            } else {
+                h->sweeps += iterations;
+            }
+            return SL_OK;
+        }
+    }
     k_begin_run<<<1, 64, 0, st>>>(h->state, 1, iterations, tol2);
     SL_HIP(hipGetLastError());
-    const bool jacobi = h->o.form == SL_JACOBI;
     int32_t done = 0;
     while (done < iterations) {
         const int32_t c = std::min(kHandleChunk, iterations - done);
@@ -348,7 +363,6 @@ sl_status smooth_handle(sl_mesh* h, int32_t iterations, double tol, hipStream_t 
         if (jacobi) h->cur = (h->cur + iterations) & 1;
         h->sweeps += iterations;
     }
-    SL_HIP(hipEventRecord(h->t1, st));
     h->timed = true;
     return h->mark(st);
 }
@@ -362,11 +376,7 @@ void fill_report(const sl_mesh* h, const MeshState& ms, sl_report* rep)
     r.accepted_last = static_cast<int64_t>(ms.acc_last);
     r.accepted_total = static_cast<int64_t>(ms.acc_total);
     r.setup_ms = h->setup_ms;
-    if (h->timed) {
-        float ms_ = 0.f;
-        if (hipEventElapsedTime(&ms_, h->t0, h->t1) == hipSuccess) r.sweep_ms = ms_;
-        else (void)hipGetLastError();
-    }
+    if (h->timed && ms.t_end > ms.t_begin) r.sweep_ms = static_cast<double>(ms.t_end - ms.t_begin) * kTickMs;
     r.kernel_used = kernel_used(h->m);
     r.tile_nodes = h->m.tile_nodes;
     *rep = r;
@@ -387,6 +397,7 @@ sl_status sl_mesh_create(const sl_mesh_desc* desc, const sl_options* opts, sl_me
     *out = nullptr;
     if (!desc) return fail(SL_EINVAL, "null mesh description");
     auto h = std::make_unique<sl_mesh>();
+    sl_options_default(&h->o0);
     sl_status r = handle_options(opts, &h->o, &h->wg_auto);
     if (r) return r;
     h->block = h->o.block_size;
@@ -394,6 +405,7 @@ sl_status sl_mesh_create(const sl_mesh_desc* desc, const sl_options* opts, sl_me
     keep_pool_warm();
     if ((r = take_stream(&h->own))) return r;
     h->m.class_tiles_ok = true;
+    h->m.want_flow = opts ? flow_wanted(*opts, desc->n_nodes) : flow_wanted(h->o0, desc->n_nodes);
     if ((r = upload_and_prepare(*desc, h->o, 0, h->m, h->own))) return r;
     if ((r = finish_create(h.get(), t0))) return r;
     *out = h.release();
@@ -411,6 +423,7 @@ sl_status sl_mesh_create_device(const double* coords, int32_t n_nodes, const int
     if (!out) return fail(SL_EINVAL, "null output pointer");
     *out = nullptr;
     auto h = std::make_unique<sl_mesh>();
+    sl_options_default(&h->o0);
     sl_status r = handle_options(opts, &h->o, &h->wg_auto);
     if (r) return r;
     h->block = h->o.block_size;
@@ -421,6 +434,7 @@ sl_status sl_mesh_create_device(const double* coords, int32_t n_nodes, const int
     hipStream_t st = static_cast<hipStream_t>(stream);
     MeshInput in{coords, n_nodes, nbr_ptr, nbr_idx, tri_ptr, tri_idx, tris, n_tris, boundary};
     h->m.class_tiles_ok = true;
+    h->m.want_flow = opts ? flow_wanted(*opts, n_nodes) : flow_wanted(h->o0, n_nodes);
     if ((r = prepare_mesh(in, h->o, 0, h->m, st))) return r;
     SL_HIP(hipStreamSynchronize(st));
     if ((r = finish_create(h.get(), t0))) return r;

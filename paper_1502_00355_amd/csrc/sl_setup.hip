@@ -375,7 +375,7 @@ __device__ __forceinline__ void fold_stats_lanes(ValStats& a)
 // An empty set's statistics.
 __device__ __forceinline__ ValStats empty_stats()
 {
-    return ValStats{0, 0, 0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}};
+    return ValStats{0, 0, 0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}, 0};
 }
 
 // LANES work-items per node, which share its neighbours and triangles; the
@@ -395,6 +395,7 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
     const int tid = threadIdx.x / LANES, sub = threadIdx.x % LANES;
     const int64_t nnz = a.nnz >= 0 ? a.nnz : a.nbr_ptr[a.n], ninc = a.ninc >= 0 ? a.ninc : a.tri_ptr[a.n];
     ValStats me = empty_stats();
+    const uint64_t t0 = wall_clock64();
     if (blockIdx.x == 0 && threadIdx.x == 0 && (a.nbr_ptr[0] != 0 || a.tri_ptr[0] != 0)) me.err |= VE_PTR;
     for (int64_t i64 = static_cast<int64_t>(blockIdx.x) * (kBS / LANES) + tid; i64 < a.n;
          i64 += static_cast<int64_t>(gridDim.x) * (kBS / LANES)) {
@@ -548,7 +549,10 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
     if (threadIdx.x < 64) {
         me = s_part[threadIdx.x & (kBS / 64 - 1)];
         fold_stats_lanes<kBS / 64>(me);
-        if (threadIdx.x == 0) part[blockIdx.x] = me;
+        if (threadIdx.x == 0) {
+            me.t0 = t0;
+            part[blockIdx.x] = me;
+        }
     }
 }
 
@@ -575,6 +579,7 @@ __global__ __launch_bounds__(1024) void k_validate_fold(const ValStats* __restri
             const int64_t ninc = a.ninc >= 0 ? a.ninc : a.tri_ptr[a.n];
             me.check_tris = (me.err & (VE_PTR | VE_RANGE | VE_NOTIN)) != 0 || me.unordered != 0 ||
                             ninc != 3 * static_cast<int64_t>(a.n_tris);
+            me.t0 = part[0].t0;
             *vs = me;
         }
     }
@@ -1105,6 +1110,7 @@ sl_status scan_exclusive(const int32_t* in, int32_t* out, int64_t n, hipStream_t
 
 void devmesh_free(DevMesh& m, hipStream_t st)
 {
+    flow_mesh_free(m.flow, st);
     block_give(m.block, st);
     m.perm = m.new_of_old = m.row_ptr = m.nbr = m.fan_ptr = nullptr;
     m.fan = nullptr;
@@ -1286,7 +1292,7 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     ValStats *vs = nullptr, *vpart = nullptr;
     if ((r = scratch.take(&vs, 1)) || (r = scratch.take(&vpart, val_groups(n)))) return r;
     ValArgs va{a.coords, n, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, a.n_tris, a.boundary,
-               a.nnz, a.ninc, o.form == SL_INPLACE_COLORED, o.precision == SL_F32 ? 0x1p61 : 0x1p500};
+               a.nnz, a.ninc, o.form == SL_INPLACE_COLORED || m.want_flow, o.precision == SL_F32 ? 0x1p61 : 0x1p500};
     queue_validation(va, want_tiles && o.form == SL_JACOBI, vs, vpart, st);
     SL_HIP(hipGetLastError());
     PinnedPad pad;   // what the host has to know, written by the kernels
@@ -1298,6 +1304,7 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     std::memcpy(&h, pad.p, sizeof(h));
     if ((r = validation_status(h.err, o))) return r;
     m.n_free = h.n_free;
+    m.t_setup = h.t0;
     m.max_deg = h.max_deg_free;
     m.max_inc = h.max_inc_free;
 
@@ -1398,6 +1405,8 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     if (want_tiles && tiles_ok &&
         (r = build_tiles(a, m, tile_size_for(o, n), mesh, st, persist, scratch, !jacobi)))
         return r;
+    // the flow path besides the tiles, for meshes whose rows are symmetric
+    if (m.want_flow && m.tile_nodes > 0 && (h.err & VE_ASYM) == 0 && (r = flow_mesh_build(a, m, st))) return r;
     if (m.tile_nodes == 0 && m.precision == SL_F32 && m.n_free > 0)
         return fail(SL_EINVAL, tiles_ok ? "single precision needs the tile path, and this mesh does not fit it"
                                         : "single precision needs the tile path, which needs every free vertex of "

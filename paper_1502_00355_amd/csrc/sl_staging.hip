@@ -263,12 +263,10 @@ void give_stream(hipStream_t st)
 
 namespace {
 
-// Free pads and event sets, per device.  Both pools are bounded by what is
-// in use at once, and keep at most kKept of each.
+// Free pads per device: bounded by what is in use at once, at most kKept kept.
 constexpr size_t kKept = 64;
 std::mutex g_small_mu;
 std::vector<void*> g_pads[64];
-std::vector<hipEvent_t> g_timers[64];
 
 }  // namespace
 
@@ -302,37 +300,6 @@ PinnedPad::~PinnedPad()
         }
     }
     (void)hipHostFree(p);
-}
-
-sl_status take_timer(hipEvent_t* ev)
-{
-    *ev = nullptr;
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(SL_EDEVICE, "no current device");
-    {
-        std::lock_guard<std::mutex> lk(g_small_mu);
-        if (!g_timers[dev].empty()) {
-            *ev = g_timers[dev].back();
-            g_timers[dev].pop_back();
-            return SL_OK;
-        }
-    }
-    SL_HIP(hipEventCreate(ev));
-    return SL_OK;
-}
-
-void give_timer(hipEvent_t ev)
-{
-    if (!ev) return;
-    int dev = -1;
-    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 64) {
-        std::lock_guard<std::mutex> lk(g_small_mu);
-        if (g_timers[dev].size() < 4 * kKept) {
-            g_timers[dev].push_back(ev);
-            return;
-        }
-    }
-    (void)hipEventDestroy(ev);
 }
 
 namespace {

@@ -590,6 +590,7 @@ __global__ __launch_bounds__(kResBS) void k_sweep_resident(const ResidentArgs* _
         ms.maxd_cur = 0;
         ms.acc_cur = 0;
         ms.active = 0;
+        ms.t_end = wall_clock64();
         *a.state = ms;
     }
 }

@@ -141,3 +141,53 @@ def test_calls_at_once():
     for t in ts:
         t.join()
     assert not bad
+
+
+def handle_check(m, calls, accept="ge", **opts):
+    """A handle smoothed by several calls (sweeps, tolerance), against the
+    oracle continued the same way."""
+    h = sl.Mesh(m, accept=accept, **opts)
+    X = m.copy()
+    total = acc = 0
+    for iters, tol in calls:
+        print("handle %s n=%d iters=%d tol=%g %s" % (m.name, m.n_nodes, iters, tol, accept), flush=True)
+        h.smooth_async(iters, tol)
+        ref = oracle.smooth(X, iters, tol=tol, accept_gt=accept == "gt", threads=oracle.max_threads())
+        X.coords = ref.coords
+        total += ref.iterations_run
+        acc += int(ref.accepted.sum())
+        got, rep = h.download()
+        assert (got == ref.coords).all()
+        assert rep.iterations_run == total and rep.accepted_total == acc
+        if ref.iterations_run:
+            assert rep.accepted_last == int(ref.accepted[-1]) and rep.max_disp_sq_last == ref.disp[-1]
+    assert rep.kernel_used == sl.KERNELS["tile"]
+    h.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(3, 3), (10, 8), (10, 12), (66, 63), (130, 128), (129, 256), (257, 256), (500, 512),
+                                   (502, 512)])
+def test_handles(nx, ny):
+    """Runs that follow each other (the exchange goes on where it was), with
+    and without a tolerance, of one sweep (not on this path), of few tiles and
+    sweeps (one work-group makes them) and beyond the path's size."""
+    m = grid(nx, ny)
+    long = 40 if m.n_nodes < 40000 else 9
+    handle_check(m, [(2, 0.0), (3, 0.0), (1, 0.0), (4, 0.0), (long, 1e-9), (2, 1e-30), (5, 0.0), (2, 0.0), (0, 0.0)])
+    handle_check(m, [(2, 1e-30), (2, 10.0), (7, 0.0)], accept="gt")
+
+
+def test_handles_at_once():
+    """More handles at work at once than the device holds tiles for; each
+    gets its result, and the places pass from one to the next."""
+    import torch
+    ms = [grid(120 + 9 * k, 170, seed=k) for k in range(7)]
+    hs = [sl.Mesh(m) for m in ms]
+    sts = [torch.cuda.Stream() for _ in ms]
+    for _ in range(3):
+        for h, st in zip(hs, sts):
+            h.smooth_async(12, stream=st)
+    for h, m in zip(hs, ms):
+        assert (h.download()[0] == oracle.smooth(m, 36, threads=oracle.max_threads()).coords).all()
+    for h in hs:
+        h.close()

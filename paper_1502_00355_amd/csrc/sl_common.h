@@ -66,6 +66,8 @@ struct ValStats {
     int32_t nnz_free, ninc_free;   // row entries and incidences of the free nodes
     int32_t unordered;             // != 0: some incidence row is not strictly ascending
     int32_t check_tris;            // != 0: the triangles need a check of their own
+    int32_t uncovered;             // != 0: some free node's row has an entry in none of its triangles
+    int32_t check_sym;             // != 0: the symmetry of the rows needs a check of its own
     uint64_t box[4];               // min x, min y, max x, max y as order-preserving bit patterns
     uint64_t t0;                   // the device's clock when the checks began
 };

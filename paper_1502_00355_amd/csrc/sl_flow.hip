@@ -1128,6 +1128,7 @@ public:
             for (size_t k = keepers.size(); k-- > 0;) {
                 FlowSlots* const f = keepers[k];
                 if (f->dev == dev && f->ev && hipEventQuery(f->ev) == hipSuccess) f->drop();
+                else (void)hipGetLastError();   // (a query's "not ready" is not an error)
             }
         if (used[dev] + groups > limit[dev]) return false;
         used[dev] += groups;

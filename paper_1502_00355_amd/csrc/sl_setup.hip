@@ -255,7 +255,6 @@ struct ValArgs {
 
 constexpr int kRowRegs = 16;   // row entries held in registers (k_rows_fans)
 constexpr int kRowLds = 16;    // row entries held in LDS (k_validate_nodes)
-constexpr int kSymRegs = 8;    // entries of a neighbour's row looked at together
 
 __device__ __forceinline__ bool row_has(const int32_t* __restrict__ idx, int32_t b, int32_t e, int32_t v)
 {
@@ -321,14 +320,34 @@ __device__ __forceinline__ void check_triangle(int64_t t, const int32_t* __restr
     if (lists > 0 && lists < free_v) atomicOr(&vs->err, static_cast<uint32_t>(VI_INCIDENCE));
 }
 
-// Runs after the fold; most inputs leave it nothing to do (4096^2: 550 us of
-// random reads before that was seen).
+// What the fold found to need a check of its own.  Most inputs leave it
+// nothing to do (4096^2: 550 us of random reads before that was seen; the
+// symmetry test within the node checks 40-70 us at 2.2M nodes).
 template <bool INCIDENCE>
-__global__ __launch_bounds__(kBS) void k_validate_tris(const int32_t* __restrict__ tris, int32_t n_tris, int32_t n,
+__global__ __launch_bounds__(kBS) void k_validate_rest(const int32_t* __restrict__ tris, int32_t n_tris, int32_t n,
                                                        const uint8_t* __restrict__ bnd,
+                                                       const int32_t* __restrict__ nbr_ptr,
+                                                       const int32_t* __restrict__ nbr_idx,
                                                        const int32_t* __restrict__ tri_ptr,
                                                        const int32_t* __restrict__ tri_idx, int64_t ninc, ValStats* vs)
 {
+    if (vs->check_sym != 0) {
+        // each neighbour of a free node that is free too lists the node
+        const int64_t nnz = nbr_ptr[n];
+        for (int64_t i64 = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x; i64 < n;
+             i64 += static_cast<int64_t>(gridDim.x) * kBS) {
+            const int32_t i = static_cast<int32_t>(i64), b = nbr_ptr[i], en = nbr_ptr[i + 1];
+            if (bnd[i] != 0 || !(0 <= b && b <= en && en <= nnz)) continue;
+            bool bad = false;
+            for (int32_t k = b; k < en; ++k) {
+                const int32_t j = nbr_idx[k];
+                if (j < 0 || j >= n || bnd[j] != 0) continue;
+                const int32_t jb = nbr_ptr[j], je = nbr_ptr[j + 1];
+                bad |= !(0 <= jb && jb <= je && je <= nnz) || !row_has(nbr_idx, jb, je, i);
+            }
+            if (bad) atomicOr(&vs->err, static_cast<uint32_t>(VE_ASYM));
+        }
+    }
     if (vs->check_tris == 0) return;
     if (ninc < 0) ninc = tri_ptr[n];   // not known on the host
     for (int64_t t = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x; t < n_tris;
@@ -346,6 +365,7 @@ __device__ __forceinline__ void fold_stats(ValStats& a, const ValStats& b)
     a.nnz_free += b.nnz_free;
     a.ninc_free += b.ninc_free;
     a.unordered |= b.unordered;
+    a.uncovered |= b.uncovered;
     a.box[0] = min(a.box[0], b.box[0]);
     a.box[1] = min(a.box[1], b.box[1]);
     a.box[2] = max(a.box[2], b.box[2]);
@@ -366,6 +386,7 @@ __device__ __forceinline__ void fold_stats_lanes(ValStats& a)
         b.nnz_free = __shfl_xor(a.nnz_free, off);
         b.ninc_free = __shfl_xor(a.ninc_free, off);
         b.unordered = __shfl_xor(a.unordered, off);
+        b.uncovered = __shfl_xor(a.uncovered, off);
         for (int q = 0; q < 4; ++q)
             b.box[q] = static_cast<uint64_t>(__shfl_xor(static_cast<unsigned long long>(a.box[q]), off));
         fold_stats(a, b);
@@ -375,7 +396,7 @@ __device__ __forceinline__ void fold_stats_lanes(ValStats& a)
 // An empty set's statistics.
 __device__ __forceinline__ ValStats empty_stats()
 {
-    return ValStats{0, 0, 0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}, 0};
+    return ValStats{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, {~0ull, ~0ull, 0ull, 0ull}, 0};
 }
 
 // LANES work-items per node, which share its neighbours and triangles; the
@@ -423,56 +444,22 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
             deg = en - b;
             if (is_free && deg == 0) e |= VE_EMPTY;
             if (is_free && deg > kMaxValence) e |= VE_VALENCE;
-            const bool sym = is_free && a.check_symmetry;
-            // U neighbours at a time; for the symmetry test their offsets
-            // and then the first kSymRegs entries of their rows together
 #pragma unroll 1
             for (int k0 = U * sub; k0 < deg; k0 += U * LANES) {
-                int32_t j[U], jb[U], je[U];
-                bool look[U];
+                int32_t j[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) j[u] = a.nbr_idx[b + min(k0 + u, deg - 1)];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if (in_lds && k0 + u < deg) s_row[k0 + u][tid] = j[u];
-                    const bool in = j[u] >= 0 && j[u] < a.n;
-                    if (!in) e |= VE_RANGE;
+                    if (j[u] < 0 || j[u] >= a.n) e |= VE_RANGE;
                     if (j[u] == i) e |= VE_SELF;
-                    look[u] = in && sym;
                 }
-                if (!sym) continue;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int32_t jj = look[u] ? j[u] : i;
-                    if (a.boundary[jj] != 0) look[u] = false;
-                    jb[u] = a.nbr_ptr[jj];
-                    je[u] = a.nbr_ptr[jj + 1];
-                }
-                int32_t x[U][kSymRegs];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (look[u] && !(0 <= jb[u] && jb[u] <= je[u] && je[u] <= nnz)) {
-                        e |= VE_ASYM;
-                        look[u] = false;
-                    }
-                    if (!look[u]) jb[u] = b, je[u] = en;   // (this node's own row: any in range)
-#pragma unroll
-                    for (int q = 0; q < kSymRegs; ++q) x[u][q] = je[u] > jb[u] ? a.nbr_idx[min(jb[u] + q, je[u] - 1)] : -1;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    bool found = !look[u];
-#pragma unroll
-                    for (int q = 0; q < kSymRegs; ++q) found |= x[u][q] == i;
-                    look[u] = !found;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u)
-                    if (look[u] && !row_has(a.nbr_idx, min(jb[u] + kSymRegs, je[u]), je[u], i)) e |= VE_ASYM;
             }
         }
         // (a node's lanes are of one wave: their LDS writes are in order)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint32_t covered = 0;   // the row entries found in the node's triangles
         if (trow_ok) {
             inc = te - tb;
             // incident triangles U at a time: their loads are in flight together
@@ -513,11 +500,14 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
 #pragma unroll 1
                     for (int k = 0; k < deg; ++k) {
                         const int32_t r = s_row[k][tid];
+                        bool hit = false;
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             f1[u] |= r == o1[u];
                             f2[u] |= r == o2[u];
+                            hit |= r == o1[u] || r == o2[u];
                         }
+                        covered |= hit ? 1u << k : 0u;
                     }
                 } else if (row_ok && is_free) {
 #pragma unroll
@@ -532,6 +522,9 @@ __global__ __launch_bounds__(kBS) void k_validate_nodes(ValArgs a, ValStats* __r
             }
         }
         me.err |= e;
+#pragma unroll
+        for (int off = LANES / 2; off > 0; off >>= 1) covered |= __shfl_xor(covered, off);
+        if (is_free && (!in_lds || covered != (1u << deg) - 1u)) me.uncovered = 1;
         if (is_free && sub == 0) {
             me.n_free += 1;
             me.max_deg_free = max(me.max_deg_free, deg);
@@ -579,6 +572,11 @@ __global__ __launch_bounds__(1024) void k_validate_fold(const ValStats* __restri
             const int64_t ninc = a.ninc >= 0 ? a.ninc : a.tri_ptr[a.n];
             me.check_tris = (me.err & (VE_PTR | VE_RANGE | VE_NOTIN)) != 0 || me.unordered != 0 ||
                             ninc != 3 * static_cast<int64_t>(a.n_tris);
+            // Rows are symmetric when nothing is wrong so far and every free
+            // node's row holds vertices of its own triangles only: the
+            // triangle that puts j into i's row is in j's list too (above),
+            // and j's row holds its vertices.
+            me.check_sym = a.check_symmetry != 0 && (me.err != 0 || me.check_tris != 0 || me.uncovered != 0);
             me.t0 = part[0].t0;
             *vs = me;
         }
@@ -1208,13 +1206,13 @@ static void queue_validation(const ValArgs& a, bool incidence, ValStats* vs, Val
     else if (lanes == 2) k_validate_nodes<2><<<gb, kBS, 0, st>>>(a, part);
     else k_validate_nodes<1><<<gb, kBS, 0, st>>>(a, part);
     k_validate_fold<<<1, 1024, 0, st>>>(part, gb, a, vs);
-    if (a.n_tris > 0) {
-        const int gt = std::min(div_up(a.n_tris, kBS), 8192);
-        if (incidence && a.ninc != 0)
-            k_validate_tris<true><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
-        else
-            k_validate_tris<false><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.tri_ptr, a.tri_idx, a.ninc, vs);
-    }
+    const int gt = std::min(std::max(div_up(a.n_tris, kBS), div_up(a.n, kBS)), 8192);   // (n > 0)
+    if (incidence && a.ninc != 0)
+        k_validate_rest<true><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.nbr_ptr, a.nbr_idx, a.tri_ptr,
+                                                  a.tri_idx, a.ninc, vs);
+    else
+        k_validate_rest<false><<<gt, kBS, 0, st>>>(a.tris, a.n_tris, a.n, a.boundary, a.nbr_ptr, a.nbr_idx, a.tri_ptr,
+                                                   a.tri_idx, a.ninc, vs);
 }
 
 // SL_OK, or the error that the validation's bits stand for.

@@ -117,6 +117,29 @@ def test_rows_that_are_not_symmetric():
         check(m, 8, form="colored")
 
 
+def with_entries(m, pairs):
+    """m with further entries (i, j) at the end of node i's row."""
+    m = m.copy()
+    for i, j in pairs:
+        m.nbr_idx = np.insert(m.nbr_idx, int(m.nbr_ptr[i + 1]), j).astype(np.int32)
+        m.nbr_ptr = m.nbr_ptr.copy()
+        m.nbr_ptr[i + 1:] += 1
+    return m
+
+
+@pytest.mark.parametrize("size", [12, 90, 300, 600])
+def test_neighbours_of_no_triangle(size):
+    """Entries that no triangle explains: taken by Form B when both nodes
+    list each other, or when the other is fixed; refused when one does not."""
+    m = meshgen.make_grid(size, "random", 0.2, 5)
+    free = np.flatnonzero(m.boundary == 0)
+    i, j, f = int(free[2]), int(free[-2]), int(np.flatnonzero(m.boundary)[-1])
+    check(with_entries(m, [(i, j), (j, i), (i, f)]), 2, form="colored")
+    for pair in [(i, j), (j, i)]:
+        with pytest.raises(sl.SmartlapError, match="not symmetric"):
+            sl.smooth_mesh_device(*sl.to_device(with_entries(m, [pair]), "cuda:0"), iterations=2, form="colored")
+
+
 def test_calls_at_once():
     """More calls at once, each on its own stream, than the device holds
     tiles for: some run on the other kernels, all give the same results."""

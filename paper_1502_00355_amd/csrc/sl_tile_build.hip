@@ -21,8 +21,9 @@ namespace sl {
 namespace {
 
 constexpr int kTileMaxDeg = 16;   // row entries, and incidences, per own node on average over a tile
-constexpr int kBuildBS = 256;
-constexpr int kBuildU = 4;        // entries a work-item takes per chunk: their gathers are in flight together
+constexpr int kRowU = 8;          // row entries, and incidences, of a node held in registers by the tile build
+constexpr int kClassBS = 512;
+constexpr int kClassU = 4;        // entries a work-item of the class build takes per chunk: their loads are in flight together
 
 // ------------------------------------------------------ block primitives --
 
@@ -48,40 +49,42 @@ __device__ int block_excl_scan(int v, int* total, int* s_warp)
     return base + x - v;
 }
 
-// Open-addressing set of node labels in LDS (-1 = empty slot), linear
-// probing from the label's low bits: halo labels come in runs of nearby
-// labels, which then land in nearby slots with few collisions.  A
-// colour-class tile's halo is a run in each of the other classes' label
-// ranges, runs whose low bits overlap: MIX starts the probe at a
-// multiplicative hash of the label instead.  Probing stops after HS slots,
-// so a full table reports failure instead of looping.
-template <int HS, bool MIX>
+// Open-addressing set of caller node ids in LDS (-1 = empty slot), probed
+// linearly from a multiplicative hash: the ids are runs of grid rows, ranges
+// of a shuffled order, or anything else, and their low bits may all be alike.
+// Probing stops after HS slots, so a full table reports failure (-1) instead
+// of looping.
+template <int HS>
 __device__ __forceinline__ int set_home(int32_t key)
 {
-    if (!MIX) return key & (HS - 1);
     return static_cast<int>((static_cast<uint32_t>(key) * 2654435761u) >> (32 - __builtin_ctz(HS)));
 }
 
-template <int HS, bool MIX>
-__device__ bool set_insert(int32_t* tab, int32_t key)
+// *won: the key was not there before.
+template <int HS>
+__device__ __forceinline__ int set_insert(int32_t* tab, int32_t key, bool* won)
 {
-    int s = set_home<HS, MIX>(key);
+    int s = set_home<HS>(key);
+    *won = false;
+#pragma unroll 1
     for (int p = 0; p < HS; ++p) {
         const int32_t cur = tab[s];
-        if (cur == key) return true;
+        if (cur == key) return s;
         if (cur == -1) {
             const int32_t prev = atomicCAS(&tab[s], -1, key);
-            if (prev == -1 || prev == key) return true;
+            *won = prev == -1;
+            if (prev == -1 || prev == key) return s;
         }
         s = (s + 1) & (HS - 1);
     }
-    return false;
+    return -1;
 }
 
-template <int HS, bool MIX>
+template <int HS>
 __device__ int set_find(const int32_t* tab, int32_t key)
 {
-    int s = set_home<HS, MIX>(key);
+    int s = set_home<HS>(key);
+#pragma unroll 1
     for (int p = 0; p < HS; ++p) {
         const int32_t cur = tab[s];
         if (cur == key) return s;
@@ -92,6 +95,11 @@ __device__ int set_find(const int32_t* tab, int32_t key)
 }
 
 // ------------------------------------------------------------ tile build --
+
+// A triangle of the caller's array, in one 12-byte load.
+struct Corners {
+    int32_t v0, v1, v2;
+};
 
 struct TileBuildArgs {
     const int32_t* perm;
@@ -149,242 +157,317 @@ __host__ __device__ __forceinline__ int64_t class_record(int32_t row_start, int3
 }
 __host__ __device__ __forceinline__ int64_t class_halo_at(int T) { return 2 * halo_at(T) + align16(4 * static_cast<int64_t>(T)); }
 
-// One work-group per tile, in one pass: every output of tile k goes to a
-// place fixed by the row and incidence offsets of its first node, so no
-// tile needs another's counts.
-//   Halo: every neighbour of an own node that is not own, once, in the
-//   order of an LDS hash set (local index T + position).
+// Writes the R words of s_w grouped by which of their vertices are own nodes
+// (indices below T): all three first, then the patterns with two, then with
+// one, in the order of s_w inside a group.  Each of the BS work-items takes a
+// contiguous segment; its counts per group are packed 16 bits each (R is
+// below 2^16).
+template <int T, int BS>
+__device__ __forceinline__ void group_words(const uint64_t* s_w, int R, uint64_t* __restrict__ out,
+                                            uint64_t (*s_cnt)[BS / 64])
+{
+    // rank of each own-vertex pattern (bit r: vertex r is own)
+    constexpr uint32_t kRank = (0u << 28) | (1u << 12) | (2u << 20) | (3u << 24) | (4u << 4) | (5u << 8) |
+                               (6u << 16) | (7u << 0);
+    auto rank = [&](uint64_t w) -> uint32_t {
+        const uint32_t lo = static_cast<uint32_t>(w), hi = static_cast<uint32_t>(w >> 32);
+        const uint32_t p = ((lo & 0xFFFFu) < T) | (((lo >> 16) < T) << 1) | ((hi < T) << 2);
+        return (kRank >> (4u * p)) & 7u;
+    };
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int per = (R + BS - 1) / BS, b = min(R, tid * per), e = min(R, b + per);
+    uint64_t cnt[2] = {0, 0};
+    for (int j = b; j < e; ++j) {
+        const uint32_t k = rank(s_w[j]);
+        const uint64_t one = 1ull << (16u * (k & 3u));
+        cnt[0] += k < 4u ? one : 0;
+        cnt[1] += k < 4u ? 0 : one;
+    }
+    uint64_t at[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        uint64_t x = cnt[c];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint64_t y = static_cast<uint64_t>(__shfl_up(static_cast<unsigned long long>(x), off));
+            if (lane >= off) x += y;
+        }
+        if (lane == 63) s_cnt[c][wv] = x;
+        at[c] = x - cnt[c];
+    }
+    __syncthreads();
+    uint64_t tot[2] = {0, 0};
+#pragma unroll
+    for (int q = 0; q < BS / 64; ++q)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const uint64_t x = s_cnt[c][q];
+            if (q < wv) at[c] += x;
+            tot[c] += x;
+        }
+    uint32_t base = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        at[k >> 2] += static_cast<uint64_t>(base) << (16 * (k & 3));
+        base += static_cast<uint32_t>(tot[k >> 2] >> (16 * (k & 3))) & 0xFFFFu;
+    }
+    for (int j = b; j < e; ++j) {
+        const uint64_t w = s_w[j];
+        const uint32_t k = rank(w), sh = 16u * (k & 3u);
+        out[((k < 4u ? at[0] : at[1]) >> sh) & 0xFFFFu] = w;
+        at[0] += k < 4u ? 1ull << sh : 0;
+        at[1] += k < 4u ? 0 : 1ull << sh;
+    }
+}
+
+// One work-group per Form A tile, one work-item per own node, in one pass:
+// every output of tile k goes to a place fixed by the row and incidence
+// offsets of its first node, so no tile needs another's counts.
+//   Halo: every neighbour of an own node that is not own, once, numbered by
+//   the work-item that first put it into the LDS set: in the order of the own
+//   nodes, so that neighbouring entries are neighbours in memory (local
+//   index T + number).
 //   Rows: the tile's neighbour rows in local indices, one segment padded to
 //   4 entries.
 //   Triangles: each triangle incident to an own node, listed once per tile,
-//   by its own vertex of smallest label, in incidence order.
-// The tile's row entries and incidences are walked as flat ranges, a few
-// per work-item at a time, so the dependent gathers (entry -> neighbour or
-// triangle -> device label) of different entries overlap.  An entry's own
-// node is found from the owner of its 16-entry block, stepping forward over
-// the node offsets (a node has at least one row entry); the small LDS
-// footprint lets more tiles build at once.  Neither the halo order nor the triangle order
-// changes a result: sums run over rows, minima are exact.
-// CLS: a colour-class tile (Form B).  Its nodes are spread out (no two
-// adjacent), so its halo is several times longer and the halo set has 8 T
-// slots instead of 4 T; and instead of triangle words it gets one fan entry
-// per incidence, in incidence order: the node's position p in the
-// triangle's stored order and the row slots of the vertices at p+1 and
-// p+2 (mod 3), p | slot << 2 | slot << 9, with the fan starts.
-template <int T, bool CLS>
-__global__ __launch_bounds__(kBuildBS) void k_tile_build(TileBuildArgs a)
+//   by its own vertex of smallest label, grouped by which of its vertices are
+//   own nodes (all three first, then the patterns with two, then with one),
+//   in incidence order inside a group.  The sweep evaluates a vertex's
+//   candidate quality only for own vertices; with the list grouped, the lanes
+//   of a wave mostly agree on which of the three evaluations to skip.
+// Neither the halo order nor the triangle order changes a result: sums run
+// over rows, minima are exact.
+// The set is keyed by caller ids, own nodes included, so only the halo's
+// device labels are gathered; a triangle's vertices are found among the
+// node's own row, of which kRowU entries are held in registers (two compares
+// per entry), the others through the set.  A triangle then is 26 bits
+// (position, two local indices) and kRowU of them wait in registers for the
+// scan of the counts; longer fans, and triangles with a vertex beyond the
+// row's registers, are read again in a rolled loop.  It is bound by its
+// chains of dependent loads (node -> offsets -> row and fan -> triangles),
+// which the 32 waves of a CU hide for each other, and on a mesh in arbitrary
+// numbering by the cache lines those touch (1M nodes: about 10 lines a node,
+// 7 TB/s).  With the label of every row entry and every triangle vertex
+// gathered instead, entries walked as flat ranges and the grouping in a
+// launch of its own it took 435 us on a shuffled 1024 x 1024 grid (now 135),
+// 408 on a 3.1M-node annulus (169), 1727 on the 4096 x 4096 grid (924).  No
+// global load or store stands in a branch that its neighbours' waits would
+// serialise: the halo goes through LDS (970 us without that at 4096 x 4096).
+template <int T>
+__global__ __launch_bounds__(T) void k_tile_build(TileBuildArgs a)
 {
-    constexpr int HS = CLS ? 8 * T : 4 * T;
-    constexpr int BS = kBuildBS, U = kBuildU, CAP = T * kTileMaxDeg, SPT = HS / BS;
-    __shared__ int32_t htab[HS];
-    __shared__ uint16_t hidx[HS];
-    __shared__ uint16_t own[CAP / 16];   // owner of entries 16b, 16b+1, ... starts the search
-    __shared__ int32_t s_nb[T], s_tb[T], s_rs[T + 1], s_fs[T + 1];
-    __shared__ uint16_t s_seg[CLS ? CAP : 1];   // class tiles: the rows in local indices, for the slot search
-    __shared__ int32_t s_warp[BS / 64];
+    constexpr int HS = 8 * T, CAP = T * kTileMaxDeg, U = kRowU;
+    __shared__ alignas(8) int32_t htab[HS];
+    __shared__ uint16_t hidx[HS];        // the local index of each slot's node
+    __shared__ int32_t s_warp[T / 64];
+    __shared__ uint64_t s_cnt[2][T / 64];
+    __shared__ int32_t s_halo[4 * T];    // the halo's caller ids
     __shared__ int32_t s_full;
+    static_assert(5 * T <= 4096, "local indices of 12 bits");
     const int tid = threadIdx.x;
     const int tile = blockIdx.x;
-    int32_t k0 = tile * T, kend = a.n_free;
-    if (a.n_class > 0) {
-        int c = 0;
-        while (c + 1 < a.n_class && tile >= a.cls_tile[c + 1]) ++c;
-        k0 = a.cls_start[c] + (tile - a.cls_tile[c]) * T;
-        kend = a.cls_start[c + 1];
-    }
-    const int nown = min(T, kend - k0);
+    const int32_t k0 = tile * T;
+    const int nown = min(T, a.n_free - k0);
     const int32_t rb = a.row_ptr[k0], fb = a.fan_ptr[k0];
     const int32_t len = a.row_ptr[k0 + nown] - rb, flen = a.fan_ptr[k0 + nown] - fb;
-    if (len > CAP || flen > CAP) {   // denser than the LDS maps hold: the mesh takes the node path
+    if (len > CAP || flen > CAP) {   // denser than the halo set is meant for: the mesh takes the node path
         if (tid == 0) atomicOr(a.err, 2);
         return;
     }
-    for (int s = tid; s < HS; s += BS) htab[s] = -1;
-    if (tid == 0) {
-        s_full = 0;
-        s_rs[nown] = len;
-        s_fs[nown] = flen;
-    }
-    for (int i = tid; i < nown; i += BS) {
-        const int32_t o = a.perm[k0 + i];
-        s_nb[i] = a.nbr_ptr[o];
-        s_tb[i] = a.tri_ptr[o];
-        s_rs[i] = a.row_ptr[k0 + i] - rb;
-        s_fs[i] = a.fan_ptr[k0 + i] - fb;
+    const bool live = tid < nown;
+    const int own = min(tid, nown - 1);
+    const int32_t o = a.perm[k0 + own];
+    const int32_t rs = a.row_ptr[k0 + own] - rb, fs = a.fan_ptr[k0 + own] - fb;
+    const int deg0 = a.row_ptr[k0 + own + 1] - rb - rs, deg = live ? deg0 : 0;   // (a free node's row is not empty)
+    const int inc = live ? a.fan_ptr[k0 + own + 1] - fb - fs : 0;
+    const int32_t* const row = a.nbr_idx + a.nbr_ptr[o];
+    const int32_t* const fan = a.tri_idx + a.tri_ptr[o];
+    for (int s = tid; s < HS; s += T) htab[s] = -1;
+    if (tid == 0) s_full = 0;
+    int32_t r[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) r[q] = row[min(q, deg0 - 1)];
+    int32_t t[U];
+    if (inc > 0) {
+#pragma unroll
+        for (int q = 0; q < U; ++q) t[q] = fan[min(q, inc - 1)];
     }
     __syncthreads();
-    for (int i = tid; i < nown; i += BS)
-        for (int b = (s_rs[i] + 15) >> 4; (b << 4) < s_rs[i + 1]; ++b) own[b] = static_cast<uint16_t>(i);
+    if (live) {
+        bool won;
+        hidx[set_insert<HS>(htab, o, &won)] = static_cast<uint16_t>(tid);
+    }
     __syncthreads();
 
-    auto in_tile = [&](int32_t jd) { return jd >= k0 && jd < k0 + nown; };
-    auto row_label = [&](int j) -> int32_t {
-        int i = own[j >> 4];
-        while (s_rs[i + 1] <= j) ++i;
-        return a.new_of_old[a.nbr_idx[s_nb[i] + (j - s_rs[i])]];
-    };
-
-    // ---- halo set; the row entries' device labels are parked in the halo
-    // part of the record (room for len entries) until the rows are
-    // rewritten below
-    unsigned char* rec = a.data + (CLS ? class_record(rb, fb, tile, T) : tile_record(rb, fb, tile, T));
+    // ---- node set: the slots of the entries beyond the registers are parked
+    // in the row part of the record until the slots have local indices
+    unsigned char* rec = a.data + tile_record(rb, fb, tile, T);
     uint16_t* rr = reinterpret_cast<uint16_t*>(rec);
-    const int64_t hat = CLS ? class_halo_at(T) : halo_at(T);
-    int32_t* halo = reinterpret_cast<int32_t*>(rec + hat);
+    int32_t* halo = reinterpret_cast<int32_t*>(rec + halo_at(T));
+    const int32_t len4 = (len + 3) & ~3;
+    const int64_t seg_at = align16(halo_at(T) + 4 * static_cast<int64_t>(len));
+    uint16_t* const seg = reinterpret_cast<uint16_t*>(rec + seg_at);
+    constexpr uint32_t kWon = 0x8000u;   // in a parked slot: the entry is the halo node's first
     bool full = false;
-    for (int base = 0; base < len; base += BS * U) {
-        int32_t jd[U];
+    int wins = 0;
+    uint32_t sl[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = base + u * BS + tid;
-            jd[u] = j < len ? row_label(j) : k0;
+    for (int q = 0; q < U; ++q) {
+        sl[q] = 0;
+        if (q >= deg) {
+            r[q] = -1;
+            continue;
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int j = base + u * BS + tid;
-            if (j < len) halo[j] = jd[u];
-            if (!in_tile(jd[u]) && !set_insert<HS, CLS>(htab, jd[u])) full = true;
-        }
+        bool won;
+        const int s = set_insert<HS>(htab, r[q], &won);
+        full |= s < 0;
+        wins += won;
+        sl[q] = static_cast<uint32_t>(s) | (won ? kWon : 0u);
+    }
+#pragma unroll 1
+    for (int k = U; k < deg; ++k) {
+        bool won;
+        const int s = set_insert<HS>(htab, row[k], &won);
+        full |= s < 0;
+        wins += won;
+        seg[rs + k] = static_cast<uint16_t>(static_cast<uint32_t>(s) | (won ? kWon : 0u));
     }
     if (full) s_full = 1;
-    __syncthreads();
-    if (s_full) {   // more distinct halo nodes than the set holds: the node path
+    int H;
+    int h = block_excl_scan<T>(wins, &H, s_warp);
+    // more distinct nodes than the set holds, or own nodes with few
+    // neighbours in common: the node path
+    if (s_full || H > 4 * T) {
         if (tid == 0) atomicOr(a.err, 2);
         return;
     }
-    int c = 0;
 #pragma unroll
-    for (int q = 0; q < SPT; ++q) c += htab[tid * SPT + q] != -1;
-    int H;
-    const int h0 = block_excl_scan<BS>(c, &H, s_warp);
-    {
-        int h = h0;
-#pragma unroll
-        for (int q = 0; q < SPT; ++q) {
-            const int s = tid * SPT + q;
-            if (htab[s] != -1) hidx[s] = static_cast<uint16_t>(h++);
+    for (int q = 0; q < U; ++q)
+        if (sl[q] & kWon) {
+            s_halo[h] = r[q];
+            hidx[sl[q] & (HS - 1)] = static_cast<uint16_t>(T + h++);
         }
-    }
+#pragma unroll 1
+    for (int k = U; k < deg; ++k)
+        if (seg[rs + k] & kWon) {
+            s_halo[h] = row[k];
+            hidx[seg[rs + k] & (HS - 1)] = static_cast<uint16_t>(T + h++);
+        }
     __syncthreads();
-    auto local = [&](int32_t jd) -> int {
-        if (in_tile(jd)) return jd - k0;
-        const int s = set_find<HS, CLS>(htab, jd);
-        if (s < 0) {
-            atomicOr(a.err, 1);
-            return T;
-        }
-        return T + hidx[s];
-    };
+    for (int j = tid; j < H; j += T) halo[j] = a.new_of_old[s_halo[j]];
 
     // ---- rows in local indices, and their offsets
-    const int32_t len4 = (len + 3) & ~3;
-    const int64_t seg_at = align16(hat + 4 * static_cast<int64_t>(len));
-    uint16_t* seg = reinterpret_cast<uint16_t*>(rec + seg_at);
-    for (int j = tid; j < len; j += BS) {
-        const uint16_t l = static_cast<uint16_t>(local(halo[j]));
-        seg[j] = l;
-        if (CLS) s_seg[j] = l;
-    }
-    for (int j = len + tid; j < len4; j += BS) seg[j] = 0;
-    __syncthreads();   // every parked label is read: the halo list takes their place
-    {
-        int h = h0;
+    uint32_t l[U];
 #pragma unroll
-        for (int q = 0; q < SPT; ++q) {
-            const int32_t key = htab[tid * SPT + q];
-            if (key != -1) halo[h++] = key;
-        }
+    for (int q = 0; q < U; ++q) {
+        l[q] = hidx[sl[q] & (HS - 1)];
+        if (q < deg) seg[rs + q] = static_cast<uint16_t>(l[q]);
     }
-    for (int i = tid; i <= T; i += BS) rr[i] = static_cast<uint16_t>(s_rs[min(i, nown)]);
-    __syncthreads();   // the entry map is rebuilt for the incidences
-    for (int i = tid; i < nown; i += BS)
-        for (int b = (s_fs[i] + 15) >> 4; (b << 4) < s_fs[i + 1]; ++b) own[b] = static_cast<uint16_t>(i);
-    __syncthreads();
+#pragma unroll 1
+    for (int k = U; k < deg; ++k) seg[rs + k] = hidx[seg[rs + k] & (HS - 1)];
+    if (tid < len4 - len) seg[len + tid] = 0;
+    rr[tid] = static_cast<uint16_t>(live ? rs : len);
+    if (tid == 0) rr[T] = static_cast<uint16_t>(len);
 
-    uint64_t* tri = reinterpret_cast<uint64_t*>(rec + align16(seg_at + 2 * static_cast<int64_t>(len4)));
-    int R = 0;
-    if (CLS) {
-        // ---- fan entries, one per incidence, and the fan starts
-        uint16_t* fans = reinterpret_cast<uint16_t*>(tri);
-        uint16_t* fr = rr + halo_at(T) / 2;
-        for (int i = tid; i <= T; i += BS) fr[i] = static_cast<uint16_t>(s_fs[min(i, nown)]);
-        for (int base = 0; base < flen; base += BS * U) {
-            int32_t v[U][3], kd[U], i_of[U];
+    // ---- triangles
+    uint64_t* const tri = reinterpret_cast<uint64_t*>(rec + align16(seg_at + 2 * static_cast<int64_t>(len4)));
+    const Corners* const corners = reinterpret_cast<const Corners*>(a.tris);
+    constexpr uint32_t kNotListed = ~0u;
+    // a triangle, as the node's position in its stored order and the local
+    // indices of the vertices that follow it there: position | local << 2 |
+    // local << 14; kNotListed if an own vertex with a smaller label lists it
+    auto pack = [&](uint32_t p, uint32_t lx, uint32_t ly) -> uint32_t {
+        return min(lx, ly) < static_cast<uint32_t>(tid) ? kNotListed : p | (lx << 2) | (ly << 14);
+    };
+    auto turn = [&](const Corners& v, int32_t& x, int32_t& y) -> uint32_t {
+        const uint32_t p = v.v0 == o ? 0u : (v.v1 == o ? 1u : 2u);
+        x = p == 0 ? v.v1 : (p == 1 ? v.v2 : v.v0);
+        y = p == 0 ? v.v2 : (p == 1 ? v.v0 : v.v1);
+        return p;
+    };
+    uint32_t w[U];
+    uint32_t miss = 0;   // triangles with a vertex beyond the row's registers
+    int listed = 0;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int f = base + u * BS + tid;
-                int64_t t = 0;
-                kd[u] = k0;
-                i_of[u] = 0;
-                if (f < flen) {
-                    int i = own[f >> 4];
-                    while (s_fs[i + 1] <= f) ++i;
-                    kd[u] = k0 + i;
-                    i_of[u] = i;
-                    t = a.tri_idx[s_tb[i] + (f - s_fs[i])];
-                }
+    for (int q = 0; q < U; ++q) w[q] = kNotListed;
+    if (inc > 0) {
+        Corners v[U];
 #pragma unroll
-                for (int q = 0; q < 3; ++q) v[u][q] = f < flen ? a.new_of_old[a.tris[3 * t + q]] : kd[u];
+        for (int q = 0; q < U; ++q) v[q] = corners[t[q]];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            int32_t x, y;
+            const uint32_t p = turn(v[q], x, y);
+            uint32_t lx = kNotListed, ly = kNotListed;
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                lx = r[k] == x ? l[k] : lx;
+                ly = r[k] == y ? l[k] : ly;
             }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int f = base + u * BS + tid;
-                if (f >= flen) continue;
-                const int p = v[u][0] == kd[u] ? 0 : (v[u][1] == kd[u] ? 1 : 2);
-                const int la = local(v[u][(p + 1) % 3]), lb = local(v[u][(p + 2) % 3]);
-                const int r0 = s_rs[i_of[u]], r1 = s_rs[i_of[u] + 1];
-                int sa = -1, sb = -1;
-                for (int j = r0; j < r1; ++j) {
-                    const int l = s_seg[j];
-                    if (l == la) sa = j - r0;
-                    if (l == lb) sb = j - r0;
-                }
-                if (sa < 0 || sb < 0) atomicOr(a.err, 1);   // validation rules this out
-                fans[f] = static_cast<uint16_t>(p | (max(sa, 0) << 2) | (max(sb, 0) << 9));
+            if (q < inc) {
+                if (max(lx, ly) == kNotListed) miss |= 1u << q;
+                else w[q] = pack(p, lx, ly);
             }
+            listed += w[q] != kNotListed;
         }
-        R = flen;
     }
-    // ---- triangles: work-item t takes incidences U*t .. U*t+U-1 of each
-    // chunk, so that a scan of the per-item counts keeps incidence order
-    for (int base = 0; !CLS && base < flen; base += BS * U) {
-        int32_t v[U][3], kd[U];
-        bool keep[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int f = base + tid * U + u;
-            keep[u] = f < flen;
-            int64_t t = 0;
-            kd[u] = k0;
-            if (keep[u]) {
-                int i = own[f >> 4];
-                while (s_fs[i + 1] <= f) ++i;
-                kd[u] = k0 + i;
-                t = a.tri_idx[s_tb[i] + (f - s_fs[i])];
+    auto later = [&](int k) -> uint32_t {
+        int32_t x, y;
+        const uint32_t p = turn(corners[fan[k]], x, y);
+        const int sx = set_find<HS>(htab, x), sy = set_find<HS>(htab, y);
+        if (sx < 0 || sy < 0) {   // validation rules this out
+            atomicOr(a.err, 1);
+            return kNotListed;
+        }
+        return pack(p, hidx[sx], hidx[sy]);
+    };
+    // the triangles left for later: those of `miss`, then those from U on
+    auto for_later = [&](auto&& f) {
+#pragma unroll 1
+        for (uint32_t m = miss, k = U;;) {
+            uint32_t q;
+            if (m != 0) {
+                q = static_cast<uint32_t>(__builtin_ctz(m));
+                m &= m - 1;
+            } else if (static_cast<int>(k) < inc) {
+                q = k++;
+            } else {
+                break;
             }
-#pragma unroll
-            for (int q = 0; q < 3; ++q) v[u][q] = keep[u] ? a.new_of_old[a.tris[3 * t + q]] : kd[u];
+            f(later(static_cast<int>(q)));
         }
-        int cnt = 0;
+    };
+    for_later([&](uint32_t w) { listed += w != kNotListed; });
+    int R;
+    int at = block_excl_scan<T>(listed, &R, s_warp);
+
+    // ---- grouped through LDS, in the set's place; fans beyond the registers
+    // still need the set, so their tile's list goes by way of its place in
+    // the record.  (A list longer than the set is left in incidence order:
+    // any order gives the same results.)
+    uint64_t* const s_tri = reinterpret_cast<uint64_t*>(htab);
+    if (inc > U || miss != 0) s_full = 1;
+    __syncthreads();
+    const bool direct = R <= HS / 2 && !s_full;
+    uint64_t* const to = direct ? s_tri : tri;
+    auto put = [&](uint32_t w) {
+        if (w == kNotListed) return;
+        const uint64_t me = static_cast<uint64_t>(tid), lx = (w >> 2) & 4095u, ly = w >> 14;
+        const uint32_t p = w & 3u;
+        const uint64_t v0 = p == 0 ? me : (p == 1 ? ly : lx), v1 = p == 0 ? lx : (p == 1 ? me : ly),
+                       v2 = p == 0 ? ly : (p == 1 ? lx : me);
+        to[at++] = v0 | (v1 << 16) | (v2 << 32);
+    };
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            // listed by this incidence iff no other own vertex has a smaller label
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-                if (v[u][q] != kd[u] && in_tile(v[u][q]) && v[u][q] < kd[u]) keep[u] = false;
-            cnt += keep[u];
+    for (int q = 0; q < U; ++q) put(w[q]);
+    for_later(put);
+    if (R <= HS / 2) {
+        __syncthreads();
+        if (!direct) {
+            for (int j = tid; j < R; j += T) s_tri[j] = tri[j];
+            __syncthreads();
         }
-        int tot;
-        int pos = R + block_excl_scan<BS>(cnt, &tot, s_warp);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (!keep[u]) continue;
-            uint64_t w = 0;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) w |= static_cast<uint64_t>(local(v[u][q])) << (16 * q);
-            tri[pos++] = w;
-        }
-        R += tot;
+        group_words<T, T>(s_tri, R, tri, s_cnt);
     }
     if (tid == 0) {
         TileWork w;
@@ -404,57 +487,180 @@ __global__ __launch_bounds__(kBuildBS) void k_tile_build(TileBuildArgs a)
     }
 }
 
-// Groups each tile's triangle list by which of its vertices are own nodes
-// (all three first, then the patterns with two, then with one), keeping
-// incidence order inside a group.  The sweep evaluates a vertex's candidate
-// quality only for own vertices; with the list grouped, the lanes of a wave
-// mostly agree on which of the three evaluations to skip.  Lists longer than
-// the LDS staging keep their order (any order gives the same results).
-constexpr int kOrderWords = 4096;
-
+// One work-group per colour-class tile, in one pass like the Form A build.
+// Its nodes are spread out (no two adjacent), so its halo is every node of
+// its rows; instead of triangle words it gets one fan entry per incidence,
+// in incidence order: the node's position p in the triangle's stored order
+// and the row slots of the vertices at p+1 and p+2 (mod 3),
+// p | slot << 2 | slot << 9, with the fan starts.  The row entries and
+// incidences are walked as flat ranges, a few per work-item at a time, so
+// that a node with a long row is shared by many lanes (finding a vertex in
+// its row is a search).  An entry's own node is found from the owner of its
+// 16-entry block, stepping forward over the node offsets.
 template <int T>
-// LDS: room for `cap` triangle words (the longest list, at most kOrderWords).
-__global__ __launch_bounds__(256) void k_tile_order(const TileWork* __restrict__ work, int cap)
+__global__ __launch_bounds__(kClassBS) void k_class_build(TileBuildArgs a)
 {
-    constexpr int BS = 256;
-    extern __shared__ uint64_t s_w[];
+    constexpr int HS = 8 * T;
+    constexpr int BS = kClassBS, U = kClassU, CAP = T * kTileMaxDeg, SPT = HS / BS;
+    __shared__ int32_t htab[HS];
+    __shared__ uint16_t hidx[HS];        // the local index of each slot's node
+    __shared__ uint16_t own[CAP / 16];   // owner of entries 16b, 16b+1, ... starts the search
+    __shared__ int32_t s_id[T], s_nb[T], s_tb[T], s_rs[T + 1], s_fs[T + 1];
+    __shared__ uint16_t s_seg[CAP];   // the rows in local indices, for the slot search
     __shared__ int32_t s_warp[BS / 64];
-    const TileWork d = work[blockIdx.x];
-    const int R = d.tri_cnt;
-    if (R > cap || R == 0) return;
-    uint64_t* tris = const_cast<uint64_t*>(d.tris);
-    for (int j = threadIdx.x; j < R; j += BS) s_w[j] = tris[j];
+    __shared__ int32_t s_full;
+    const int tid = threadIdx.x;
+    const int tile = blockIdx.x;
+    int cl = 0;
+    while (cl + 1 < a.n_class && tile >= a.cls_tile[cl + 1]) ++cl;
+    const int32_t k0 = a.cls_start[cl] + (tile - a.cls_tile[cl]) * T;
+    const int nown = min(T, a.cls_start[cl + 1] - k0);
+    const int32_t rb = a.row_ptr[k0], fb = a.fan_ptr[k0];
+    const int32_t len = a.row_ptr[k0 + nown] - rb, flen = a.fan_ptr[k0 + nown] - fb;
+    if (len > CAP || flen > CAP) {   // denser than the LDS maps hold: the mesh takes the node path
+        if (tid == 0) atomicOr(a.err, 2);
+        return;
+    }
+    for (int s = tid; s < HS; s += BS) htab[s] = -1;
+    if (tid == 0) {
+        s_full = 0;
+        s_rs[nown] = len;
+        s_fs[nown] = flen;
+    }
+    for (int i = tid; i < nown; i += BS) {
+        const int32_t o = a.perm[k0 + i];
+        s_id[i] = o;
+        s_nb[i] = a.nbr_ptr[o];
+        s_tb[i] = a.tri_ptr[o];
+        s_rs[i] = a.row_ptr[k0 + i] - rb;
+        s_fs[i] = a.fan_ptr[k0 + i] - fb;
+    }
     __syncthreads();
-    // rank of each own-vertex pattern (bit r: vertex r is own) in the output
-    constexpr uint32_t kRank = (0u << 28) | (1u << 12) | (2u << 20) | (3u << 24) | (4u << 4) | (5u << 8) |
-                               (6u << 16) | (7u << 0);
-    auto rank = [&](uint64_t w) -> int {
-        const int p = (static_cast<int>(w & 0xFFFF) < T) | ((static_cast<int>((w >> 16) & 0xFFFF) < T) << 1) |
-                      ((static_cast<int>((w >> 32) & 0xFFFF) < T) << 2);
-        return static_cast<int>((kRank >> (4 * p)) & 7u);
+    for (int i = tid; i < nown; i += BS)
+        for (int b = (s_rs[i] + 15) >> 4; (b << 4) < s_rs[i + 1]; ++b) own[b] = static_cast<uint16_t>(i);
+    __syncthreads();
+
+    // ---- halo set (own nodes are in no row of the tile): the slot of each row entry is parked in the row part of
+    // the record until the slots have local indices
+    unsigned char* rec = a.data + class_record(rb, fb, tile, T);
+    uint16_t* rr = reinterpret_cast<uint16_t*>(rec);
+    const int64_t hat = class_halo_at(T);
+    int32_t* halo = reinterpret_cast<int32_t*>(rec + hat);
+    const int32_t len4 = (len + 3) & ~3;
+    const int64_t seg_at = align16(hat + 4 * static_cast<int64_t>(len));
+    uint16_t* seg = reinterpret_cast<uint16_t*>(rec + seg_at);
+    bool full = false;
+    for (int base = 0; base < len; base += BS * U) {
+        int32_t id[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = min(base + u * BS + tid, len - 1);
+            int i = own[j >> 4];
+            while (s_rs[i + 1] <= j) ++i;
+            id[u] = a.nbr_idx[s_nb[i] + (j - s_rs[i])];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = base + u * BS + tid;
+            if (j >= len) continue;
+            bool won;
+            const int s = set_insert<HS>(htab, id[u], &won);
+            if (s < 0) full = true;
+            else seg[j] = static_cast<uint16_t>(s);
+        }
+    }
+    if (full) s_full = 1;
+    __syncthreads();
+    if (s_full) {   // more distinct nodes than the set holds: the node path
+        if (tid == 0) atomicOr(a.err, 2);
+        return;
+    }
+    int c = 0;
+#pragma unroll
+    for (int q = 0; q < SPT; ++q) c += htab[tid * SPT + q] != -1;
+    int H;
+    int h = block_excl_scan<BS>(c, &H, s_warp);
+#pragma unroll
+    for (int q = 0; q < SPT; ++q) {
+        const int s = tid * SPT + q;
+        const int32_t key = htab[s];
+        if (key == -1) continue;
+        halo[h] = a.new_of_old[key];
+        hidx[s] = static_cast<uint16_t>(T + h++);
+    }
+    __syncthreads();
+    auto local = [&](int32_t id) -> int {
+        const int s = set_find<HS>(htab, id);
+        if (s < 0) {
+            atomicOr(a.err, 1);
+            return T;
+        }
+        return hidx[s];
     };
-    // each work-item takes a contiguous segment; counts per rank packed two to an int
-    const int per = (R + BS - 1) / BS, b = min(R, static_cast<int>(threadIdx.x) * per), e = min(R, b + per);
-    int cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int j = b; j < e; ++j) ++cnt[rank(s_w[j])];
-    int pre[8], tot[8];
-    for (int k = 0; k < 4; ++k) {
-        int t;
-        const int x = block_excl_scan<BS>(cnt[2 * k] | (cnt[2 * k + 1] << 16), &t, s_warp);
-        pre[2 * k] = x & 0xFFFF;
-        pre[2 * k + 1] = x >> 16;
-        tot[2 * k] = t & 0xFFFF;
-        tot[2 * k + 1] = t >> 16;
+
+    // ---- rows in local indices, and their offsets
+    for (int j = tid; j < len; j += BS) {
+        const uint16_t l = hidx[seg[j]];
+        seg[j] = l;
+        s_seg[j] = l;
     }
-    int base = 0;
-    for (int k = 0; k < 8; ++k) {
-        const int c = tot[k];
-        pre[k] += base;
-        base += c;
+    for (int j = len + tid; j < len4; j += BS) seg[j] = 0;
+    for (int i = tid; i <= T; i += BS) rr[i] = static_cast<uint16_t>(s_rs[min(i, nown)]);
+    // the entry map is rebuilt for the incidences
+    for (int i = tid; i < nown; i += BS)
+        for (int b = (s_fs[i] + 15) >> 4; (b << 4) < s_fs[i + 1]; ++b) own[b] = static_cast<uint16_t>(i);
+    __syncthreads();
+
+    // ---- fan entries, one per incidence, and the fan starts
+    uint64_t* tri = reinterpret_cast<uint64_t*>(rec + align16(seg_at + 2 * static_cast<int64_t>(len4)));
+    uint16_t* fans = reinterpret_cast<uint16_t*>(tri);
+    uint16_t* fr = rr + halo_at(T) / 2;
+    for (int i = tid; i <= T; i += BS) fr[i] = static_cast<uint16_t>(s_fs[min(i, nown)]);
+    for (int base = 0; base < flen; base += BS * U) {
+        int32_t v[U][3], i_of[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = min(base + u * BS + tid, flen - 1);
+            int i = own[f >> 4];
+            while (s_fs[i + 1] <= f) ++i;
+            i_of[u] = i;
+            const int64_t t = a.tri_idx[s_tb[i] + (f - s_fs[i])];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) v[u][q] = a.tris[3 * t + q];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int f = base + u * BS + tid;
+            if (f >= flen) continue;
+            const int32_t id = s_id[i_of[u]];
+            const int p = v[u][0] == id ? 0 : (v[u][1] == id ? 1 : 2);
+            const int la = local(v[u][(p + 1) % 3]), lb = local(v[u][(p + 2) % 3]);
+            const int r0 = s_rs[i_of[u]], r1 = s_rs[i_of[u] + 1];
+            int sa = -1, sb = -1;
+            for (int j = r0; j < r1; ++j) {
+                const int l = s_seg[j];
+                if (l == la) sa = j - r0;
+                if (l == lb) sb = j - r0;
+            }
+            if (sa < 0 || sb < 0) atomicOr(a.err, 1);   // validation rules this out
+            fans[f] = static_cast<uint16_t>(p | (max(sa, 0) << 2) | (max(sb, 0) << 9));
+        }
     }
-    for (int j = b; j < e; ++j) {
-        const uint64_t w = s_w[j];
-        tris[pre[rank(w)]++] = w;
+    if (tid == 0) {
+        TileWork w;
+        w.X = a.X;
+        w.halo = halo;
+        w.rows = reinterpret_cast<const uint64_t*>(seg);
+        w.tris = tri;
+        w.rr = rr;
+        w.own_start = k0;
+        w.nown = nown;
+        w.halo_cnt = H;
+        w.tri_cnt = flen;
+        w.row_words = len4 >> 2;
+        w.mesh = a.mesh;
+        w.n = a.n;
+        a.work[tile] = w;
     }
 }
 
@@ -593,12 +799,12 @@ sl_status build_tiles(const SetupArgs& a, DevMesh& m, int tile_nodes, int mesh, 
         b.cls_tile[c] = m.class_tile_h[c];
     }
     if (classes) {
-        if (T == 128) k_tile_build<128, true><<<nt, kBuildBS, 0, st>>>(b);
-        else if (T == 256) k_tile_build<256, true><<<nt, kBuildBS, 0, st>>>(b);
-        else k_tile_build<512, true><<<nt, kBuildBS, 0, st>>>(b);
+        if (T == 128) k_class_build<128><<<nt, kClassBS, 0, st>>>(b);
+        else if (T == 256) k_class_build<256><<<nt, kClassBS, 0, st>>>(b);
+        else k_class_build<512><<<nt, kClassBS, 0, st>>>(b);
     } else {
-        if (T == 256) k_tile_build<256, false><<<nt, kBuildBS, 0, st>>>(b);
-        else k_tile_build<512, false><<<nt, kBuildBS, 0, st>>>(b);
+        if (T == 256) k_tile_build<256><<<nt, 256, 0, st>>>(b);
+        else k_tile_build<512><<<nt, 512, 0, st>>>(b);
     }
     k_tile_caps<<<div_up(nt, 256), 256, 0, st>>>(m.work, nt, flags + 1);
     k_tile_tell<<<1, 64, 0, st>>>(flags, static_cast<int32_t*>(pad.p));
@@ -621,13 +827,6 @@ sl_status build_tiles(const SetupArgs& a, DevMesh& m, int tile_nodes, int mesh, 
         if (T == 128) k_class_fan_sort<128><<<nt, 256, 0, st>>>(m.work);
         else if (T == 256) k_class_fan_sort<256><<<nt, 256, 0, st>>>(m.work);
         else k_class_fan_sort<512><<<nt, 256, 0, st>>>(m.work);
-    }
-    // (class tiles have fan entries, not triangle words: nothing to group)
-    const int cap = classes ? 0 : std::min(h[3], kOrderWords);
-    if (cap > 0) {
-        const size_t lds = sizeof(uint64_t) * static_cast<size_t>(cap);
-        if (T == 256) k_tile_order<256><<<nt, 256, lds, st>>>(m.work, cap);
-        else k_tile_order<512><<<nt, 256, lds, st>>>(m.work, cap);
     }
     SL_HIP(hipGetLastError());
     m.halo_max = h[1];

@@ -713,6 +713,7 @@ __device__ __forceinline__ void append_group(bool keep, int32_t v, int32_t* __re
 
 constexpr int kColorRounds = 3;    // rounds between two looks of the host
 constexpr int kColorTries = 80;    // tries of a node inside a round
+constexpr int kColorWindow = 256 * 2048;   // listed nodes that are tried at the same time: the device's work-items
 
 // One Jones-Plassmann round over the listed (uncoloured) free nodes: a node
 // whose neighbours of higher priority are all coloured takes the smallest
@@ -720,15 +721,23 @@ constexpr int kColorTries = 80;    // tries of a node inside a round
 // several times before it gives up, so that a chain of nodes that wait for
 // each other is walked inside one launch as far as its nodes run at the same
 // time (a bounded number of tries, no waiting: 2.2M nodes take 2 rounds
-// instead of 21; small work-groups, whose places free up early).  The colour a node gets depends only on those neighbours'
-// colours, so neither the rounds nor the list order change the result.
+// instead of 21; small work-groups, whose places free up early).  A node does
+// not wait for one that cannot get its colour in this round: one that has
+// given up, which marks itself with the round's number, or one so far ahead
+// in the numbering that its work-group has not begun (a list of n_list of
+// the n nodes, in about their order, is n / n_list times as dense).  Without
+// that a mesh in arbitrary numbering spent its rounds on tries in vain
+// (2.2M shuffled nodes: setup 7.4 ms; 3.4 with, and 3.6 with one try a
+// round; in grid numbering 0.93 either way, and 1.9 with one try).  The
+// colour a node gets depends only on those neighbours' colours, so neither
+// the rounds nor the list order change the result.
 // cnt[0]: the list's length, cnt[1]: the next one's; top: the largest
 // colour.  list null: the first round, over all n nodes.
 __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restrict__ nbr_ptr,
                                                      const int32_t* __restrict__ nbr_idx,
                                                      const uint8_t* __restrict__ bnd, int32_t* color,
-                                                     const int32_t* __restrict__ list, int32_t n, int32_t* cnt,
-                                                     int32_t* __restrict__ next, int32_t* top)
+                                                     const int32_t* __restrict__ list, int32_t n, int32_t round,
+                                                     int32_t* cnt, int32_t* __restrict__ next, int32_t* top)
 {
     constexpr int R = 8;
     __shared__ int32_t s_tmp[kColorBS / 64 + 1];
@@ -751,7 +760,11 @@ __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restr
             if (cj < 64) used0 |= 1ull << cj;
             else used1 |= 1ull << (cj - 64);
         };
-        for (int tries = 0; tries < kColorTries && left; ++tries) {
+        const int32_t given_up = -2 - round;
+        const int32_t reach = static_cast<int32_t>(
+            min(static_cast<int64_t>(kColorWindow) * n / n_list, static_cast<int64_t>(INT32_MAX)));
+        bool wait = true;
+        for (int tries = 0; tries < kColorTries && left && wait; ++tries) {
             bool ready = true;
             int32_t cj[R];
 #pragma unroll
@@ -768,6 +781,7 @@ __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restr
                     above[j] = -1;
                 } else {
                     ready = false;
+                    wait &= cj[j] != given_up && above[j] - i <= reach;
                 }
             }
             if (d > R && ready)
@@ -776,7 +790,10 @@ __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restr
                     if (bnd[j] || splitmix64(static_cast<uint64_t>(j)) < pi) continue;
                     const int32_t q = __hip_atomic_load(color + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if (q >= 0) use(q);
-                    else ready = false;
+                    else {
+                        ready = false;
+                        wait &= q != given_up && j - i <= reach;
+                    }
                 }
             if (ready) {
                 c = (~used0) ? __builtin_ctzll(~used0) : 64 + __builtin_ctzll(~used1);
@@ -784,6 +801,7 @@ __global__ __launch_bounds__(kColorBS) void k_color_round(const int32_t* __restr
                 left = false;
             }
         }
+        if (left) __hip_atomic_store(color + i, given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     append_group(left, i, next, cnt + 1, s_tmp);
     for (int off = 32; off > 0; off >>= 1) c = max(c, __shfl_xor(c, off));
@@ -1336,7 +1354,7 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
             for (int k = 0; k < kColorRounds; ++k) {
                 k_color_round<<<div_up(left, kColorBS), kColorBS, 0, st>>>(a.nbr_ptr, a.nbr_idx, a.boundary, color,
                                                                           round + k > 0 ? list : nullptr, n,
-                                                                          words + 1 + k, next, words);
+                                                                          round + k, words + 1 + k, next, words);
                 std::swap(list, next);
             }
             k_tell<<<1, 64, 0, st>>>(words, kColorRounds + 2, 1, static_cast<int32_t*>(pad.p));

@@ -262,6 +262,31 @@ __device__ __forceinline__ void reset_sched(int32_t* sched)
         __hip_atomic_store(sched + kSchedStride * threadIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The work-group's largest m and sum of c, on every work-item.
+template <int BS>
+__device__ __forceinline__ void group_fold(double& m, unsigned long long& c)
+{
+    __shared__ double s_d2[BS / 64];
+    __shared__ unsigned long long s_acc[BS / 64];
+    for (int off = 32; off > 0; off >>= 1) {
+        const double t = __shfl_xor(m, off);
+        m = t > m ? t : m;
+        c += __shfl_xor(c, off);
+    }
+    __syncthreads();   // s_d2 / s_acc free
+    if ((threadIdx.x & 63) == 0) {
+        s_d2[threadIdx.x >> 6] = m;
+        s_acc[threadIdx.x >> 6] = c;
+    }
+    __syncthreads();
+    m = s_d2[0];
+    c = s_acc[0];
+    for (int q = 1; q < BS / 64; ++q) {
+        m = s_d2[q] > m ? s_d2[q] : m;
+        c += s_acc[q];
+    }
+}
+
 // A launch over one mesh folds its work-groups' displacement maxima and
 // accepted counts through per-group slots: each group writes its own slot
 // (device-scope stores, performed before its count, as the folds below
@@ -277,32 +302,11 @@ __device__ __forceinline__ void reset_sched(int32_t* sched)
 template <int BS, bool NEED_LAST>
 __device__ __forceinline__ bool fold_through_slots(int32_t* sched, MeshState* ms, double d2, unsigned long long acc)
 {
-    __shared__ double s_d2[BS / 64];
-    __shared__ unsigned long long s_acc[BS / 64];
     __shared__ int s_last;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
     unsigned long long* const slots = reinterpret_cast<unsigned long long*>(sched + kTileSlotsAt);
-    auto block_fold = [&](double& m, unsigned long long& c) {
-        for (int off = 32; off > 0; off >>= 1) {
-            const double t = __shfl_xor(m, off);
-            m = t > m ? t : m;
-            c += __shfl_xor(c, off);
-        }
-        __syncthreads();   // s_d2 / s_acc free
-        if (lane == 0) {
-            s_d2[wv] = m;
-            s_acc[wv] = c;
-        }
-        __syncthreads();
-        m = s_d2[0];
-        c = s_acc[0];
-        for (int q = 1; q < BS / 64; ++q) {
-            m = s_d2[q] > m ? s_d2[q] : m;
-            c += s_acc[q];
-        }
-    };
     unsigned long long c = lane == 0 ? acc : 0ull;   // one lane per wave contributes
-    block_fold(d2, c);
+    group_fold<BS>(d2, c);
     const bool direct = static_cast<int>(gridDim.x) <= kDirectFoldGroups;
     if (direct && !NEED_LAST) {
         if (tid == 0) {
@@ -336,7 +340,7 @@ __device__ __forceinline__ bool fold_through_slots(int32_t* sched, MeshState* ms
         m = mg > m ? mg : m;
         cnt += __hip_atomic_load(slots + 2 * g + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    block_fold(m, cnt);
+    group_fold<BS>(m, cnt);
     if (tid == 0) {
         if (m > 0.0) atomicMax(&ms->maxd_cur, static_cast<unsigned long long>(__double_as_longlong(m)));
         if (cnt) atomicAdd(&ms->acc_cur, cnt);

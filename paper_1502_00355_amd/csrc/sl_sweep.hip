@@ -58,14 +58,79 @@ struct SweepArgs {
     uint64_t* bits;                 // nullable: this sweep's accept bits (device labels)
     int32_t* sched;                 // [kTileSchedInts]: the launch's counters and per-group slots
     int32_t close;                  // 1: the launch's last group closes the sweep of *state
+    int32_t keep;                   // 1: a sweep of several launches: folds wait in the slots for the last of them
+    int32_t n_slots;                // keep and close: the slots the sweep's launches have used
 };
+
+// In a sweep of several launches (Form B: one per class) that closes itself,
+// each group folds into the slot of its index, which it reads when it starts,
+// and is done; only the sweep's last launch counts its groups and folds the
+// slots, which it leaves zeroed.  A fold at every launch's end (the count's
+// atomics, then the last group's reads of all slots) is a chain of over 1 us
+// in launches of 7 to 20 (Form B, 7 classes: 360K nodes 69.8 -> 61.6 us a
+// sweep, 2.2M 143.8 -> 133.3).
+struct Kept {
+    unsigned long long m = 0, c = 0;   // (work-item 0)
+};
+
+__device__ __forceinline__ Kept load_kept(const SweepArgs& a)
+{
+    Kept k;
+    if (a.keep && threadIdx.x == 0) {
+        unsigned long long* const slot = reinterpret_cast<unsigned long long*>(a.sched + kTileSlotsAt) + 2 * blockIdx.x;
+        k.m = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        k.c = __hip_atomic_load(slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return k;
+}
+
+template <int BS>
+__device__ __forceinline__ void finish_kept(const SweepArgs& a, const Kept& kept, double d2, unsigned long long acc)
+{
+    __shared__ int s_last;
+    const int tid = threadIdx.x;
+    unsigned long long* const slots = reinterpret_cast<unsigned long long*>(a.sched + kTileSlotsAt);
+    unsigned long long c = (tid & 63) == 0 ? acc : 0ull;   // one lane per wave contributes
+    group_fold<BS>(d2, c);
+    if (tid == 0) {
+        // non-negative doubles order like their bit patterns
+        const unsigned long long m = static_cast<unsigned long long>(__double_as_longlong(d2));
+        if (m > kept.m) __hip_atomic_store(slots + 2 * blockIdx.x, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (c) __hip_atomic_store(slots + 2 * blockIdx.x + 1, kept.c + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (a.close) s_last = count_group_done(a.sched);
+    }
+    if (!a.close) return;
+    __syncthreads();
+    if (!s_last) return;
+    double m = 0.0;
+    unsigned long long cnt = 0;
+    for (int g = tid; g < a.n_slots; g += BS) {
+        const double mg = __longlong_as_double(static_cast<long long>(
+            __hip_atomic_load(slots + 2 * g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+        m = mg > m ? mg : m;
+        cnt += __hip_atomic_load(slots + 2 * g + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(slots + 2 * g, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(slots + 2 * g + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    group_fold<BS>(m, cnt);
+    if (tid == 0) {
+        if (m > 0.0) atomicMax(&a.state->maxd_cur, static_cast<unsigned long long>(__double_as_longlong(m)));
+        if (cnt) atomicAdd(&a.state->acc_cur, cnt);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // (close_state reads them)
+        close_state(a.state);
+    }
+    reset_sched(a.sched);
+}
 
 // The end of a node-path launch: the groups' folds, and, when the launch
 // closes the sweep, the close by its last group (in place of a k_advance).
 template <int BS>
-__device__ __forceinline__ void finish_node_launch(const SweepArgs& a, double d2, unsigned long long acc)
+__device__ __forceinline__ void finish_node_launch(const SweepArgs& a, const Kept& kept, double d2,
+                                                   unsigned long long acc)
 {
-    if (a.close) {
+    if (a.keep) {
+        finish_kept<BS>(a, kept, d2, acc);
+    } else if (a.close) {
         if (fold_through_slots<BS, true>(a.sched, a.state, d2, acc) && threadIdx.x == 0) close_state(a.state);
     } else {
         fold_through_slots<BS, false>(a.sched, a.state, d2, acc);
@@ -74,19 +139,20 @@ __device__ __forceinline__ void finish_node_launch(const SweepArgs& a, double d2
 
 constexpr int kNodeRow = 8;   // neighbour entries whose loads are in flight together
 constexpr int kNodeFan = 4;   // fan entries read together
+constexpr int kFanLds = 8;    // fan entries of a node held in LDS
 
 // The fan entries [g_begin, g_end) of one node, all of stored position P,
-// a few at a time with clamped indices so that their loads overlap; the
-// vertices come from the work-item's LDS column.
-template <int P, int MAXV, int BLOCK>
-__device__ __forceinline__ void node_fan_range(int g_begin, int g_end, const uint16_t* fan,
+// a few at a time with clamped indices so that their reads overlap; entry(j)
+// is the node's j-th, the vertices come from the work-item's LDS column.
+template <int P, int MAXV, int BLOCK, class F>
+__device__ __forceinline__ void node_fan_range(int g_begin, int g_end, const F& entry,
                                                const double2 (*nb)[BLOCK], int tid, const double2 o, const double2 c,
                                                double& qo, double& qn)
 {
     for (int g0 = g_begin; g0 < g_end; g0 += kNodeFan) {
         uint32_t e[kNodeFan];
 #pragma unroll
-        for (int u = 0; u < kNodeFan; ++u) e[u] = fan[min(g0 + u, g_end - 1)];
+        for (int u = 0; u < kNodeFan; ++u) e[u] = entry(min(g0 + u, g_end - 1));
 #pragma unroll
         for (int u = 0; u < kNodeFan; ++u) {
             if (g0 + u < g_end) {
@@ -101,32 +167,56 @@ __device__ __forceinline__ void node_fan_range(int g_begin, int g_end, const uin
     }
 }
 
+// The node kernel for rows of at most 8 entries (MAXV), one work-item per
+// node.  A wave's time is its chain of dependent loads, offsets -> ids and
+// fan entries -> positions, and then the qualities; so the fan entries are
+// read with the ids, and the next tile's offsets during this one's
+// arithmetic (1500 x 1500, Form B: 21.2 -> 20.6 us a class; about 9 of them
+// are the qualities at full issue, 5 the launch and its last fold).
 // Persistent work-groups over the launch's tiles (BLOCK consecutive nodes
 // each): the tiles are cut into 8 contiguous runs, one per XCD (work-groups
 // are dealt to the XCDs round-robin), so that neighbouring tiles share an L2.
 template <int BLOCK, int MAXV, bool SOA, bool GT>
 __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a)
 {
-    if (!a.state->active) return;   // the whole launch returns: no group counts
     const int xcd = static_cast<int>(blockIdx.x & 7), nw = static_cast<int>(gridDim.x >> 3);
     const int t_begin = xcd * a.tiles_per_xcd, t_end = min(t_begin + a.tiles_per_xcd, a.n_tiles);
+    const int t_first = t_begin + static_cast<int>(blockIdx.x >> 3);
 
     __shared__ double2 nb[MAXV][BLOCK];   // column tid: this work-item's neighbours
+    __shared__ uint16_t s_fan[kFanLds][BLOCK];   // and its first fan entries
     __shared__ double s_recip[kMaxValence + 1];
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    // what a tile's other loads depend on; a lane past the range repeats the
+    // last node's loads and stores nothing
+    struct Head {
+        int32_t r0, r1, f0, f1;
+        uint32_t sp;
+        double2 o;
+    };
+    auto head = [&](int tile) -> Head {
+        const int kk = static_cast<int>(min(static_cast<int64_t>(a.k_begin) + static_cast<int64_t>(tile) * BLOCK + tid,
+                                            static_cast<int64_t>(a.k_end) - 1));
+        return Head{a.row_ptr[kk], a.row_ptr[kk + 1], a.fan_ptr[kk], a.fan_ptr[kk + 1],
+                    a.fan_split ? a.fan_split[kk] : kFanUngrouped, ld<SOA>(a.Xin, a.n, kk)};
+    };
+    Head h = head(t_first);
+    const Kept kept = load_kept(a);
+    if (!a.state->active) return;   // the whole launch returns: no group counts
     for (int i = tid; i <= kMaxValence; i += BLOCK) s_recip[i] = i ? 1.0 / static_cast<double>(i) : 0.0;
     __syncthreads();   // the reciprocal table
     double run_d2 = 0.0;
     unsigned long long run_acc = 0;
-    for (int tile = t_begin + static_cast<int>(blockIdx.x >> 3); tile < t_end; tile += nw) {
+    for (int tile = t_first; tile < t_end; tile += nw) {
         const int k = a.k_begin + tile * BLOCK + tid;
         const bool live = k < a.k_end;
-        // a lane past the range repeats the last node's loads and stores nothing
-        const int kk = live ? k : a.k_end - 1;
-        const int32_t r0 = a.row_ptr[kk], d = a.row_ptr[kk + 1] - r0;   // d >= 1 for a free node
-        const int32_t f0 = a.fan_ptr[kk], f1 = a.fan_ptr[kk + 1];
-        const double2 o = ld<SOA>(a.Xin, a.n, kk);
+        const int32_t r0 = h.r0, d = h.r1 - r0, f0 = h.f0, inc = h.f1 - f0;   // d >= 1 for a free node
+        const uint32_t sp = h.sp;
+        const double2 o = h.o;
+        uint16_t fan[kFanLds];
+#pragma unroll
+        for (int u = 0; u < kFanLds; ++u) fan[u] = a.fan[min(f0 + u, max(h.f1 - 1, 0))];
         // the row's ids, then its positions, each group's loads in flight
         // together; the sums run in stored order
         double sx = 0.0, sy = 0.0;
@@ -137,6 +227,11 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a)
             double2 p[kNodeRow];
 #pragma unroll
             for (int u = 0; u < kNodeRow; ++u) p[u] = ld<SOA>(a.Xin, a.n, id[u]);
+            if (j0 == 0) {
+                h = head(tile + nw);   // the next tile's
+#pragma unroll
+                for (int u = 0; u < kFanLds; ++u) s_fan[u][tid] = fan[u];
+            }
 #pragma unroll
             for (int u = 0; u < kNodeRow; ++u)
                 if (j0 + u < d) {
@@ -157,21 +252,23 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a)
         }
         double qo = INFINITY, qn = INFINITY;
         const double2 c = make_double2(cx, cy);
-        const uint32_t sp = a.fan_split ? a.fan_split[kk] : kFanUngrouped;   // a uniform test
+        auto entry = [&](int j) -> uint32_t {
+            return j < kFanLds ? s_fan[j][tid] : a.fan[f0 + j];
+        };
         if (sp != kFanUngrouped) {
-            // entries with p = 0 in [f0, b1), p = 1 in [b1, b2), p = 2 in [b2, f1)
-            const int b1 = f0 + static_cast<int>(sp & 0xFFFFu), b2 = f0 + static_cast<int>(sp >> 16);
-            node_fan_range<0, MAXV, BLOCK>(f0, b1, a.fan, nb, tid, o, c, qo, qn);
-            node_fan_range<1, MAXV, BLOCK>(b1, b2, a.fan, nb, tid, o, c, qo, qn);
-            node_fan_range<2, MAXV, BLOCK>(b2, f1, a.fan, nb, tid, o, c, qo, qn);
+            // entries with p = 0 in [0, b1), p = 1 in [b1, b2), p = 2 in [b2, inc)
+            const int b1 = static_cast<int>(sp & 0xFFFFu), b2 = static_cast<int>(sp >> 16);
+            node_fan_range<0, MAXV, BLOCK>(0, b1, entry, nb, tid, o, c, qo, qn);
+            node_fan_range<1, MAXV, BLOCK>(b1, b2, entry, nb, tid, o, c, qo, qn);
+            node_fan_range<2, MAXV, BLOCK>(b2, inc, entry, nb, tid, o, c, qo, qn);
         } else {
-            for (int g0 = f0; g0 < f1; g0 += kNodeFan) {
+            for (int g0 = 0; g0 < inc; g0 += kNodeFan) {
                 uint32_t e[kNodeFan];
 #pragma unroll
-                for (int u = 0; u < kNodeFan; ++u) e[u] = a.fan[min(g0 + u, f1 - 1)];
+                for (int u = 0; u < kNodeFan; ++u) e[u] = entry(min(g0 + u, inc - 1));
 #pragma unroll
                 for (int u = 0; u < kNodeFan; ++u) {
-                    if (g0 + u < f1) {
+                    if (g0 + u < inc) {
                         const int p = static_cast<int>(e[u] & 3u);
                         const double2 va = nb[(e[u] >> 2) & 127u][tid];
                         const double2 vb = nb[(e[u] >> 9) & 127u][tid];
@@ -203,7 +300,139 @@ __global__ __launch_bounds__(BLOCK) void k_sweep(SweepArgs a)
         }
     }
     // every group folds, those without a tile too: the last one counts them all
-    finish_node_launch<BLOCK>(a, run_d2, run_acc);
+    finish_node_launch<BLOCK>(a, kept, run_d2, run_acc);
+}
+
+// The node kernel for rows of more than 8 entries: W work-items of a wave per
+// node, which share its row in LDS and take every W-th fan entry.  What
+// bounds such a mesh with one work-item per node is the LDS its rows take:
+// 64 KB per 256 nodes at 16 entries leave a CU 8 waves, too few to hide the
+// chain offsets -> ids -> positions -> qualities; with W = 2 it is 16 waves,
+// and a node's chain of qualities is half as long.  (Refined grids, valence
+// up to 12, Form B: 611K nodes 117 -> 102 us a sweep, 2.4M 246 -> 236.  On
+// meshes of at most 8 entries, whose rows leave 16 waves as they are, W = 2
+// is slower: 1500 x 1500 157 us against 144, 4096 x 4096 840 against 778.)
+template <int BLOCK, int MAXV, int W, bool SOA, bool GT>
+__global__ __launch_bounds__(BLOCK) void k_sweep_split(SweepArgs a)
+{
+    constexpr int G = BLOCK / W, NPW = 64 / W;         // nodes per work-group, per wave
+    constexpr int R = kNodeRow / W, F = kNodeFan;      // row and fan entries of a work-item in flight together
+    const int xcd = static_cast<int>(blockIdx.x & 7), nw = static_cast<int>(gridDim.x >> 3);
+    const int t_begin = xcd * a.tiles_per_xcd, t_end = min(t_begin + a.tiles_per_xcd, a.n_tiles);
+    const int t_first = t_begin + static_cast<int>(blockIdx.x >> 3);
+
+    __shared__ double2 nb[MAXV][G];   // column g: that node's neighbours
+    __shared__ double s_recip[kMaxValence + 1];
+
+    const int tid = threadIdx.x, g = tid / W, sub = tid % W, lane = tid & 63, wv = tid >> 6;
+    // what a tile's other loads depend on; a lane past the range repeats the
+    // last node's loads and stores nothing
+    struct Head {
+        int32_t r0, r1, f0, f1;
+        double2 o;
+    };
+    auto head = [&](int tile) -> Head {
+        const int kk = static_cast<int>(min(static_cast<int64_t>(a.k_begin) + static_cast<int64_t>(tile) * G + g,
+                                            static_cast<int64_t>(a.k_end) - 1));
+        return Head{a.row_ptr[kk], a.row_ptr[kk + 1], a.fan_ptr[kk], a.fan_ptr[kk + 1], ld<SOA>(a.Xin, a.n, kk)};
+    };
+    Head h = head(t_first);
+    const Kept kept = load_kept(a);
+    if (!a.state->active) return;   // the whole launch returns: no group counts
+    for (int i = tid; i <= kMaxValence; i += BLOCK) s_recip[i] = i ? 1.0 / static_cast<double>(i) : 0.0;
+    __syncthreads();   // the reciprocal table
+    double run_d2 = 0.0;
+    unsigned long long run_acc = 0;
+    for (int tile = t_first; tile < t_end; tile += nw) {
+        const int k = a.k_begin + tile * G + g;
+        const bool live = k < a.k_end;
+        const int32_t r0 = h.r0, d = h.r1 - r0, f0 = h.f0, inc = h.f1 - f0;   // d >= 1 for a free node
+        const double2 o = h.o;
+        uint32_t e[F];
+#pragma unroll
+        for (int u = 0; u < F; ++u) e[u] = a.fan[max(f0 + min(sub + W * u, inc - 1), 0)];
+        // the row's ids, then its positions, each group's loads in flight together
+        for (int j0 = 0; j0 < d; j0 += kNodeRow) {
+            int32_t id[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) id[u] = a.nbr[r0 + min(j0 + sub + W * u, d - 1)];
+            double2 p[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) p[u] = ld<SOA>(a.Xin, a.n, id[u]);
+            if (j0 == 0) h = head(tile + nw);   // the next tile's
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (j0 + sub + W * u < d) nb[j0 + sub + W * u][g] = p[u];
+        }
+        // (a node's lanes are of one wave: their LDS accesses are in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        // the row-order sum, on every lane of the node
+        double sx = 0.0, sy = 0.0;
+        for (int j0 = 0; j0 < d; j0 += kNodeRow) {
+            double2 p[kNodeRow];
+#pragma unroll
+            for (int u = 0; u < kNodeRow; ++u) p[u] = nb[min(j0 + u, d - 1)][g];
+#pragma unroll
+            for (int u = 0; u < kNodeRow; ++u)
+                if (j0 + u < d) {
+                    sx += p[u].x;
+                    sy += p[u].y;
+                }
+        }
+        const double dn = static_cast<double>(d), y = s_recip[d];
+        double cx = div_small(sx, dn, y), cy = div_small(sy, dn, y);
+        const bool tiny = !(fabs(sx) >= kStepMin) || !(fabs(sy) >= kStepMin);
+        // a wave-uniform branch: the full division only when some lane needs it
+        if (__builtin_amdgcn_ballot_w64(tiny) != 0ull) {
+            if (tiny) {
+                cx = sx / dn;
+                cy = sy / dn;
+            }
+        }
+        double qo = INFINITY, qn = INFINITY;
+        const double2 c = make_double2(cx, cy);
+        for (int g0 = sub; g0 < inc; g0 += W * F) {
+            if (g0 != sub) {
+#pragma unroll
+                for (int u = 0; u < F; ++u) e[u] = a.fan[f0 + min(g0 + W * u, inc - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < F; ++u) {
+                if (g0 + W * u < inc) {
+                    const double2 va = nb[(e[u] >> 2) & 127u][g];
+                    const double2 vb = nb[(e[u] >> 9) & 127u][g];
+                    double v, w;
+                    fan_qualities(static_cast<int>(e[u] & 3u), o, c, va, vb, v, w);
+                    if (v < qo) qo = v;
+                    if (w < qn) qn = w;
+                }
+            }
+        }
+        qo = group_min<W>(qo);
+        qn = group_min<W>(qn);
+        bool accepted = false;
+        if (live && sub == 0) {
+            accepted = GT ? (qn > qo) : (qn >= qo);
+            const double nx = accepted ? cx : o.x, ny = accepted ? cy : o.y;
+            st<SOA>(a.Xout, a.n, k, nx, ny);
+            const double dx = nx - o.x, dy = ny - o.y;
+            const double d2 = dx * dx + dy * dy;
+            run_d2 = d2 > run_d2 ? d2 : run_d2;
+        }
+        const unsigned long long ball = __ballot(accepted);
+        run_acc += __popcll(ball);
+        if (a.bits != nullptr && lane == 0 && ball != 0ull) {
+            unsigned long long nodes = 0;   // bit q: the wave's node q accepted
+#pragma unroll
+            for (int q = 0; q < NPW; ++q) nodes |= ((ball >> (q * W)) & 1ull) << q;
+            const int kw = a.k_begin + tile * G + wv * NPW, sh = kw & 63;
+            unsigned long long* word = reinterpret_cast<unsigned long long*>(a.bits) + (kw >> 6);
+            atomicOr(word, nodes << sh);
+            if (sh != 0 && (nodes >> (64 - sh)) != 0ull) atomicOr(word + 1, nodes >> (64 - sh));
+        }
+    }
+    // every group folds, those without a tile too: the last one counts them all
+    finish_node_launch<BLOCK>(a, kept, run_d2, run_acc);
 }
 
 // Persistent grid: 8 XCDs x 32 CUs x the work-groups a CU holds (by the
@@ -220,13 +449,14 @@ int persistent_grid(int tiles_per_xcd, int block, size_t lds_bytes)
 // Static LDS of a node-kernel work-group.
 constexpr size_t node_lds(int block, int maxv)
 {
-    return static_cast<size_t>(maxv) * block * 16 + (block / 64) * 16 + (kMaxValence + 1) * 8;
+    return static_cast<size_t>(maxv) * block * 16 + kFanLds * block * 2 + (block / 64) * 16 + (kMaxValence + 1) * 8;
 }
 
 template <int BLOCK, int MAXV>
-void launch_variant(const SweepArgs& a, bool soa, bool gt, hipStream_t st)
+int launch_variant(SweepArgs a, bool soa, bool gt, hipStream_t st)
 {
     const int grid = persistent_grid(a.tiles_per_xcd, BLOCK, node_lds(BLOCK, MAXV));
+    a.n_slots = std::max(a.n_slots, grid);
     if (soa) {
         if (gt) k_sweep<BLOCK, MAXV, true, true><<<grid, BLOCK, 0, st>>>(a);
         else k_sweep<BLOCK, MAXV, true, false><<<grid, BLOCK, 0, st>>>(a);
@@ -234,35 +464,42 @@ void launch_variant(const SweepArgs& a, bool soa, bool gt, hipStream_t st)
         if (gt) k_sweep<BLOCK, MAXV, false, true><<<grid, BLOCK, 0, st>>>(a);
         else k_sweep<BLOCK, MAXV, false, false><<<grid, BLOCK, 0, st>>>(a);
     }
+    return a.n_slots;
 }
 
-// Work-group size of the variant used for a given largest valence.
-int block_for(int max_deg, int requested)
+template <int MAXV, int W>
+int launch_split(SweepArgs a, int64_t cnt, bool soa, bool gt, hipStream_t st)
 {
-    if (max_deg <= 8) return (requested == 64 || requested == 128) ? requested : 256;
-    if (max_deg <= 16) return 256;
-    if (max_deg <= 32) return 128;
-    return 64;
+    constexpr int BLOCK = 256, G = BLOCK / W;
+    a.n_tiles = div_up(cnt, G);
+    a.tiles_per_xcd = div_up(a.n_tiles, 8);
+    const size_t lds = static_cast<size_t>(MAXV) * G * 16 + (BLOCK / 64) * 16 + (kMaxValence + 1) * 8;
+    const int grid = persistent_grid(a.tiles_per_xcd, BLOCK, lds);
+    a.n_slots = std::max(a.n_slots, grid);
+    if (soa) {
+        if (gt) k_sweep_split<BLOCK, MAXV, W, true, true><<<grid, BLOCK, 0, st>>>(a);
+        else k_sweep_split<BLOCK, MAXV, W, true, false><<<grid, BLOCK, 0, st>>>(a);
+    } else {
+        if (gt) k_sweep_split<BLOCK, MAXV, W, false, true><<<grid, BLOCK, 0, st>>>(a);
+        else k_sweep_split<BLOCK, MAXV, W, false, false><<<grid, BLOCK, 0, st>>>(a);
+    }
+    return a.n_slots;
 }
 
-void launch_range(SweepArgs a, int max_deg, int requested_block, bool soa, bool gt, hipStream_t st)
+// Returns the slots the sweep has used with this launch.
+int launch_range(SweepArgs a, int max_deg, int requested_block, bool soa, bool gt, hipStream_t st)
 {
     const int64_t cnt = static_cast<int64_t>(a.k_end) - a.k_begin;
-    if (cnt <= 0) return;
-    const int block = block_for(max_deg, requested_block);
+    if (cnt <= 0) return a.n_slots;
+    if (max_deg > 32) return launch_split<128, 8>(a, cnt, soa, gt, st);
+    if (max_deg > 16) return launch_split<32, 4>(a, cnt, soa, gt, st);
+    if (max_deg > 8) return launch_split<16, 2>(a, cnt, soa, gt, st);
+    const int block = requested_block == 64 || requested_block == 128 ? requested_block : 256;
     a.n_tiles = div_up(cnt, block);
     a.tiles_per_xcd = div_up(a.n_tiles, 8);
-    if (max_deg <= 8) {
-        if (block == 64) launch_variant<64, 8>(a, soa, gt, st);
-        else if (block == 128) launch_variant<128, 8>(a, soa, gt, st);
-        else launch_variant<256, 8>(a, soa, gt, st);
-    } else if (max_deg <= 16) {
-        launch_variant<256, 16>(a, soa, gt, st);
-    } else if (max_deg <= 32) {
-        launch_variant<128, 32>(a, soa, gt, st);
-    } else {
-        launch_variant<64, 128>(a, soa, gt, st);
-    }
+    if (block == 64) return launch_variant<64, 8>(a, soa, gt, st);
+    if (block == 128) return launch_variant<128, 8>(a, soa, gt, st);
+    return launch_variant<256, 8>(a, soa, gt, st);
 }
 
 // ----------------------------------------------------------- lane groups --
@@ -288,6 +525,7 @@ template <int W, int MAXV, bool SOA, bool GT>
 __global__ __launch_bounds__((lane_block<W, MAXV>())) void k_sweep_lanes(SweepArgs a)
 {
     constexpr int BS = lane_block<W, MAXV>(), G = BS / W, NPW = 64 / W;   // groups per work-group, per wave
+    const Kept kept = load_kept(a);
     if (!a.state->active) return;   // the whole launch returns: no group counts
     // persistent work-groups over tiles of G nodes, a contiguous run of
     // tiles per XCD, as in the node kernel
@@ -370,17 +608,18 @@ __global__ __launch_bounds__((lane_block<W, MAXV>())) void k_sweep_lanes(SweepAr
             if (sh != 0 && (nodes >> (64 - sh)) != 0ull) atomicOr(word + 1, nodes >> (64 - sh));
         }
     }
-    finish_node_launch<BS>(a, run_d2, run_acc);
+    finish_node_launch<BS>(a, kept, run_d2, run_acc);
 }
 
 template <int W, int MAXV>
-void launch_lanes_v(SweepArgs a, int64_t cnt, bool soa, bool gt, hipStream_t st)
+int launch_lanes_v(SweepArgs a, int64_t cnt, bool soa, bool gt, hipStream_t st)
 {
     constexpr int BS = lane_block<W, MAXV>(), G = BS / W;
     a.n_tiles = static_cast<int32_t>(div_up(cnt, G));
     a.tiles_per_xcd = div_up(a.n_tiles, 8);
     const size_t lds = static_cast<size_t>(G) * (MAXV + 1) * 16 + (BS / 64) * 16 + (kMaxValence + 1) * 8;
     const int grid = persistent_grid(a.tiles_per_xcd, BS, lds);
+    a.n_slots = std::max(a.n_slots, grid);
     if (soa) {
         if (gt) k_sweep_lanes<W, MAXV, true, true><<<grid, BS, 0, st>>>(a);
         else k_sweep_lanes<W, MAXV, true, false><<<grid, BS, 0, st>>>(a);
@@ -388,24 +627,25 @@ void launch_lanes_v(SweepArgs a, int64_t cnt, bool soa, bool gt, hipStream_t st)
         if (gt) k_sweep_lanes<W, MAXV, false, true><<<grid, BS, 0, st>>>(a);
         else k_sweep_lanes<W, MAXV, false, false><<<grid, BS, 0, st>>>(a);
     }
+    return a.n_slots;
 }
 
 template <int W>
-void launch_lanes_w(const SweepArgs& a, int64_t cnt, int max_deg, bool soa, bool gt, hipStream_t st)
+int launch_lanes_w(const SweepArgs& a, int64_t cnt, int max_deg, bool soa, bool gt, hipStream_t st)
 {
-    if (max_deg <= 8) launch_lanes_v<W, 8>(a, cnt, soa, gt, st);
-    else if (max_deg <= 16) launch_lanes_v<W, 16>(a, cnt, soa, gt, st);
-    else if (max_deg <= 32) launch_lanes_v<W, 32>(a, cnt, soa, gt, st);
-    else launch_lanes_v<W, 128>(a, cnt, soa, gt, st);
+    if (max_deg <= 8) return launch_lanes_v<W, 8>(a, cnt, soa, gt, st);
+    if (max_deg <= 16) return launch_lanes_v<W, 16>(a, cnt, soa, gt, st);
+    if (max_deg <= 32) return launch_lanes_v<W, 32>(a, cnt, soa, gt, st);
+    return launch_lanes_v<W, 128>(a, cnt, soa, gt, st);
 }
 
-void launch_lanes(const SweepArgs& a, int max_deg, int width, bool soa, bool gt, hipStream_t st)
+int launch_lanes(const SweepArgs& a, int max_deg, int width, bool soa, bool gt, hipStream_t st)
 {
     const int64_t cnt = static_cast<int64_t>(a.k_end) - a.k_begin;
-    if (cnt <= 0) return;
-    if (width == 4) launch_lanes_w<4>(a, cnt, max_deg, soa, gt, st);
-    else if (width == 16) launch_lanes_w<16>(a, cnt, max_deg, soa, gt, st);
-    else launch_lanes_w<8>(a, cnt, max_deg, soa, gt, st);
+    if (cnt <= 0) return a.n_slots;
+    if (width == 4) return launch_lanes_w<4>(a, cnt, max_deg, soa, gt, st);
+    if (width == 16) return launch_lanes_w<16>(a, cnt, max_deg, soa, gt, st);
+    return launch_lanes_w<8>(a, cnt, max_deg, soa, gt, st);
 }
 
 // ------------------------------------------------------- resident meshes --
@@ -917,11 +1157,14 @@ sl_status launch_sweep_nodes(const DevMesh& m, int32_t parity, int32_t form, int
     if (!sched) return fail(SL_EINVAL, "internal: node launch without its counters");
     // the launch that closes the sweep: Form A's one, or Form B's last
     // non-empty class; with no free node, a k_advance
-    int last = -1;
+    int first = -1, last = -1;
     if (form == SL_JACOBI) last = m.n_free > 0 ? 0 : -1;
     else
         for (int c = 0; c < m.n_colors; ++c)
-            if (m.color_start_h[c + 1] > m.color_start_h[c]) last = c;
+            if (m.color_start_h[c + 1] > m.color_start_h[c]) {
+                last = c;
+                if (first < 0) first = c;
+            }
     SweepArgs a{};
     a.sched = sched;
     a.n = m.n;
@@ -944,12 +1187,13 @@ sl_status launch_sweep_nodes(const DevMesh& m, int32_t parity, int32_t form, int
     } else {
         a.Xin = static_cast<const double*>(m.X[0]);
         a.Xout = static_cast<double*>(m.X[0]);
+        a.keep = close && last > first ? 1 : 0;
         for (int c = 0; c < m.n_colors; ++c) {
             a.k_begin = m.color_start_h[c];
             a.k_end = m.color_start_h[c + 1];
             a.close = close && c == last ? 1 : 0;
-            if (m.lane_width > 0) launch_lanes(a, m.max_deg, m.lane_width, soa, gt, st);
-            else launch_range(a, m.max_deg, block, soa, gt, st);
+            a.n_slots = m.lane_width > 0 ? launch_lanes(a, m.max_deg, m.lane_width, soa, gt, st)
+                                         : launch_range(a, m.max_deg, block, soa, gt, st);
         }
     }
     SL_HIP(hipGetLastError());

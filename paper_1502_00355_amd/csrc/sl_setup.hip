@@ -253,7 +253,7 @@ struct ValArgs {
     double coord_limit;    // coordinates must be below this in magnitude
 };
 
-constexpr int kRowRegs = 16;   // row entries held in registers (k_rows_fans)
+constexpr int kRowRegs = 8;    // row entries, and incidences, of a node held in registers (k_rows_fans)
 constexpr int kRowLds = 16;    // row entries held in LDS (k_validate_nodes)
 
 __device__ __forceinline__ bool row_has(const int32_t* __restrict__ idx, int32_t b, int32_t e, int32_t v)
@@ -866,6 +866,22 @@ __global__ __launch_bounds__(kBS) void k_offset_tiles(const int32_t* __restrict_
     scan_tile(blockIdx.y ? inc : deg, out, n, true, sums + (blockIdx.y ? gridDim.x : 0), out + n, s_wave);
 }
 
+// The node path's rows in device labels and fan entries, p | slot << 2 |
+// slot << 9: the node's position p in the triangle's stored order and the row
+// slots of the vertices at p+1 and p+2 (mod 3).  GROUP: each node's entries
+// grouped by p (0, then 1, then 2; incidence order inside a group) with the
+// groups' bounds, c0 | (c0 + c1) << 16 for c_p entries of position p, so that
+// the node kernel evaluates each group with the position fixed at compile
+// time.  A minimum over a fan is exact, so the order of its entries changes
+// no result.
+// One work-item per node, its first kRowRegs entries and triangles in
+// registers, every load of a stage in flight together and none in a branch.
+// With 16 row entries in registers, loads and stores in branches (each waits
+// for the last) and the grouping in a launch of its own it took 399 us on a
+// 1500 x 1500 grid (now 194); at 4096 x 4096 the whole setup went from 6.31
+// to 5.13 ms.  In arbitrary numbering it is bound by the cache lines it
+// touches (2.4M nodes: 911 -> 790 us).
+template <bool GROUP>
 __global__ __launch_bounds__(kBS) void k_rows_fans(const int32_t* __restrict__ perm,
                                                    const int32_t* __restrict__ new_of_old, int32_t n_free,
                                                    const int32_t* __restrict__ nbr_ptr,
@@ -874,96 +890,88 @@ __global__ __launch_bounds__(kBS) void k_rows_fans(const int32_t* __restrict__ p
                                                    const int32_t* __restrict__ tri_idx,
                                                    const int32_t* __restrict__ tris,
                                                    const int32_t* __restrict__ row_ptr, int32_t* __restrict__ nbr,
-                                                   const int32_t* __restrict__ fan_ptr, uint16_t* __restrict__ fan)
+                                                   const int32_t* __restrict__ fan_ptr, uint16_t* __restrict__ fan,
+                                                   uint32_t* __restrict__ split)
 {
+    constexpr int U = kRowRegs;
     const int64_t k = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
     if (k >= n_free) return;
     const int32_t o = perm[k];
-    const int32_t b = nbr_ptr[o], d = nbr_ptr[o + 1] - b;
-    const int32_t out = row_ptr[k];
-    // rows of up to kRowRegs entries are held in registers (their loads in
-    // flight together) for the slot searches below; longer rows are
-    // searched in memory
-    const bool in_regs = d <= kRowRegs;
-    int32_t rowv[kRowRegs];
-#pragma unroll
-    for (int j = 0; j < kRowRegs; ++j) rowv[j] = (in_regs && j < d) ? nbr_idx[b + j] : -1;
-    if (in_regs) {
-#pragma unroll
-        for (int j = 0; j < kRowRegs; ++j)
-            if (j < d) nbr[out + j] = new_of_old[rowv[j]];
-    } else {
-        for (int32_t j = 0; j < d; ++j) nbr[out + j] = new_of_old[nbr_idx[b + j]];
-    }
-    // the row position of u (the last one, should u repeat)
-    auto slot = [&](int32_t u) -> int {
-        int sj = 0;
-        if (in_regs) {
-#pragma unroll
-            for (int j = 0; j < kRowRegs; ++j)
-                if (j < d && rowv[j] == u) sj = j;
-        } else {
-            for (int32_t j = 0; j < d; ++j)
-                if (nbr_idx[b + j] == u) sj = j;
-        }
-        return sj;
-    };
+    const int32_t b = nbr_ptr[o], d = nbr_ptr[o + 1] - b;   // d >= 1 for a free node
     const int32_t tb = tri_ptr[o], nt = tri_ptr[o + 1] - tb;
-    const int32_t fo = fan_ptr[k];
-    // incidences four at a time: their loads are in flight together
-    for (int32_t q0 = 0; q0 < nt; q0 += 4) {
-        int64_t t[4];
-        int32_t v[4][3];
+    const int32_t out = row_ptr[k], fo = fan_ptr[k];
+    int32_t r[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) t[u] = q0 + u < nt ? tri_idx[tb + q0 + u] : -1;
+    for (int j = 0; j < U; ++j) r[j] = nbr_idx[b + min(j, d - 1)];
+    Corners v[U];
+    if (nt > 0) {
+        int32_t t[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int q = 0; q < U; ++q) t[q] = tri_idx[tb + min(q, nt - 1)];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) v[u][c] = t[u] >= 0 ? tris[3 * t[u] + c] : -1;
+        for (int q = 0; q < U; ++q) v[q] = reinterpret_cast<const Corners*>(tris)[t[q]];
+    }
+    int32_t lab[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (q0 + u >= nt) break;
-            const int p = v[u][0] == o ? 0 : (v[u][1] == o ? 1 : 2);
-            const int32_t va = v[u][(p + 1) % 3], vc = v[u][(p + 2) % 3];
-            fan[fo + q0 + u] = static_cast<uint16_t>(p | (slot(va) << 2) | (slot(vc) << 9));
+    for (int j = 0; j < U; ++j) lab[j] = new_of_old[r[j]];
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+        if (j < d) nbr[out + j] = lab[j];
+        else r[j] = -1;
+    }
+#pragma unroll 1
+    for (int32_t j = U; j < d; ++j) nbr[out + j] = new_of_old[nbr_idx[b + j]];
+    // a triangle's fan entry; a vertex that repeats in the row is its last entry
+    auto entry = [&](const Corners& c) -> uint32_t {
+        const uint32_t p = c.v0 == o ? 0u : (c.v1 == o ? 1u : 2u);
+        const int32_t x = p == 0 ? c.v1 : (p == 1 ? c.v2 : c.v0), y = p == 0 ? c.v2 : (p == 1 ? c.v0 : c.v1);
+        uint32_t sx = 0, sy = 0;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            sx = r[j] == x ? static_cast<uint32_t>(j) : sx;
+            sy = r[j] == y ? static_cast<uint32_t>(j) : sy;
         }
-    }
-}
-
-// Groups each free node's fan entries by the node's position p in the
-// triangle's stored order (0, then 1, then 2; incidence order inside a
-// group) and stores the groups' bounds, c0 | (c0 + c1) << 16 for c_p entries
-// of position p, so that the node kernel evaluates each group with the
-// position fixed at compile time.  A minimum over a fan is exact, so the
-// order of its entries changes no result.  Fans longer than kGroupFan keep
-// their order and get kFanUngrouped.  The entries are held in registers.
-__global__ __launch_bounds__(kBS) void k_fan_group(const int32_t* __restrict__ fan_ptr, uint16_t* __restrict__ fan,
-                                                   uint32_t* __restrict__ split, int32_t n_free)
-{
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
-    if (k >= n_free) return;
-    const int32_t f0 = fan_ptr[k], n = fan_ptr[k + 1] - f0;
-    if (n > kGroupFan) {
-        split[k] = kFanUngrouped;
-        return;
-    }
-    uint32_t e[kGroupFan];
-    int c0 = 0, c1 = 0;
+#pragma unroll 1
+        for (int32_t j = U; j < d; ++j) {
+            const int32_t w = nbr_idx[b + j];
+            sx = w == x ? static_cast<uint32_t>(j) : sx;
+            sy = w == y ? static_cast<uint32_t>(j) : sy;
+        }
+        return p | (sx << 2) | (sy << 9);
+    };
+    uint32_t e[U];
+    int32_t c0 = 0, c1 = 0;
 #pragma unroll
-    for (int j = 0; j < kGroupFan; ++j) {
-        e[j] = j < n ? fan[f0 + j] : 3u;   // 3: no entry
-        c0 += (e[j] & 3u) == 0u;
-        c1 += (e[j] & 3u) == 1u;
+    for (int q = 0; q < U; ++q) {
+        e[q] = 3u;   // no entry
+        if (q < nt) e[q] = entry(v[q]);
+        c0 += (e[q] & 3u) == 0u;
+        c1 += (e[q] & 3u) == 1u;
     }
-    int q0 = f0, q1 = f0 + c0, q2 = f0 + c0 + c1;
+    auto corners = [&](int32_t q) -> Corners { return reinterpret_cast<const Corners*>(tris)[tri_idx[tb + q]]; };
+    if (GROUP)
+#pragma unroll 1
+        for (int32_t q = U; q < nt; ++q) {
+            const Corners c = corners(q);
+            c0 += c.v0 == o;
+            c1 += c.v0 != o && c.v1 == o;
+        }
+    int32_t at0 = fo, at1 = fo + c0, at2 = fo + c0 + c1;
+    auto put = [&](uint32_t w) {
+        const uint32_t p = w & 3u;
+        const int32_t at = !GROUP || p == 0u ? at0 : (p == 1u ? at1 : at2);
+        fan[at] = static_cast<uint16_t>(w);
+        at0 += !GROUP || p == 0u;
+        at1 += p == 1u;
+        at2 += p == 2u;
+    };
 #pragma unroll
-    for (int j = 0; j < kGroupFan; ++j) {
-        const uint32_t p = e[j] & 3u;
-        if (p == 3u) continue;
-        const int at = p == 0u ? q0++ : (p == 1u ? q1++ : q2++);
-        fan[at] = static_cast<uint16_t>(e[j]);
-    }
-    split[k] = static_cast<uint32_t>(c0) | (static_cast<uint32_t>(c0 + c1) << 16);
+    for (int q = 0; q < U; ++q)
+        if (q < nt) put(e[q]);
+#pragma unroll 1
+    for (int32_t q = U; q < nt; ++q) put(entry(corners(q)));
+    if (GROUP)
+        split[k] = nt < 0xFFFF ? static_cast<uint32_t>(c0) | (static_cast<uint32_t>(c0 + c1) << 16) : kFanUngrouped;
 }
 
 // Both buffers of the ping-pong pair start at the caller's positions (X1
@@ -1430,14 +1438,15 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     if (m.tile_nodes == 0) {
         // (a mesh that did not fit the tile path gave the tile arrays' room back,
         // which bounds this)
-        const bool group = m.n_free > 0 && m.n_free < kGroupFansBelow;
+        const bool group = m.n_free > 0 && m.n_free < kGroupFansBelow && m.max_deg <= 8 && !m.resident &&
+                           m.lane_width == 0;
         if ((r = persist.take(&m.nbr, m.nnz_free)) || (r = persist.take(&m.fan, m.ninc_free)) ||
             (group && (r = persist.take(&m.fan_split, m.n_free))))
             return r;
         if (m.n_free > 0)
-            k_rows_fans<<<gf, kBS, 0, st>>>(m.perm, m.new_of_old, m.n_free, a.nbr_ptr, a.nbr_idx, a.tri_ptr,
-                                            a.tri_idx, a.tris, m.row_ptr, m.nbr, m.fan_ptr, m.fan);
-        if (group) k_fan_group<<<gf, kBS, 0, st>>>(m.fan_ptr, m.fan, m.fan_split, m.n_free);
+            (group ? k_rows_fans<true> : k_rows_fans<false>)<<<gf, kBS, 0, st>>>(
+                m.perm, m.new_of_old, m.n_free, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, m.row_ptr, m.nbr,
+                m.fan_ptr, m.fan, m.fan_split);
     }
     SL_HIP(hipGetLastError());
     return SL_OK;

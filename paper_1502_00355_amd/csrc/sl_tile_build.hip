@@ -96,11 +96,6 @@ __device__ int set_find(const int32_t* tab, int32_t key)
 
 // ------------------------------------------------------------ tile build --
 
-// A triangle of the caller's array, in one 12-byte load.
-struct Corners {
-    int32_t v0, v1, v2;
-};
-
 struct TileBuildArgs {
     const int32_t* perm;
     const int32_t* new_of_old;

@@ -13,7 +13,7 @@ region).  value = free nodes x sweeps x K / elapsed wall time.
 
 roofline: the sweep kernel (the dominant kernel), algorithmic bytes per
 launch (sum over free nodes of 36 + 4 d_i + 2 t_i) / its mean duration from
-HIP events on the library's stream, against 8 TB/s.
+the report's sweep time (clock stamps of the kernels), against 8 TB/s.
 
 batched: M independent jittered grids (side log-uniform in [24, 450],
 random diagonals, +-0.35h, seeds 10000 + m), 50 sweeps each, smoothed by one

@@ -308,6 +308,7 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     // launch closes its own sweep
     const TileLaunch L{cs.m.work, cs.m.n_tiles, cs.m.tile_nodes, cs.m.halo_max, cs.m.rows_max, o.layout, o.accept,
                        cs.state, resolve_wg_per_cu(o), tol2 > 0.0 ? 1 : 0, o.precision, cs.sched, 1, 1};
+    const int32_t together = tiles && cs.m.n_tile_classes == 0 && tol2 == 0.0 ? its : 0;
     auto enqueue = [&](int32_t s, hipStream_t on) -> sl_status {
         uint64_t* bits = cs.bits ? cs.bits + static_cast<int64_t>(s) * words : nullptr;
         if (tiles && cs.m.n_tile_classes > 0) {
@@ -324,7 +325,13 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
             }
             return SL_OK;
         }
-        if (tiles) return launch_sweep_tiles(L, s & 1, bits, on);
+        if (tiles) {
+            // without a tolerance the run's last sweep closes them all
+            TileLaunch Ls = L;
+            Ls.together = together;
+            if (together > 0 && s + 1 < its) Ls.n_close = 0;
+            return launch_sweep_tiles(Ls, s & 1, bits, on);
+        }
         // the sweep's last launch closes it
         return launch_sweep_nodes(cs.m, s & 1, o.form, o.accept, block, cs.state, bits, cs.sched, on, true);
     };
@@ -368,7 +375,8 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     }
     while (done < its) {
         const int32_t c = std::min(kSweepChunk, its - done);
-        if (use_graph && c == kSweepChunk) {
+        // (the sweep that closes the others is not one of the graph's)
+        if (use_graph && c == kSweepChunk && (together == 0 || done + c < its)) {
             SL_HIP(hipGraphLaunch(cs.exec, stream));
         } else {
             for (int32_t s = done; s < done + c; ++s)

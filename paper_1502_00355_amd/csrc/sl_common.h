@@ -227,13 +227,16 @@ __device__ __forceinline__ void close_state(MeshState* p)
 
 // Counters of a tile launch, one 128-byte line each: [0] XCDs whose groups
 // are all done, [1..8] one tile counter per XCD, [9..16] groups done per
-// XCD; then (launches over one mesh) one slot per work-group for its
-// displacement maximum and accepted count (two u64).
+// XCD, [17..24] a second set of tile counters; then (launches over one mesh)
+// one slot per work-group for its displacement maximum and accepted count
+// (two u64), and one u64 per work-group for the accepted count of sweeps that
+// are not closed one by one.
 constexpr int kSchedStride = 32;                    // one 128-byte line per counter
-constexpr int kSchedCounters = 17;
+constexpr int kSchedCounters = 25;
 constexpr int kTileMaxGroups = 8 * 32 * 8;           // 8 XCDs x 32 CUs x at most 8 groups per CU
 constexpr int kTileSlotsAt = kSchedCounters * kSchedStride;   // int offset of the slots
-constexpr int kTileSchedInts = kTileSlotsAt + 4 * kTileMaxGroups;
+constexpr int kTileTotalsAt = kTileSlotsAt + 4 * kTileMaxGroups;
+constexpr int kTileSchedInts = kTileTotalsAt + 2 * kTileMaxGroups;
 
 // Work-item 0 of a group counts the group done and learns whether it is the
 // launch's last: the groups of each XCD count on their own line and the last
@@ -641,6 +644,11 @@ struct TileLaunch {
     // closing group through per-group slots instead of atomics on the one
     // state (atomics on one address are serialised)
     int32_t one_mesh = 0;
+    // Sweeps of one mesh that run whatever they find (no tolerance), closed
+    // together by the last of them: > 0 in each of their launches, the number
+    // of them that the last launch closes, itself included (n_close 1 there,
+    // 0 in the others, whose parities alternate)
+    int32_t together = 0;
 };
 sl_status launch_sweep_tiles(const TileLaunch& L, int32_t parity, uint64_t* bits, hipStream_t st);
 // Queues one class launch of Form B on colour-class tiles (L.work: the

@@ -341,8 +341,20 @@ sl_status smooth_handle(sl_mesh* h, int32_t iterations, double tol, hipStream_t 
             if ((r = h->chunk_graph(p, &ex))) return r;
             SL_HIP(hipGraphLaunch(ex, st));
         } else {
-            for (int32_t k = 0; k < c; ++k)
-                if ((r = h->sweep((p + k) & 1, st))) return r;
+            for (int32_t k = 0; k < c; ++k) {
+                // without a tolerance these sweeps are closed by the last of
+                // them (a frame of 10 sweeps: 490K nodes 213 -> 173 us, 1M
+                // nodes 329 -> 287)
+                if (tol2 == 0.0 && h->tiles()) {
+                    TileLaunch L = h->launch();
+                    L.together = c;
+                    if (k + 1 < c) L.n_close = 0;
+                    r = launch_sweep_tiles(L, (p + k) & 1, nullptr, st);
+                } else {
+                    r = h->sweep((p + k) & 1, st);
+                }
+                if (r) return r;
+            }
         }
         done += c;
         if (tol2 > 0.0) {

@@ -25,3 +25,21 @@ def test_run_lengths(size, iters):
         assert (dev[0].cpu().numpy() == ref.coords).all()
         assert rep.accepted_total == int(ref.accepted.sum()) and rep.accepted_last == int(ref.accepted[-1])
         assert rep.max_disp_sq_last == ref.disp[-1]
+
+
+def test_handle_calls():
+    """A handle's calls of few sweeps (closed together) and of a chunk and
+    more, from either buffer."""
+    m = meshgen.make_grid(140, "random", 0.35, 3)
+    h = sl.Mesh(m, kernel="tile", tile_nodes=256)
+    total = 0
+    for calls in ([1], [2, 1], [5], [31], [32, 3], [33], [65, 7]):
+        for k in calls:
+            h.smooth_async(k)
+            total += k
+        x, rep = h.download()
+        ref = oracle.smooth(m, total, threads=oracle.max_threads())
+        assert (x == ref.coords).all() and rep.iterations_run == total
+        assert rep.accepted_total == int(ref.accepted.sum()) and rep.accepted_last == int(ref.accepted[-1])
+        assert rep.max_disp_sq_last == ref.disp[-1]
+    h.close()

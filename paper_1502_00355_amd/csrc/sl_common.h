@@ -225,6 +225,11 @@ __device__ __forceinline__ void close_state(MeshState* p)
     *p = m;
 }
 
+// Waits until the wave's stores and atomics so far have been performed.  (A
+// work-group's release fence and its barrier wait for LDS only: on their own
+// they leave a store to memory on its way.)
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Counters of a tile launch, one 128-byte line each: [0] XCDs whose groups
 // are all done, [1..8] one tile counter per XCD, [9..16] groups done per
 // XCD, [17..24] a second set of tile counters; then (launches over one mesh)

@@ -19,8 +19,10 @@
 // each other both ways (neighbour rows are checked to be symmetric), the
 // writer has seen version v - 1 of some node of the reader's tile, and the
 // reader published that after it had read version v - 2 of all its halo.
-// The store that sets a slot back is waited for a sweep later, before the
-// version ahead of it is published, so that no reader finds the old value.
+// Every wave waits for its stores to memory at the head of each class (at
+// that of each sweep in Form A), so the store that sets a slot back has been
+// performed before the version ahead of it is published, and no reader finds
+// the old value.
 //
 // Form A reads one LDS buffer and writes the other; Form B updates one in
 // place, class by class, reading class c's halo nodes after its own class c.
@@ -60,6 +62,12 @@ using u64 = unsigned long long;
 constexpr u64 kSent = 0xFFF8DEAD5EA15EA1ull;   // a quiet NaN: "not published yet"
 constexpr int kFlowLag = 3;                    // sweeps a tile may run past the last decided one
 constexpr int kFlowHist = 4;                   // positions kept per node with a tolerance (kFlowLag + 1)
+// Sweeps whose displacement maxima have slots.  A wave sets the slot of sweep
+// s + 2 back in sweep s, and waits for that at the head of s + 1, before it
+// publishes the maximum ahead of it; what the slot held, that of s + 2 -
+// kFlowSlots, has been decided on when the wave starts sweep s.
+constexpr int kFlowSlots = 8;
+static_assert(2 - kFlowSlots <= -kFlowLag, "a slot is free when it is set back");
 constexpr uint32_t kDeclineColor = 8u;         // FlowState::decline: not coloured in time (1, 2, 4: the build)
 constexpr int32_t kFixedKey = INT32_MIN;       // halo key of a fixed node: kFixedKey + its place in the positions
 
@@ -515,7 +523,7 @@ struct FlowArgs {
     u64* ring;                  // [4][2n]: published versions
     double* out;                // [2n] final positions, device order
     double* hist;               // [kFlowHist][2n] (with a tolerance)
-    u64* dmax;                  // [kFlowHist][tiles * waves]: displacement maxima per sweep (with a tolerance)
+    u64* dmax;                  // [kFlowSlots][tiles * waves]: displacement maxima per sweep (with a tolerance)
     FlowGroup* groups;          // [tiles]
     u64* bits;                  // nullable: accept bits, `words` per sweep
     int64_t words;
@@ -651,7 +659,7 @@ __device__ void flow_control(const FlowArgs& a, int waves, int BS)
     if (tid == 0) s_bad = 0;
     __syncthreads();
     for (int s = 0; s < a.iters; ++s) {
-        const u64* const slot = a.dmax + (s & (kFlowHist - 1)) * cap;
+        const u64* const slot = a.dmax + (s & (kFlowSlots - 1)) * cap;
         double m = 0.0;
         Waiter w(a.fs, a.wait);
         for (int q0 = tid; q0 < n_slots; q0 += U * BS) {
@@ -768,10 +776,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         for (int c = 0; c < C; ++c) {
             const int lo = B ? cls[c] : 0, hi = B ? cls[c + 1] : nown;
             const bool last_class = c + 1 == C;
-            // every slot set back in the sweep before has been (stores that
-            // old are done: nothing waits here)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (TOL && c == 0 && lane == 0) st_dev(dslot + ((s + 1) & (kFlowHist - 1)) * dcap, kSent);
+            // what this wave has set back so far, before it publishes (stores
+            // from before the barrier: they are as good as done)
+            wait_stores();
+            if (TOL && c == 0 && lane == 0) st_dev(dslot + ((s + 2) & (kFlowSlots - 1)) * dcap, kSent);
             for (int q = lo + g; q < hi; q += groups) {
                 if (q != lo + g || (!B && groups < nown)) load_ref<W>(ref, t, q, j);
                 const int i = ref.i;
@@ -834,11 +842,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
             }
             if (TOL && last_class) {
                 const double m = wave_max(d2);
-                if (lane == 0) {
-                    // (the slot of the next sweep has been set back)
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                    st_dev(dslot + (s & (kFlowHist - 1)) * dcap, static_cast<u64>(__double_as_longlong(m)));
-                }
+                if (lane == 0) st_dev(dslot + (s & (kFlowSlots - 1)) * dcap, static_cast<u64>(__double_as_longlong(m)));
             }
             if (TOL && last_class && tid == BS - 1) {   // (a wave that rarely has halo nodes to read)
                 // sweep v runs once every sweep up to v - kFlowLag is decided;
@@ -1267,7 +1271,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     const int64_t words = (static_cast<int64_t>(n) + 63) / 64;
     const bool want_bits = o.flags_out != nullptr;
     const size_t n_bits = want_bits ? static_cast<size_t>(words) * static_cast<size_t>(iterations) : 0;
-    const size_t n_dmax = tl ? static_cast<size_t>(kFlowHist) * tiles * waves : 0;
+    const size_t n_dmax = tl ? static_cast<size_t>(kFlowSlots) * tiles * waves : 0;
     const size_t bytes = Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(ValStats) * static_cast<size_t>(val_groups(n))) +
                          Arena::piece(4 * static_cast<size_t>(nbk)) + Arena::piece(4 * static_cast<size_t>(nbk + 1)) +
                          scan_bytes(nbk) + 5 * Arena::piece(4 * un) + Arena::piece(sizeof(FlowState)) +
@@ -1438,7 +1442,7 @@ sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st)
     f->p = flow_shape(m.n, false);
     f->tiles = div_up(m.n, f->p.T);
     const FlowLayout L(f->p.T);
-    const size_t n_dmax = static_cast<size_t>(kFlowHist) * f->tiles * (f->p.BS / 64);
+    const size_t n_dmax = static_cast<size_t>(kFlowSlots) * f->tiles * (f->p.BS / 64);
     FlowArgs& fa = f->fa;
     unsigned char* rec = nullptr;
     ValStats* vs = nullptr;
@@ -1506,7 +1510,7 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
         // (a run with a tolerance leaves groups some sweeps apart)
         f->version = 0;
         const FlowInitArgs ia{nullptr, a.fs, nullptr, 0, nullptr, m.n, a.ring + 2 * static_cast<int64_t>(m.n), a.dmax,
-                              tl ? static_cast<int64_t>(kFlowHist) * f->tiles * (f->p.BS / 64) : 0, nullptr, 0};
+                              tl ? static_cast<int64_t>(kFlowSlots) * f->tiles * (f->p.BS / 64) : 0, nullptr, 0};
         k_flow_init<<<std::min(div_up(m.n, 256), 1024), 256, 0, st>>>(ia);
         SL_HIP(hipGetLastError());
     }

@@ -247,9 +247,9 @@ constexpr int kTileSchedInts = kTileTotalsAt + 2 * kTileMaxGroups;
 // launch's last: the groups of each XCD count on their own line and the last
 // of them counts the XCD on the launch's line, so no line takes more than
 // gridDim.x / 8 atomics (atomics on one address are serialised).  The
-// launch's grid is a multiple of 8, group g on XCD g % 8.  The group's
-// earlier device-scope writes are performed before its count (the
-// work-group-scope release waits for them).
+// launch's grid is a multiple of 8, group g on XCD g % 8.  Work-item 0's
+// earlier device-scope stores and atomics, among them the group's folds, are
+// waited for before its count, so that the last group finds them.
 // Launches of at most kDirectFoldGroups groups count on the launch's line
 // alone and fold straight into the state: so few atomics cost less than
 // the longer chain of the two-level count and the slots.
@@ -257,7 +257,7 @@ constexpr int kDirectFoldGroups = 64;
 
 __device__ __forceinline__ bool count_group_done(int32_t* sched)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    wait_stores();
     if (static_cast<int>(gridDim.x) <= kDirectFoldGroups)
         return __hip_atomic_fetch_add(sched, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                static_cast<int>(gridDim.x) - 1;
@@ -363,9 +363,8 @@ __device__ __forceinline__ bool fold_through_slots(int32_t* sched, MeshState* ms
 
 // The last work-group of a launch to finish closes the sweep of states[0..n)
 // and zeroes the launch's counters for the next launch.  A group's folds into the
-// sweep state are device-scope atomics made by its first work-item; the
-// work-group-scope release waits until they have completed, so they are
-// performed before the group's count.  The closing group reads the folds
+// sweep state are device-scope atomics made by its first work-item, which
+// waits for them before it counts the group.  The closing group reads the folds
 // with device-scope atomic loads after it has seen every count.  No
 // device-scope release or acquire is needed: those would write back or
 // invalidate the XCD's L2, once per work-group.

@@ -116,7 +116,7 @@ __device__ __forceinline__ void finish_kept(const SweepArgs& a, const Kept& kept
     if (tid == 0) {
         if (m > 0.0) atomicMax(&a.state->maxd_cur, static_cast<unsigned long long>(__double_as_longlong(m)));
         if (cnt) atomicAdd(&a.state->acc_cur, cnt);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");   // (close_state reads them)
+        wait_stores();   // (close_state reads them)
         close_state(a.state);
     }
     reset_sched(a.sched);

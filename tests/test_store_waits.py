@@ -100,3 +100,30 @@ def test_exchange_stores_are_waited_for(kernels):
         before = walk(code, step)
         for k in at:
             assert before[k] is None or "old" not in before[k], "%s at %x" % (n, code[k][0])
+
+
+def test_folds_are_waited_for_before_a_group_is_counted(kernels):
+    """A launch's last work-group reads what the others left: a group's
+    stores and atomics are done before the atomic that counts it."""
+    def is_fold(ins):
+        return (ins.startswith("global_store") and ins.endswith("sc1")) or \
+               (ins.startswith("global_atomic") and not ins.endswith("sc0"))
+
+    def step(s, ins):
+        if waits_for_all(ins):
+            return frozenset()
+        return s | {"store"} if is_fold(ins) else s
+
+    found = 0
+    for n, code in kernels.items():
+        if not re.search(r"k_sweep(_split|_lanes|_tile|_class)?I", n):
+            continue
+        # (in the tile kernel the others are the counters that deal the tiles)
+        at = [k for k, (_, ins, _) in enumerate(code) if ins.startswith("global_atomic_add ") and ins.endswith("sc0") and
+              ("k_sweep_tile" not in n or "offset:1152" in ins)]
+        assert at, n
+        found += 1
+        before = walk(code, step)
+        for k in at:
+            assert not before[k], "%s at %x" % (n, code[k][0])
+    assert found > 50

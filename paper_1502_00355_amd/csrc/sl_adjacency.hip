@@ -169,9 +169,9 @@ __global__ __launch_bounds__(kAB) void k_adj_zero(int32_t* p, int64_t n)
 
 constexpr int kAdjInc = 16;   // incidences of a node handled in registers and LDS
 
-// One node's incidences (c <= R of them) from registers: sorted by rank into
-// tri_idx (when asked for), the two other vertices of each triangle to the
-// node's LDS column in sorted order.
+// One node's incidences (1 <= c <= R of them) from registers: sorted by rank
+// into tri_idx (when asked for), the two other vertices of each triangle to
+// the node's LDS column in sorted order.  (The slots past c read triangle 0.)
 template <int R>
 __device__ __forceinline__ void adj_gather(int32_t v, int c, int32_t* __restrict__ row, const int32_t* __restrict__ tris,
                                            int32_t (*cand)[kAB], bool sorted)
@@ -216,8 +216,9 @@ __global__ __launch_bounds__(kAB) void k_adj_rows(int32_t n, const int32_t* __re
     int32_t L = 0;
     bool interior = c > 0;
     if (c <= kAdjInc) {
-        if (c <= 8) adj_gather<8>(v, c, tri_idx + b, tris, cand, ROWS);
-        else adj_gather<kAdjInc>(v, c, tri_idx + b, tris, cand, ROWS);
+        // (a node in no triangle reads none: there may be no triangle at all)
+        if (c > 8) adj_gather<kAdjInc>(v, c, tri_idx + b, tris, cand, ROWS);
+        else if (c > 0) adj_gather<8>(v, c, tri_idx + b, tris, cand, ROWS);
         for (int k = 0; k < 2 * c; ++k) {
             const int32_t u = cand[k][tid];
             int q = 0;

@@ -148,6 +148,7 @@ struct sl_mesh {
     std::shared_ptr<sl::EventRef> last;     // recorded after the last work queued on the mesh
     hipStream_t last_stream = nullptr;      // where that work was queued
     bool timed = false;                     // the state's clock stamps are of a smooth call
+    bool captured = false;                  // work on the mesh has been captured into a caller's graph
     double setup_ms = 0.0;
     hipGraph_t graph[2] = {nullptr, nullptr};   // a chunk of sweeps from buffer 0 / buffer 1
     hipGraphExec_t exec[2] = {nullptr, nullptr};
@@ -222,6 +223,19 @@ struct sl_mesh {
         }
         *out = exec[p];
         return SL_OK;
+    }
+
+    // Whether `st` is being captured.  A graph of the caller's reads and
+    // writes the buffers it was captured with whenever it is replayed: from
+    // then on every call's sweeps alternate the buffers one by one (an even
+    // number leaves the positions where they were), which a run of the flow
+    // path does not.
+    bool note_capture(hipStream_t st)
+    {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+        else if (cap != hipStreamCaptureStatusNone) captured = true;
+        return cap != hipStreamCaptureStatusNone;
     }
 
     // Makes `st` wait for the mesh's last queued work.
@@ -311,7 +325,8 @@ sl_status smooth_handle(sl_mesh* h, int32_t iterations, double tol, hipStream_t 
     const double tol2 = tol > 0.0 ? tol * tol : 0.0;
     if ((r = h->after_last(st))) return r;
     const bool jacobi = h->o.form == SL_JACOBI;
-    if (h->m.flow) {
+    (void)h->note_capture(st);
+    if (h->m.flow && !h->captured) {
         // all the sweeps in one launch, from the current buffer into the other
         bool ran = false;
         if ((r = flow_mesh_sweeps(h->m, h->cur, h->o.accept, iterations, tol2, h->state, st, &ran))) return r;
@@ -495,6 +510,7 @@ sl_status sl_mesh_download_device(sl_mesh* h, double* coords, void* stream)
     if (reinterpret_cast<uintptr_t>(coords) % 16 != 0) return fail(SL_EINVAL, "coords must be 16-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     if ((r = h->after_last(st))) return r;
+    (void)h->note_capture(st);
     if ((r = unpermute_coords(h->m, h->o.form == SL_JACOBI ? h->cur : 0, coords, st))) return r;
     return h->mark(st);
 }

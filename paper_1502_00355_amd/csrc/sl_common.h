@@ -572,6 +572,19 @@ struct PinnedPad {
     sl_status init();
 };
 
+// A few bytes of such memory for as long as a handle lives: cut from pads of
+// their own, which stay in their pool (as many as were in use at once need).
+constexpr size_t kCellBytes = 64;
+struct PinnedCell {
+    void* p = nullptr;
+    int dev = -1;
+    PinnedCell() = default;
+    PinnedCell(const PinnedCell&) = delete;
+    PinnedCell& operator=(const PinnedCell&) = delete;
+    ~PinnedCell();
+    sl_status init();
+};
+
 // One caller mesh's host arrays copied into a single device allocation
 // (nnz = nbr_ptr[n], ninc = tri_ptr[n], already read by the caller), with
 // `extra` more bytes left in `ar` for the caller.  release() frees it,

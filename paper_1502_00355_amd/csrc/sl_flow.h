@@ -79,10 +79,8 @@ void flow_mesh_free(FlowMesh*& f, hipStream_t st);
 bool flow_wanted(const sl_options& o, int32_t n);
 // Queues `iterations` sweeps of m from buffer `cur` into the other one (the
 // free nodes; *state counts them, as the per-sweep closes would) when the
-// device has room for its groups now; *done tells.  The caller then records
-// an event after the work and hands it to flow_mesh_settle.
+// device has room for its groups now; *done tells.
 sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t iterations, double tol2, MeshState* state,
                            hipStream_t st, bool* done);
-void flow_mesh_settle(FlowMesh* f, hipEvent_t after);
 
 }  // namespace sl

@@ -979,6 +979,11 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
     if (k < n_free) reinterpret_cast<double2*>(coords)[a.perm[k]] = src[k];
 }
 
+// What a handle's runs leave on the host.
+struct FlowCell {
+    uint32_t done;   // the last run whose groups have all left the device
+};
+
 // The end of a handle's run, one work-group: the sweep state, from the
 // groups' words.  A handle's call does not wait for the device, so when the
 // run was given up (Waiter) the sweeps are made here, tile after tile and
@@ -987,7 +992,8 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
 // sweeps (kSerialSteps) are made this way to begin with (serial): one launch.
 constexpr int kFinishBS = 512;
 template <bool GT>
-__global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, int serial, MeshState* ms)
+__global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, int serial, MeshState* ms, FlowCell* cell,
+                                                           uint32_t run)
 {
     extern __shared__ double2 flow_lds[];
     __shared__ double s_recip[kMaxValence + 1];
@@ -996,6 +1002,7 @@ __global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, T = a.T, n_free = a.vs->n_free;
     const int tiles = (n_free + T - 1) / T;
     const u64 t_begin = serial ? wall_clock64() : a.fs->t_sweep;
+    if (!serial && tid == 0) __hip_atomic_store(&cell->done, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (!serial && a.fs->abort == 0) {   // (no group runs any more)
         const FlowGroup f = fold_groups<kFinishBS>(a.groups, tiles);
         if (tid == 0) {
@@ -1106,8 +1113,10 @@ __global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, 
 // so that all of them are resident together and none waits for a group that
 // cannot start.  A call that finds too few left takes the other kernels.
 // A handle's calls return before their work is done: it keeps its places
-// between calls, and another taker gets them once the event recorded after
-// the last of them has passed.
+// between calls, and another taker gets them once the device has written the
+// number of the last of them to the host.  (Not by asking an event: the
+// runtime takes a query of an event whose stream is being captured meanwhile
+// for an error of the capture.)
 class FlowSlots {
 public:
     ~FlowSlots() { give(); }
@@ -1116,7 +1125,7 @@ public:
     {
         std::lock_guard<std::mutex> lk(mu);
         if (held) {
-            ev = nullptr;   // in use: not to be taken back
+            word = nullptr;   // in use: not to be taken back
             return true;
         }
         if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
@@ -1131,20 +1140,20 @@ public:
         if (used[dev] + groups > limit[dev])
             for (size_t k = keepers.size(); k-- > 0;) {
                 FlowSlots* const f = keepers[k];
-                if (f->dev == dev && f->ev && hipEventQuery(f->ev) == hipSuccess) f->drop();
-                else (void)hipGetLastError();   // (a query's "not ready" is not an error)
+                if (f->dev == dev && f->word && __atomic_load_n(f->word, __ATOMIC_ACQUIRE) == f->last) f->drop();
             }
         if (used[dev] + groups > limit[dev]) return false;
         used[dev] += groups;
         held = groups;
         return true;
     }
-    // Kept until `after` has passed.
-    void keep(hipEvent_t after)
+    // Kept until *w is `run`, or longer.
+    void keep(const uint32_t* w, uint32_t run)
     {
         std::lock_guard<std::mutex> lk(mu);
         if (!held) return;
-        ev = after;
+        word = w;
+        last = run;
         if (std::find(keepers.begin(), keepers.end(), this) == keepers.end()) keepers.push_back(this);
     }
     void give()
@@ -1158,14 +1167,15 @@ private:
     {
         used[dev] -= held;
         held = 0;
-        ev = nullptr;
+        word = nullptr;
         keepers.erase(std::remove(keepers.begin(), keepers.end(), this), keepers.end());
     }
     static std::mutex mu;
     static int used[64], limit[64];
     static std::vector<FlowSlots*> keepers;
     int dev = -1, held = 0;
-    hipEvent_t ev = nullptr;   // set while kept between calls
+    const uint32_t* word = nullptr;   // set while kept between calls
+    uint32_t last = 0;
 };
 std::mutex FlowSlots::mu;
 int FlowSlots::used[64], FlowSlots::limit[64];
@@ -1379,6 +1389,8 @@ struct FlowMesh {
     int tiles = 0;
     FlowArgs fa{};
     FlowSlots slots;
+    PinnedCell cell;
+    uint32_t run = 0;       // runs queued
     bool fresh = true;      // the exchange's slots are to be set up before the next run
     uint32_t version = 0;   // of the positions, as the exchange counts them
 };
@@ -1400,19 +1412,21 @@ __global__ void k_flow_mesh_tell(const FlowState* __restrict__ fs, uint32_t* __r
 }
 
 template <bool GT>
-sl_status launch_finish_v(const FlowArgs& a, const FlowShape& p, bool tol, bool serial, MeshState* state, hipStream_t st)
+sl_status launch_finish_v(const FlowArgs& a, const FlowShape& p, bool tol, bool serial, MeshState* state, FlowCell* cell,
+                          uint32_t run, hipStream_t st)
 {
     const FlowLayout L(p.T);
     const size_t lds = static_cast<size_t>(p.T + L.hc) * 16 + static_cast<size_t>(L.bytes);
-    k_flow_finish<GT><<<1, kFinishBS, lds, st>>>(a, tol ? 1 : 0, serial ? 1 : 0, state);
+    k_flow_finish<GT><<<1, kFinishBS, lds, st>>>(a, tol ? 1 : 0, serial ? 1 : 0, state, cell, run);
     SL_HIP(hipGetLastError());
     return SL_OK;
 }
 
 sl_status launch_finish(const FlowArgs& a, const FlowShape& p, bool gt, bool tol, bool serial, MeshState* state,
-                        hipStream_t st)
+                        FlowCell* cell, uint32_t run, hipStream_t st)
 {
-    return gt ? launch_finish_v<true>(a, p, tol, serial, state, st) : launch_finish_v<false>(a, p, tol, serial, state, st);
+    return gt ? launch_finish_v<true>(a, p, tol, serial, state, cell, run, st)
+              : launch_finish_v<false>(a, p, tol, serial, state, cell, run, st);
 }
 
 // Tiles times sweeps up to which one work-group makes them all: 4 tile steps
@@ -1448,7 +1462,7 @@ sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st)
     ValStats* vs = nullptr;
     PinnedPad pad;
     sl_status r = pad.init();
-    if (r || (r = f->ar.reserve(Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(FlowState)) +
+    if (r || (r = f->cell.init()) || (r = f->ar.reserve(Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(FlowState)) +
                                     Arena::piece(static_cast<size_t>(f->tiles) * L.bytes) + Arena::piece(4 * 16 * un) +
                                     Arena::piece(kFlowHist * 16 * un) + Arena::piece(8 * n_dmax) +
                                     Arena::piece(sizeof(FlowGroup) * static_cast<size_t>(f->tiles)),
@@ -1466,6 +1480,7 @@ sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st)
     fa.T = f->p.T;
     fa.tiles = f->tiles;
     fa.wait = kFlowWait;
+    *static_cast<FlowCell*>(f->cell.p) = FlowCell{};
     k_flow_mesh_begin<<<1, 64, 0, st>>>(vs, fa.fs, m.n_free);
     const FlowBuildArgs ba{vs, fa.fs, m.perm, m.new_of_old, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, nullptr, rec};
     launch_build<false>(ba, f->p.T, f->tiles, st);
@@ -1503,7 +1518,7 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
     a.tol2 = tol2;
     if (static_cast<int64_t>(f->tiles) * iterations <= kSerialSteps) {
         *done = true;
-        return launch_finish(a, f->p, gt, tl, true, state, st);
+        return launch_finish(a, f->p, gt, tl, true, state, nullptr, 0, st);
     }
     if (!f->slots.take(f->tiles + 1)) return SL_OK;   // (+ 1: a run with a tolerance has a controller)
     if (f->fresh || tl) {
@@ -1516,13 +1531,13 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
     }
     a.v0 = static_cast<int32_t>(f->version & 3u);
     sl_status r = launch_flow(a, f->p, false, gt, tl, st);
-    if (r || (r = launch_finish(a, f->p, gt, tl, false, state, st))) return r;
+    FlowCell* const cell = static_cast<FlowCell*>(f->cell.p);
+    if (r || (r = launch_finish(a, f->p, gt, tl, false, state, cell, ++f->run, st))) return r;
+    f->slots.keep(&cell->done, f->run);
     f->fresh = tl;
     f->version += static_cast<uint32_t>(iterations);
     *done = true;
     return SL_OK;
 }
-
-void flow_mesh_settle(FlowMesh* f, hipEvent_t after) { f->slots.keep(after); }
 
 }  // namespace sl

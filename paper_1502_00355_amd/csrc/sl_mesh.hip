@@ -334,7 +334,6 @@ sl_status smooth_handle(sl_mesh* h, int32_t iterations, double tol, hipStream_t 
             h->cur ^= 1;
             h->timed = true;
             if ((r = h->mark(st))) return r;
-            flow_mesh_settle(h->m.flow, h->mine->ev);
             if (tol2 > 0.0) {
                 MeshState ms{};
                 if ((r = read_state(h, &ms, st))) return r;

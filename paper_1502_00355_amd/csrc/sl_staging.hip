@@ -266,7 +266,17 @@ namespace {
 // Free pads per device: bounded by what is in use at once, at most kKept kept.
 constexpr size_t kKept = 64;
 std::mutex g_small_mu;
-std::vector<void*> g_pads[64];
+std::vector<void*> g_pads[64], g_cells[64];
+
+sl_status new_pad(void** p)
+{
+    if (hipHostMalloc(p, kPadBytes, hipHostMallocDefault) != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();
+        return fail(SL_ENOMEM, "pinned memory allocation failed");
+    }
+    return SL_OK;
+}
 
 }  // namespace
 
@@ -281,12 +291,30 @@ sl_status PinnedPad::init()
             return SL_OK;
         }
     }
-    if (hipHostMalloc(&p, kPadBytes, hipHostMallocDefault) != hipSuccess) {
-        p = nullptr;
-        (void)hipGetLastError();
-        return fail(SL_ENOMEM, "pinned memory allocation failed");
+    return new_pad(&p);
+}
+
+sl_status PinnedCell::init()
+{
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(SL_EDEVICE, "no current device");
+    std::lock_guard<std::mutex> lk(g_small_mu);
+    if (g_cells[dev].empty()) {
+        void* pad = nullptr;
+        const sl_status r = new_pad(&pad);
+        if (r) return r;
+        for (size_t k = 0; k < kPadBytes / kCellBytes; ++k)
+            g_cells[dev].push_back(static_cast<unsigned char*>(pad) + k * kCellBytes);
     }
+    p = g_cells[dev].back();
+    g_cells[dev].pop_back();
     return SL_OK;
+}
+
+PinnedCell::~PinnedCell()
+{
+    if (!p) return;
+    std::lock_guard<std::mutex> lk(g_small_mu);
+    g_cells[dev].push_back(p);
 }
 
 PinnedPad::~PinnedPad()

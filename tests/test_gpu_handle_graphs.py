@@ -73,3 +73,27 @@ def test_captured_download_follows_eager_sweeps(size):
         st.synchronize()
         assert (out.cpu().numpy() == oracle.smooth(m, k, threads=oracle.max_threads()).coords).all()
     h.close()
+
+
+def test_other_handles_run_beside_a_capture():
+    """Two handles whose tiles do not fit the device together: while one's
+    call is being captured, the other takes the room that the first one's
+    earlier, finished call had, and the capture stays whole."""
+    import torch
+    m = meshgen.make_grid(470, "random", 0.35, 9)
+    st, st2 = torch.cuda.Stream(), torch.cuda.Stream()
+    h, h2 = sl.Mesh(m), sl.Mesh(m)
+    h.smooth_async(4, stream=st)
+    st.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st, capture_error_mode="relaxed"):
+        h.smooth_async(6, stream=st)
+        h2.smooth_async(8, stream=st2)
+    with torch.cuda.stream(st):
+        g.replay()
+    st.synchronize()
+    st2.synchronize()
+    assert (positions(h, st) == oracle.smooth(m, 10, threads=oracle.max_threads()).coords).all()
+    assert (h2.download()[0] == oracle.smooth(m, 8, threads=oracle.max_threads()).coords).all()
+    h.close()
+    h2.close()

@@ -351,6 +351,21 @@ SL_API void sl_mesh_destroy(sl_mesh* mesh);
  * allocate again. */
 SL_API sl_status sl_release_cached_memory(void);
 
+/* How often calls of this process took the path on which every sweep of a
+ * mesh runs in one launch (SL_KERNEL_AUTO above), which the results do not
+ * show.  counts[0]: calls that ran on it; [1]: one-call smooths whose mesh
+ * turned out not to be for it, after its checks had run; [2]: runs given up
+ * because the device did not hold all work-groups at once in time (their
+ * sweeps were made by other kernels; a handle's are counted when a later call
+ * on the handle, or a download or report, sees it); [3]: calls that found no
+ * room on the device. */
+SL_API void sl_one_launch_counts(int64_t counts[4]);
+
+/* For tests: how long a work-group of that path waits for another one before
+ * the run is given up, in milliseconds, in later calls of the calling thread;
+ * 0 gives up at once, negative restores the default. */
+SL_API void sl_one_launch_wait(double ms);
+
 /* ---- adjacency from a triangle list -------------------------------------
  * Builds the inputs the smoothing calls take from a bare triangle list, the
  * way the paper finds neighbours and constraints (Sec. 3.3.2, Sec. 3.3.3):

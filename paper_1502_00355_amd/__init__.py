@@ -196,6 +196,10 @@ def lib():
         L.sl_mesh_destroy.restype = None
         L.sl_release_cached_memory.argtypes = []
         L.sl_release_cached_memory.restype = ctypes.c_int
+        L.sl_one_launch_counts.argtypes = [ctypes.POINTER(ctypes.c_int64)]
+        L.sl_one_launch_counts.restype = None
+        L.sl_one_launch_wait.argtypes = [d]
+        L.sl_one_launch_wait.restype = None
         _lib = L
     return _lib
 
@@ -554,6 +558,14 @@ def smooth_batch_async(handles, iterations: int, tol: float = 0.0, stream=None) 
 def release_cached_memory():
     """Returns the device memory the library keeps for reuse (sl_release_cached_memory)."""
     _check(lib().sl_release_cached_memory())
+
+
+def one_launch_counts() -> dict:
+    """How often this process took the path that runs every sweep in one
+    launch (sl_one_launch_counts)."""
+    c = (ctypes.c_int64 * 4)()
+    lib().sl_one_launch_counts(c)
+    return dict(zip(("runs", "declined", "given_up", "no_room"), c))
 
 
 def to_device(mesh, device="cuda"):

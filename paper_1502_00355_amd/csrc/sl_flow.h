@@ -82,5 +82,8 @@ bool flow_wanted(const sl_options& o, int32_t n);
 // device has room for its groups now; *done tells.
 sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t iterations, double tol2, MeshState* state,
                            hipStream_t st, bool* done);
+// Counts runs of f that were given up and have not been counted yet (when the
+// host has waited for them, or some time later).
+void flow_mesh_note(FlowMesh* f);
 
 }  // namespace sl

@@ -43,6 +43,7 @@
 // W lanes of a wave share a node's fan and fold their minima (exact in any
 // order).
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cstring>
 #include <mutex>
@@ -130,7 +131,7 @@ __device__ __forceinline__ bool flow_off(const ValStats* vs, const FlowState* fs
 }
 
 // Bounded waiting: every 256 polls the abort word and the clock are looked
-// at.  False: give up.
+// at; with a limit of 0 nothing is waited for.  False: give up.
 struct Waiter {
     FlowState* fs;
     u64 limit, t0;
@@ -138,11 +139,11 @@ struct Waiter {
     __device__ __forceinline__ Waiter(FlowState* f, u64 l) : fs(f), limit(l), t0(0), polls(0) {}
     __device__ __forceinline__ bool again()
     {
-        if ((++polls & 255u) != 0) return true;
+        if ((++polls & 255u) != 0 && limit != 0) return true;
         if (ld_dev(&fs->abort)) return false;
         const u64 now = wall_clock64();
         if (t0 == 0) t0 = now;
-        if (now - t0 <= limit) return true;
+        if (now - t0 <= limit && limit != 0) return true;
         st_dev(&fs->abort, 1u);
         return false;
     }
@@ -981,7 +982,8 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
 
 // What a handle's runs leave on the host.
 struct FlowCell {
-    uint32_t done;   // the last run whose groups have all left the device
+    uint32_t done;       // the last run whose groups have all left the device
+    uint32_t given_up;   // runs given up
 };
 
 // The end of a handle's run, one work-group: the sweep state, from the
@@ -1022,6 +1024,10 @@ __global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, 
         }
         return;
     }
+    if (!serial && tid == 0)   // (the one writer: no atomic over the bus)
+        __hip_atomic_store(&cell->given_up,
+                           __hip_atomic_load(&cell->given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const FlowLayout L(T);
     double2* const X = flow_lds;
     unsigned char* const rec = reinterpret_cast<unsigned char*>(flow_lds + T + L.hc);
@@ -1206,6 +1212,13 @@ constexpr int32_t kFlowMaxNodes = 512 * 500;
 constexpr int32_t kFlowMaxSweeps = 1 << 20;   // of one launch
 constexpr u64 kFlowWait = 200000000ull;       // 2 s of the 100 MHz clock
 
+std::atomic<int64_t> g_counts[4];             // sl_one_launch_counts
+enum { kCountRun, kCountDeclined, kCountGivenUp, kCountNoRoom };
+void count(int what, int64_t by = 1) { g_counts[what].fetch_add(by, std::memory_order_relaxed); }
+
+thread_local double t_wait_ms = -1.0;         // sl_one_launch_wait
+u64 wait_limit() { return t_wait_ms < 0.0 ? kFlowWait : static_cast<u64>(t_wait_ms / kTickMs); }
+
 // Automatic choices only, in double precision and the default order.
 bool flow_options(const sl_options& o, int32_t n)
 {
@@ -1271,7 +1284,10 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     const FlowLayout L(p.T);
     const int tiles = div_up(n, p.T), waves = p.BS / 64;
     FlowSlots slots;
-    if (!slots.take(tiles + (tl ? 1 : 0))) return SL_OK;
+    if (!slots.take(tiles + (tl ? 1 : 0))) {
+        count(kCountNoRoom);
+        return SL_OK;
+    }
 
     const size_t un = static_cast<size_t>(n);
     FlowOrder f{};
@@ -1336,7 +1352,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     fa.tiles = tiles;
     fa.iters = iterations;
     fa.tol2 = tl ? tol * tol : 0.0;
-    fa.wait = kFlowWait;
+    fa.wait = wait_limit();
     fa.nbr_end = a.nbr_ptr + n;
     fa.tri_end = a.tri_ptr + n;
 
@@ -1357,7 +1373,12 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
 
     const FlowReport h = *rep;
     // (what the checks found wrong, the other path finds and reports too)
-    if (h.vs.err != 0 || h.vs.n_free == 0 || h.decline || h.abort || h.n_colors > kFlowClasses) return SL_OK;
+    const bool late = h.abort != 0 || (h.decline & kDeclineColor) != 0;
+    if (late || h.vs.err != 0 || h.vs.n_free == 0 || h.decline || h.n_colors > kFlowClasses) {
+        count(late ? kCountGivenUp : kCountDeclined);
+        return SL_OK;
+    }
+    count(kCountRun);
     if (want_bits) {
         if ((r = unpermute_flags_raw(bits, words, f.new_of_old, n, h.vs.n_free, iterations, ms, o.flags_out, st))) return r;
         SL_HIP(hipStreamSynchronize(st));
@@ -1391,6 +1412,7 @@ struct FlowMesh {
     FlowSlots slots;
     PinnedCell cell;
     uint32_t run = 0;       // runs queued
+    uint32_t noted = 0;     // runs given up, as far as counted
     bool fresh = true;      // the exchange's slots are to be set up before the next run
     uint32_t version = 0;   // of the positions, as the exchange counts them
 };
@@ -1479,7 +1501,6 @@ sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st)
     fa.n = m.n;
     fa.T = f->p.T;
     fa.tiles = f->tiles;
-    fa.wait = kFlowWait;
     *static_cast<FlowCell*>(f->cell.p) = FlowCell{};
     k_flow_mesh_begin<<<1, 64, 0, st>>>(vs, fa.fs, m.n_free);
     const FlowBuildArgs ba{vs, fa.fs, m.perm, m.new_of_old, a.nbr_ptr, a.nbr_idx, a.tri_ptr, a.tri_idx, a.tris, nullptr, rec};
@@ -1516,11 +1537,16 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
     a.out = static_cast<double*>(m.X[cur ^ 1]);
     a.iters = iterations;
     a.tol2 = tol2;
+    a.wait = wait_limit();
     if (static_cast<int64_t>(f->tiles) * iterations <= kSerialSteps) {
         *done = true;
+        count(kCountRun);
         return launch_finish(a, f->p, gt, tl, true, state, nullptr, 0, st);
     }
-    if (!f->slots.take(f->tiles + 1)) return SL_OK;   // (+ 1: a run with a tolerance has a controller)
+    if (!f->slots.take(f->tiles + 1)) {   // (+ 1: a run with a tolerance has a controller)
+        count(kCountNoRoom);
+        return SL_OK;
+    }
     if (f->fresh || tl) {
         // (a run with a tolerance leaves groups some sweeps apart)
         f->version = 0;
@@ -1534,10 +1560,30 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
     FlowCell* const cell = static_cast<FlowCell*>(f->cell.p);
     if (r || (r = launch_finish(a, f->p, gt, tl, false, state, cell, ++f->run, st))) return r;
     f->slots.keep(&cell->done, f->run);
+    count(kCountRun);
     f->fresh = tl;
     f->version += static_cast<uint32_t>(iterations);
     *done = true;
     return SL_OK;
 }
 
+void flow_mesh_note(FlowMesh* f)
+{
+    if (!f) return;
+    const uint32_t n = __atomic_load_n(&static_cast<const FlowCell*>(f->cell.p)->given_up, __ATOMIC_ACQUIRE);
+    if (n != f->noted) count(kCountGivenUp, static_cast<int32_t>(n - f->noted));
+    f->noted = n;
+}
+
 }  // namespace sl
+
+extern "C" {
+
+void sl_one_launch_counts(int64_t counts[4])
+{
+    for (int k = 0; counts && k < 4; ++k) counts[k] = sl::g_counts[k].load(std::memory_order_relaxed);
+}
+
+void sl_one_launch_wait(double ms) { sl::t_wait_ms = ms; }
+
+}  // extern "C"

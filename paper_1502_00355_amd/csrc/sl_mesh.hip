@@ -313,6 +313,7 @@ sl_status read_state(sl_mesh* h, MeshState* out, hipStream_t st)
 {
     SL_HIP(hipMemcpyAsync(out, h->state, sizeof(MeshState), hipMemcpyDeviceToHost, st));
     SL_HIP(hipStreamSynchronize(st));
+    flow_mesh_note(h->m.flow);
     return SL_OK;
 }
 
@@ -326,6 +327,7 @@ sl_status smooth_handle(sl_mesh* h, int32_t iterations, double tol, hipStream_t 
     if ((r = h->after_last(st))) return r;
     const bool jacobi = h->o.form == SL_JACOBI;
     (void)h->note_capture(st);
+    flow_mesh_note(h->m.flow);
     if (h->m.flow && !h->captured) {
         // all the sweeps in one launch, from the current buffer into the other
         bool ran = false;

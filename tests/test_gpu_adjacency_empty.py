@@ -9,6 +9,15 @@ import paper_1502_00355_amd as sl
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.set_device(0)
+    sl.lib()
+    yield
+
+
 @pytest.mark.parametrize("n", [1, 5, 257, 70000])
 def test_no_triangles(n):
     import torch

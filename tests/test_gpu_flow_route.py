@@ -1,0 +1,134 @@
+"""Which calls run all their sweeps in one launch, and what happens to a run
+that is given up because its work-groups are not on the device together in
+time: forced from the host by a wait of length zero, after which every kernel
+ends as it always does.
+
+Every operation is the oracle's, in its order, so equality is exact."""
+import contextlib
+
+import numpy as np
+import pytest
+
+import meshgen
+import oracle
+import paper_1502_00355_amd as sl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.set_device(0)
+    sl.lib()
+    yield
+
+
+@contextlib.contextmanager
+def counted(**want):
+    """The counts grow by these numbers, and no others do."""
+    a = sl.one_launch_counts()
+    yield
+    b = sl.one_launch_counts()
+    got = {k: b[k] - a[k] for k in b if b[k] != a[k]}
+    assert got == want
+
+
+@contextlib.contextmanager
+def no_waiting():
+    sl.lib().sl_one_launch_wait(0.0)
+    try:
+        yield
+    finally:
+        sl.lib().sl_one_launch_wait(-1.0)
+
+
+def one_call(m, iters, tol=0.0, form="jacobi", **opts):
+    dev = sl.to_device(m, "cuda:0")
+    rep = sl.smooth_mesh_device(*dev, iterations=iters, tol=tol, form=form, **opts)
+    ref = oracle.smooth(m, iters, tol=tol, threads=oracle.max_threads(), form=form)
+    assert rep.iterations_run == ref.iterations_run
+    assert (dev[0].cpu().numpy() == ref.coords).all()
+    assert rep.accepted_total == int(ref.accepted.sum()) and rep.max_disp_sq_last == ref.disp[-1]
+
+
+@pytest.mark.parametrize("form", ["jacobi", "colored"])
+@pytest.mark.parametrize("tol", [0.0, 1e-9])
+@pytest.mark.parametrize("size", [5, 64, 160, 300, 500])
+def test_meshes_that_fit_run_in_one_launch(size, tol, form):
+    m = meshgen.make_grid(size, "random", 0.35, size)
+    with counted(runs=1):
+        one_call(m, 6, tol, form)
+    with counted():
+        one_call(m, 6, tol, form, kernel="node")
+    if form == "jacobi":
+        h = sl.Mesh(m)
+        with counted(runs=1):
+            h.smooth_async(6, tol)
+            assert (h.download()[0] == oracle.smooth(m, 6, tol=tol, threads=oracle.max_threads()).coords).all()
+        h.close()
+
+
+def test_meshes_that_do_not_fit():
+    big = meshgen.make_annulus(502, 512, diag="random", jitter=0.3, seed=1)
+    with counted():
+        one_call(big, 2)
+    # rows that are not symmetric
+    m = meshgen.make_grid(50, "random", 0.3, 4)
+    free = np.flatnonzero(m.boundary == 0)
+    i, j = int(free[3]), int(free[-3])
+    m.nbr_idx = np.insert(m.nbr_idx, int(m.nbr_ptr[i + 1]), j).astype(np.int32)
+    m.nbr_ptr = m.nbr_ptr.copy()
+    m.nbr_ptr[i + 1:] += 1
+    with counted(declined=1):
+        one_call(m, 5)
+
+
+@pytest.mark.parametrize("form", ["jacobi", "colored"])
+@pytest.mark.parametrize("tol", [0.0, 1e-9])
+@pytest.mark.parametrize("size,iters", [(20, 70), (40, 20), (160, 70), (300, 20)])
+def test_one_call_given_up(size, iters, tol, form):
+    """The call returns to the kernels that a larger mesh would take (the
+    resident one, tiles, nodes; replays of a graph in the longer runs)."""
+    m = meshgen.permute_mesh(meshgen.make_grid(size, "random", 0.35, size), 3)
+    print("given up: size %d tol %g %s" % (size, tol, form), flush=True)
+    with no_waiting(), counted(given_up=1):
+        one_call(m, iters, tol, form)
+
+
+@pytest.mark.parametrize("calls", [[(7, 0.0)], [(8, 0.0)], [(30, 1e-30)], [(30, 4e-4)], [(5, 0.0), (6, 1e-9), (9, 0.0)]])
+@pytest.mark.parametrize("size", [40, 160, 300])
+def test_handle_runs_given_up(size, calls):
+    """The result, the state, and the runs that follow on the same handle."""
+    m = meshgen.make_grid(size, "random", 0.35, size)
+    h = sl.Mesh(m)
+    X = m.copy()
+    total = acc = 0
+    for k, (iters, tol) in enumerate([(4, 0.0)] + calls + [(6, 0.0), (5, 1e-9)]):
+        force = 0 < k <= len(calls)
+        print("handle size %d: %d sweeps, tol %g%s" % (size, iters, tol, ", given up" if force else ""), flush=True)
+        with no_waiting() if force else contextlib.nullcontext():
+            with counted(runs=1, given_up=1) if force else counted(runs=1):
+                h.smooth_async(iters, tol)
+                got, rep = h.download()
+        ref = oracle.smooth(X, iters, tol=tol, threads=oracle.max_threads())
+        X.coords = ref.coords
+        total += ref.iterations_run
+        acc += int(ref.accepted.sum())
+        assert (got == ref.coords).all()
+        assert rep.iterations_run == total and rep.accepted_total == acc
+        assert rep.accepted_last == int(ref.accepted[-1]) and rep.max_disp_sq_last == ref.disp[-1]
+    h.close()
+
+
+def test_runs_given_up_in_a_row():
+    """Nothing is waited for between the calls."""
+    m = meshgen.make_grid(200, "random", 0.35, 2)
+    h = sl.Mesh(m)
+    with no_waiting():
+        for _ in range(3):
+            h.smooth_async(5)
+    h.smooth_async(5)
+    assert (h.download()[0] == oracle.smooth(m, 20, threads=oracle.max_threads()).coords).all()
+    h.close()

@@ -12,6 +12,15 @@ import paper_1502_00355_amd as sl
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    torch.cuda.set_device(0)
+    sl.lib()
+    yield
+
+
 def positions(h, st):
     import torch
     x = torch.empty((h.n_nodes, 2), dtype=torch.float64, device="cuda:0")

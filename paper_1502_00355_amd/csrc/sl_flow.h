@@ -12,13 +12,18 @@ constexpr uint32_t kFlowStop = 0x80000000u;    // FlowState::decided: no sweep a
 // Device state of one call, zeroed before it.
 struct FlowState {
     uint32_t decline;       // != 0: the mesh does not fit the tiles' limits
-    uint32_t abort;         // != 0: a wait took too long
+    uint32_t abort;         // number of the run (never 0) in which a wait took too long last
     int32_t n_colors;       // colour classes (Form B)
     uint32_t pad0[29];
     uint32_t decided;       // with a tolerance: sweeps decided, | kFlowStop with the last one
     uint32_t pad1[31];
     unsigned long long maxd;   // with a tolerance: displacement maximum of the last sweep
     unsigned long long t_begin, t_sweep;   // the device's clock at the call's first kernel and at the sweeps
+    // zero but while k_flow_finish makes the sweeps of a run given up: tile
+    // steps dealt and made, groups that have left, and displacement maxima and
+    // accepted counts by sweep (mod 4) and in all
+    uint32_t dealt, made, left, pad2;
+    unsigned long long r_maxd[4], r_acc[4], r_total;
 };
 
 // What a tile's work-group leaves.

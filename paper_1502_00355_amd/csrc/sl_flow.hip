@@ -69,6 +69,7 @@ constexpr int kFlowHist = 4;                   // positions kept per node with a
 // kFlowSlots, has been decided on when the wave starts sweep s.
 constexpr int kFlowSlots = 8;
 static_assert(2 - kFlowSlots <= -kFlowLag, "a slot is free when it is set back");
+constexpr uint32_t kOneCall = 1u;              // the number of a call's one run
 constexpr uint32_t kDeclineColor = 8u;         // FlowState::decline: not coloured in time (1, 2, 4: the build)
 constexpr int32_t kFixedKey = INT32_MIN;       // halo key of a fixed node: kFixedKey + its place in the positions
 
@@ -135,16 +136,16 @@ __device__ __forceinline__ bool flow_off(const ValStats* vs, const FlowState* fs
 struct Waiter {
     FlowState* fs;
     u64 limit, t0;
-    uint32_t polls;
-    __device__ __forceinline__ Waiter(FlowState* f, u64 l) : fs(f), limit(l), t0(0), polls(0) {}
+    uint32_t run, polls;
+    __device__ __forceinline__ Waiter(FlowState* f, u64 l, uint32_t r) : fs(f), limit(l), t0(0), run(r), polls(0) {}
     __device__ __forceinline__ bool again()
     {
         if ((++polls & 255u) != 0 && limit != 0) return true;
-        if (ld_dev(&fs->abort)) return false;
+        if (ld_dev(&fs->abort) == run) return false;
         const u64 now = wall_clock64();
         if (t0 == 0) t0 = now;
         if (now - t0 <= limit && limit != 0) return true;
-        st_dev(&fs->abort, 1u);
+        st_dev(&fs->abort, run);
         return false;
     }
 };
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(256) void k_flow_color(const int32_t* __restrict__ 
 #pragma unroll
     for (int j = 0; j < R; ++j)
         if (above[j] >= 0 && (bnd[above[j]] != 0 || splitmix64(static_cast<uint64_t>(above[j])) < pi)) above[j] = -1;
-    Waiter w(fs, wait);
+    Waiter w(fs, wait, kOneCall);
     bool done = !mine;
     int32_t c = -1;
     uint64_t used0 = 0, used1 = 0;
@@ -534,6 +535,7 @@ struct FlowArgs {
     int32_t v0;                 // version of the start positions (mod 4)
     double tol2;
     u64 wait;                   // clock ticks a wait may take
+    uint32_t run;               // the run's number: kOneCall, or a handle's count of its runs
     const int32_t *nbr_end, *tri_end;   // nbr_ptr + n, tri_ptr + n
 };
 
@@ -662,7 +664,7 @@ __device__ void flow_control(const FlowArgs& a, int waves, int BS)
     for (int s = 0; s < a.iters; ++s) {
         const u64* const slot = a.dmax + (s & (kFlowSlots - 1)) * cap;
         double m = 0.0;
-        Waiter w(a.fs, a.wait);
+        Waiter w(a.fs, a.wait, a.run);
         for (int q0 = tid; q0 < n_slots; q0 += U * BS) {
             u64 v[U];
             for (;;) {
@@ -815,7 +817,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
             }
             // this class's halo nodes at the new version
             if (!(last_class && v == a.iters)) {
-                Waiter w(a.fs, a.wait);
+                Waiter w(a.fs, a.wait, a.run);
                 const int hlo = B ? hcls[c] : 0, hhi = B ? hcls[c + 1] : head[2];
                 for (int h = hlo + tid; h < hhi; h += BS) {
                     const u64* const p = ring_v + 2 * static_cast<int64_t>(halo[h]);
@@ -849,7 +851,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                 // sweep v runs once every sweep up to v - kFlowLag is decided;
                 // after the last sweep the final decision is awaited
                 const uint32_t need = static_cast<uint32_t>(max(v - kFlowLag + 1, 0));
-                Waiter w(a.fs, a.wait);
+                Waiter w(a.fs, a.wait, a.run);
                 for (;;) {
                     const uint32_t dec = ld_dev(&a.fs->decided);
                     if (dec & kFlowStop) {
@@ -953,14 +955,14 @@ __global__ __launch_bounds__(256) void k_flow_result(FlowArgs a, int tol, double
                                                      FlowReport* __restrict__ rep, MeshState* __restrict__ ms)
 {
     const u64 t_end = wall_clock64();
-    const bool off = flow_off(a.vs, a.fs) || a.fs->abort != 0;
+    const bool gave_up = a.fs->abort == a.run, off = flow_off(a.vs, a.fs) || gave_up;
     const int n_free = a.vs->n_free, sweeps = tol ? static_cast<int>(a.fs->decided & ~kFlowStop) : a.iters;
     if (blockIdx.x == 0) {
         const FlowGroup f = fold_groups<256>(a.groups, off ? 0 : (n_free + a.T - 1) / a.T);
         if (threadIdx.x == 0) {
             rep->vs = *a.vs;
             rep->decline = a.fs->decline;
-            rep->abort = a.fs->abort;
+            rep->abort = gave_up ? 1u : 0u;
             rep->n_colors = a.fs->n_colors;
             rep->sweeps = sweeps;
             rep->maxd = tol ? a.fs->maxd : f.maxd;
@@ -986,45 +988,57 @@ struct FlowCell {
     uint32_t given_up;   // runs given up
 };
 
-// The end of a handle's run, one work-group: the sweep state, from the
-// groups' words.  A handle's call does not wait for the device, so when the
-// run was given up (Waiter) the sweeps are made here, tile after tile and
-// sweep after sweep from the untouched start positions: no group waits for
-// another, slow, and as good as never needed.  Calls of very few tiles and
-// sweeps (kSerialSteps) are made this way to begin with (serial): one launch.
-constexpr int kFinishBS = 512;
+// The end of a handle's run: the sweep state, from the groups' words (by the
+// first work-group; the others find nothing to do).  A handle's call does not
+// wait for the device, so when the run was given up (Waiter) the sweeps are
+// made here, from the untouched start positions, by kFinishGroups
+// work-groups: they take tile steps in order, sweep after sweep, and begin a
+// sweep when all steps of the one before have been made.  A group waits only
+// for steps dealt before its own, whose groups are running, so the wait ends
+// with however few groups the device has room for.  (One group alone took 7 us
+// a tile step: 600 sweeps of 100K nodes 842 ms; now 38, and 10 with a launch
+// per sweep.)  Calls of very few tiles and
+// sweeps (kSerialSteps) are made by one such group to begin with (serial): one
+// launch.
+// No two groups can be at different sweeps when one of them stops: the grid is
+// at most a sweep's tiles, so the steps of the sweep that does not run are not
+// all dealt before each group has taken one and left.
+constexpr int kFinishBS = 512, kFinishGroups = 64;
 template <bool GT>
-__global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, int serial, MeshState* ms, FlowCell* cell,
-                                                           uint32_t run)
+__global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, int serial, MeshState* ms, FlowCell* cell)
 {
     extern __shared__ double2 flow_lds[];
     __shared__ double s_recip[kMaxValence + 1];
-    __shared__ double s_d2[kFinishBS / 64];
-    __shared__ u64 s_acc[kFinishBS / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, T = a.T, n_free = a.vs->n_free;
+    __shared__ uint32_t s_item;
+    __shared__ int s_stop;
+    const int tid = threadIdx.x, T = a.T, n_free = a.vs->n_free;
     const int tiles = (n_free + T - 1) / T;
+    const bool first = blockIdx.x == 0 && tid == 0, alone = gridDim.x == 1;
     const u64 t_begin = serial ? wall_clock64() : a.fs->t_sweep;
-    if (!serial && tid == 0) __hip_atomic_store(&cell->done, run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (!serial && a.fs->abort == 0) {   // (no group runs any more)
+    if (!serial && first) __hip_atomic_store(&cell->done, a.run, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    auto close = [&](int ran, u64 maxd, u64 acc_last, u64 acc_total) {
+        MeshState m = *ms;
+        m.iters = m.s + a.iters;
+        m.s += ran;
+        m.active = 0;
+        m.tol2 = a.tol2;
+        m.maxd_cur = m.acc_cur = 0;
+        m.maxd_last = maxd;
+        m.acc_last = acc_last;
+        m.acc_total += acc_total;
+        m.t_begin = t_begin;
+        m.t_end = wall_clock64();
+        *ms = m;
+    };
+    if (!serial && a.fs->abort != a.run) {   // (no group of the run is there any more)
+        if (blockIdx.x != 0) return;
         const FlowGroup f = fold_groups<kFinishBS>(a.groups, tiles);
-        if (tid == 0) {
-            MeshState m = *ms;
-            const int ran = tol ? static_cast<int>(a.fs->decided & ~kFlowStop) : a.iters;
-            m.iters = m.s + a.iters;
-            m.s += ran;
-            m.active = 0;
-            m.tol2 = a.tol2;
-            m.maxd_cur = m.acc_cur = 0;
-            m.maxd_last = tol ? a.fs->maxd : f.maxd;
-            m.acc_last = f.acc_last;
-            m.acc_total += f.acc_total;
-            m.t_begin = t_begin;
-            m.t_end = wall_clock64();
-            *ms = m;
-        }
+        if (tid == 0)
+            close(tol ? static_cast<int>(a.fs->decided & ~kFlowStop) : a.iters, tol ? a.fs->maxd : f.maxd, f.acc_last,
+                  f.acc_total);
         return;
     }
-    if (!serial && tid == 0)   // (the one writer: no atomic over the bus)
+    if (!serial && first)   // (the one writer: no atomic over the bus)
         __hip_atomic_store(&cell->given_up,
                            __hip_atomic_load(&cell->given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) + 1u,
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1033,82 +1047,111 @@ __global__ __launch_bounds__(kFinishBS) void k_flow_finish(FlowArgs a, int tol, 
     unsigned char* const rec = reinterpret_cast<unsigned char*>(flow_lds + T + L.hc);
     for (int q = tid; q <= kMaxValence; q += kFinishBS) s_recip[q] = q ? 1.0 / static_cast<double>(q) : 0.0;
     double2* const buf[2] = {reinterpret_cast<double2*>(const_cast<double*>(a.coords)), reinterpret_cast<double2*>(a.out)};
-    int s = 0;
-    double m = 0.0;
-    u64 acc = 0, acc_total = 0;
-    while (s < a.iters) {
+    FlowState* const fs = a.fs;
+    uint32_t next = 0;
+    int whole = 0, ran = a.iters;   // sweeps known to be whole; sweeps run
+    double m = 0.0;                 // (alone) the sweep's displacement maximum
+    u64 acc = 0, total = 0;         // (alone) its accepted nodes, and all sweeps'
+    for (;; ++next) {
+        __syncthreads();   // s_item and the last tile's LDS are read
+        if (tid == 0) s_item = alone ? next : atomicAdd(&fs->dealt, 1u);
+        __syncthreads();
+        const int s = static_cast<int>(s_item / static_cast<uint32_t>(tiles)),
+                  tile = static_cast<int>(s_item % static_cast<uint32_t>(tiles));
+        if (s > whole) {
+            bool stop = tol && a.tol2 > 0.0;
+            if (alone) {
+                stop = stop && m < a.tol2;
+                if (!stop && s < a.iters) {
+                    m = 0.0;
+                    acc = 0;
+                }
+            } else if (s < a.iters) {
+                if (tid == 0) {
+                    while (ld_dev(&fs->made) < static_cast<uint32_t>(s) * static_cast<uint32_t>(tiles))
+                        __builtin_amdgcn_s_sleep(1);
+                    s_stop = stop && __longlong_as_double(static_cast<long long>(ld_dev(&fs->r_maxd[(s - 1) & 3]))) < a.tol2;
+                }
+                __syncthreads();
+                __threadfence();   // the other groups' positions
+                stop = s_stop != 0;
+            }
+            whole = s;
+            if (stop && s < a.iters) ran = s;
+            if (stop) break;
+        }
+        if (s >= a.iters) break;
         const double2* const in = buf[s & 1];
         double2* const to = buf[(s & 1) ^ 1];
+        const uint4* src = reinterpret_cast<const uint4*>(a.rec + static_cast<int64_t>(tile) * L.bytes);
+        for (int q = tid; q < L.bytes / 16; q += kFinishBS) reinterpret_cast<uint4*>(rec)[q] = src[q];
+        __syncthreads();
+        const int32_t* const head = reinterpret_cast<const int32_t*>(rec);
+        const int32_t* const halo = reinterpret_cast<const int32_t*>(rec + L.halo);
+        const int k0 = tile * T, nown = head[0];
+        for (int i = tid; i < nown; i += kFinishBS) X[i] = in[k0 + i];
+        for (int h = tid; h < head[1]; h += kFinishBS) X[T + h] = in[halo[h] < 0 ? halo[h] - kFixedKey : halo[h]];
+        __syncthreads();
+        const FlowRec t{reinterpret_cast<const uint16_t*>(rec + L.rs),   reinterpret_cast<const uint16_t*>(rec + L.fs),
+                        reinterpret_cast<const uint16_t*>(rec + L.ord),  reinterpret_cast<const uint16_t*>(rec + L.rows),
+                        reinterpret_cast<const uint32_t*>(rec + L.fans), rec + L.flag};
         double d2 = 0.0;
         u64 n_acc = 0;
-        for (int tile = 0; tile < tiles; ++tile) {
-            __syncthreads();   // the previous tile's LDS is read
-            const uint4* src = reinterpret_cast<const uint4*>(a.rec + static_cast<int64_t>(tile) * L.bytes);
-            for (int q = tid; q < L.bytes / 16; q += kFinishBS) reinterpret_cast<uint4*>(rec)[q] = src[q];
-            __syncthreads();
-            const int32_t* const head = reinterpret_cast<const int32_t*>(rec);
-            const int32_t* const halo = reinterpret_cast<const int32_t*>(rec + L.halo);
-            const int k0 = tile * T, nown = head[0];
-            for (int i = tid; i < nown; i += kFinishBS) X[i] = in[k0 + i];
-            for (int h = tid; h < head[1]; h += kFinishBS) X[T + h] = in[halo[h] < 0 ? halo[h] - kFixedKey : halo[h]];
-            __syncthreads();
-            const FlowRec t{reinterpret_cast<const uint16_t*>(rec + L.rs),   reinterpret_cast<const uint16_t*>(rec + L.fs),
-                            reinterpret_cast<const uint16_t*>(rec + L.ord),  reinterpret_cast<const uint16_t*>(rec + L.rows),
-                            reinterpret_cast<const uint32_t*>(rec + L.fans), rec + L.flag};
-            for (int q = tid; q < nown; q += kFinishBS) {
-                NodeRef ref;
-                load_ref<1>(ref, t, q, 0);
-                double2 o, c;
-                double qo, qn;
-                flow_node<1>(ref, t, X, s_recip, o, c, qo, qn);
-                const bool accepted = GT ? (qn > qo) : (qn >= qo);
-                const double nx = accepted ? c.x : o.x, ny = accepted ? c.y : o.y;
-                to[k0 + ref.i] = make_double2(nx, ny);
-                const double dx = nx - o.x, dy = ny - o.y, e = dx * dx + dy * dy;
-                d2 = e > d2 ? e : d2;
-                n_acc += accepted ? 1 : 0;
+        for (int q = tid; q < nown; q += kFinishBS) {
+            NodeRef ref;
+            load_ref<1>(ref, t, q, 0);
+            double2 o, c;
+            double qo, qn;
+            flow_node<1>(ref, t, X, s_recip, o, c, qo, qn);
+            const bool accepted = GT ? (qn > qo) : (qn >= qo);
+            const double nx = accepted ? c.x : o.x, ny = accepted ? c.y : o.y;
+            to[k0 + ref.i] = make_double2(nx, ny);
+            const double dx = nx - o.x, dy = ny - o.y, e = dx * dx + dy * dy;
+            d2 = e > d2 ? e : d2;
+            n_acc += accepted ? 1 : 0;
+        }
+        __threadfence();   // the next sweep reads these positions
+        group_fold<kFinishBS>(d2, n_acc);
+        if (alone) {
+            m = d2 > m ? d2 : m;
+            acc += n_acc;
+            total += n_acc;
+        } else if (tid == 0) {
+            if (d2 > 0.0) atomicMax(&fs->r_maxd[s & 3], static_cast<u64>(__double_as_longlong(d2)));
+            if (n_acc) {
+                atomicAdd(&fs->r_acc[s & 3], n_acc);
+                atomicAdd(&fs->r_total, n_acc);
             }
+            if (tile == 0) {   // the next sweep's, which nobody reads or adds to before this step is made
+                st_dev(&fs->r_maxd[(s + 1) & 3], 0ull);
+                st_dev(&fs->r_acc[(s + 1) & 3], 0ull);
+            }
+            wait_stores();
+            atomicAdd(&fs->made, 1u);
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            const double t = __shfl_xor(d2, off);
-            d2 = t > d2 ? t : d2;
-            n_acc += __shfl_xor(n_acc, off);
-        }
-        __syncthreads();
-        if (lane == 0) {
-            s_d2[wv] = d2;
-            s_acc[wv] = n_acc;
-        }
-        __threadfence();   // the next sweep reads this one's positions
-        __syncthreads();
-        m = 0.0;
-        acc = 0;
-        for (int q = 0; q < kFinishBS / 64; ++q) {
-            m = s_d2[q] > m ? s_d2[q] : m;
-            acc += s_acc[q];
-        }
-        acc_total += acc;
-        ++s;
-        if (tol && a.tol2 > 0.0 && m < a.tol2) break;
     }
-    if ((s & 1) == 0)   // the result belongs in `out`
+    if (!alone) {   // the last group to leave ends the run
+        __syncthreads();
+        if (tid == 0) s_item = atomicAdd(&fs->left, 1u);
+        __syncthreads();
+        if (s_item != gridDim.x - 1) return;
+        __threadfence();
+        m = __longlong_as_double(static_cast<long long>(ld_dev(&fs->r_maxd[(ran - 1) & 3])));
+        acc = ld_dev(&fs->r_acc[(ran - 1) & 3]);
+        total = ld_dev(&fs->r_total);
+    }
+    if ((ran & 1) == 0)   // the result belongs in `out`
         for (int k = tid; k < n_free; k += kFinishBS) buf[1][k] = buf[0][k];
     // after a run given up: the exchange as a new mesh finds it
     for (int64_t q = serial ? 8 * a.n : tid; q < 8 * a.n; q += kFinishBS) a.ring[q] = kSent;
+    __syncthreads();
     if (tid == 0) {
-        MeshState st = *ms;
-        st.iters = st.s + a.iters;
-        st.s += s;
-        st.active = 0;
-        st.tol2 = a.tol2;
-        st.maxd_cur = st.acc_cur = 0;
-        st.maxd_last = static_cast<u64>(__double_as_longlong(m));
-        st.acc_last = acc;
-        st.acc_total += acc_total;
-        st.t_begin = t_begin;
-        st.t_end = wall_clock64();
-        *ms = st;
-        if (!serial) a.fs->abort = 0;
+        close(ran, static_cast<u64>(__double_as_longlong(m)), acc, total);
+        if (!alone) {
+            fs->dealt = fs->made = fs->left = 0;
+            for (int k = 0; k < 4; ++k) fs->r_maxd[k] = fs->r_acc[k] = 0;
+            fs->r_total = 0;
+        }
     }
 }
 
@@ -1209,7 +1252,7 @@ FlowShape flow_shape(int32_t n, bool b)
     return FlowShape{512, b ? 4 : 1, 512};
 }
 constexpr int32_t kFlowMaxNodes = 512 * 500;
-constexpr int32_t kFlowMaxSweeps = 1 << 20;   // of one launch
+constexpr int32_t kFlowMaxSweeps = 1 << 20;   // of one launch (times 500 tiles: within 32 bits)
 constexpr u64 kFlowWait = 200000000ull;       // 2 s of the 100 MHz clock
 
 std::atomic<int64_t> g_counts[4];             // sl_one_launch_counts
@@ -1353,6 +1396,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     fa.iters = iterations;
     fa.tol2 = tl ? tol * tol : 0.0;
     fa.wait = wait_limit();
+    fa.run = kOneCall;
     fa.nbr_end = a.nbr_ptr + n;
     fa.tri_end = a.tri_ptr + n;
 
@@ -1433,22 +1477,16 @@ __global__ void k_flow_mesh_tell(const FlowState* __restrict__ fs, uint32_t* __r
     if (threadIdx.x == 0) *out = fs->decline;
 }
 
-template <bool GT>
-sl_status launch_finish_v(const FlowArgs& a, const FlowShape& p, bool tol, bool serial, MeshState* state, FlowCell* cell,
-                          uint32_t run, hipStream_t st)
+sl_status launch_finish(const FlowArgs& a, const FlowShape& p, int32_t n_free, bool gt, bool tol, bool serial,
+                        MeshState* state, FlowCell* cell, hipStream_t st)
 {
     const FlowLayout L(p.T);
     const size_t lds = static_cast<size_t>(p.T + L.hc) * 16 + static_cast<size_t>(L.bytes);
-    k_flow_finish<GT><<<1, kFinishBS, lds, st>>>(a, tol ? 1 : 0, serial ? 1 : 0, state, cell, run);
+    const int groups = serial ? 1 : std::min(kFinishGroups, div_up(n_free, p.T));
+    (gt ? k_flow_finish<true> : k_flow_finish<false>)<<<groups, kFinishBS, lds, st>>>(a, tol ? 1 : 0, serial ? 1 : 0, state,
+                                                                                      cell);
     SL_HIP(hipGetLastError());
     return SL_OK;
-}
-
-sl_status launch_finish(const FlowArgs& a, const FlowShape& p, bool gt, bool tol, bool serial, MeshState* state,
-                        FlowCell* cell, uint32_t run, hipStream_t st)
-{
-    return gt ? launch_finish_v<true>(a, p, tol, serial, state, cell, run, st)
-              : launch_finish_v<false>(a, p, tol, serial, state, cell, run, st);
 }
 
 // Tiles times sweeps up to which one work-group makes them all: 4 tile steps
@@ -1541,7 +1579,7 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
     if (static_cast<int64_t>(f->tiles) * iterations <= kSerialSteps) {
         *done = true;
         count(kCountRun);
-        return launch_finish(a, f->p, gt, tl, true, state, nullptr, 0, st);
+        return launch_finish(a, f->p, m.n_free, gt, tl, true, state, nullptr, st);
     }
     if (!f->slots.take(f->tiles + 1)) {   // (+ 1: a run with a tolerance has a controller)
         count(kCountNoRoom);
@@ -1556,9 +1594,11 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
         SL_HIP(hipGetLastError());
     }
     a.v0 = static_cast<int32_t>(f->version & 3u);
+    if (++f->run == 0) f->run = 1;
+    a.run = f->run;
     sl_status r = launch_flow(a, f->p, false, gt, tl, st);
     FlowCell* const cell = static_cast<FlowCell*>(f->cell.p);
-    if (r || (r = launch_finish(a, f->p, gt, tl, false, state, cell, ++f->run, st))) return r;
+    if (r || (r = launch_finish(a, f->p, m.n_free, gt, tl, false, state, cell, st))) return r;
     f->slots.keep(&cell->done, f->run);
     count(kCountRun);
     f->fresh = tl;

@@ -132,3 +132,21 @@ def test_runs_given_up_in_a_row():
     h.smooth_async(5)
     assert (h.download()[0] == oracle.smooth(m, 20, threads=oracle.max_threads()).coords).all()
     h.close()
+
+
+def test_recovery_takes_the_device():
+    """A long run that is given up is made by as many work-groups as there
+    are, not by one: at most ten times what a launch per sweep takes."""
+    m = meshgen.make_grid(316, "random", 0.35, 6)
+    sweeps = 600
+    with sl.Mesh(m, kernel="tile", tile_nodes=512) as h:
+        h.smooth_async(sweeps)
+        want, plain = h.download()
+    with sl.Mesh(m) as h:
+        with no_waiting(), counted(runs=1, given_up=1):
+            h.smooth_async(sweeps)
+            got, rep = h.download()
+    assert (got == want).all()
+    assert rep.accepted_total == plain.accepted_total and rep.max_disp_sq_last == plain.max_disp_sq_last
+    print("%d sweeps given up %.1f ms, launch per sweep %.1f ms" % (sweeps, rep.sweep_ms, plain.sweep_ms), flush=True)
+    assert rep.sweep_ms < 10 * plain.sweep_ms

@@ -30,9 +30,10 @@
 // Waits end: a wait longer than the limit, or another group's failure, sets
 // the abort word, every group leaves, the caller's positions are untouched
 // and the call runs again on the one-launch-per-sweep kernels.  The groups
-// of all flow launches in flight on a device are limited to what it holds at
-// once (FlowSlots), so the limit is reached only if other work keeps part of
-// the device for that long.
+// of all flow launches that the process has in flight on a device are limited
+// to what it holds at once (FlowSlots), so the limit is reached only if other
+// work, such as another process's, keeps part of the device for that long;
+// no run is begun there for a while then.
 //
 // With a tolerance one more work-group (the controller) folds the waves'
 // displacement maxima of each sweep and publishes whether the next one runs;
@@ -1174,6 +1175,7 @@ public:
     {
         std::lock_guard<std::mutex> lk(mu);
         if (held) {
+            if (resting(dev)) return false;
             word = nullptr;   // in use: not to be taken back
             return true;
         }
@@ -1186,6 +1188,7 @@ public:
             }
             limit[dev] = 2 * cus;
         }
+        if (resting(dev)) return false;
         if (used[dev] + groups > limit[dev])
             for (size_t k = keepers.size(); k-- > 0;) {
                 FlowSlots* const f = keepers[k];
@@ -1210,8 +1213,25 @@ public:
         std::lock_guard<std::mutex> lk(mu);
         if (held) drop();
     }
+    // A run in these places has been given up: other work has the device
+    // (another process that runs this path too, or a kernel that stays long).
+    // No places are given out there for kRest, so that waits in vain take a
+    // hundredth of the time at most; calls take the other kernels meanwhile.
+    void rest()
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (dev >= 0) until[dev] = Clock::now() + kRest;
+    }
+    static void wake()
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        for (auto& t : until) t = Clock::time_point();
+    }
 
 private:
+    using Clock = std::chrono::steady_clock;
+    static constexpr std::chrono::milliseconds kRest{500};
+    static bool resting(int d) { return until[d] != Clock::time_point() && Clock::now() < until[d]; }
     void drop()
     {
         used[dev] -= held;
@@ -1221,6 +1241,7 @@ private:
     }
     static std::mutex mu;
     static int used[64], limit[64];
+    static Clock::time_point until[64];
     static std::vector<FlowSlots*> keepers;
     int dev = -1, held = 0;
     const uint32_t* word = nullptr;   // set while kept between calls
@@ -1228,6 +1249,7 @@ private:
 };
 std::mutex FlowSlots::mu;
 int FlowSlots::used[64], FlowSlots::limit[64];
+FlowSlots::Clock::time_point FlowSlots::until[64];
 std::vector<FlowSlots*> FlowSlots::keepers;
 
 // Tile size, lanes per node and work-group size for n nodes.  The smallest
@@ -1253,7 +1275,10 @@ FlowShape flow_shape(int32_t n, bool b)
 }
 constexpr int32_t kFlowMaxNodes = 512 * 500;
 constexpr int32_t kFlowMaxSweeps = 1 << 20;   // of one launch (times 500 tiles: within 32 bits)
-constexpr u64 kFlowWait = 200000000ull;       // 2 s of the 100 MHz clock
+// 5 ms of the 100 MHz clock: a thousand exchanges, and longer than any launch
+// of this library keeps a place.  (It was 2 s: two processes with a medium
+// mesh each could hold half of the other's room for that long.)
+constexpr u64 kFlowWait = 500000ull;
 
 std::atomic<int64_t> g_counts[4];             // sl_one_launch_counts
 enum { kCountRun, kCountDeclined, kCountGivenUp, kCountNoRoom };
@@ -1420,6 +1445,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     const bool late = h.abort != 0 || (h.decline & kDeclineColor) != 0;
     if (late || h.vs.err != 0 || h.vs.n_free == 0 || h.decline || h.n_colors > kFlowClasses) {
         count(late ? kCountGivenUp : kCountDeclined);
+        if (late) slots.rest();
         return SL_OK;
     }
     count(kCountRun);
@@ -1611,8 +1637,10 @@ void flow_mesh_note(FlowMesh* f)
 {
     if (!f) return;
     const uint32_t n = __atomic_load_n(&static_cast<const FlowCell*>(f->cell.p)->given_up, __ATOMIC_ACQUIRE);
-    if (n != f->noted) count(kCountGivenUp, static_cast<int32_t>(n - f->noted));
+    if (n == f->noted) return;
+    count(kCountGivenUp, static_cast<int32_t>(n - f->noted));
     f->noted = n;
+    f->slots.rest();
 }
 
 }  // namespace sl
@@ -1624,6 +1652,10 @@ void sl_one_launch_counts(int64_t counts[4])
     for (int k = 0; counts && k < 4; ++k) counts[k] = sl::g_counts[k].load(std::memory_order_relaxed);
 }
 
-void sl_one_launch_wait(double ms) { sl::t_wait_ms = ms; }
+void sl_one_launch_wait(double ms)
+{
+    sl::t_wait_ms = ms;
+    if (ms < 0.0) sl::FlowSlots::wake();
+}
 
 }  // extern "C"

@@ -5,6 +5,10 @@ ends as it always does.
 
 Every operation is the oracle's, in its order, so equality is exact."""
 import contextlib
+import os
+import subprocess
+import sys
+import time
 
 import numpy as np
 import pytest
@@ -37,6 +41,7 @@ def counted(**want):
 
 @contextlib.contextmanager
 def no_waiting():
+    sl.lib().sl_one_launch_wait(-1.0)   # (a run given up earlier may have been seen since)
     sl.lib().sl_one_launch_wait(0.0)
     try:
         yield
@@ -58,6 +63,7 @@ def one_call(m, iters, tol=0.0, form="jacobi", **opts):
 @pytest.mark.parametrize("size", [5, 64, 160, 300, 500])
 def test_meshes_that_fit_run_in_one_launch(size, tol, form):
     m = meshgen.make_grid(size, "random", 0.35, size)
+    sl.lib().sl_one_launch_wait(-1.0)
     with counted(runs=1):
         one_call(m, 6, tol, form)
     with counted():
@@ -150,3 +156,75 @@ def test_recovery_takes_the_device():
     assert rep.accepted_total == plain.accepted_total and rep.max_disp_sq_last == plain.max_disp_sq_last
     print("%d sweeps given up %.1f ms, launch per sweep %.1f ms" % (sweeps, rep.sweep_ms, plain.sweep_ms), flush=True)
     assert rep.sweep_ms < 10 * plain.sweep_ms
+
+
+def test_device_is_left_to_others_after_a_run_given_up():
+    """No run is begun for half a second; calls take the other kernels."""
+    m = meshgen.make_grid(160, "random", 0.35, 2)
+    h = sl.Mesh(m)
+    sl.lib().sl_one_launch_wait(-1.0)
+    sl.lib().sl_one_launch_wait(0.0)
+    try:
+        with counted(given_up=1):
+            one_call(m, 20)
+        t0 = time.time()
+        with counted(no_room=2):
+            one_call(m, 20)
+            h.smooth_async(20)
+            assert (h.download()[0] == oracle.smooth(m, 20, threads=oracle.max_threads()).coords).all()
+        assert time.time() - t0 < 0.4
+        time.sleep(0.6 - (time.time() - t0))
+        with counted(given_up=1, runs=1):
+            h.smooth_async(20)
+            h.report()
+    finally:
+        sl.lib().sl_one_launch_wait(-1.0)
+    with counted(runs=1):
+        one_call(m, 20)
+    h.close()
+
+
+OTHER = """
+import sys, time
+sys.path.insert(0, %r)
+import torch
+torch.cuda.set_device(0)
+import meshgen, paper_1502_00355_amd as sl
+m = meshgen.make_grid(470, "random", 0.35, 4)
+print("ready", flush=True)
+sys.stdin.readline()
+t0 = time.time()
+while time.time() - t0 < 2.0:
+    sl.smooth_mesh_device(*sl.to_device(m, "cuda:0"), iterations=30)
+"""
+
+
+def test_two_processes():
+    """Another process runs meshes of the same size on the device: results
+    stay the same, and no call waits long for places that the other has."""
+    import torch
+    m = meshgen.make_grid(470, "random", 0.35, 4)
+    want = oracle.smooth(m, 30, threads=oracle.max_threads()).coords
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    sl.lib().sl_one_launch_wait(-1.0)
+    p = subprocess.Popen([sys.executable, "-c", OTHER % root], stdin=subprocess.PIPE, stdout=subprocess.PIPE, text=True)
+    try:
+        assert p.stdout.readline() == "ready\n"
+        a = sl.one_launch_counts()
+        p.stdin.write("go\n")
+        p.stdin.flush()
+        ms = []
+        t0 = time.time()
+        while time.time() - t0 < 2.0:
+            dev = sl.to_device(m, "cuda:0")
+            torch.cuda.synchronize()
+            rep = sl.smooth_mesh_device(*dev, iterations=30)
+            ms.append(rep.total_ms)
+            assert (dev[0].cpu().numpy() == want).all()
+        b = sl.one_launch_counts()
+        print("%d calls, median %.2f ms, longest %.2f ms, %s" % (len(ms), np.median(ms), max(ms),
+                                                               {k: b[k] - a[k] for k in b}), flush=True)
+    finally:
+        p.stdin.close()
+        assert p.wait(timeout=60) == 0
+    assert np.median(ms) < 50 and max(ms) < 1000

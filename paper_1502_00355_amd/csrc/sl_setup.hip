@@ -600,18 +600,24 @@ __device__ __forceinline__ uint32_t hilbert_index(int bits, uint32_t x, uint32_t
     return d;
 }
 
-// Bucket of each free node: colour * 4^bits + Hilbert cell (bits may be 0).
-// Fixed nodes: buckets of 2^fixed_shift cells from fixed_base on, or none
+// Bucket of each free node: colour * 4^bits + Hilbert cell.  Fixed nodes:
+// cells of their own, 4^fixed_bits of them from fixed_base on, or none
 // (fixed_base < 0).
+// Lanes of a wave that share a bucket count together, for up to
+// kBucketShared buckets a wave: where many nodes fall into few buckets
+// (strongly graded meshes), an atomic per node on one address is a queue
+// (360K nodes, most of them in a handful of cells: setup 952 -> 243 us).
+constexpr int kBucketShared = 4;
 __global__ __launch_bounds__(kBS) void k_bucket(const double* __restrict__ coords, const uint8_t* __restrict__ bnd,
                                                 const int32_t* __restrict__ color, int32_t n, int bits,
-                                                int32_t fixed_base, int fixed_shift, const ValStats* __restrict__ vs, int32_t* __restrict__ key,
+                                                int32_t fixed_base, int fixed_bits, const ValStats* __restrict__ vs, int32_t* __restrict__ key,
                                                 int32_t* __restrict__ count, int32_t* __restrict__ rank)
 {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x;
     if (i >= n) return;
     const bool fixed = bnd[i] != 0;
     if (fixed && fixed_base < 0) return;
+    if (fixed) bits = fixed_bits;
     uint32_t cell = 0;
     if (bits > 0) {
         const double x0 = from_ord_bits(vs->box[0]), y0 = from_ord_bits(vs->box[1]);
@@ -624,10 +630,25 @@ __global__ __launch_bounds__(kBS) void k_bucket(const double* __restrict__ coord
         const uint32_t cy = fy <= 0.0 ? 0u : (fy >= lim ? lim : static_cast<uint32_t>(fy));
         cell = hilbert_index(bits, cx, cy);
     }
-    const int32_t k = fixed ? fixed_base + static_cast<int32_t>(cell >> fixed_shift)
-                            : (color ? color[i] : 0) * (1 << (2 * bits)) + static_cast<int32_t>(cell);
+    const int32_t k = (fixed ? fixed_base : (color ? color[i] : 0) * (1 << (2 * bits))) + static_cast<int32_t>(cell);
     key[i] = k;
-    rank[i] = atomicAdd(count + k, 1);   // place inside the bucket (in no particular order)
+    const int lane = static_cast<int>(threadIdx.x & 63);
+    int lead = lane, many = 1, at = 0;   // who counts for this lane, for how many, and the lane's place among them
+    unsigned long long todo = __ballot(1);
+#pragma unroll 1
+    for (int r = 0; r < kBucketShared && todo != 0; ++r) {
+        const int l = __builtin_ctzll(todo);
+        const unsigned long long same = __ballot(k == __builtin_amdgcn_readlane(k, l)) & todo;
+        if ((same >> lane) & 1ull) {
+            lead = l;
+            many = __popcll(same);
+            at = __popcll(same & ((1ull << lane) - 1ull));
+        }
+        todo &= ~same;
+    }
+    int32_t base = 0;
+    if (lead == lane) base = atomicAdd(count + k, many);
+    rank[i] = __shfl(base, lead) + at;   // place inside the bucket (in no particular order)
 }
 
 __global__ __launch_bounds__(kBS) void k_bucket_scatter(int32_t n, const int32_t* __restrict__ key,
@@ -1050,12 +1071,16 @@ int hilbert_bits(int64_t n_free, int nc)
 
 namespace {
 
-constexpr int kFixedShift = 6;   // cells per bucket of fixed nodes: 2^6
+// Bits per axis of the fixed nodes' cells: 2^6 of the free nodes' cells each
+// while they are few (a boundary), and few nodes a cell where most of a mesh
+// is fixed (1.2M nodes, 400 of them free, the others in 4 cells: setup 13.7
+// ms; so 0.21).
+int fixed_bits(int64_t n_fixed, int bits) { return std::max({bits - 3, hilbert_bits(n_fixed, 1) - 1, 0}); }
 
 // Scratch bytes make_order takes for n nodes (at most 128 colour classes).
 size_t order_bytes(int64_t n)
 {
-    // (and the fixed nodes' buckets: at least 4 cells each, or a single one)
+    // (and the fixed nodes' buckets: a 64th of the free ones', or half the fixed nodes)
     const int64_t nbk = std::max<int64_t>(4 * 128, 2 * n) + n / 2 + 16;
     return 3 * Arena::piece(4 * static_cast<size_t>(n + 1)) + 2 * Arena::piece(4 * static_cast<size_t>(nbk + 1)) + scan_bytes(std::max<int64_t>(n, nbk));
 }
@@ -1077,15 +1102,15 @@ sl_status make_order(const SetupArgs& a, const sl_options& o, const uint8_t* bnd
         // which no result depends on (rows and triangles keep their order).
         const int nc = color ? n_colors : 1;
         const int bits = hilbert_bits(n_free, nc);
-        // the fixed nodes' buckets follow (coarser cells: they are few)
+        // the fixed nodes' buckets follow
         const int64_t nfree_bk = static_cast<int64_t>(nc) << (2 * bits);
-        const int fshift = std::min(kFixedShift, 2 * bits);
-        const int64_t nbk = nfree_bk + (int64_t(1) << (2 * bits - fshift));
+        const int fbits = fixed_bits(n - n_free, bits);
+        const int64_t nbk = nfree_bk + (int64_t(1) << (2 * fbits));
         int32_t *count = nullptr, *start = nullptr, *key = nullptr;
         if ((r = scratch.take(&count, nbk)) || (r = scratch.take(&start, nbk + 1)) || (r = scratch.take(&key, n)))
             return r;
         k_fill_i32<<<div_up(nbk, 256), 256, 0, st>>>(count, nbk, 0);
-        k_bucket<<<gb, kBS, 0, st>>>(a.coords, bnd, color, n, bits, static_cast<int32_t>(nfree_bk), fshift, vs, key, count, flag);
+        k_bucket<<<gb, kBS, 0, st>>>(a.coords, bnd, color, n, bits, static_cast<int32_t>(nfree_bk), fbits, vs, key, count, flag);
         if ((r = scan_exclusive(count, start, nbk, st, &scratch))) return r;
         if (color) {
             // nc <= 128: the class starts fit the mesh's table and the pad

@@ -272,12 +272,21 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     bool flowed = false;
     const SetupArgs fa{coords, n, nbr_ptr, nbr_idx, tri_ptr, tri_idx, tris, n_tris, boundary,
                        in.ends_known ? in.ends[1] : -1, in.ends_known ? in.ends[3] : -1};
-    if ((r = flow_run(fa, o, iterations, tol, report, coords, stream, ws ? ws->base : nullptr, ws ? ws->bytes : 0, &flowed)))
+    FlowSeen seen;
+    if ((r = flow_run(fa, o, iterations, tol, report, coords, stream, ws ? ws->base : nullptr, ws ? ws->bytes : 0, &flowed,
+                      &seen)))
         return r;
     if (flowed) {
         if (report)
             report->total_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
         return SL_OK;
+    }
+    if (seen.valid) {   // not for that path; its checks need not run again
+        cs.m.checked = &seen.vs;
+        in.ends_known = true;
+        in.ends[0] = in.ends[2] = 0;
+        in.ends[1] = seen.nnz;
+        in.ends[3] = seen.ninc;
     }
     if ((r = cs.pad.init())) return r;
     if ((r = prepare_mesh(in, o, 0, cs.m, stream))) return r;

@@ -441,6 +441,9 @@ struct DevMesh {
     // is for it.
     bool want_flow = false;
     struct FlowMesh* flow = nullptr;
+    // Set before setup: what an attempt on the flow path has found in the same
+    // call's checks of the same arrays, with the same options.
+    const ValStats* checked = nullptr;
     uint64_t t_setup = 0;                // the device's clock when setup began
     bool resident = false;               // Form A on the resident kernel (node-path arrays built)
     int32_t lane_width = 0;              // node path: > 0 sweeps with lane groups of this width

@@ -71,9 +71,15 @@ sl_status unpermute_flags_raw(const uint64_t* bits, int64_t words, const int32_t
 // free groups allow it.  *done = false (with SL_OK): not run, or the mesh
 // turned out not to fit; the caller's arrays are untouched.  ws / ws_bytes:
 // a region to carve every device array from, instead of allocating.  The
-// CSR ends in `a` need not be known (-1).
+// CSR ends in `a` need not be known (-1).  *seen: what the checks found, when
+// they ran and found nothing that the call will fail for.
+struct FlowSeen {
+    bool valid = false;
+    ValStats vs;
+    int32_t nnz, ninc;   // nbr_ptr[n], tri_ptr[n]
+};
 sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, double tol, sl_report* report,
-                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, bool* done);
+                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, bool* done, FlowSeen* seen);
 
 // A set-up mesh's part of the flow path (mesh handles): its tile records and
 // the exchange's slots.  Built by setup when DevMesh::want_flow is set; null

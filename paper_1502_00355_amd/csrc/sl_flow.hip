@@ -1339,9 +1339,10 @@ void launch_build(const FlowBuildArgs& b, int T, int tiles, hipStream_t st)
 }  // namespace
 
 sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, double tol, sl_report* report,
-                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, bool* done)
+                   double* coords, hipStream_t st, unsigned char* ws, size_t ws_bytes, bool* done, FlowSeen* seen)
 {
     *done = false;
+    seen->valid = false;
     const int32_t n = a.n;
     const bool b = o.form == SL_INPLACE_COLORED, tl = tol > 0.0;
     // automatic choices only, in double precision and the default order, for
@@ -1441,7 +1442,9 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     SL_HIP(hipStreamSynchronize(st));
 
     const FlowReport h = *rep;
-    // (what the checks found wrong, the other path finds and reports too)
+    // (what the checks found wrong, the other path finds and reports too; it
+    // takes rows that are not symmetric or incidences that disagree in Form A)
+    *seen = FlowSeen{(h.vs.err & ~(b ? 0u : static_cast<uint32_t>(VE_ASYM) | VI_INCIDENCE)) == 0, h.vs, h.nnz, h.ninc};
     const bool late = h.abort != 0 || (h.decline & kDeclineColor) != 0;
     if (late || h.vs.err != 0 || h.vs.n_free == 0 || h.decline || h.n_colors > kFlowClasses) {
         count(late ? kCountGivenUp : kCountDeclined);

@@ -44,8 +44,9 @@ __host__ __device__ __forceinline__ double from_ord_bits(uint64_t u)
 // ---------------------------------------------------------------- scan ----
 //
 // Reduce, then scan: one pass sums each tile of kScanTile values, and a
-// second pass scans each tile from its offset.  Each work-item holds 16 consecutive values, loaded and stored as
-// four 16-byte vectors when the arrays allow it.
+// second pass scans each tile from its offset.  Each work-item holds 16
+// consecutive values, loaded and stored as four 16-byte vectors when the
+// arrays allow it.
 
 constexpr int kScanPer = 16;
 constexpr int kScanTile = kBS * kScanPer;
@@ -122,12 +123,33 @@ __device__ __forceinline__ int32_t sums_before(const int32_t* __restrict__ sums,
     return all;
 }
 
-// Scans this work-group's tile from its offset, the sum of the earlier
-// tiles' sums, which it adds up itself: at most a few thousand values out of
-// L2, which costs less than a launch of one work-group to scan them first.
-// The last tile also writes the total.
+// Exclusive scan of nb tile sums in place, by one work-group per row of nb.
+__global__ __launch_bounds__(kSumsBS) void k_scan_offsets(int32_t* __restrict__ sums, int32_t nb)
+{
+    __shared__ int32_t s_wave[kSumsBS / 64];
+    sums += static_cast<int64_t>(blockIdx.x) * nb;
+    int32_t carry = 0;
+    for (int32_t c0 = 0; c0 < nb; c0 += kSumsBS) {
+        const int32_t b = c0 + static_cast<int32_t>(threadIdx.x), x = b < nb ? sums[b] : 0;
+        int32_t all;
+        const int32_t off = carry + group_excl_scan<kSumsBS>(x, s_wave, &all);
+        if (b < nb) sums[b] = off;
+        carry += all;
+    }
+}
+
+// More tiles than this have their sums scanned before (k_scan_offsets).  Up to
+// there each tile adds up the earlier tiles' sums itself, out of L2, which
+// costs no more than the launch (adjacency of 130M nodes and a triangle 4.3 ms
+// with, 4.2 without); but those reads grow with the square of the tiles (400M
+// nodes 13.3 -> 10.3 ms, 10^9 47 -> 26).
+constexpr int kSumsInPlace = 32768;
+
+// Scans this work-group's tile from its offset: the sum of the earlier
+// tiles' sums (scanned: already their scan).  The last tile also writes the
+// total.
 __device__ __forceinline__ void scan_tile(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n, bool vec,
-                                          const int32_t* __restrict__ sums, int32_t* total, int32_t* s_wave)
+                                          const int32_t* __restrict__ sums, bool scanned, int32_t* total, int32_t* s_wave)
 {
     const int64_t base = (static_cast<int64_t>(blockIdx.x) * kBS + threadIdx.x) * kScanPer;
     int32_t v[kScanPer];
@@ -135,7 +157,7 @@ __device__ __forceinline__ void scan_tile(const int32_t* __restrict__ in, int32_
     int32_t x = 0;
 #pragma unroll
     for (int j = 0; j < kScanPer; ++j) x += v[j];
-    const int32_t off = sums_before<kBS>(sums, static_cast<int>(blockIdx.x), s_wave);
+    const int32_t off = scanned ? sums[blockIdx.x] : sums_before<kBS>(sums, static_cast<int>(blockIdx.x), s_wave);
     int32_t all;
     int32_t run = off + group_excl_scan<kBS>(x, s_wave, &all);
 #pragma unroll
@@ -158,10 +180,10 @@ __device__ __forceinline__ void scan_tile(const int32_t* __restrict__ in, int32_
 
 __global__ __launch_bounds__(kBS) void k_scan_tiles(const int32_t* __restrict__ in, int32_t* __restrict__ out,
                                                     int64_t n, bool vec, const int32_t* __restrict__ sums,
-                                                    int32_t* __restrict__ total)
+                                                    bool scanned, int32_t* __restrict__ total)
 {
     __shared__ int32_t s_wave[kBS / 64];
-    scan_tile(in, out, n, vec, sums, total, s_wave);
+    scan_tile(in, out, n, vec, sums, scanned, total, s_wave);
 }
 
 // Exclusive scan of a short in[0..n) by one work-group, kSumsBS*kScanPer
@@ -223,7 +245,8 @@ sl_status scan_rec(const int32_t* in, int32_t* out, int64_t n, int32_t* total, h
     if (r) return r;
     const bool vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
     k_scan_sums<<<nb, kBS, 0, st>>>(in, n, vec, sums);
-    k_scan_tiles<<<nb, kBS, 0, st>>>(in, out, n, vec, sums, total);
+    if (nb > kSumsInPlace) k_scan_offsets<<<1, kSumsBS, 0, st>>>(sums, nb);
+    k_scan_tiles<<<nb, kBS, 0, st>>>(in, out, n, vec, sums, nb > kSumsInPlace, total);
     if (!ar) dfree(sums, st);
     SL_HIP(hipGetLastError());
     return SL_OK;
@@ -883,13 +906,14 @@ __global__ __launch_bounds__(kBS) void k_degree_sums(const int32_t* __restrict__
 
 // Row offsets (blockIdx.y == 0) and incidence offsets (1).
 __global__ __launch_bounds__(kBS) void k_offset_tiles(const int32_t* __restrict__ deg, const int32_t* __restrict__ inc,
-                                                      int64_t n, const int32_t* __restrict__ sums,
+                                                      int64_t n, const int32_t* __restrict__ sums, bool scanned,
                                                       int32_t* __restrict__ row_ptr, int32_t* __restrict__ fan_ptr)
 {
     __shared__ int32_t s_wave[kBS / 64];
     int32_t* const out = blockIdx.y ? fan_ptr : row_ptr;
     // (arena pieces: 256-byte aligned)
-    scan_tile(blockIdx.y ? inc : deg, out, n, true, sums + (blockIdx.y ? gridDim.x : 0), out + n, s_wave);
+    scan_tile(blockIdx.y ? inc : deg, out, n, true, sums + (blockIdx.y ? gridDim.x : 0), scanned, out + n,
+              s_wave);
 }
 
 // The node path's rows in device labels and fan entries, p | slot << 2 |
@@ -1435,7 +1459,8 @@ sl_status setup_mesh(const SetupArgs& a, const sl_options& o, DevMesh& m, int32_
     int32_t* dsum = nullptr;
     if ((r = scratch.take(&dsum, 2 * static_cast<size_t>(gt)))) return r;
     k_degree_sums<<<gt, kBS, 0, st>>>(m.perm, m.n_free, a.nbr_ptr, a.tri_ptr, deg, inc, dsum);
-    k_offset_tiles<<<dim3(gt, 2), kBS, 0, st>>>(deg, inc, m.n_free, dsum, m.row_ptr, m.fan_ptr);
+    if (gt > kSumsInPlace) k_scan_offsets<<<2, kSumsBS, 0, st>>>(dsum, gt);
+    k_offset_tiles<<<dim3(gt, 2), kBS, 0, st>>>(deg, inc, m.n_free, dsum, gt > kSumsInPlace, m.row_ptr, m.fan_ptr);
     SL_HIP(hipGetLastError());
     scratch.rewind(mk);
     m.nnz_free = h.nnz_free;     // the offsets' totals, counted by the validation

@@ -295,9 +295,10 @@ typedef struct sl_mesh sl_mesh;
 
 /* Creates a handle from host arrays (as for smooth_mesh; desc->coords gives
  * the initial positions and is not written).  Synchronous.  Device memory:
- * about 135 bytes per node in double precision (350 for Form A meshes of at
- * most 256,000 nodes with automatic options, whose sweeps run in one launch),
- * freed by sl_mesh_destroy. */
+ * about 135 bytes per node in double precision, freed by sl_mesh_destroy;
+ * for Form A meshes of at most 256,000 nodes with automatic options, whose
+ * sweeps run in one launch, 130 more where there is room, and 64 more from
+ * the first call with a tolerance on. */
 SL_API sl_status sl_mesh_create(const sl_mesh_desc* desc, const sl_options* opts, sl_mesh** out);
 
 /* The same from device arrays (as for smooth_mesh_device), read on `stream`

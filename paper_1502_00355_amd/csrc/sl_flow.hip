@@ -1478,7 +1478,7 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
 // -------------------------------------------------------------- handles --
 
 struct FlowMesh {
-    Arena ar;
+    Arena ar, tol;          // (tol: what only runs with a tolerance need, from the first of them on)
     FlowShape p{};
     int tiles = 0;
     FlowArgs fa{};
@@ -1534,6 +1534,7 @@ void flow_mesh_free(FlowMesh*& f, hipStream_t st)
 {
     if (!f) return;
     f->ar.release(st);
+    f->tol.release(st);
     delete f;
     f = nullptr;
 }
@@ -1545,7 +1546,6 @@ sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st)
     f->p = flow_shape(m.n, false);
     f->tiles = div_up(m.n, f->p.T);
     const FlowLayout L(f->p.T);
-    const size_t n_dmax = static_cast<size_t>(kFlowSlots) * f->tiles * (f->p.BS / 64);
     FlowArgs& fa = f->fa;
     unsigned char* rec = nullptr;
     ValStats* vs = nullptr;
@@ -1553,15 +1553,15 @@ sl_status flow_mesh_build(const SetupArgs& a, DevMesh& m, hipStream_t st)
     sl_status r = pad.init();
     if (r || (r = f->cell.init()) || (r = f->ar.reserve(Arena::piece(sizeof(ValStats)) + Arena::piece(sizeof(FlowState)) +
                                     Arena::piece(static_cast<size_t>(f->tiles) * L.bytes) + Arena::piece(4 * 16 * un) +
-                                    Arena::piece(kFlowHist * 16 * un) + Arena::piece(8 * n_dmax) +
                                     Arena::piece(sizeof(FlowGroup) * static_cast<size_t>(f->tiles)),
                                 st)) ||
         (r = f->ar.take(&vs, 1)) || (r = f->ar.take(&fa.fs, 1)) ||
         (r = f->ar.take(&rec, static_cast<size_t>(f->tiles) * L.bytes)) || (r = f->ar.take(&fa.ring, 8 * un)) ||
-        (r = f->ar.take(&fa.hist, kFlowHist * 2 * un)) || (r = f->ar.take(&fa.dmax, n_dmax)) ||
         (r = f->ar.take(&fa.groups, static_cast<size_t>(f->tiles)))) {
         flow_mesh_free(f, st);
-        return r;
+        if (r != SL_ENOMEM) return r;
+        set_error("");
+        return SL_OK;   // no room for it: the tile path
     }
     fa.vs = vs;
     fa.rec = rec;
@@ -1599,6 +1599,16 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
         return SL_OK;
     }
     const bool gt = accept == SL_ACCEPT_GT;
+    const int64_t n_dmax = static_cast<int64_t>(kFlowSlots) * f->tiles * (f->p.BS / 64);
+    if (tl && !f->fa.hist) {
+        const size_t n2 = static_cast<size_t>(kFlowHist) * 2 * static_cast<size_t>(m.n);
+        sl_status r = f->tol.reserve(Arena::piece(8 * n2) + Arena::piece(8 * static_cast<size_t>(n_dmax)), st);
+        if (r == SL_ENOMEM) {
+            set_error("");
+            return SL_OK;
+        }
+        if (r || (r = f->tol.take(&f->fa.dmax, static_cast<size_t>(n_dmax))) || (r = f->tol.take(&f->fa.hist, n2))) return r;
+    }
     FlowArgs a = f->fa;
     a.coords = static_cast<const double*>(m.X[cur]);
     a.out = static_cast<double*>(m.X[cur ^ 1]);
@@ -1618,7 +1628,7 @@ sl_status flow_mesh_sweeps(const DevMesh& m, int cur, int32_t accept, int32_t it
         // (a run with a tolerance leaves groups some sweeps apart)
         f->version = 0;
         const FlowInitArgs ia{nullptr, a.fs, nullptr, 0, nullptr, m.n, a.ring + 2 * static_cast<int64_t>(m.n), a.dmax,
-                              tl ? static_cast<int64_t>(kFlowSlots) * f->tiles * (f->p.BS / 64) : 0, nullptr, 0};
+                              tl ? n_dmax : 0, nullptr, 0};
         k_flow_init<<<std::min(div_up(m.n, 256), 1024), 256, 0, st>>>(ia);
         SL_HIP(hipGetLastError());
     }

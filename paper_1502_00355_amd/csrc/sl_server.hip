@@ -5,7 +5,7 @@
 // this file is its device executor.  Admission uploads a request's mesh and
 // builds its tiles on a stream of the setup thread that admits it, while
 // the current step keeps sweeping on the compute stream; results are
-// un-permuted and copied out on a third stream while the next step runs.
+// un-permuted and copied out on streams of the collect threads meanwhile.
 // A step runs a few sweeps over the tiles of all
 // joined requests with one launch per sweep (continuous batching): a
 // request joins at the first step after its setup, when its sweep state is
@@ -52,9 +52,8 @@ thread_local int t_bound_device = -1;   // the device a setup thread has made cu
 
 }  // namespace
 
-// Device side of the server: one compute stream for the steps, one collect
-// stream for results, pooled streams for admissions, per-slot sweep states
-// with pinned host mirrors.
+// Device side of the server: one compute stream for the steps, pooled streams
+// for admissions and results, per-slot sweep states with pinned host mirrors.
 struct HipExec {
     using Payload = HipPayload;
     using Req = sched::Request<Payload>;
@@ -62,15 +61,14 @@ struct HipExec {
     sl_options opts{};
     int32_t max_active = 0, sweeps_per_step = 0;
     int device = 0;
-    hipStream_t st_compute = nullptr, st_collect = nullptr;
+    hipStream_t st_compute = nullptr;
+    hipStream_t st_free = nullptr;      // no work: blocks given back on it are free at once
     MeshState* states = nullptr;        // [max_active]
     int32_t* sched = nullptr;           // the tile launches' counters
     MeshState* h_states = nullptr;      // [max_active], pinned: read-back after each step
     MeshState* h_join = nullptr;        // [max_active], pinned: the state a joining request starts from
     TileWork* work = nullptr;
     int64_t work_cap = 0;
-    double* out = nullptr;
-    size_t out_cap = 0;
     int32_t parity = 0;
     int32_t n_work = 0, T = 0, hcap = 0, rcap = 0;
     int32_t wg_per_cu = 0, block = 0;
@@ -86,7 +84,7 @@ struct HipExec {
         sl_status r;
         SL_HIP(hipGetDevice(&device));
         SL_HIP(hipStreamCreateWithFlags(&st_compute, hipStreamNonBlocking));
-        SL_HIP(hipStreamCreateWithFlags(&st_collect, hipStreamNonBlocking));
+        SL_HIP(hipStreamCreateWithFlags(&st_free, hipStreamNonBlocking));
         if ((r = dalloc(&states, static_cast<size_t>(max_active), st_compute))) return r;
         if ((r = dalloc(&sched, kTileSchedInts, st_compute))) return r;
         SL_HIP(hipMemsetAsync(sched, 0, sizeof(int32_t) * kTileSchedInts, st_compute));
@@ -106,8 +104,7 @@ struct HipExec {
         dfree(work, st_compute);
         dfree(states, st_compute);
         dfree(sched, st_compute);
-        dfree(out, st_collect);
-        for (hipStream_t st : {st_compute, st_collect}) {
+        for (hipStream_t st : {st_compute, st_free}) {
             if (!st) continue;
             (void)hipStreamSynchronize(st);
             (void)hipStreamDestroy(st);
@@ -115,7 +112,7 @@ struct HipExec {
         if (h_states) (void)hipHostFree(h_states);
         if (h_join) (void)hipHostFree(h_join);
         h_states = h_join = nullptr;
-        st_compute = st_collect = nullptr;
+        st_compute = st_free = nullptr;
     }
 
     size_t footprint(const sl_mesh_desc& d) { return estimate_footprint(d); }
@@ -252,29 +249,31 @@ struct HipExec {
         return SL_OK;
     }
 
-    // Copies a finished request's positions back to host memory, on the
-    // collect stream: the request is in no step any more, so this overlaps
-    // the step that runs meanwhile.
+    // Copies a finished request's positions back to host memory, on a stream
+    // of the calling thread's: the request is in no step any more, so this
+    // overlaps the step that runs meanwhile.  Called by several collect
+    // threads at once.
     sl_status collect(Req& q, const sched::StepOutcome&)
     {
+        bind_thread();
         const DevMesh& m = q.x.mesh;
         const MeshState& ms = q.x.last;
         const size_t n = static_cast<size_t>(m.n);
-        if (out_cap < 2 * n) {
-            dfree(out, st_collect);
-            sl_status r = dalloc(&out, 2 * n, st_collect);
-            if (r) {
-                out_cap = 0;
-                return r;
-            }
-            out_cap = 2 * n;
-        }
+        PooledStream ps;
+        Arena ar;
+        double* out = nullptr;
+        sl_status r;
+        if ((r = ps.init()) || (r = ar.reserve(Arena::piece(2 * n * sizeof(double)), ps.s)) || (r = ar.take(&out, 2 * n)))
+            return r;
         const bool jacobi = opts.form == SL_JACOBI;
         const int src = jacobi ? ((q.x.parity0 + ms.s) & 1) : 0;
-        sl_status r = unpermute_coords(m, src, out, st_collect);
-        if (r) return r;
         q.result.resize(2 * n);
-        if ((r = copy_to_host(q.result.data(), out, 2 * n * sizeof(double), st_collect))) return r;
+        if (!(r = unpermute_coords(m, src, out, ps.s))) r = copy_to_host(q.result.data(), out, 2 * n * sizeof(double), ps.s);
+        ar.release(ps.s);
+        if (r) {
+            (void)hipStreamSynchronize(ps.s);   // nothing reads the mesh any more
+            return r;
+        }
         sl_report rep{};
         rep.iterations_run = ms.s;
         rep.n_colors = m.n_colors;
@@ -287,9 +286,8 @@ struct HipExec {
         return SL_OK;
     }
 
-    // After its last step and its collection (stream-ordered on the collect
-    // stream, which follows both).
-    void release(Req& q) { devmesh_free(q.x.mesh, st_collect); }
+    // After its last step and its collection, which the host has waited for.
+    void release(Req& q) { devmesh_free(q.x.mesh, st_free); }
 };
 
 }  // namespace sl

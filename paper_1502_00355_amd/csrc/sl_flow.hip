@@ -1380,8 +1380,13 @@ sl_status flow_run(const SetupArgs& a, const sl_options& o, int32_t iterations, 
     if (r) return r;
     static_assert(sizeof(FlowReport) <= kPadBytes, "report size");
     Arena ar;
-    if (ws) ar.adopt(ws, ws_bytes);
-    else if ((r = ar.reserve(bytes, st))) return r;
+    if (ws) {
+        ar.adopt(ws, ws_bytes);
+    } else if ((r = ar.reserve(bytes, st))) {
+        if (r != SL_ENOMEM) return r;
+        set_error("");
+        return SL_OK;   // no room for it: the other kernels' arrays may still fit
+    }
     struct GiveBack {
         Arena& ar;
         hipStream_t st;

@@ -196,10 +196,9 @@ struct CallState {
     uint64_t* bits = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipStream_t capture = nullptr;      // where the sweep chunk is captured
+    CaptureStream capture;              // where the sweep chunk is captured
     ~CallState()
     {
-        if (capture) give_stream(capture);
         devmesh_free(m, st);
         aux.release(st);
         (void)hipStreamSynchronize(st);
@@ -373,11 +372,11 @@ sl_status run_device(double* coords, int32_t n, const int32_t* nbr_ptr, const in
     if (use_graph) {
         for (; done < kDirectSweeps; ++done)
             if ((r = enqueue(done, stream))) return r;
-        if ((r = take_stream(&cs.capture))) return r;
-        SL_HIP(hipStreamBeginCapture(cs.capture, hipStreamCaptureModeThreadLocal));
+        if ((r = cs.capture.init())) return r;
+        SL_HIP(hipStreamBeginCapture(cs.capture.s, hipStreamCaptureModeThreadLocal));
         sl_status cr = SL_OK;
-        for (int32_t s = 0; s < kSweepChunk && !cr; ++s) cr = enqueue(s, cs.capture);
-        const hipError_t ce = hipStreamEndCapture(cs.capture, &cs.graph);
+        for (int32_t s = 0; s < kSweepChunk && !cr; ++s) cr = enqueue(s, cs.capture.s);
+        const hipError_t ce = hipStreamEndCapture(cs.capture.s, &cs.graph);
         if (cr) return cr;
         if (ce != hipSuccess) return fail(SL_EDEVICE, std::string("graph capture failed: ") + hipGetErrorString(ce));
         SL_HIP(hipGraphInstantiate(&cs.exec, cs.graph, nullptr, nullptr, 0));

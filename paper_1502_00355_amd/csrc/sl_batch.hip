@@ -273,10 +273,10 @@ sl_status sl_batch_smooth(const sl_mesh_desc* meshes, int32_t n_meshes, int32_t 
                        bs.sched, all_tiles ? n_meshes : 0};
     const int32_t block = resolve_block_size(o);
     const int32_t chunk = iterations <= 128 ? iterations + (iterations & 1) : 64;   // even: parity repeats
-    auto enqueue_chunk = [&]() -> sl_status {
+    auto enqueue_chunk = [&](hipStream_t on) -> sl_status {
         for (int32_t s = 0; s < chunk; ++s) {
             sl_status rr = SL_OK;
-            if (jacobi && total_tiles > 0) rr = launch_sweep_tiles(L, s & 1, nullptr, st);
+            if (jacobi && total_tiles > 0) rr = launch_sweep_tiles(L, s & 1, nullptr, on);
             for (int32_t i = 0; i < n_meshes && !rr; ++i) {
                 const DevMesh& m = bs.meshes[i];
                 if (m.resident || (jacobi && m.tile_nodes > 0)) continue;
@@ -287,13 +287,13 @@ sl_status sl_batch_smooth(const sl_mesh_desc* meshes, int32_t n_meshes, int32_t 
                         TileLaunch Lc{m.work + m.class_tile_h[c], m.class_tile_h[c + 1] - m.class_tile_h[c],
                                       m.tile_nodes, m.halo_max, m.rows_max, o.layout, o.accept, bs.states,
                                       wg_auto ? 0 : o.tile_wg_per_cu, 0, o.precision, bs.sched, 0};
-                        rr = launch_sweep_class(Lc, m.fans_max, nullptr, st);
+                        rr = launch_sweep_class(Lc, m.fans_max, nullptr, on);
                     }
                     continue;
                 }
-                rr = launch_sweep_nodes(m, s & 1, o.form, o.accept, block, bs.states + i, nullptr, bs.sched, st);
+                rr = launch_sweep_nodes(m, s & 1, o.form, o.accept, block, bs.states + i, nullptr, bs.sched, on);
             }
-            if (!rr && !all_tiles) rr = launch_advance(bs.states, n_meshes, st);
+            if (!rr && !all_tiles) rr = launch_advance(bs.states, n_meshes, on);
             if (rr) return rr;
         }
         return SL_OK;
@@ -308,10 +308,12 @@ sl_status sl_batch_smooth(const sl_mesh_desc* meshes, int32_t n_meshes, int32_t 
             return r;
     }
     if (iterations > 0 && ((jacobi && total_tiles > 0) || any_node)) {
-        SL_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-        sl_status cr = enqueue_chunk();
+        CaptureStream cap;
+        if ((r = cap.init())) return r;
+        SL_HIP(hipStreamBeginCapture(cap.s, hipStreamCaptureModeThreadLocal));
+        sl_status cr = enqueue_chunk(cap.s);
         hipGraph_t g = nullptr;
-        const hipError_t ce = hipStreamEndCapture(st, &g);
+        const hipError_t ce = hipStreamEndCapture(cap.s, &g);
         bs.graph = g;
         if (cr) return cr;
         if (ce != hipSuccess) return fail(SL_EDEVICE, std::string("graph capture failed: ") + hipGetErrorString(ce));

@@ -560,6 +560,21 @@ struct PooledStream {
     sl_status init() { return take_stream(&s); }
 };
 
+// A stream to capture sweeps on, from a pool of its own: nothing else ever
+// runs there, so no event is recorded there.  (The runtime takes a wait for an
+// event, from any thread, whose stream is being captured meanwhile for an
+// error of both the wait and the capture; blocks given back, for one, carry
+// events recorded on pooled streams.)
+struct CaptureStream {
+    hipStream_t s = nullptr;
+    CaptureStream() = default;
+    CaptureStream(const CaptureStream&) = delete;
+    CaptureStream& operator=(const CaptureStream&) = delete;
+    ~CaptureStream();
+    sl_status init();
+    int dev = -1;
+};
+
 // A small piece of pinned host memory from a per-device pool: kernels write
 // a call's few result words straight into it, which the host reads after its
 // wait (a copy into pageable memory is an extra trip through the runtime's

@@ -207,16 +207,13 @@ struct sl_mesh {
     sl_status chunk_graph(int p, hipGraphExec_t* out)
     {
         if (!exec[p]) {
-            hipStream_t cap = nullptr;
-            sl_status r = sl::take_stream(&cap);
+            sl::CaptureStream cap;
+            sl_status r = cap.init();
             if (r) return r;
-            if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-                sl::give_stream(cap);
+            if (hipStreamBeginCapture(cap.s, hipStreamCaptureModeThreadLocal) != hipSuccess)
                 return sl::fail(SL_EDEVICE, "graph capture could not start");
-            }
-            for (int32_t k = 0; k < sl::kHandleChunk && !r; ++k) r = sweep((p + k) & 1, cap);
-            const hipError_t ce = hipStreamEndCapture(cap, &graph[p]);
-            sl::give_stream(cap);
+            for (int32_t k = 0; k < sl::kHandleChunk && !r; ++k) r = sweep((p + k) & 1, cap.s);
+            const hipError_t ce = hipStreamEndCapture(cap.s, &graph[p]);
             if (r) return r;
             if (ce != hipSuccess) return sl::fail(SL_EDEVICE, std::string("graph capture failed: ") + hipGetErrorString(ce));
             SL_HIP(hipGraphInstantiate(&exec[p], graph[p], nullptr, nullptr, 0));

@@ -228,7 +228,7 @@ sl_status upload_inputs(const sl_mesh_desc& d, int64_t nnz, int64_t ninc, size_t
 namespace {
 
 std::mutex g_stream_mu;
-std::vector<hipStream_t> g_stream_free[64];
+std::vector<hipStream_t> g_stream_free[64], g_capture_free[64];
 std::unordered_map<hipStream_t, int> g_stream_dev;
 
 }  // namespace
@@ -259,6 +259,28 @@ void give_stream(hipStream_t st)
     std::lock_guard<std::mutex> lk(g_stream_mu);
     auto it = g_stream_dev.find(st);
     if (it != g_stream_dev.end()) g_stream_free[it->second].push_back(st);
+}
+
+sl_status CaptureStream::init()
+{
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(SL_EDEVICE, "no current device");
+    {
+        std::lock_guard<std::mutex> lk(g_stream_mu);
+        if (!g_capture_free[dev].empty()) {
+            s = g_capture_free[dev].back();
+            g_capture_free[dev].pop_back();
+            return SL_OK;
+        }
+    }
+    SL_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+    return SL_OK;
+}
+
+CaptureStream::~CaptureStream()
+{
+    if (!s) return;
+    std::lock_guard<std::mutex> lk(g_stream_mu);
+    g_capture_free[dev].push_back(s);
 }
 
 namespace {

@@ -359,13 +359,13 @@ SL_API sl_status sl_release_cached_memory(void);
  * because the device did not hold all work-groups at once in time (their
  * sweeps were made by other kernels; a handle's are counted when a later call
  * on the handle, or a download or report, sees it); [3]: calls that found no
- * room on the device, or that came within half a second of a run given up
- * there. */
+ * room on the device, or that came within a tenth of a second of a run
+ * given up there. */
 SL_API void sl_one_launch_counts(int64_t counts[4]);
 
 /* For tests: how long a work-group of that path waits for another one before
  * the run is given up, in milliseconds, in later calls of the calling thread;
- * 0 gives up at once, negative restores the default (5) and forgets the runs
+ * 0 gives up at once, negative restores the default (2) and forgets the runs
  * given up so far. */
 SL_API void sl_one_launch_wait(double ms);
 

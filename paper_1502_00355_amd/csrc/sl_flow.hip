@@ -1216,7 +1216,7 @@ public:
     // A run in these places has been given up: other work has the device
     // (another process that runs this path too, or a kernel that stays long).
     // No places are given out there for kRest, so that waits in vain take a
-    // hundredth of the time at most; calls take the other kernels meanwhile.
+    // fiftieth of the time at most; calls take the other kernels meanwhile.
     void rest()
     {
         std::lock_guard<std::mutex> lk(mu);
@@ -1230,7 +1230,7 @@ public:
 
 private:
     using Clock = std::chrono::steady_clock;
-    static constexpr std::chrono::milliseconds kRest{500};
+    static constexpr std::chrono::milliseconds kRest{100};
     static bool resting(int d) { return until[d] != Clock::time_point() && Clock::now() < until[d]; }
     void drop()
     {
@@ -1275,10 +1275,13 @@ FlowShape flow_shape(int32_t n, bool b)
 }
 constexpr int32_t kFlowMaxNodes = 512 * 500;
 constexpr int32_t kFlowMaxSweeps = 1 << 20;   // of one launch (times 500 tiles: within 32 bits)
-// 5 ms of the 100 MHz clock: a thousand exchanges, and longer than any launch
-// of this library keeps a place.  (It was 2 s: two processes with a medium
-// mesh each could hold half of the other's room for that long.)
-constexpr u64 kFlowWait = 500000ull;
+// 2 ms of the 100 MHz clock: a thousand exchanges, and longer than most
+// launches of this library keep a place.  (It was 2 s: two processes with a
+// medium mesh each could hold half of the other's room for that long, and
+// eight threads that run one-call smooths, handles, a batch, a server and
+// adjacencies at once got through 0.3K smooths a second; 1.7K with 5 ms and a
+// rest of 500, 1.8K with 2 and 100.)
+constexpr u64 kFlowWait = 200000ull;
 
 std::atomic<int64_t> g_counts[4];             // sl_one_launch_counts
 enum { kCountRun, kCountDeclined, kCountGivenUp, kCountNoRoom };

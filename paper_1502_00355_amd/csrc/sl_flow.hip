@@ -1490,8 +1490,8 @@ struct FlowMesh {
     FlowShape p{};
     int tiles = 0;
     FlowArgs fa{};
+    PinnedCell cell;        // (before the places, which look at it until they are given back)
     FlowSlots slots;
-    PinnedCell cell;
     uint32_t run = 0;       // runs queued
     uint32_t noted = 0;     // runs given up, as far as counted
     bool fresh = true;      // the exchange's slots are to be set up before the next run
